@@ -54,7 +54,8 @@ enum {
 typedef struct scorch_spmm_plan_s scorch_spmm_plan_t; /* small host-side handle */
 
 /*
- * Plan-free SpMM: C = A.B in natural row order.  A wavefront takes a short run of consecutive rows
+ * Plan-free SpMM: C = A.B in natural row order.  A matrix of few rows (at most 2048 pairs of a row and a 32-column
+ * tile) gets a workgroup per pair.  Otherwise a wavefront takes a short run of consecutive rows
  * (up to 4, up to 16 for small n), walks the short ones (up to 32 entries) side by side and streams the longer ones; the
  * four wavefronts of a workgroup work together on rows with more than 2048 entries (more than 256
  * where such rows are rare).  With B of 8 MB or more and n a multiple of 64 (128) the columns are walked in slices of

@@ -429,6 +429,85 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
     }
 }
 
+// Plan-free path for matrices of few rows (a batch of sparse activations): one workgroup per row and per tile of at
+// most 32 columns.  The run kernel below gives a row to one wavefront and covers as many columns as a wavefront can, so
+// a matrix of 64 rows would occupy 16 compute units; here the NW wavefronts of a workgroup take interleaved chunks of
+// the row, its lane groups (8 lanes, one 128-byte line of a row of B) interleaved entries, and the column tiles are
+// dealt over the dies.  Bound by the latency of two dependent reads (entries, rows of B) per chunk, hence chunks of
+// 128 entries, all of whose gathers are in flight at once (64 rows x 2458 entries, n = 256, operands in the memory-side cache: 62.0 -> 11.7 us).
+constexpr int kRowChunk = 128;
+
+template <int V, int G, bool UA, int NW>
+__global__ __launch_bounds__(NW * kWave) void spmm_row_kernel(const ExecArgs a) {
+    using vec = typename Vec<V>::type;
+    constexpr int S = kWave / G;
+    constexpr int TW = G * V;
+    constexpr int U = kRowChunk / S >= 16 ? 16 : kRowChunk / S;
+    constexpr int kPer = kRowChunk / kWave;
+    __shared__ int s_col[NW][kRowChunk];
+    __shared__ float s_val[NW][kRowChunk];
+    __shared__ float s_red[NW * TW];
+    const int tid = threadIdx.x;
+    const int wv = tid >> 6;
+    const int lane = tid & 63;
+    const int grp = lane / G;
+    const int lig = lane % G;
+    uint32_t ct, row;
+    if (!tile_of_workgroup(a.xcd_slices, a.ncoltiles, (uint32_t)a.m, ct, row)) return;  // the same for the whole workgroup
+    const int c0 = (int)ct * TW + lig * V;
+    const bool colok = c0 < a.n;
+    const int coff[1] = {min(c0, a.n - V)};  // see spmm_fused_kernel
+    const uint32_t ldb = (uint32_t)a.ldb;
+    int *lcol = s_col[wv];
+    float *lval = s_val[wv];
+    // unsigned: an index past the end of a list of nearly 2^31 entries must not turn negative
+    const uint32_t p0 = (uint32_t)a.rowptr[row], p1 = (uint32_t)a.rowptr[row + 1];
+    constexpr uint32_t kStride = NW * kRowChunk;
+    int cn[kPer];
+    float vn[kPer];
+    auto fetch = [&](uint32_t base) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const uint32_t p = base + i * kWave + lane;
+            cn[i] = p < p1 ? a.colidx[p] : 0;
+            vn[i] = p < p1 ? a.vals[p] : 0.f;
+        }
+    };
+    vec acc[1] = {vzero<V>()};
+    fetch(p0 + wv * kRowChunk);
+    for (uint32_t base = p0 + wv * kRowChunk; base < p1; base += kStride) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            lcol[i * kWave + lane] = cn[i];
+            lval[i * kWave + lane] = vn[i];
+        }
+        fetch(base + kStride);
+        wave_lds_sync();
+        gather_fma<V, 1, U, UA>(acc, lcol, lval, grp, (int)min((uint32_t)kRowChunk, p1 - base), S, a.B, ldb, colok, coff);
+        wave_lds_sync();
+    }
+    reduce_groups<V, G, 1>(acc);
+    if (grp == 0) {
+        if constexpr (V == 1) s_red[wv * TW + lig] = acc[0];
+        else
+#pragma unroll
+            for (int i = 0; i < V; ++i) s_red[wv * TW + lig * V + i] = acc[0][i];
+    }
+    __syncthreads();
+    if (wv == 0 && grp == 0 && colok) {
+        vec r;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            float sum = s_red[lig * V + i];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) sum += s_red[w * TW + lig * V + i];
+            if constexpr (V == 1) r = sum;
+            else r[i] = sum;
+        }
+        vstore<V, true, UA>(a.C + (int64_t)row * a.ldc + coff[0], r);
+    }
+}
+
 // Plan-free path: rows in natural order, a run of up to kNaturalRowsMax consecutive rows per wavefront (the host
 // picks the run length from m alone, so that the grid still fills the chip; nothing about the row lengths is known
 // before the launch).  A wavefront reads the row pointers of its run once (a lane per row) and then proceeds
@@ -754,6 +833,26 @@ static kernel_fn pick_natural(int V, int G, int T, bool UA) {
     }
 }
 
+template <int NW> static kernel_fn pick_row(int V, int G, bool UA) {
+#define SCORCH_ROW_G4(UA)                              \
+    switch (G) {                                       \
+        case 1: return spmm_row_kernel<4, 1, UA, NW>;  \
+        case 2: return spmm_row_kernel<4, 2, UA, NW>;  \
+        case 4: return spmm_row_kernel<4, 4, UA, NW>;  \
+        default: return spmm_row_kernel<4, 8, UA, NW>; \
+    }
+    if (V == 4) {
+        if (UA) { SCORCH_ROW_G4(true) } else { SCORCH_ROW_G4(false) }
+    }
+#undef SCORCH_ROW_G4
+    if (V == 2) return spmm_row_kernel<2, 1, false, NW>;
+    switch (G) {
+        case 1: return spmm_row_kernel<1, 1, false, NW>;
+        case 2: return spmm_row_kernel<1, 2, false, NW>;
+        default: return spmm_row_kernel<1, 4, false, NW>;
+    }
+}
+
 static inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
@@ -858,7 +957,21 @@ scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *r
         if (n >= 256 && n % 128 == 0) slice_cols = 128;
         else if (n >= 128 && n % 64 == 0) slice_cols = 64;
     }
-    const Mapping mp = pick_mapping(n, B, ldb, C, ldc, slice_cols);
+    Mapping mp = pick_mapping(n, B, ldb, C, ldc, slice_cols);
+    // Few rows, up to 2048 pairs of a row and a 32-column tile: a workgroup for each pair (spmm_row_kernel).  Measured with
+    // n = 256: 64 rows of 2458 entries 62.0 -> 11.7 us, 16 rows of 6000 66 -> 8.8, 256 rows (2048 pairs) of 5000 71 -> 58,
+    // of 1000 even; with twice the pairs the run kernel is ahead for long rows (256 rows of 5000, n = 512: 98 against 114).
+    const int row_tile = 8 * mp.V;
+    const int64_t row_units = (int64_t)m * ((n + row_tile - 1) / row_tile);
+    const bool row_kernel = row_units <= 2048;
+    // More rows than that, but fewer than two wavefronts per SIMD at one row each: narrower column tiles, at least 8
+    // lanes wide (1024 rows, n = 128, mean 1024 / 256 entries: one tile 32.4 / 16.6 us, two 21.0 / 10.7, four 26.1 / 10.6).
+    while (!row_kernel && mp.G * mp.T > 8 && (int64_t)m * mp.ncoltiles < 2048) {
+        if (mp.T == 2) mp.T = 1;
+        else mp.G /= 2;
+        mp.ncoltiles = (n + mp.G * mp.V - 1) / (mp.G * mp.V);
+        mp.xcd_slices = 1;
+    }
     ExecArgs a{};
     a.rowptr = rowptr;
     a.colidx = colidx;
@@ -869,6 +982,19 @@ scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *r
     a.ldc = ldc;
     a.m = m;
     a.n = n;
+    if (row_kernel) {
+        // up to 256 pairs, one per compute unit, get 16 wavefronts each (16 rows of 6000 entries, n = 32: 10.4 -> 8.6 us)
+        const int waves = row_units <= 256 ? 16 : kWavesPerBlock;
+        mp.T = 1;
+        mp.G = std::min(mp.G, 8);
+        a.ncoltiles = (n + mp.G * mp.V - 1) / (mp.G * mp.V);
+        a.xcd_slices = 1;
+        kernel_fn fn = waves == 16 ? pick_row<16>(mp.V, mp.G, mp.UA) : pick_row<kWavesPerBlock>(mp.V, mp.G, mp.UA);
+        hipLaunchKernelGGL(fn, dim3((uint32_t)xcd_grid_size(a.xcd_slices, a.ncoltiles, m)), dim3(waves * kWave), 0, stream, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail(e, "launch spmm_row_kernel");
+        return SCORCH_OK;
+    }
     a.xcd_slices = mp.xcd_slices;
     // rows per wavefront: 4 once that leaves a workgroup for every compute unit (measured: 1, 2, 4, 8, 16 rows on the
     // five benchmark workloads; 4 is within 1 % of the best of each that has 16 384 rows or more)
