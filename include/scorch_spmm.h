@@ -161,7 +161,8 @@ scorch_status_t scorch_spmm_csr_planned_epilogue(const scorch_spmm_plan_t *plan,
  * process ends.  The call allocates nothing on the device (no hipMalloc, hipFree or allocating library routine).
  *   - A problem whose plan needs more than SCORCH_STATIC_SCRATCH_BYTES (see scorch_spmm_plan_workspace_bytes) is
  *     refused with SCORCH_ERR_UNSUPPORTED and a message naming both sizes; nothing is enqueued then.
- *   - The pattern is analysed at every call (one wait on `stream` while the list sizes come back), then the
+ *   - The pattern is analysed at every call (the host waits for the list sizes, once; they are written to host memory
+ *     that the library allocates at its first plan), then the
  *     execution is enqueued and the call returns without waiting for it.
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two host
  *     threads) race on it and give undefined results; calls on one stream are ordered and safe.  Nothing the previous

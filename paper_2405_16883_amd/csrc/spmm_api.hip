@@ -95,17 +95,6 @@ scorch_status_t scorch_spmm_plan(int32_t m, int32_t k, int32_t n, const int32_t 
         return SCORCH_ERR_INVALID_ARG;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int32_t nnz32 = 0;
-    if (m > 0) {
-        hipError_t e = hipMemcpyAsync(&nnz32, rowptr + m, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-        if (e != hipSuccess) return hip_fail(e, "read nnz from rowptr[m]");
-        e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return hip_fail(e, "wait for nnz");
-        if (nnz32 < 0) {
-            set_error("rowptr[m] = %d is negative", nnz32);
-            return SCORCH_ERR_INVALID_ARG;
-        }
-    }
     scorch_spmm_plan_t *plan = new (std::nothrow) scorch_spmm_plan_t();
     if (!plan) {
         set_error("out of host memory");
@@ -114,20 +103,14 @@ scorch_status_t scorch_spmm_plan(int32_t m, int32_t k, int32_t n, const int32_t 
     plan->m = m;
     plan->k = k;
     plan->n = n;
-    plan->nnz = nnz32;
     plan->tuning = read_tuning_from_env();
-    plan->params = choose_params(m, k, nnz32, n, plan->tuning);
-    plan->layout = layout_workspace(m, k, nnz32, n, plan->params);
     plan->workspace = static_cast<char *>(workspace);
     if (hipGetDevice(&plan->device) != hipSuccess) plan->device = -1;
-    if (workspace_bytes < plan->layout.total) {
-        set_error("workspace of %zu bytes is smaller than the %llu needed", workspace_bytes,
-                  (unsigned long long)plan->layout.total);
-        delete plan;
-        return SCORCH_ERR_WORKSPACE_TOO_SMALL;
-    }
-    scorch_status_t st = build_plan(plan, rowptr, colidx, s);
+    scorch_status_t st = build_plan(plan, rowptr, colidx, workspace_bytes, true, s);
     if (st != SCORCH_OK) {
+        if (st == SCORCH_ERR_WORKSPACE_TOO_SMALL)
+            set_error("workspace of %zu bytes is smaller than the %llu needed", workspace_bytes,
+                      (unsigned long long)plan->layout.total);
         delete plan;
         return st;
     }

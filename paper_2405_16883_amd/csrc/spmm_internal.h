@@ -44,7 +44,7 @@ struct PlanParams {
 
 // SCORCH_SPMM_TUNE, parsed (only scorch_spmm_plan and scorch_spmm_plan_workspace_bytes call this)
 Tuning read_tuning_from_env();
-PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t);
+__host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t);
 
 struct WorkspaceLayout {
     uint64_t off_counts, off_totals, off_win, off_stage, off_wave, off_wave_span, off_items, off_split, off_partials, off_tickets, off_bpack,
@@ -54,7 +54,14 @@ struct WorkspaceLayout {
     int64_t cap_wave, cap_items, cap_split, cap_slots;
     int32_t partial_stride;
 };
-WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64_t nnz, int32_t n, const PlanParams &p);
+__host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64_t nnz, int32_t n, const PlanParams &p);
+
+// What the planning kernels report, in host memory.
+struct alignas(64) PlanResult {
+    int32_t nnz;
+    int32_t totals[5];  // wave rows, items, split rows, slots, short rows
+    int32_t done;       // written last
+};
 
 // Everything the execution kernels need, passed by value.
 struct ExecArgs {
@@ -141,8 +148,11 @@ void set_error(const char *fmt, ...);
 scorch_status_t hip_fail(hipError_t e, const char *what);
 
 // spmm_plan.hip
+// Fills in a plan whose m, k, n, tuning, workspace and device are set.  The number of stored entries is read on the device;
+// SCORCH_ERR_WORKSPACE_TOO_SMALL (nothing written) if the layout needs more than workspace_bytes.  wait_all: all
+// planning work has finished when the call returns; otherwise only what the host needs to know has arrived.
 scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
-                           hipStream_t stream);
+                           uint64_t workspace_bytes, bool wait_all, hipStream_t stream);
 
 scorch_status_t launch_rowptr_from_keys(int32_t m, int64_t count, const int32_t *keys, const int32_t *pos,
                                         bool strictly_increasing, int32_t *rowptr, int32_t *bad_flag,

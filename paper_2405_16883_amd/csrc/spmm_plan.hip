@@ -16,24 +16,34 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <mutex>
+#include <vector>
 
 namespace scorch {
 
 constexpr int kQ = 5;  // counted quantities: wave rows, items, split rows, slots, short rows
 
+// Arguments of the two planning kernels.  The number of stored entries is not known on the host when they are launched:
+// every workgroup reads it from rowptr[m] and works out the parameters and the workspace layout itself
+// (choose_params and layout_workspace are the same code on both sides), so that the host waits once, at the end.
 struct PlanArgs {
     const int32_t *rowptr;
-    int32_t m;
-    int32_t LW, CH, BCH;
-    int64_t nblk;
-    int32_t *counts;  // [kQ][nblk], turned into exclusive offsets by the scan
-    int32_t *totals;  // [kQ]
-    int32_t *wave_rows;
-    int2 *wave_span;  // entry range [p0, p1) of every wave row, beside its id
-    int4 *items;
-    int4 *split;
-    int64_t cap_wave, cap_items, cap_split;  // list capacities: writes beyond them are dropped
+    int32_t m, k, n;
+    Tuning tuning;
+    char *workspace;
+    uint64_t workspace_bytes;
+    int32_t tiles_per_block;  // a workgroup takes this many tiles of kBlock rows
+    int32_t counted;          // 1: plan_count_kernel has run; 0: every workgroup counts the rows before its own
+    PlanResult *result;       // host memory
 };
+
+// a / b for a >= 0, b > 0.  The planning kernels divide 64-bit numbers only where they have to: a division takes a
+// wavefront a third of a microsecond.
+__host__ __device__ static inline int64_t div_pos(int64_t a, int64_t b) {
+    if ((b & (b - 1)) == 0) return a >> __builtin_ctzll((unsigned long long)b);
+    if ((((uint64_t)a | (uint64_t)b) >> 32) == 0) return (uint32_t)a / (uint32_t)b;
+    return a / b;
+}
 
 struct RowClass {
     int wave, items, split, slots, is_short;
@@ -76,137 +86,210 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int &total, int *s_wa
     return base + inc - v;
 }
 
+// Sums of kQ quantities over the workgroup, returned in every thread.
+__device__ __forceinline__ void block_sums(int (&v)[kQ], int (*s_sum)[kQ] /*[4]*/) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1)
+#pragma unroll
+        for (int k = 0; k < kQ; ++k) v[k] += __shfl_xor(v[k], off, kWave);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int k = 0; k < kQ; ++k) s_sum[threadIdx.x >> 6][k] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kQ; ++k) v[k] = s_sum[0][k] + s_sum[1][k] + s_sum[2][k] + s_sum[3][k];
+}
+
+// Exclusive prefix sum of a truth value over the workgroup.
+__device__ __forceinline__ int block_rank(bool v, int &total, int *s_wave /*[4]*/) {
+    const unsigned long long mask = __ballot(v);
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    __syncthreads();
+    if (lane == 0) s_wave[wv] = (int)__builtin_popcountll(mask);
+    __syncthreads();
+    int base = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) {
+        if (w < wv) base += s_wave[w];
+        total += s_wave[w];
+    }
+    return base + (int)__builtin_popcountll(mask & ((1ull << lane) - 1ull));
+}
+
+__device__ __forceinline__ void count_row(int (&q)[kQ], int len, const PlanParams &p) {
+    const RowClass rc = classify(len, p.LW, p.CH, p.BCH);
+    q[0] += rc.wave;
+    q[1] += rc.items;
+    q[2] += rc.split;
+    q[3] += rc.slots;
+    q[4] += rc.is_short;
+}
+
+// counts[q][b] = quantity q over the rows of workgroup b.
 __global__ __launch_bounds__(kBlock) void plan_count_kernel(const PlanArgs a) {
-    __shared__ int s_wave[kWavesPerBlock];
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    RowClass rc{0, 0, 0, 0, 0};
-    if (i < a.m) rc = classify(a.rowptr[i + 1] - a.rowptr[i], a.LW, a.CH, a.BCH);
-    const int q[kQ] = {rc.wave, rc.items, rc.split, rc.slots, rc.is_short};
+    __shared__ int s_sum[kWavesPerBlock][kQ];
+    const int32_t nnz = a.rowptr[a.m];
+    if (nnz < 0) return;
+    const PlanParams p = choose_params(a.m, a.k, nnz, a.n, a.tuning);
+    if (layout_workspace(a.m, a.k, nnz, a.n, p).total > a.workspace_bytes) return;  // the host reports it
+    int32_t *counts = reinterpret_cast<int32_t *>(a.workspace);  // the first section of the layout
+    int q[kQ] = {0, 0, 0, 0, 0};
+    const int64_t row0 = (int64_t)blockIdx.x * a.tiles_per_block * kBlock + threadIdx.x;
+    for (int t = 0; t < a.tiles_per_block; ++t) {
+        const int64_t i = row0 + (int64_t)t * kBlock;
+        if (i < a.m) count_row(q, a.rowptr[i + 1] - a.rowptr[i], p);
+    }
+    block_sums(q, s_sum);
+    if (threadIdx.x < kQ) {
+        int v = q[0];
 #pragma unroll
-    for (int k = 0; k < kQ; ++k) {
-        int total;
-        (void)block_exclusive_scan(q[k], total, s_wave);
-        if (threadIdx.x == 0) a.counts[(int64_t)k * a.nblk + blockIdx.x] = total;
+        for (int k = 1; k < kQ; ++k) v = (int)threadIdx.x == k ? q[k] : v;
+        counts[(int)threadIdx.x * (int)gridDim.x + (int)blockIdx.x] = v;
     }
 }
 
-// One workgroup of 1024 threads turns each of the kQ count arrays into exclusive offsets and stores the totals:
-// every thread sums a contiguous slice, the 1024 slice sums are scanned with wavefront shuffles (16 wavefronts),
-// then every thread rewrites its slice.
-__global__ __launch_bounds__(1024) void plan_scan_kernel(const PlanArgs a) {
-    __shared__ int s_wave[16];
+// Writes every list of the plan, tile of kBlock rows by tile.
+//   lists    stable compaction of the row classes (ascending row order): what precedes the workgroup's rows comes from
+//            the counts of the workgroups before it, or is counted here when there are few of them
+//   windows  win_row_start[w] = number of rows whose key rowptr[i] + ALPHA*i is below w*BN.  A tile owns the windows
+//            that start in it; it keeps the row pointers of its rows and of the 64 after them in LDS, and every thread
+//            finds the first and the last row of a window there.
+//   stages   what a window's wavefront stages in LDS: the entries from the first to the last short row of the window
+//            (rows of up to LW entries), at most kStageMax of them, so that the execution kernel can fetch colidx/vals at
+//            once instead of waiting for the row pointers first.  (first entry, number of entries), or (0, -1)
+//            for a window without short rows.
+// Bound by launch and memory latency, hence one kernel for all of it with its first loads issued together.  Lists,
+// windows and stages took a launch each before, with a scan in between and for every window a binary search over rowptr
+// in global memory: 19 717 rows, 108 000 entries: five kernels of 21 us in all, now two of 12; a coordinate list of that size
+// through scorch_coo_to_csr_rowptr and scorch_spmm_csr_static, with two waits before and one now: 80.7 -> 32.1 us.
+__global__ __launch_bounds__(kBlock) void plan_build_kernel(const PlanArgs a) {
+    __shared__ int s_wave[kWavesPerBlock];
+    __shared__ int s_sum[kWavesPerBlock][kQ];
+    __shared__ int s_rp[kBlock + kWindowRowsMax + 1];
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
-    const int64_t per = (a.nblk + 1023) / 1024;
-    for (int k = 0; k < kQ; ++k) {
-        int32_t *c = a.counts + (int64_t)k * a.nblk;
-        const int64_t lo = std::min<int64_t>((int64_t)tid * per, a.nblk);
-        const int64_t hi = std::min<int64_t>(lo + per, a.nblk);
-        int sum = 0;
-        for (int64_t j = lo; j < hi; ++j) sum += c[j];
-        int inc = sum;
+    const int nblk = (int)gridDim.x, blk = (int)blockIdx.x;
+    const bool last_block = blk == nblk - 1;
+    const int row_first = blk * a.tiles_per_block * kBlock;  // below m < 2^31 for every workgroup of the grid
+    const int32_t *counts = reinterpret_cast<const int32_t *>(a.workspace);
+    // everything that does not depend on the parameters is requested at once: the number of entries, the counts of the
+    // workgroups before this one, the row pointers of the first tile
+    const int32_t nnz = a.m > 0 ? a.rowptr[a.m] : 0;
+    int run[kQ] = {0, 0, 0, 0, 0};
+    if (a.counted)
+        for (int j = tid; j < blk; j += kBlock)
 #pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int o = __shfl_up(inc, off, kWave);
-            if (lane >= off) inc += o;
+            for (int k = 0; k < kQ; ++k) run[k] += counts[k * nblk + j];
+    const int32_t rp_first = a.m > 0 ? a.rowptr[min((int64_t)row_first + tid, (int64_t)a.m)] : 0;
+    const int32_t rp_first2 = a.m > 0 && tid <= kWindowRowsMax ? a.rowptr[min((int64_t)row_first + kBlock + tid, (int64_t)a.m)] : 0;
+    PlanParams p{};
+    WorkspaceLayout L{};
+    bool fits = nnz >= 0;
+    if (fits) {
+        p = choose_params(a.m, a.k, nnz, a.n, a.tuning);
+        L = layout_workspace(a.m, a.k, nnz, a.n, p);
+        fits = L.total <= a.workspace_bytes;
+    }
+    if (fits) {
+        int32_t *win_row_start = reinterpret_cast<int32_t *>(a.workspace + L.off_win);
+        int2 *stage = reinterpret_cast<int2 *>(a.workspace + L.off_stage);
+        int32_t *wave_rows = reinterpret_cast<int32_t *>(a.workspace + L.off_wave);
+        int2 *wave_span = reinterpret_cast<int2 *>(a.workspace + L.off_wave_span);
+        int4 *items = reinterpret_cast<int4 *>(a.workspace + L.off_items);
+        int4 *split = reinterpret_cast<int4 *>(a.workspace + L.off_split);
+        if (!a.counted) {
+#pragma unroll 4
+            for (int i = tid; i < row_first; i += kBlock) count_row(run, a.rowptr[i + 1] - a.rowptr[i], p);
         }
-        __syncthreads();  // s_wave of the previous quantity has been read
-        if (lane == kWave - 1) s_wave[wv] = inc;
-        __syncthreads();
-        int base = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) {
-            const int t = s_wave[w];
-            if (w < wv) base += t;
-            total += t;
-        }
-        if (tid == 0) a.totals[k] = total;
-        int run = base + inc - sum;
-        for (int64_t j = lo; j < hi; ++j) {
-            const int t = c[j];
-            c[j] = run;
-            run += t;
-        }
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void plan_scatter_kernel(const PlanArgs a) {
-    __shared__ int s_wave[kWavesPerBlock];
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    RowClass rc{0, 0, 0, 0, 0};
-    int p0 = 0, p1 = 0;
-    if (i < a.m) {
-        p0 = a.rowptr[i];
-        p1 = a.rowptr[i + 1];
-        rc = classify(p1 - p0, a.LW, a.CH, a.BCH);
-    }
-    int total;
-    const int pos_wave = a.counts[0 * a.nblk + blockIdx.x] + block_exclusive_scan(rc.wave, total, s_wave);
-    const int pos_item = a.counts[1 * a.nblk + blockIdx.x] + block_exclusive_scan(rc.items, total, s_wave);
-    const int pos_split = a.counts[2 * a.nblk + blockIdx.x] + block_exclusive_scan(rc.split, total, s_wave);
-    const int pos_slot = a.counts[3 * a.nblk + blockIdx.x] + block_exclusive_scan(rc.slots, total, s_wave);
-    // The capacities hold for every valid rowptr; the guards only keep a malformed one in bounds
-    // (the host then reports the overflow from the totals).
-    if (rc.wave && pos_wave < a.cap_wave) {
-        a.wave_rows[pos_wave] = (int)i;
-        a.wave_span[pos_wave] = make_int2(p0, p1);
-    }
-    for (int c = 0; c < rc.items && (int64_t)pos_item + c < a.cap_items; ++c) {
-        const int b = p0 + c * a.BCH;
-        a.items[pos_item + c] = make_int4((int)i, b, min(p1, b + a.BCH), rc.split ? pos_slot + c : -1);
-    }
-    if (rc.split && pos_split < a.cap_split) a.split[pos_split] = make_int4((int)i, pos_slot, rc.items, 0);
-}
-
-// win_row_start[w] = number of rows whose key rowptr[i] + ALPHA*i is below w*BN.
-__global__ __launch_bounds__(kBlock) void plan_window_kernel(const int32_t *rowptr, int32_t m, int32_t BN,
-                                                             int32_t ALPHA, int64_t n_windows,
-                                                             int32_t *win_row_start) {
-    const int64_t w = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (w > n_windows) return;
-    if (w == n_windows) {
-        win_row_start[w] = m;
-        return;
-    }
-    const int64_t target = w * (int64_t)BN;
-    int64_t lo = 0, hi = m;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        const int64_t key = (int64_t)rowptr[mid] + (int64_t)ALPHA * mid;
-        if (key < target) lo = mid + 1;
-        else hi = mid;
-    }
-    win_row_start[w] = (int32_t)lo;
-}
-
-// What a window's wavefront stages in LDS: the entries from the first to the last short row of the window (rows of
-// up to LW entries; the window holds at most 64 rows), at most stage_max of them.  Stored in the plan so that the
-// execution kernel can fetch colidx/vals at once instead of waiting for the row pointers first.
-// stage[w] = (first entry, number of entries), or (0, -1) for a window without short rows.
-__global__ __launch_bounds__(kBlock) void plan_stage_kernel(const int32_t *rowptr, const int32_t *win_row_start,
-                                                            int64_t n_windows, int32_t LW, int32_t stage_max,
-                                                            int2 *stage) {
-    const int64_t w = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (w >= n_windows) return;
-    const int r0 = win_row_start[w];
-    const int r1 = min(win_row_start[w + 1], r0 + kWindowRowsMax);
-    int first = -1, last = -1;
-    int prev = r0 < r1 ? rowptr[r0] : 0;
-    int sbeg = 0, send = 0;
-    for (int r = r0; r < r1; ++r) {
-        const int next = rowptr[r + 1];
-        if (next - prev <= LW) {
-            if (first < 0) {
-                first = r;
-                sbeg = prev;
+        block_sums(run, s_sum);
+        for (int t = 0; t < a.tiles_per_block; ++t) {
+            const int64_t t0 = (int64_t)row_first + (int64_t)t * kBlock;
+            if (t0 >= a.m && !(a.m == 0 && t == 0)) break;
+            const int rows = (int)min((int64_t)kBlock, a.m - t0);  // 0 only for an empty matrix
+            __syncthreads();  // s_rp of the previous tile has been read
+            if (t == 0) {
+                s_rp[tid] = rp_first;
+                if (tid <= kWindowRowsMax) s_rp[kBlock + tid] = rp_first2;
+            } else {
+                for (int i = tid; i < kBlock + kWindowRowsMax + 1; i += kBlock) s_rp[i] = a.rowptr[min(t0 + i, (int64_t)a.m)];
             }
-            last = r;
-            send = next;
+            const int before = t0 > 0 ? a.rowptr[t0 - 1] : 0;
+            __syncthreads();
+            // ---- lists ----
+            RowClass rc{0, 0, 0, 0, 0};
+            int p0 = 0, p1 = 0;
+            if (tid < rows) {
+                p0 = s_rp[tid];
+                p1 = s_rp[tid + 1];
+                rc = classify(p1 - p0, p.LW, p.CH, p.BCH);
+            }
+            int total;
+            const int pos_wave = run[0] + block_rank(rc.wave, total, s_wave);
+            run[0] += total;
+            int pos_item = 0, pos_split = 0, pos_slot = 0;
+            if (__syncthreads_or(rc.items)) {  // few tiles hold a long row
+                pos_item = run[1] + block_exclusive_scan(rc.items, total, s_wave);
+                run[1] += total;
+                pos_split = run[2] + block_rank(rc.split, total, s_wave);
+                run[2] += total;
+                pos_slot = run[3] + block_exclusive_scan(rc.slots, total, s_wave);
+                run[3] += total;
+            }
+            (void)block_rank(rc.is_short, total, s_wave);
+            run[4] += total;
+            // The capacities hold for every valid rowptr; the guards only keep a malformed one in bounds
+            // (the host then reports the overflow from the totals).
+            if (rc.wave && pos_wave < L.cap_wave) {
+                wave_rows[pos_wave] = (int)t0 + tid;
+                wave_span[pos_wave] = make_int2(p0, p1);
+            }
+            for (int c = 0; c < rc.items && (int64_t)pos_item + c < L.cap_items; ++c) {
+                const int b = p0 + c * p.BCH;
+                items[pos_item + c] = make_int4((int)t0 + tid, b, min(p1, b + p.BCH), rc.split ? pos_slot + c : -1);
+            }
+            if (rc.split && pos_split < L.cap_split) split[pos_split] = make_int4((int)t0 + tid, pos_slot, rc.items, 0);
+            // ---- windows that start in this tile (the last tile also owns those that start past the last row) ----
+            auto key = [&](int j) { return (int64_t)s_rp[j] + (int64_t)p.ALPHA * (t0 + j); };
+            const bool last_tile = t0 + rows >= a.m;
+            const int own = last_tile ? rows : rows - 1;  // index of the last row (or of the end) that this tile owns
+            const int64_t w_lo = t0 > 0 ? max((int64_t)0, div_pos(max((int64_t)0, (int64_t)before + (int64_t)p.ALPHA * (t0 - 1)), p.BN) + 1) : 0;
+            const int64_t w_hi = min(L.n_windows - 1, div_pos(max((int64_t)0, key(own)), p.BN));
+            for (int64_t w = w_lo + tid; w <= w_hi; w += kBlock) {
+                int lo = 0, hi = own;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (key(mid) < w * p.BN) lo = mid + 1;
+                    else hi = mid;
+                }
+                const int r0 = lo;
+                win_row_start[w] = (int)(t0 + r0);
+                hi = (int)min((int64_t)r0 + kWindowRowsMax, a.m - t0);  // a window holds at most kWindowRowsMax rows
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (key(mid) < (w + 1) * p.BN) lo = mid + 1;
+                    else hi = mid;
+                }
+                int sbeg = 0, send = -1;
+                for (int r = r0, prev = s_rp[r0]; r < lo; ++r) {
+                    const int next = s_rp[r + 1];
+                    if (next - prev <= p.LW) {
+                        if (send < 0) sbeg = prev;
+                        send = next;
+                    }
+                    prev = next;
+                }
+                stage[w] = send < 0 ? make_int2(0, -1) : make_int2(sbeg, min(send - sbeg, kStageMax));
+            }
+            if (last_tile && tid == 0) win_row_start[L.n_windows] = a.m;
         }
-        prev = next;
     }
-    stage[w] = first < 0 ? make_int2(0, -1) : make_int2(sbeg, min(send - sbeg, stage_max));
-    (void)last;
+    if (last_block && tid == 0) {
+        a.result->nnz = nnz;
+#pragma unroll
+        for (int k = 0; k < kQ; ++k) a.result->totals[k] = run[k];
+        __hip_atomic_store(&a.result->done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // Sets *flag when some row's column indices are not strictly increasing (one wavefront per row).
@@ -290,7 +373,8 @@ __global__ __launch_bounds__(kBlock) void plan_hotmask_kernel(const int32_t *deg
     }
 }
 
-static scorch_status_t mark_hot_columns(scorch_spmm_plan_t *plan, const int32_t *colidx, bool forced, hipStream_t stream) {
+static scorch_status_t mark_hot_columns(scorch_spmm_plan_t *plan, const int32_t *colidx, bool forced, bool wait_all,
+                                        hipStream_t stream) {
     const WorkspaceLayout &L = plan->layout;
     char *ws = plan->workspace;
     int32_t *deg = reinterpret_cast<int32_t *>(ws + L.off_coldeg);
@@ -335,6 +419,7 @@ static scorch_status_t mark_hot_columns(scorch_spmm_plan_t *plan, const int32_t 
     hipLaunchKernelGGL(plan_hotmask_kernel, dim3(g3), dim3(kBlock), 0, stream, deg, plan->k, min_bin, nwords, mask);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "launch plan_hotmask_kernel");
+    if (wait_all && (e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e, "wait for plan_hotmask_kernel");
     plan->n_hot = (int32_t)std::min<int64_t>(rows, 0x7fffffff);
     return SCORCH_OK;
 }
@@ -375,10 +460,9 @@ scorch_status_t launch_rowptr_from_keys(int32_t m, int64_t count, const int32_t 
 // ------------------------------------------------------------------------------------------
 Tuning read_tuning_from_env() { return parse_tuning(std::getenv("SCORCH_SPMM_TUNE")); }
 
-static int32_t pow2_floor(int64_t x) {
-    int32_t p = 1;
-    while ((int64_t)p * 2 <= x) p *= 2;
-    return p;
+// largest power of two that is at most x (1 <= x), 2^30 at most
+__host__ __device__ static int32_t pow2_floor(int64_t x) {
+    return 1 << (63 - __builtin_clzll((unsigned long long)(x < (1ll << 30) ? x : (1ll << 30))));
 }
 
 // XCD-sliced execution pays when B as a whole overflows an XCD's 4 MB L2 at least twice over but a 128-byte-wide
@@ -393,11 +477,11 @@ static int32_t pow2_floor(int64_t x) {
 // 50 k to 1 M nodes, 5 to 100 entries per row, n = 128 to 1024 in multiples of 64: 5-30 % less time than whole rows
 // (one case of 21: 1 %); uniform and pruned patterns outside the 128-byte rule: 0-43 % less; n = 160: 0-16 % less;
 // n = 96, 100, 132: 4-30 % more, hence the multiple of 64.  Returns the columns per slice (0 = whole rows).
-static int32_t want_sliced(int32_t m, int32_t k, int64_t nnz, int32_t n, bool hot_candidate) {
+__host__ __device__ static int32_t want_sliced(int32_t m, int32_t k, int64_t nnz, int32_t n, bool hot_candidate) {
     if (m <= 0 || n % 4 != 0 || n < 2 * kSliceCols) return 0;
     const int64_t slice_bytes = (int64_t)k * kSliceCols * 4;
     const int64_t b_bytes = (int64_t)k * n * 4;
-    const bool long_rows = nnz / m >= 64 && b_bytes >= 8ll << 20;
+    const bool long_rows = nnz >= 64 * (int64_t)m && b_bytes >= 8ll << 20;
     if (long_rows && slice_bytes <= kL2SliceBudget) return kSliceCols;
     if (hot_candidate) return 0;  // the hot/cold split needs whole rows
     if (long_rows && slice_bytes <= 13ll << 20 && n >= 128) return kSliceCols;  // n = 64 with a 13 MB slice: 2-6 % more time
@@ -413,8 +497,8 @@ static int32_t want_sliced(int32_t m, int32_t k, int64_t nnz, int32_t n, bool ho
 //   narrow tiles: about even with the gather kernels at 10 % (0.50 against 0.52 ms, 0.54 against 0.62), behind at
 //     4-8 %; used from 10 % upwards when only they give 256 workgroups.
 // Returns the kernel shape (0 = do not use, 1 = 256-column tiles, 2 = 512-column tiles).
-static int32_t want_panel(int32_t m, int32_t k, int64_t nnz, int32_t n) {
-    if (m <= 0 || k < 1024 || n % 4 != 0 || n < kPanelCols || nnz / m < 128) return 0;
+__host__ __device__ static int32_t want_panel(int32_t m, int32_t k, int64_t nnz, int32_t n) {
+    if (m <= 0 || k < 1024 || n % 4 != 0 || n < kPanelCols || nnz < 128 * (int64_t)m) return 0;
     const double density = (double)nnz / ((double)m * (double)k);
     const int64_t row_blocks = ((int64_t)m + 63) / 64;
     if (n >= 2 * kPanelCols && density >= 0.03 && row_blocks * ((n + 2 * kPanelCols - 1) / (2 * kPanelCols)) >= 256) return 2;
@@ -426,7 +510,7 @@ static int32_t want_panel(int32_t m, int32_t k, int64_t nnz, int32_t n) {
     return 0;
 }
 
-PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t) {
+__host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t) {
     PlanParams p;
     p.ALPHA = 4;
     // Windows of 128 key units, but small problems get smaller windows so that there are a few thousand
@@ -488,17 +572,17 @@ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tun
     return p;
 }
 
-static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
+__host__ __device__ static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) & ~(a - 1); }  // a: a power of two
 
-WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64_t nnz, int32_t n, const PlanParams &p) {
+__host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64_t nnz, int32_t n, const PlanParams &p) {
     WorkspaceLayout L{};
     L.nblk = ((int64_t)m + kBlock - 1) / kBlock;
-    L.n_windows = (nnz + (int64_t)p.ALPHA * m) / p.BN + 1;
-    L.cap_wave = std::min<int64_t>(m, nnz / (p.LW + 1));
-    const int64_t long_rows = std::min<int64_t>(m, nnz / ((int64_t)p.CH + 1));
-    L.cap_items = nnz / p.BCH + long_rows;
-    L.cap_split = std::min<int64_t>(m, nnz / ((int64_t)p.BCH + 1));
-    L.cap_slots = nnz / p.BCH + L.cap_split;
+    L.n_windows = div_pos(nnz + (int64_t)p.ALPHA * m, p.BN) + 1;
+    L.cap_wave = std::min<int64_t>(m, div_pos(nnz, p.LW + 1));
+    const int64_t long_rows = std::min<int64_t>(m, div_pos(nnz, (int64_t)p.CH + 1));
+    L.cap_items = div_pos(nnz, p.BCH) + long_rows;
+    L.cap_split = std::min<int64_t>(m, div_pos(nnz, (int64_t)p.BCH + 1));
+    L.cap_slots = div_pos(nnz, p.BCH) + L.cap_split;
     L.partial_stride = (n + 3) / 4 * 4;
     uint64_t off = 0;
     L.off_counts = off;
@@ -535,86 +619,129 @@ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64_t nnz, int32_t n, c
     return L;
 }
 
-scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
-                           hipStream_t stream) {
-    const WorkspaceLayout &L = plan->layout;
-    char *ws = plan->workspace;
-    int32_t totals[kQ] = {0, 0, 0, 0, 0};
-    int32_t unsorted = 0;
-    // The panel kernel needs every row's columns in strictly increasing order; without colidx this cannot be
-    // verified, so the mode is dropped.
-    if (plan->params.PANEL && (!colidx || plan->m == 0 || plan->nnz == 0)) plan->params.PANEL = 0;
-    if (plan->params.PANEL) {
-        int32_t *flag = reinterpret_cast<int32_t *>(ws + L.off_totals) + 8;
-        hipError_t e = hipMemsetAsync(flag, 0, sizeof(int32_t), stream);
-        if (e != hipSuccess) return hip_fail(e, "clear sortedness flag");
-        const uint32_t g = (uint32_t)std::min<int64_t>(((int64_t)plan->m + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 16);
-        hipLaunchKernelGGL(plan_sorted_kernel, dim3(g), dim3(kBlock), 0, stream, rowptr, colidx, plan->m, flag);
-        e = hipMemcpyAsync(&unsorted, flag, sizeof(int32_t), hipMemcpyDeviceToHost, stream);
-        if (e != hipSuccess) return hip_fail(e, "copy sortedness flag");
+// How the rows are dealt to the workgroups of the planning kernels: at most kPlanBlocksMax workgroups, so that the
+// counts of all workgroups before one are few enough to be added up by each.  Up to kPlanRecount workgroups the counting launch
+// is left out and every workgroup counts the rows before its own, 8 batches of row pointers at most; with 78 of them the
+// build kernel took 30 us instead of 7.7 + 4.3 for the counts.
+constexpr int32_t kPlanBlocksMax = 1024;
+constexpr int32_t kPlanRecount = 8;
+
+// Slots of host memory that the planning kernels write their result to: taken for the length of one call and given back
+// (as many as calls were in flight at once, 64 bytes each).
+static std::mutex g_result_mutex;
+static std::vector<PlanResult *> g_result_free;
+
+static scorch_status_t take_result(PlanResult **out) {
+    std::lock_guard<std::mutex> lock(g_result_mutex);
+    if (g_result_free.empty()) {
+        constexpr size_t kSlots = 4096 / sizeof(PlanResult);
+        void *page = nullptr;
+        hipError_t e = hipHostMalloc(&page, kSlots * sizeof(PlanResult), hipHostMallocPortable | hipHostMallocMapped);
+        if (e != hipSuccess) return hip_fail(e, "allocate host memory for the plan's result");
+        for (size_t i = 0; i < kSlots; ++i) g_result_free.push_back(static_cast<PlanResult *>(page) + i);
     }
-    plan->n_hot = 0;
-    plan->hot_share = 0.f;
-    if (plan->params.HOT && colidx && plan->nnz > 0 && plan->k > 0) {
-        scorch_status_t st = mark_hot_columns(plan, colidx, plan->tuning.hot > 0, stream);
-        if (st != SCORCH_OK) return st;
-    }
-    if (plan->m > 0) {
-        PlanArgs a{};
-        a.rowptr = rowptr;
-        a.m = plan->m;
-        a.LW = plan->params.LW;
-        a.CH = plan->params.CH;
-        a.BCH = plan->params.BCH;
-        a.nblk = L.nblk;
-        a.counts = reinterpret_cast<int32_t *>(ws + L.off_counts);
-        a.totals = reinterpret_cast<int32_t *>(ws + L.off_totals);
-        a.wave_rows = reinterpret_cast<int32_t *>(ws + L.off_wave);
-        a.wave_span = reinterpret_cast<int2 *>(ws + L.off_wave_span);
-        a.items = reinterpret_cast<int4 *>(ws + L.off_items);
-        a.split = reinterpret_cast<int4 *>(ws + L.off_split);
-        a.cap_wave = L.cap_wave;
-        a.cap_items = L.cap_items;
-        a.cap_split = L.cap_split;
-        hipLaunchKernelGGL(plan_count_kernel, dim3((uint32_t)L.nblk), dim3(kBlock), 0, stream, a);
-        hipLaunchKernelGGL(plan_scan_kernel, dim3(1), dim3(1024), 0, stream, a);
-        hipLaunchKernelGGL(plan_scatter_kernel, dim3((uint32_t)L.nblk), dim3(kBlock), 0, stream, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "launch plan kernels");
-        e = hipMemcpyAsync(totals, a.totals, sizeof(totals), hipMemcpyDeviceToHost, stream);
-        if (e != hipSuccess) return hip_fail(e, "copy plan totals");
-    }
-    {
-        // also for m == 0: the window table then reads [0, 0]
-        const int64_t wblocks = (L.n_windows + 1 + kBlock - 1) / kBlock;
-        hipLaunchKernelGGL(plan_window_kernel, dim3((uint32_t)wblocks), dim3(kBlock), 0, stream, rowptr, plan->m,
-                           plan->params.BN, plan->params.ALPHA, L.n_windows,
-                           reinterpret_cast<int32_t *>(ws + L.off_win));
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "launch plan_window_kernel");
-        hipLaunchKernelGGL(plan_stage_kernel, dim3((uint32_t)wblocks), dim3(kBlock), 0, stream, rowptr,
-                           reinterpret_cast<const int32_t *>(ws + L.off_win), L.n_windows, plan->params.LW, kStageMax,
-                           reinterpret_cast<int2 *>(ws + L.off_stage));
-        e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "launch plan_stage_kernel");
-        // the arrival counters of split rows start at zero; every launch leaves them at zero again
-        if (L.cap_slots > 0) {
-            e = hipMemsetAsync(ws + L.off_tickets, 0, (size_t)L.cap_slots * L.ticket_tiles * 4, stream);
-            if (e != hipSuccess) return hip_fail(e, "clear arrival counters");
+    *out = g_result_free.back();
+    g_result_free.pop_back();
+    return SCORCH_OK;
+}
+
+static void give_result_back(PlanResult *r) {
+    std::lock_guard<std::mutex> lock(g_result_mutex);
+    g_result_free.push_back(r);
+}
+
+// The result once it has arrived.  wait_all: everything enqueued on the stream so far has finished as well.  Otherwise
+// the host only watches for the result itself, which arrives some microseconds before a wait on the stream returns; after
+// about a millisecond (the stream was busy with something else) it waits for the stream.
+static scorch_status_t wait_for_result(PlanResult *r, bool wait_all, hipStream_t stream) {
+    if (!wait_all) {
+        for (int i = 0; i < 20000; ++i) {
+            if (__atomic_load_n(&r->done, __ATOMIC_ACQUIRE)) return SCORCH_OK;
+            __builtin_ia32_pause();
         }
-        e = hipStreamSynchronize(stream);
-        if (e != hipSuccess) return hip_fail(e, "wait for plan kernels");
     }
-    if (unsorted) plan->params.PANEL = 0;
-    plan->n_wave = totals[0];
-    plan->n_items = totals[1];
-    plan->n_split = totals[2];
-    plan->n_slots = totals[3];
-    plan->n_short = totals[4];
+    const hipError_t e = hipStreamSynchronize(stream);
+    if (e != hipSuccess) return hip_fail(e, "wait for plan kernels");
+    if (!__atomic_load_n(&r->done, __ATOMIC_ACQUIRE)) {
+        set_error("plan kernels ended without a result");
+        return SCORCH_ERR_HIP;
+    }
+    return SCORCH_OK;
+}
+
+scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
+                           uint64_t workspace_bytes, bool wait_all, hipStream_t stream) {
+    PlanResult *result = nullptr;
+    scorch_status_t st = take_result(&result);
+    if (st != SCORCH_OK) return st;
+    result->done = 0;
+    const int64_t tiles = std::max<int64_t>(1, ((int64_t)plan->m + kBlock - 1) / kBlock);
+    PlanArgs a{};
+    a.rowptr = rowptr;
+    a.m = plan->m;
+    a.k = plan->k;
+    a.n = plan->n;
+    a.tuning = plan->tuning;
+    a.workspace = plan->workspace;
+    a.workspace_bytes = workspace_bytes;
+    a.tiles_per_block = (int32_t)((tiles + kPlanBlocksMax - 1) / kPlanBlocksMax);
+    const uint32_t nblk = (uint32_t)((tiles + a.tiles_per_block - 1) / a.tiles_per_block);
+    a.counted = nblk > (uint32_t)kPlanRecount;
+    a.result = result;
+    if (a.counted) hipLaunchKernelGGL(plan_count_kernel, dim3(nblk), dim3(kBlock), 0, stream, a);
+    hipLaunchKernelGGL(plan_build_kernel, dim3(nblk), dim3(kBlock), 0, stream, a);
+    hipError_t e = hipGetLastError();
+    st = e != hipSuccess ? hip_fail(e, "launch plan kernels") : wait_for_result(result, wait_all, stream);
+    const PlanResult got = *result;
+    // after a failed wait the kernel may still be running: its slot is not used again
+    if (st != SCORCH_OK) return st;
+    give_result_back(result);
+    if (got.nnz < 0) {
+        set_error("rowptr[m] = %d is negative", got.nnz);
+        return SCORCH_ERR_INVALID_ARG;
+    }
+    plan->nnz = got.nnz;
+    plan->params = choose_params(plan->m, plan->k, plan->nnz, plan->n, plan->tuning);
+    plan->layout = layout_workspace(plan->m, plan->k, plan->nnz, plan->n, plan->params);
+    const WorkspaceLayout &L = plan->layout;
+    if (L.total > workspace_bytes) return SCORCH_ERR_WORKSPACE_TOO_SMALL;  // the caller words the message
+    char *ws = plan->workspace;
+    plan->n_wave = got.totals[0];
+    plan->n_items = got.totals[1];
+    plan->n_split = got.totals[2];
+    plan->n_slots = got.totals[3];
+    plan->n_short = got.totals[4];
     if (plan->n_wave > L.cap_wave || plan->n_items > L.cap_items || plan->n_split > L.cap_split ||
         plan->n_slots > L.cap_slots) {
         set_error("plan lists exceed the workspace bound (rowptr changed or is not non-decreasing?)");
         return SCORCH_ERR_INVALID_ARG;
+    }
+    // The panel kernel needs every row's columns in strictly increasing order; without colidx this cannot be
+    // verified, so the mode is dropped.
+    if (plan->params.PANEL && (!colidx || plan->m == 0 || plan->nnz == 0)) plan->params.PANEL = 0;
+    if (plan->params.PANEL) {
+        int32_t unsorted = 0;
+        int32_t *flag = reinterpret_cast<int32_t *>(ws + L.off_totals);
+        e = hipMemsetAsync(flag, 0, sizeof(int32_t), stream);
+        if (e != hipSuccess) return hip_fail(e, "clear sortedness flag");
+        const uint32_t g = (uint32_t)std::min<int64_t>(((int64_t)plan->m + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 16);
+        hipLaunchKernelGGL(plan_sorted_kernel, dim3(g), dim3(kBlock), 0, stream, rowptr, colidx, plan->m, flag);
+        e = hipMemcpyAsync(&unsorted, flag, sizeof(int32_t), hipMemcpyDeviceToHost, stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) return hip_fail(e, "read the sortedness flag");
+        if (unsorted) plan->params.PANEL = 0;
+    }
+    plan->n_hot = 0;
+    plan->hot_share = 0.f;
+    if (plan->params.HOT && colidx && plan->nnz > 0 && plan->k > 0) {
+        st = mark_hot_columns(plan, colidx, plan->tuning.hot > 0, wait_all, stream);
+        if (st != SCORCH_OK) return st;
+    }
+    // the arrival counters of split rows (only used with fix=1) start at zero; every launch leaves them at zero again
+    if (L.cap_slots > 0 && plan->tuning.fix > 0) {
+        e = hipMemsetAsync(ws + L.off_tickets, 0, (size_t)L.cap_slots * L.ticket_tiles * 4, stream);
+        if (e == hipSuccess && wait_all) e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) return hip_fail(e, "clear arrival counters");
     }
     return SCORCH_OK;
 }

@@ -72,38 +72,28 @@ extern "C" scorch_status_t scorch_spmm_csr_static(int32_t m, int32_t k, int32_t 
     char *ws = nullptr;
     scorch_status_t st = scratch_of_current_device(&ws);
     if (st != SCORCH_OK) return st;
-    int32_t nnz32 = 0;
-    hipError_t e = hipMemcpyAsync(&nnz32, rowptr + m, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "read nnz from rowptr[m]");
-    if (nnz32 < 0) {
-        set_error("rowptr[m] = %d is negative", nnz32);
-        return SCORCH_ERR_INVALID_ARG;
-    }
-    if (nnz32 > 0 && (!colidx || !vals || !B)) {
-        set_error("colidx, vals and B must not be NULL when nnz > 0");
-        return SCORCH_ERR_INVALID_ARG;
-    }
     scorch_spmm_plan_t plan{};  // on the host stack: nothing is allocated, nothing outlives the call but the enqueued work
     plan.m = m;
     plan.k = k;
     plan.n = n;
-    plan.nnz = nnz32;
     plan.tuning = read_tuning_from_env();
-    plan.params = choose_params(m, k, nnz32, n, plan.tuning);
-    plan.layout = layout_workspace(m, k, nnz32, n, plan.params);
     plan.workspace = ws;
     if (hipGetDevice(&plan.device) != hipSuccess) plan.device = -1;
-    if (plan.layout.total > kStaticScratchBytes) {
+    // The array keeps what the previous call left.  Everything execution reads is rewritten by build_plan (it clears
+    // its own flags and counters and writes every list up to the counts it returns); the partial rows are written
+    // by the pieces of a split row before the same launch order reads them.  The host waits until it knows the list sizes;
+    // the execution is ordered behind the planning kernels by the stream.
+    st = build_plan(&plan, rowptr, colidx && vals && B ? colidx : nullptr, kStaticScratchBytes, false, s);
+    if ((st == SCORCH_OK || st == SCORCH_ERR_WORKSPACE_TOO_SMALL) && plan.nnz > 0 && (!colidx || !vals || !B)) {
+        set_error("colidx, vals and B must not be NULL when nnz > 0");
+        return SCORCH_ERR_INVALID_ARG;
+    }
+    if (st == SCORCH_ERR_WORKSPACE_TOO_SMALL) {
         set_error("this problem needs %llu bytes of plan workspace, the static scratch array holds %zu: "
                   "use scorch_spmm_plan with a workspace of your own",
                   (unsigned long long)plan.layout.total, kStaticScratchBytes);
         return SCORCH_ERR_UNSUPPORTED;
     }
-    // The array keeps what the previous call left.  Everything execution reads is rewritten by build_plan (it clears
-    // its own flags and counters and writes every list up to the counts it returns); the partial rows are written
-    // by the pieces of a split row before the same launch order reads them.
-    st = build_plan(&plan, rowptr, colidx, s);  // waits for the stream: the list sizes come back to the host
     if (st != SCORCH_OK) return st;
     return launch_planned(&plan, rowptr, colidx, vals, B, ldb, C, ldc, nullptr, 0, s);
 }

@@ -1,0 +1,29 @@
+"""Plan lists against the plan oracle, bit for bit, at the edges of the planning kernels' tiles of 256 rows, of the
+workgroups that count the rows before their own (up to 8), and of windows that reach past a tile."""
+import numpy as np
+import pytest
+
+from oracle.plan import plan_oracle
+from workloads import csr_from_row_lengths
+
+from gpu_util import DeviceProblem, read_plan_arrays, tuning
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m", [1, 255, 256, 257, 320, 2047, 2048, 2049, 5000])
+@pytest.mark.parametrize("tune", [None, "bn=256,alpha=4,lw=8,ch=40,bch=64", "bn=16,alpha=1,lw=0,ch=32,bch=48", "bn=48,alpha=3"])
+def test_lists_at_tile_edges(m, tune):
+    rng = np.random.default_rng(m)
+    lens = rng.integers(0, 3, size=m)  # nearly empty rows: 64 rows per window
+    lens[rng.integers(0, m, size=m // 20 + 1)] = rng.integers(30, 300, size=m // 20 + 1)
+    lens[-1] = 700
+    with tuning(tune):
+        p = csr_from_row_lengths(lens, 900, 8, seed=m)
+        plan = DeviceProblem(p).make_plan()
+        info, got = read_plan_arrays(plan)
+        want = plan_oracle(p.rowptr, info.BN, info.ALPHA, info.LW, info.CH, info.BCH)
+        assert info.nnz == p.nnz and info.n_short_rows == int(want["n_short"])
+        for key in ("win_row_start", "win_stage", "wave_rows", "wave_span", "items", "split"):
+            assert np.array_equal(got[key], want[key]), key
+        plan.destroy()
