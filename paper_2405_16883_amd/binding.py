@@ -1,8 +1,9 @@
-"""Thin ctypes binding of the C ABI in include/scorch_spmm.h.
+"""Thin binding of the C ABI in include/scorch_spmm.h.
 
 Argument marshalling only: every step of the SpMM path runs inside libscorch_spmm.so.  torch is
-used for device memory and streams.  There is no fallback: if the library is missing or a call
-fails, an exception is raised.
+used for device memory and streams.  The execution calls are marshalled by a small extension module
+(csrc/binding.cpp), plans and plumbing through ctypes.  There is no fallback: if the library or the extension is
+missing or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
@@ -95,6 +96,23 @@ def load_library() -> ctypes.CDLL:
     return lib
 
 
+BINDING_PATH = os.path.join(_PKG_DIR, "_scorch_binding.so")
+_native = None
+
+
+def _load_native():
+    """The extension module of the execution calls; raises if it has not been built."""
+    global _native
+    load_library()
+    if not os.path.exists(BINDING_PATH):
+        raise FileNotFoundError(
+            f"{BINDING_PATH} is missing: build it with `python -m paper_2405_16883_amd.build` "
+            "(there is no CPU fallback)")
+    from . import _scorch_binding
+    _native = _scorch_binding
+    return _native
+
+
 def _check(status: int) -> None:
     if status != SCORCH_OK:
         lib = load_library()
@@ -125,10 +143,9 @@ def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
 def scorch_spmm_csr(m: int, k: int, n: int, rowptr: torch.Tensor, colidx: torch.Tensor, vals: torch.Tensor,
                     B: torch.Tensor, C: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
     """C[:m, :n] = A @ B[:k, :n] through the plan-free entry point.  B and C may be row-strided views."""
-    lib = load_library()
-    _check(lib.scorch_spmm_csr(m, k, n, _dev_ptr(rowptr, torch.int32, "rowptr"), _dev_ptr(colidx, torch.int32, "colidx"),
-                               _dev_ptr(vals, torch.float32, "vals"), _dev_ptr(B, torch.float32, "B"), _ld(B, "B"),
-                               _dev_ptr(C, torch.float32, "C"), _ld(C, "C"), _stream_handle(stream)))
+    st = (_native or _load_native()).spmm_csr(m, k, n, rowptr, colidx, vals, B, C, stream)
+    if st:
+        _check(st)
 
 
 STATIC_SCRATCH_BYTES = 16 << 20
@@ -138,10 +155,9 @@ def scorch_spmm_csr_static(m: int, k: int, n: int, rowptr: torch.Tensor, colidx:
                            B: torch.Tensor, C: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
     """C[:m, :n] = A @ B[:k, :n] through the entry point that allocates nothing on the device (the plan lives in the
     library's static scratch array; problems whose plan needs more than STATIC_SCRATCH_BYTES are refused)."""
-    lib = load_library()
-    _check(lib.scorch_spmm_csr_static(m, k, n, _dev_ptr(rowptr, torch.int32, "rowptr"), _dev_ptr(colidx, torch.int32, "colidx"),
-                                      _dev_ptr(vals, torch.float32, "vals"), _dev_ptr(B, torch.float32, "B"), _ld(B, "B"),
-                                      _dev_ptr(C, torch.float32, "C"), _ld(C, "C"), _stream_handle(stream)))
+    st = (_native or _load_native()).spmm_csr_static(m, k, n, rowptr, colidx, vals, B, C, stream)
+    if st:
+        _check(st)
 
 
 def scorch_spmm_plan_workspace_bytes(m: int, k: int, n: int, nnz: int) -> int:
@@ -199,33 +215,26 @@ def scorch_spmm_plan(m: int, k: int, n: int, rowptr: torch.Tensor, nnz: int,
 
 def scorch_spmm_csr_planned(plan: SpmmPlan, rowptr: torch.Tensor, colidx: torch.Tensor, vals: torch.Tensor,
                             B: torch.Tensor, C: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
-    lib = load_library()
-    _check(lib.scorch_spmm_csr_planned(plan.handle, _dev_ptr(rowptr, torch.int32, "rowptr"),
-                                       _dev_ptr(colidx, torch.int32, "colidx"), _dev_ptr(vals, torch.float32, "vals"),
-                                       _dev_ptr(B, torch.float32, "B"), _ld(B, "B"),
-                                       _dev_ptr(C, torch.float32, "C"), _ld(C, "C"), _stream_handle(stream)))
+    st = (_native or _load_native()).spmm_csr_planned(plan.handle, rowptr, colidx, vals, B, C, stream)
+    if st:
+        _check(st)
 
 
 def scorch_sddmm_csr(m: int, k: int, d: int, rowptr: torch.Tensor, colidx: torch.Tensor, vals: torch.Tensor,
                      B: torch.Tensor, Ct: torch.Tensor, out_vals: torch.Tensor,
                      stream: Optional[torch.cuda.Stream] = None) -> None:
     """out_vals[p] = vals[p] * <B[i, :d], Ct[colidx[p], :d]> through the plan-free entry point."""
-    lib = load_library()
-    _check(lib.scorch_sddmm_csr(m, k, d, _dev_ptr(rowptr, torch.int32, "rowptr"), _dev_ptr(colidx, torch.int32, "colidx"),
-                                _dev_ptr(vals, torch.float32, "vals"), _dev_ptr(B, torch.float32, "B"), _ld(B, "B"),
-                                _dev_ptr(Ct, torch.float32, "Ct"), _ld(Ct, "Ct"),
-                                _dev_ptr(out_vals, torch.float32, "out_vals"), _stream_handle(stream)))
+    st = (_native or _load_native()).sddmm_csr(m, k, d, rowptr, colidx, vals, B, Ct, out_vals, stream)
+    if st:
+        _check(st)
 
 
 def scorch_sddmm_csr_planned(plan: SpmmPlan, d: int, rowptr: torch.Tensor, colidx: torch.Tensor, vals: torch.Tensor,
                              B: torch.Tensor, Ct: torch.Tensor, out_vals: torch.Tensor,
                              stream: Optional[torch.cuda.Stream] = None) -> None:
-    lib = load_library()
-    _check(lib.scorch_sddmm_csr_planned(plan.handle, d, _dev_ptr(rowptr, torch.int32, "rowptr"),
-                                        _dev_ptr(colidx, torch.int32, "colidx"), _dev_ptr(vals, torch.float32, "vals"),
-                                        _dev_ptr(B, torch.float32, "B"), _ld(B, "B"), _dev_ptr(Ct, torch.float32, "Ct"),
-                                        _ld(Ct, "Ct"), _dev_ptr(out_vals, torch.float32, "out_vals"),
-                                        _stream_handle(stream)))
+    st = (_native or _load_native()).sddmm_csr_planned(plan.handle, d, rowptr, colidx, vals, B, Ct, out_vals, stream)
+    if st:
+        _check(st)
 
 
 ACT_IDENTITY = 0
@@ -236,23 +245,17 @@ def scorch_spmm_csr_planned_epilogue(plan: SpmmPlan, rowptr: torch.Tensor, colid
                                      B: torch.Tensor, bias: Optional[torch.Tensor], activation: int, C: torch.Tensor,
                                      stream: Optional[torch.cuda.Stream] = None) -> None:
     """C = act(A @ B + bias) in one pass (bias may be None; activation ACT_IDENTITY or ACT_RELU)."""
-    lib = load_library()
-    _check(lib.scorch_spmm_csr_planned_epilogue(plan.handle, _dev_ptr(rowptr, torch.int32, "rowptr"),
-                                                _dev_ptr(colidx, torch.int32, "colidx"),
-                                                _dev_ptr(vals, torch.float32, "vals"), _dev_ptr(B, torch.float32, "B"),
-                                                _ld(B, "B"), _dev_ptr(bias, torch.float32, "bias"), activation,
-                                                _dev_ptr(C, torch.float32, "C"), _ld(C, "C"), _stream_handle(stream)))
+    st = (_native or _load_native()).spmm_csr_planned_epilogue(plan.handle, rowptr, colidx, vals, B, bias, activation, C, stream)
+    if st:
+        _check(st)
 
 
 def scorch_coo_to_csr_rowptr(m: int, row_idx: torch.Tensor, rowptr_out: torch.Tensor,
                              bad_flag: Optional[torch.Tensor] = None, stream: Optional[torch.cuda.Stream] = None) -> None:
     """rowptr_out[0..m] for a coordinate list whose int32 row coordinates ``row_idx`` are sorted by row."""
-    lib = load_library()
-    if rowptr_out.numel() != m + 1:
-        raise ValueError("rowptr_out must have m + 1 entries")
-    _check(lib.scorch_coo_to_csr_rowptr(m, row_idx.numel(), _dev_ptr(row_idx, torch.int32, "row_idx"),
-                                        _dev_ptr(rowptr_out, torch.int32, "rowptr_out"),
-                                        _dev_ptr(bad_flag, torch.int32, "bad_flag"), _stream_handle(stream)))
+    st = (_native or _load_native()).coo_to_csr_rowptr(m, row_idx, rowptr_out, bad_flag, stream)
+    if st:
+        _check(st)
 
 
 def scorch_dcsr_to_csr_rowptr(m: int, row_ids: torch.Tensor, row_pos: torch.Tensor, rowptr_out: torch.Tensor,

@@ -50,6 +50,27 @@ def build_library(verbose: bool = False) -> str:
     return LIB_PATH
 
 
+BINDING_PATH = os.path.join(PKG_DIR, "_scorch_binding.so")
+
+
+def build_binding(verbose: bool = False) -> str:
+    """Compiles the Python entry points (host code only) and links them to libscorch_spmm.so beside them."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+
+    inc = [f"-I{p}" for p in (os.path.join(ROOT, "include"), sysconfig.get_paths()["include"])]
+    inc += [f"-isystem{p}" for p in (*include_paths(), "/opt/rocm/include")]
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = BINDING_PATH + f".tmp{os.getpid()}"
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc, os.path.join(CSRC, "binding.cpp"), "-o", tmp,
+          f"-L{PKG_DIR}", "-l:libscorch_spmm.so", "-Wl,-rpath,$ORIGIN", f"-L{torch_lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"], verbose)
+    os.replace(tmp, BINDING_PATH)
+    return BINDING_PATH
+
+
 PROBES_LIB_PATH = os.path.join(PKG_DIR, "libscorch_probes.so")
 
 
@@ -67,3 +88,4 @@ def build_probes(verbose: bool = False) -> str:
 if __name__ == "__main__":
     print(build_probes(verbose="-v" in sys.argv))
     print(build_library(verbose="-v" in sys.argv))
+    print(build_binding(verbose="-v" in sys.argv))
