@@ -259,7 +259,7 @@ scorch_status_t scorch_spmm_plan_info(const scorch_spmm_plan_t *plan, scorch_spm
     out->n_split_rows = plan->n_split;
     out->n_partial_slots = plan->n_slots;
     out->partial_stride = plan->layout.partial_stride;
-    out->mode = plan->params.PANEL ? 2 : (plan->params.SLICED ? 1 : 0);
+    out->mode = plan->params.RES ? 3 : plan->params.PANEL ? 2 : (plan->params.SLICED ? 1 : 0);
     out->off_win_row_start = plan->layout.off_win;
     out->off_win_stage = plan->layout.off_stage;
     out->off_wave_span = plan->layout.off_wave_span;

@@ -20,6 +20,8 @@ constexpr int kLWMax = 64;
 constexpr int kStageMax = kBNMax + kLWMax;
 constexpr int kWindowRowsMax = 64;  // one lane per row when reading rowptr
 constexpr int kPanelCols = 256; // panel kernel: one wavefront covers 256 columns (64 lanes x float4)
+constexpr int kResidentFloats = 158 * 256;  // resident kernel: floats of B a workgroup keeps; with a row of zeros 160 KB of LDS
+constexpr int kCus = 256;
 constexpr int kSliceCols = 32;  // XCD-sliced mode: 32 fp32 columns = one 128-byte line of a B row
 constexpr int64_t kL2SliceBudget = 2560 * 1024;  // bytes of B an XCD's 4 MB L2 is trusted to keep resident
 constexpr int64_t kMallBytes = 256ll << 20;      // memory-side cache shared by all XCDs
@@ -39,6 +41,7 @@ struct PlanParams {
     int32_t PACK;   // 1: sliced execution gathers from a slice-major copy of B made at every call
     int32_t PANEL;  // dense-ish sorted rows: stream B through LDS in k-panels (spmm_panel.hip); 1: 256-column tiles, 2: 512
     int32_t PDIRECT; // panel kernel: 1 = fetch the panels from the caller's row-major B instead of a tile-major copy
+    int32_t RES;    // >0: narrow B kept in LDS in chunks (spmm_resident.hip), rows padded to this many columns
     int32_t HOT;    // >0: budget in KB for the most referenced rows of B, which alone keep the default cache policy
 };
 
@@ -48,7 +51,7 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
 
 struct WorkspaceLayout {
     uint64_t off_counts, off_totals, off_win, off_stage, off_wave, off_wave_span, off_items, off_split, off_partials, off_tickets, off_bpack,
-        off_coldeg, off_hotmask, off_degbins, total;
+        off_res_ptr, off_res_partials, off_coldeg, off_hotmask, off_degbins, total;
     int64_t ticket_tiles;  // arrival counters per split row: one for every column tile a launch may use
     int64_t n_windows, nblk;
     int64_t cap_wave, cap_items, cap_split, cap_slots;
@@ -110,6 +113,27 @@ struct PanelArgs {
     int32_t act;
 };
 
+struct ResidentArgs {
+    const int32_t *colidx;
+    const float *vals;
+    const float *B;
+    float *C;
+    int64_t ldb, ldc;
+    int32_t m, k, n;
+    const int32_t *ptr;  // [nchunks + 1][m]: a row's first entry of chunk p or later
+    float *partials;     // [nchunks][m][RES], unused with one chunk
+    int32_t nchunks;
+    int32_t rows_per_block;
+    const float *bias;
+    int32_t act;
+};
+
+// Chunks of the resident kernel for rows padded to W columns.
+__host__ __device__ inline int32_t resident_chunks(int32_t k, int32_t W) {
+    const uint32_t rows = (uint32_t)(kResidentFloats / W);
+    return (int32_t)(((uint32_t)k + rows - 1) / rows);
+}
+
 struct FixupArgs {
     const int4 *split;
     const float *partials;
@@ -170,6 +194,12 @@ bool panel_operands_ok(int32_t n, const float *B, int64_t ldb, const float *C, i
 scorch_status_t launch_panel(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
                              const float *vals, const float *B, int64_t ldb, float *C, int64_t ldc,
                              const float *bias, int32_t act, hipStream_t stream);
+
+// spmm_resident.hip
+scorch_status_t launch_plan_resident(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int32_t *flag,
+                                     hipStream_t stream);
+scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *colidx, const float *vals, const float *B,
+                                int64_t ldb, float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream);
 
 // sddmm_exec.hip (plan == nullptr: plan-free, one wavefront per row)
 scorch_status_t launch_sddmm(const scorch_spmm_plan_t *plan, int32_t m, int32_t d, const int32_t *rowptr,

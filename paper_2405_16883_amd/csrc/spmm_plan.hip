@@ -510,6 +510,31 @@ __host__ __device__ static int32_t want_panel(int32_t m, int32_t k, int64_t nnz,
     return 0;
 }
 
+// Columns a row of B is padded to in LDS by the resident kernel (spmm_resident.hip).
+__host__ __device__ static int32_t resident_width(int32_t n) {
+    int32_t W = 4;
+    while (W < n) W *= 2;
+    return W;
+}
+
+// The resident kernel against the gather kernels, for at most 64 columns: both times as fitted to sweeps over m = 1024 ...
+// 16 384, k = 1024 ... 16 384, 1 ... 50 % stored, n = 1 ... 64, in units of 0.1 ps (integers: host and device have to
+// decide alike).  Gathers: 2.3 ps (n = 1) to 11 ps (n = 64) per entry.  Resident: 2 to 3 ps per entry, but at least
+// 1.2 us per row and chunk that a wavefront goes through (4096 wavefronts), 4 us to fill LDS, and the second launch over the partial
+// rows.  Measured, gather / resident in us, 4096 x 16 384 with 10 % stored: n = 4 25.0 / 18.8, 8 38.8 / 19.8, 16 42.0 / 19.8,
+// 32 45.9 / 31.2, 64 78.4 / 47.5; with 1 %: 5.0 / 7.6, 5.3 / 9.7, 5.6 / 13.0, 5.9 / 24.8, 10.8 / 34.1; 16 384 x 4096 with 26 %: n = 16
+// 72.3 / 43.3, n = 64 153 / 80.
+__host__ __device__ static int32_t want_resident(int32_t m, int32_t k, int64_t nnz, int32_t n) {
+    if (m <= 0 || k <= 0 || n < 3 || n > 64) return 0;
+    const int32_t W = resident_width(n);
+    const int64_t chunks = resident_chunks(k, W);
+    const int64_t per_entry = n > 32 ? 110 : n % 4 != 0 ? 75 : n > 8 ? 57 : n > 4 ? 50 : 35;
+    const int64_t entries = nnz * (W > 32 ? 30 : W > 16 ? 26 : 20), rows = (int64_t)m * chunks * 2930;
+    int64_t resident = 40000000 + (entries > rows ? entries : rows);
+    if (chunks > 1) resident += 30000000 + (int64_t)m * chunks * W * 27;
+    return resident * 10 < nnz * per_entry * 9 ? W : 0;
+}
+
 __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t) {
     PlanParams p;
     p.ALPHA = 4;
@@ -538,6 +563,8 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     // workgroups of a tile column walk the same panels at the same time, so only a few panels per die have to stay in
     // L2 and the set conflicts of a power-of-two stride do not matter); pack=1 brings the copy back.
     p.PDIRECT = (p.PANEL && (t.pack != 1 || p.PANEL == 3)) ? 1 : 0;
+    p.RES = p.PANEL == 0 ? want_resident(m, k, nnz, n) : 0;
+    if (t.res >= 0) p.RES = (t.res > 0 && n <= 64 && k > 0 && m > 0 && p.PANEL == 0) ? resident_width(n) : 0;
     // Enough independent wavefront tasks to fill 256 CUs several times over, but pieces long
     // enough that the per-piece overhead stays small.
     const int64_t coltiles = p.SLICED ? (n + p.SLICED - 1) / p.SLICED : std::max<int64_t>(1, (n + 511) / 512);
@@ -609,6 +636,13 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
     off = align_up(off + (uint64_t)L.cap_slots * L.ticket_tiles * 4, 256);  // indexed by a split row's first slot
     L.off_bpack = off;
     if (p.PACK || (p.PANEL && !p.PDIRECT)) off = align_up(off + (uint64_t)k * ((n + 2 * kPanelCols - 1) / (2 * kPanelCols)) * (2 * kPanelCols) * 4, 256);
+    L.off_res_ptr = L.off_res_partials = off;
+    if (p.RES) {
+        const int64_t chunks = resident_chunks(k, p.RES);
+        off = align_up(off + (uint64_t)(chunks + 1) * m * 4, 256);
+        L.off_res_partials = off;
+        if (chunks > 1) off = align_up(off + (uint64_t)chunks * m * p.RES * 4, 256);
+    }
     L.off_coldeg = off;
     if (p.HOT) off = align_up(off + (uint64_t)k * 4, 256);
     L.off_hotmask = off;
@@ -716,20 +750,25 @@ scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, cons
         set_error("plan lists exceed the workspace bound (rowptr changed or is not non-decreasing?)");
         return SCORCH_ERR_INVALID_ARG;
     }
-    // The panel kernel needs every row's columns in strictly increasing order; without colidx this cannot be
+    // The panel and resident kernels need every row's columns in strictly increasing order; without colidx this cannot be
     // verified, so the mode is dropped.
-    if (plan->params.PANEL && (!colidx || plan->m == 0 || plan->nnz == 0)) plan->params.PANEL = 0;
-    if (plan->params.PANEL) {
+    if (!colidx || plan->m == 0 || plan->nnz == 0) plan->params.PANEL = plan->params.RES = 0;
+    if (plan->params.PANEL || plan->params.RES) {
         int32_t unsorted = 0;
         int32_t *flag = reinterpret_cast<int32_t *>(ws + L.off_totals);
         e = hipMemsetAsync(flag, 0, sizeof(int32_t), stream);
         if (e != hipSuccess) return hip_fail(e, "clear sortedness flag");
         const uint32_t g = (uint32_t)std::min<int64_t>(((int64_t)plan->m + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 16);
-        hipLaunchKernelGGL(plan_sorted_kernel, dim3(g), dim3(kBlock), 0, stream, rowptr, colidx, plan->m, flag);
+        if (plan->params.RES) {
+            st = launch_plan_resident(plan, rowptr, colidx, flag, stream);
+            if (st != SCORCH_OK) return st;
+        } else {
+            hipLaunchKernelGGL(plan_sorted_kernel, dim3(g), dim3(kBlock), 0, stream, rowptr, colidx, plan->m, flag);
+        }
         e = hipMemcpyAsync(&unsorted, flag, sizeof(int32_t), hipMemcpyDeviceToHost, stream);
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return hip_fail(e, "read the sortedness flag");
-        if (unsorted) plan->params.PANEL = 0;
+        if (unsorted) plan->params.PANEL = plan->params.RES = 0;
     }
     plan->n_hot = 0;
     plan->hot_share = 0.f;

@@ -1,0 +1,69 @@
+"""The resident kernel (narrow B kept in LDS in chunks) against the oracle: one chunk and several, the last of one row,
+every padded width, rows of no, one and many windows of a chunk, and rows whose columns are not increasing."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2405_16883_amd as sp
+from workloads import csr_from_row_lengths, integer_valued, with_padding
+
+from gpu_util import DeviceProblem, check_against_oracle, tuning
+
+pytestmark = pytest.mark.gpu
+
+
+def chunk_rows(n):
+    w = 4
+    while w < n:
+        w *= 2
+    return 158 * 256 // w
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 15, 16, 20, 32, 33, 64])
+@pytest.mark.parametrize("extra", [-1, 0, 1, 700])  # columns beyond one chunk
+@pytest.mark.parametrize("m", [1, 40, 300])
+def test_resident(m, extra, n):
+    k = chunk_rows(n) + extra
+    rng = np.random.default_rng(m * 100 + n)
+    lens = rng.integers(0, 400, size=m)  # up to six windows of 64 in a chunk
+    lens[rng.integers(0, m)] = min(k, 1100)
+    lens[-1] = 64
+    p = csr_from_row_lengths(lens, k, n, seed=m + n)
+    with tuning("res=1"):
+        for q, exact, pad in ((p, False, 0), (with_padding(p, n + 3), False, 2), (integer_valued(p, seed=n), True, 0)):
+            d = DeviceProblem(q, ldc=n + pad)
+            plan = d.make_plan()
+            assert plan.info().mode == 3
+            check_against_oracle(q, d.run_planned(plan), d.ldc, exact=exact, label=f"m={m} k={k} n={n} ldb={q.ldb}")
+            plan.destroy()
+
+
+@pytest.mark.parametrize("k", [500, 6000])
+def test_resident_epilogue_is_the_plain_result_plus_bias_and_relu(k):
+    p = integer_valued(csr_from_row_lengths([30] * 50, k, 20, seed=k), seed=1)
+    with tuning("res=1"):
+        d = DeviceProblem(p)
+        plan = d.make_plan()
+        plain = d.run_planned(plan)
+        bias = torch.arange(-10, 10, dtype=torch.float32, device=d.dev)
+        sp.scorch_spmm_csr_planned_epilogue(plan, d.rowptr, d.colidx, d.vals, d._B_arg(), bias, sp.ACT_RELU, d._C_arg())
+        torch.cuda.synchronize()
+        assert np.array_equal(d.Cfull.cpu().numpy(), np.maximum(plain + bias.cpu().numpy(), 0))
+        plan.destroy()
+
+
+def test_resident_is_left_to_rows_of_increasing_columns_and_chosen_for_a_dense_weight():
+    with tuning("res=1"):
+        for sorted_cols, duplicates in ((False, False), (True, True)):
+            p = csr_from_row_lengths([40] * 60, 50, 16, seed=3, sorted_cols=sorted_cols, duplicates=duplicates)
+            d = DeviceProblem(p)
+            plan = d.make_plan()
+            assert plan.info().mode != 3
+            check_against_oracle(p, d.run_planned(plan), d.ldc, label="not increasing")
+            plan.destroy()
+    p = csr_from_row_lengths([1000] * 4096, 4096, 16, seed=4)
+    d = DeviceProblem(p)
+    plan = d.make_plan()
+    assert plan.info().mode == 3
+    check_against_oracle(p, d.run_planned(plan), d.ldc, label="chosen")
+    plan.destroy()
