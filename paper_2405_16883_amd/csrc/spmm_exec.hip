@@ -513,14 +513,22 @@ __global__ __launch_bounds__(NW * kWave) void spmm_row_kernel(const ExecArgs a) 
 // before the launch).  A wavefront reads the row pointers of its run once (a lane per row) and then proceeds
 // greedily: the next rows, as long as they are short (up to kNaturalShort entries) and fit the LDS stage together,
 // are staged with coalesced reads and walked one row per lane group, like a window of the planned path; a longer
-// row is streamed through the stage by the whole wavefront, the lane groups taking interleaved entries; a row of
-// more than kNaturalLong entries (kNaturalMid if such rows are rare in the workgroup) is left to the end, where all 4
-// wavefronts of the workgroup take it together (interleaved 64-entry chunks, LDS tree), which shortens the serial
-// chain of a heavy row fourfold without any scratch memory.
+// row is streamed through the stage by the whole wavefront, the lane groups taking interleaved entries.
+//
+// Rows of more than kNaturalLong entries (kNaturalMid if at most a quarter of the workgroup's rows are longer than that,
+// i.e. where they are the outliers of a graph and not the normal case of a matrix with long rows) are left to
+// workgroups at the front of the grid, the scouts: each looks for them in a stretch of rows and takes them one after the
+// other, all 4 wavefronts together (interleaved 64-entry chunks, LDS tree, twice the gathers in flight), so that the
+// longest rows start first and run beside everything else.  Measured against leaving them to the end of the workgroup
+// that holds them, with the run length of before: graph of 169 343 rows (longest 10 316 entries), n = 128: 163 -> 138 us in the kernel trace; with longer runs (launch_natural) 124.
 constexpr int kNaturalLong = 2048;
 constexpr int kNaturalMid = 256;
 constexpr int kNaturalRowsMax = 16;
 constexpr int kNaturalShort = 32;
+constexpr int kScoutsMax = 2048;  // per column tile
+
+// Row length beyond which a row is left to the scouts, for a workgroup of `rows` rows of which `mid` are longer than kNaturalMid.
+__device__ __forceinline__ int natural_long_limit(int mid, int rows) { return mid * 4 <= rows ? kNaturalMid : kNaturalLong; }
 
 template <int V, int G, int T, int U, int NT, bool UA>
 __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) {
@@ -531,19 +539,16 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
     constexpr bool NTC = (NT & 1) != 0;
     __shared__ int s_raw[kWavesPerBlock * smem_ints_per_wave()];
     __shared__ float s_red[kWavesPerBlock * TW];
-    __shared__ int s_long[kWavesPerBlock * kNaturalRowsMax];  // rows left to the whole workgroup
-    __shared__ int s_nlong, s_nmid;
+    __shared__ int s_nmid;
     const int tid = threadIdx.x;
     const int wv = tid >> 6;
     const int lane = tid & 63;
     const int grp = lane / G;
     const int lig = lane % G;
-    const uint32_t per_tile = (uint32_t)a.nb_wave;
+    const uint32_t per_tile = (uint32_t)a.nb_items + (uint32_t)a.nb_wave;
     uint32_t ct, b;
     if (!tile_of_workgroup(a.xcd_slices, a.ncoltiles, per_tile, ct, b)) return;  // the same for the whole workgroup
-    const int NR = a.rows_per_wave;
-    const int64_t r0 = ((int64_t)b * kWavesPerBlock + wv) * NR;
-    const int nr = (int)max((int64_t)0, min((int64_t)NR, (int64_t)a.m - r0));
+    const int NR = a.rows_per_wave;  // a power of two
     const int c0 = (int)ct * TW + lig * V;
     bool colok[T];
     int coff[T];  // see spmm_fused_kernel
@@ -557,113 +562,117 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
     float *lval = reinterpret_cast<float *>(lcol + kStageMax);
     int *lrp = lcol + 2 * kStageMax;
     vec acc[T];
-    if (tid == 0) {
-        s_nlong = 0;
-        s_nmid = 0;
+
+    if (b < (uint32_t)a.nb_items) {
+        // ---- scout: the long rows of a stretch, 64 rows at a time, all wavefronts on each ----
+        const int group = kWavesPerBlock * NR;  // rows of one workgroup of the other kind: 4, 8, ... 64
+        const int64_t end = min((int64_t)a.m, ((int64_t)b + 1) * a.scout_rows);
+        for (int64_t first = (int64_t)b * a.scout_rows; first < end; first += kWave) {
+            const int64_t row = min(first + lane, (int64_t)a.m - 1);
+            const int q0 = a.rowptr[row];
+            const int len = first + lane < a.m ? a.rowptr[row + 1] - q0 : 0;
+            const unsigned long long mid = __ballot(len > kNaturalMid);
+            const unsigned long long mine = group >= kWave ? mid : (mid >> (lane & ~(group - 1))) & ((1ull << group) - 1ull);
+            const int limit = natural_long_limit(__builtin_popcountll(mine), group);
+            unsigned long long todo = __ballot(len > limit);
+            while (todo != 0ull) {  // the same for the whole workgroup
+                const int r = __builtin_ctzll(todo);
+                todo &= todo - 1ull;
+                const int p0 = __shfl(q0, r, kWave), p1 = p0 + __shfl(len, r, kWave);
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
+                row_accumulate<V, G, T, 2 * U, false, UA>(acc, lcol, lval, lane, grp, p0 + wv * kWave, p1, kBlock, a.colidx,
+                                                          a.vals, a.B, ldb, colok[0], coff);
+                reduce_groups<V, G, T>(acc);
+                __syncthreads();  // s_red of the previous row has been read
+                if (grp == 0) {
+#pragma unroll
+                    for (int t = 0; t < T; ++t) {
+                        if constexpr (V == 1) s_red[wv * TW + t * GV + lig] = acc[t];
+                        else
+#pragma unroll
+                            for (int i = 0; i < V; ++i) s_red[wv * TW + t * GV + lig * V + i] = acc[t][i];
+                    }
+                }
+                __syncthreads();
+                if (wv == 0 && grp == 0) {
+                    float *dst = a.C + (first + r) * a.ldc;
+#pragma unroll
+                    for (int t = 0; t < T; ++t) {
+                        if (!colok[t]) continue;
+                        vec out;
+#pragma unroll
+                        for (int i = 0; i < V; ++i) {
+                            const int o = t * GV + lig * V + i;
+                            float sum = s_red[o];
+#pragma unroll
+                            for (int x = 1; x < kWavesPerBlock; ++x) sum += s_red[x * TW + o];
+                            if constexpr (V == 1) out = sum;
+                            else out[i] = sum;
+                        }
+                        vstore<V, NTC, UA>(dst + coff[t], out);
+                    }
+                }
+            }
+        }
+        return;
     }
+
+    const int64_t r0 = ((int64_t)(b - (uint32_t)a.nb_items) * kWavesPerBlock + wv) * NR;
+    const int nr = (int)max((int64_t)0, min((int64_t)NR, (int64_t)a.m - r0));
+    if (tid == 0) s_nmid = 0;
     __syncthreads();
     const int rpv = nr > 0 ? a.rowptr[r0 + min(lane, nr)] : 0;
     const int rnext = __shfl_down(rpv, 1, kWave);  // lanes past the run hold the last pointer; lane 63 is never a row
-    // Rows of more than kNaturalMid entries: outliers of a graph if the workgroup has one or two of them (then all 4
-    // wavefronts take each of them together), the normal case of a matrix with long rows if it has more (then every
-    // wavefront keeps its own rows, up to kNaturalLong entries)
     const int nmid = (int)__builtin_popcountll(__ballot(lane < nr && rnext - rpv > kNaturalMid));
     if (lane == 0 && nmid > 0) atomicAdd(&s_nmid, nmid);
     __syncthreads();
-    const int long_limit = s_nmid <= 2 ? kNaturalMid : kNaturalLong;
-    if (nr > 0) {
-        lrp[lane] = rpv;
-        wave_lds_sync();
-        int i = 0;
-        while (i < nr) {
-            const int base = lrp[i];
-            // rows i .. j-1: the longest run of short rows (one lane group walks a row alone, so only rows of up to
-            // kNaturalShort entries qualify) that fits the stage
-            const bool stops = lane >= i && (lane >= nr || rnext - rpv > kNaturalShort || rnext - base > kStageMax);
-            const int j = __builtin_ctzll(__ballot(stops));  // lane nr always stops
-            if (j == i) {
-                const int p1 = lrp[i + 1];
-                if (p1 - base <= long_limit) {
-#pragma unroll
-                    for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
-                    row_accumulate<V, G, T, U, false, UA>(acc, lcol, lval, lane, grp, base, p1, kWave, a.colidx, a.vals,
-                                                          a.B, ldb, colok[0], coff);
-                    reduce_groups<V, G, T>(acc);
-                    if (grp == 0) {
-                        float *dst = a.C + (r0 + i) * a.ldc;
-#pragma unroll
-                        for (int t = 0; t < T; ++t)
-                            if (colok[t])
-                                vstore<V, NTC, UA>(dst + coff[t], apply_epilogue<V>(acc[t], a.bias ? a.bias + coff[t] : nullptr, a.act));
-                    }
-                } else if (lane == 0) {
-                    s_long[atomicAdd(&s_nlong, 1)] = (int)(r0 + i);
-                }
-                ++i;
-                continue;
-            }
-            const int cnt = min(lrp[j] - base, kStageMax);
-            for (int e = lane; e < cnt; e += kWave) {
-                lcol[e] = a.colidx[base + e];
-                lval[e] = a.vals[base + e];
-            }
-            wave_lds_sync();
-            for (int ri = i + grp; ri < j; ri += S) {
+    const int long_limit = natural_long_limit(s_nmid, kWavesPerBlock * NR);  // as the scouts decide
+    if (nr <= 0) return;
+    lrp[lane] = rpv;
+    wave_lds_sync();
+    int i = 0;
+    while (i < nr) {
+        const int base = lrp[i];
+        // rows i .. j-1: the longest run of short rows (one lane group walks a row alone, so only rows of up to
+        // kNaturalShort entries qualify) that fits the stage
+        const bool stops = lane >= i && (lane >= nr || rnext - rpv > kNaturalShort || rnext - base > kStageMax);
+        const int j = __builtin_ctzll(__ballot(stops));  // lane nr always stops
+        if (j == i) {
+            const int p1 = lrp[i + 1];
+            if (p1 - base <= long_limit) {
 #pragma unroll
                 for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
-                gather_fma<V, T, U, UA>(acc, lcol, lval, lrp[ri] - base, lrp[ri + 1] - base, 1, a.B, ldb, colok[0], coff);
-                float *dst = a.C + (r0 + ri) * a.ldc;
+                row_accumulate<V, G, T, U, false, UA>(acc, lcol, lval, lane, grp, base, p1, kWave, a.colidx, a.vals,
+                                                      a.B, ldb, colok[0], coff);
+                reduce_groups<V, G, T>(acc);
+                if (grp == 0) {
+                    float *dst = a.C + (r0 + i) * a.ldc;
 #pragma unroll
-                for (int t = 0; t < T; ++t)
-                    if (colok[t])
-                        vstore<V, NTC, UA>(dst + coff[t], apply_epilogue<V>(acc[t], a.bias ? a.bias + coff[t] : nullptr, a.act));
-            }
-            wave_lds_sync();  // the stage is refilled next
-            i = j;
-        }
-    }
-    __syncthreads();
-    // long rows of this workgroup, one after the other, all wavefronts on each (the loop is workgroup-uniform; the
-    // order of the list varies from run to run, the result of each row does not depend on it)
-    const int nlong = s_nlong;
-    for (int w = 0; w < nlong; ++w) {
-        const int64_t row = s_long[w];
-        const int q0 = a.rowptr[row], q1 = a.rowptr[row + 1];
-#pragma unroll
-        for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
-        // twice the gathers in flight: these rows are few, and the longest of them is the serial chain of the launch
-        row_accumulate<V, G, T, 2 * U, false, UA>(acc, lcol, lval, lane, grp, q0 + wv * kWave, q1, kBlock, a.colidx,
-                                                  a.vals, a.B, ldb, colok[0], coff);
-        reduce_groups<V, G, T>(acc);
-        __syncthreads();  // s_red of the previous long row has been read
-        if (grp == 0) {
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                if constexpr (V == 1) s_red[wv * TW + t * GV + lig] = acc[t];
-                else
-#pragma unroll
-                    for (int i = 0; i < V; ++i) s_red[wv * TW + t * GV + lig * V + i] = acc[t][i];
-            }
-        }
-        __syncthreads();
-        if (wv == 0 && grp == 0) {
-            float *dst = a.C + row * a.ldc;
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                if (!colok[t]) continue;
-                vec r;
-#pragma unroll
-                for (int i = 0; i < V; ++i) {
-                    const int o = t * GV + lig * V + i;
-                    float sum = s_red[o];
-#pragma unroll
-                    for (int x = 1; x < kWavesPerBlock; ++x) sum += s_red[x * TW + o];
-                    if constexpr (V == 1) r = sum;
-                    else r[i] = sum;
+                    for (int t = 0; t < T; ++t)
+                        if (colok[t]) vstore<V, NTC, UA>(dst + coff[t], acc[t]);
                 }
-                vstore<V, NTC, UA>(dst + coff[t], apply_epilogue<V>(r, a.bias ? a.bias + coff[t] : nullptr, a.act));
             }
+            ++i;
+            continue;
         }
+        const int cnt = min(lrp[j] - base, kStageMax);
+        for (int e = lane; e < cnt; e += kWave) {
+            lcol[e] = a.colidx[base + e];
+            lval[e] = a.vals[base + e];
+        }
+        wave_lds_sync();
+        for (int ri = i + grp; ri < j; ri += S) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
+            gather_fma<V, T, U, UA>(acc, lcol, lval, lrp[ri] - base, lrp[ri + 1] - base, 1, a.B, ldb, colok[0], coff);
+            float *dst = a.C + (r0 + ri) * a.ldc;
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (colok[t]) vstore<V, NTC, UA>(dst + coff[t], acc[t]);
+        }
+        wave_lds_sync();  // the stage is refilled next
+        i = j;
     }
 }
 
@@ -997,14 +1006,21 @@ scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *r
         return SCORCH_OK;
     }
     a.xcd_slices = mp.xcd_slices;
-    // rows per wavefront: 4 once that leaves a workgroup for every compute unit (measured: 1, 2, 4, 8, 16 rows on the
-    // five benchmark workloads; 4 is within 1 % of the best of each that has 16 384 rows or more)
-    // (narrow lane groups, i.e. many groups per wavefront: up to one row per group)
+    // Rows per wavefront (a power of two): up to 4, or up to one per lane group, as long as at least 4096 wavefronts are
+    // left; more, up to 16, where the launch would have more than 12 288 workgroups, of which the chip starts one every
+    // 1.9 ns at best.  Measured with 4 / 8 / 16 rows: 169 343 rows, two column slices 141 / 127 / 127 us, one 128 /
+    // 134 / 139; 600 000 rows 194 / 168 / 165; 1.5 M rows, two slices 977 / 821 / 733; 30 000 rows 44 / 46 / 55.
     const int64_t rows_cap = std::max(4, std::min(kNaturalRowsMax, kWave / mp.G));
-    a.rows_per_wave = (int32_t)std::min<int64_t>(rows_cap, std::max<int64_t>(1, m / 4096));
+    a.rows_per_wave = 1;
+    while (a.rows_per_wave < rows_cap && (int64_t)m >= 8192 * (int64_t)a.rows_per_wave) a.rows_per_wave *= 2;
+    while (a.rows_per_wave < kNaturalRowsMax && (int64_t)m * mp.ncoltiles > (int64_t)12288 * kWavesPerBlock * a.rows_per_wave)
+        a.rows_per_wave *= 2;
     a.nb_wave = (int32_t)ceil_div64(m, (int64_t)kWavesPerBlock * a.rows_per_wave);
+    a.scout_rows = kWave;
+    while (ceil_div64(m, a.scout_rows) > kScoutsMax) a.scout_rows *= 2;
+    a.nb_items = (int32_t)ceil_div64(m, a.scout_rows);
     a.ncoltiles = mp.ncoltiles;
-    const int64_t grid = grid_size(mp, a.nb_wave);
+    const int64_t grid = grid_size(mp, (int64_t)a.nb_items + a.nb_wave);
     if (grid > 0x7fffffffLL) {
         set_error("launch grid of %lld workgroups exceeds the HIP limit", (long long)grid);
         return SCORCH_ERR_UNSUPPORTED;
