@@ -236,6 +236,15 @@ scorch_status_t scorch_sddmm_csr_planned(const scorch_spmm_plan_t *plan, int32_t
                                          float *out_vals, void *stream);
 
 /*
+ * The dense product of a graph-convolution layer (paper, Section 5.1): Y = act(X W + bias), X m x k, W k x n, Y m x n, all
+ * fp32 and row-major with leading dimensions ldx, ldw, ldy, for many rows and a W small enough to stay in LDS: k must not
+ * exceed 144 (SCORCH_ERR_UNSUPPORTED), n is free.  bias: n floats or NULL.  Y must not overlap an input.  fp32 products and
+ * sums (matrix instructions), fixed summation order.  Enqueues one kernel, never waits.
+ */
+scorch_status_t scorch_dense_layer(int32_t m, int32_t k, int32_t n, const float *X, int32_t ldx, const float *W, int32_t ldw,
+                                   const float *bias, int32_t activation, float *Y, int32_t ldy, void *stream);
+
+/*
  * Row pointers for a row-major coordinate list (paper, Appendix C: sparse tensors default to the coordinate
  * format; a COO matrix lists (row, column, value) triples).  Given the row coordinates of nnz entries sorted by
  * row (non-decreasing), writes rowptr_out[0..m] such that the entries of row i are [rowptr_out[i], rowptr_out[i+1]);

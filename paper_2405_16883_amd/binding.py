@@ -26,7 +26,7 @@ EXPORTS = (
     "scorch_spmm_csr", "scorch_spmm_plan_workspace_bytes", "scorch_spmm_plan", "scorch_spmm_csr_planned",
     "scorch_spmm_plan_destroy", "scorch_spmm_plan_info", "scorch_status_string", "scorch_last_error",
     "scorch_sddmm_csr", "scorch_sddmm_csr_planned", "scorch_spmm_csr_planned_epilogue", "scorch_coo_to_csr_rowptr",
-    "scorch_dcsr_to_csr_rowptr", "scorch_spmm_csr_static",
+    "scorch_dcsr_to_csr_rowptr", "scorch_spmm_csr_static", "scorch_dense_layer",
 )
 
 
@@ -88,6 +88,8 @@ def load_library() -> ctypes.CDLL:
     lib.scorch_sddmm_csr.argtypes = [i32, i32, i32, vp, vp, vp, vp, i32, vp, i32, vp, vp]
     lib.scorch_sddmm_csr_planned.restype = i32
     lib.scorch_sddmm_csr_planned.argtypes = [vp, i32, vp, vp, vp, vp, i32, vp, i32, vp, vp]
+    lib.scorch_dense_layer.restype = i32
+    lib.scorch_dense_layer.argtypes = [i32, i32, i32, vp, i32, vp, i32, vp, i32, vp, i32, vp]
     lib.scorch_status_string.restype = ctypes.c_char_p
     lib.scorch_status_string.argtypes = [i32]
     lib.scorch_last_error.restype = ctypes.c_char_p
@@ -246,6 +248,17 @@ def scorch_spmm_csr_planned_epilogue(plan: SpmmPlan, rowptr: torch.Tensor, colid
                                      stream: Optional[torch.cuda.Stream] = None) -> None:
     """C = act(A @ B + bias) in one pass (bias may be None; activation ACT_IDENTITY or ACT_RELU)."""
     st = (_native or _load_native()).spmm_csr_planned_epilogue(plan.handle, rowptr, colidx, vals, B, bias, activation, C, stream)
+    if st:
+        _check(st)
+
+
+DENSE_LAYER_K_MAX = 144
+
+
+def scorch_dense_layer(X: torch.Tensor, W: torch.Tensor, bias: Optional[torch.Tensor], activation: int, Y: torch.Tensor,
+                       stream: Optional[torch.cuda.Stream] = None) -> None:
+    """Y = act(X @ W + bias) in one pass, X with at most DENSE_LAYER_K_MAX columns (bias may be None)."""
+    st = (_native or _load_native()).dense_layer(X, W, bias, activation, Y, stream)
     if st:
         _check(st)
 

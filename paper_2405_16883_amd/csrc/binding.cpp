@@ -176,6 +176,28 @@ PyObject *sddmm_planned(PyObject *, PyObject *const *v, Py_ssize_t nargs) {
     return status_of(a, [&] { return scorch_sddmm_csr_planned(plan, d, rp, ci, x, B, ldb, Ct, ldct, out, s); });
 }
 
+// (X, W, bias, activation, Y, stream)
+PyObject *dense_layer(PyObject *, PyObject *const *v, Py_ssize_t nargs) {
+    if (!count_is(nargs, 6)) return nullptr;
+    Args a{v};
+    const float *X = a.floats(0, "X"), *W = a.floats(1, "W");
+    const int32_t ldx = a.ld(0, "X"), ldw = a.ld(1, "W");
+    const float *bias = a.floats(2, "bias");
+    const int32_t act = a.i32(3);
+    float *Y = a.floats(4, "Y");
+    const int32_t ldy = a.ld(4, "Y");
+    void *s = a.stream(5);
+    if (!a.ok) return nullptr;
+    const at::Tensor &x = THPVariable_Unpack(v[0]), &w = THPVariable_Unpack(v[1]), &y = THPVariable_Unpack(v[4]);
+    if (x.size(1) != w.size(0) || y.size(0) != x.size(0) || y.size(1) != w.size(1) ||
+        (v[2] != Py_None && THPVariable_Unpack(v[2]).numel() != w.size(1))) {
+        PyErr_SetString(PyExc_ValueError, "X, W, bias and Y do not fit together");
+        return nullptr;
+    }
+    const int32_t m = (int32_t)x.size(0), k = (int32_t)x.size(1), n = (int32_t)w.size(1);
+    return status_of(a, [&] { return scorch_dense_layer(m, k, n, X, ldx, W, ldw, bias, act, Y, ldy, s); });
+}
+
 // (m, row_idx, rowptr_out, bad_flag, stream)
 PyObject *coo_to_csr_rowptr(PyObject *, PyObject *const *v, Py_ssize_t nargs) {
     if (!count_is(nargs, 5)) return nullptr;
@@ -203,6 +225,7 @@ PyMethodDef kMethods[] = {
     {"spmm_csr_planned_epilogue", (PyCFunction)(void (*)(void))spmm_planned_epilogue, METH_FASTCALL, nullptr},
     {"sddmm_csr", (PyCFunction)(void (*)(void))sddmm, METH_FASTCALL, nullptr},
     {"sddmm_csr_planned", (PyCFunction)(void (*)(void))sddmm_planned, METH_FASTCALL, nullptr},
+    {"dense_layer", (PyCFunction)(void (*)(void))dense_layer, METH_FASTCALL, nullptr},
     {"coo_to_csr_rowptr", (PyCFunction)(void (*)(void))coo_to_csr_rowptr, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

@@ -208,6 +208,28 @@ scorch_status_t scorch_sddmm_csr_planned(const scorch_spmm_plan_t *plan, int32_t
                         static_cast<hipStream_t>(stream));
 }
 
+scorch_status_t scorch_dense_layer(int32_t m, int32_t k, int32_t n, const float *X, int32_t ldx, const float *W, int32_t ldw,
+                                   const float *bias, int32_t activation, float *Y, int32_t ldy, void *stream) {
+    if (m < 0 || k < 0 || n < 0) {
+        set_error("dense layer: negative dimension (m=%d k=%d n=%d)", m, k, n);
+        return SCORCH_ERR_INVALID_ARG;
+    }
+    if (activation != SCORCH_ACT_IDENTITY && activation != SCORCH_ACT_RELU) {
+        set_error("dense layer: unknown activation %d", activation);
+        return SCORCH_ERR_INVALID_ARG;
+    }
+    if (m == 0 || n == 0) return SCORCH_OK;
+    if (!Y || (k > 0 && (!X || !W))) {
+        set_error("dense layer: X, W and Y must not be NULL");
+        return SCORCH_ERR_INVALID_ARG;
+    }
+    if (ldx < k || ldw < n || ldy < n) {
+        set_error("dense layer: leading dimension too small (ldx=%d k=%d ldw=%d ldy=%d n=%d)", ldx, k, ldw, ldy, n);
+        return SCORCH_ERR_INVALID_ARG;
+    }
+    return launch_dense_tall(m, k, n, X, ldx, W, ldw, bias, activation, Y, ldy, static_cast<hipStream_t>(stream));
+}
+
 scorch_status_t scorch_coo_to_csr_rowptr(int32_t m, int64_t nnz, const int32_t *row_idx, int32_t *rowptr_out,
                                          int32_t *bad_flag, void *stream) {
     if (m < 0 || nnz < 0 || !rowptr_out || (nnz > 0 && !row_idx)) {

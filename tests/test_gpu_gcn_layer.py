@@ -55,3 +55,22 @@ def test_gcn_layer_matches_the_oracle(n_in, n_out, relu, with_bias):
     scale = np.abs(AH) @ np.abs(W.astype(np.float64)) + 1.0
     assert (np.abs(out - full) <= 1e-4 * scale).all(), "layer differs from the fp64 evaluation"
     layer.close()
+
+
+def test_weight_gradient_of_a_widening_layer_still_flows():
+    """Where torch records the dense product (it comes last) the layer leaves it to torch."""
+    p = make_scaled_config(3, 0.02, seed=3)
+    layer = GcnLayer(p.m, torch.from_numpy(p.rowptr).to(DEV), torch.from_numpy(p.colidx).to(DEV), torch.from_numpy(p.vals).to(DEV), p.nnz)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    H, W = torch.randn((p.m, 16), generator=g, device=DEV), torch.randn((16, 32), generator=g, device=DEV).requires_grad_()
+    out = layer.forward(H, W)
+    out.sum().backward()
+    with torch.no_grad():
+        Y = torch.empty((p.m, 16), device=DEV)
+        import paper_2405_16883_amd as sp
+        sp.scorch_spmm_csr_planned(layer._plan(16), layer.rowptr, layer.colidx, layer.vals, H, Y)
+        # both products of 16 terms are within 18 2^-24 of sum |y w| of the exact one
+        assert bool(((layer.forward(H, W) - out).abs() <= 18 * 2.0 ** -23 * (Y.abs() @ W.abs())).all())
+        on = (out > 0).double()
+    assert bool(((W.grad.double() - Y.double().T @ on).abs() <= p.m * 2.0 ** -24 * (Y.double().abs().T @ on)).all())
+    layer.close()
