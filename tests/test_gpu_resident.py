@@ -67,3 +67,19 @@ def test_resident_is_left_to_rows_of_increasing_columns_and_chosen_for_a_dense_w
     assert plan.info().mode == 3
     check_against_oracle(p, d.run_planned(plan), d.ldc, label="chosen")
     plan.destroy()
+
+
+@pytest.mark.parametrize("m,n", [(40, 16), (2500, 5)])
+def test_a_plan_serves_other_columns_of_the_same_row_pointers(m, n):
+    """A plan is bound to the row pointers; the columns are the call's own (increasing, as the planner saw them)."""
+    k = 2 * chunk_rows(n) + 50
+    lens = np.random.default_rng(m).integers(0, 300, size=m)
+    p, q = (csr_from_row_lengths(lens, k, n, seed=s, duplicates=False) for s in (1, 2))
+    assert np.array_equal(p.rowptr, q.rowptr) and not np.array_equal(p.colidx, q.colidx)
+    with tuning("res=1"):
+        d, e = DeviceProblem(p), DeviceProblem(integer_valued(q, seed=3))
+        plan = d.make_plan()
+        assert plan.info().mode == 3
+        check_against_oracle(e.p, e.run_planned(plan), e.ldc, exact=True, label="other columns")
+        check_against_oracle(p, d.run_planned(plan), d.ldc, label="the planner's columns")
+        plan.destroy()
