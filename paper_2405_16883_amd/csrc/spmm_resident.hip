@@ -83,7 +83,7 @@ template <int G> __device__ __forceinline__ float sum_groups(float x) {
 // more), lane 8 i + 4 that of the next chunk (column k1).  The plan's answer is compared with the columns at hand, which may be
 // others than the planner saw, and searched for anew where it does not fit: four probes cut a range into five.  Whatever the
 // columns are, the result lies in the row.  Measured, 4096 x 16 384, 10 % stored, n = 16: searched at every call 27.5 us
-// (5 rounds of dependent reads), taken from the plan unchecked 20.9.
+// (5 rounds of dependent reads), compared 21.6, taken from the plan unchecked 20.9.
 __device__ __forceinline__ int resident_bounds(const ResidentArgs &a, int64_t row0, int row_end, int chunk, int k0, int k1, int lane) {
     const int64_t row = row0 + (lane >> 3) * kResidentWaves;
     const int target = (lane & 4) ? k1 : k0;
