@@ -527,8 +527,12 @@ constexpr int kNaturalRowsMax = 16;
 constexpr int kNaturalShort = 32;
 constexpr int kScoutsMax = 2048;  // per column tile
 
-// Row length beyond which a row is left to the scouts, for a workgroup of `rows` rows of which `mid` are longer than kNaturalMid.
-__device__ __forceinline__ int natural_long_limit(int mid, int rows) { return mid * 4 <= rows ? kNaturalMid : kNaturalLong; }
+// Row length beyond which a row is left to the scouts, for a workgroup of `rows` rows of which `mid` are longer than kNaturalMid
+// and `longs` longer than kNaturalLong.  Where such rows are the normal case nothing is left to them: 2048 rows of 3600
+// entries, n = 256, took 1324 us when 64 rows waited for one scout, 314 with every wavefront on rows of its own.
+__device__ __forceinline__ int natural_long_limit(int mid, int longs, int rows) {
+    return mid * 4 <= rows ? kNaturalMid : longs * 4 <= rows ? kNaturalLong : 0x7fffffff;
+}
 
 template <int V, int G, int T, int U, int NT, bool UA>
 __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) {
@@ -573,7 +577,9 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
             const int len = first + lane < a.m ? a.rowptr[row + 1] - q0 : 0;
             const unsigned long long mid = __ballot(len > kNaturalMid);
             const unsigned long long mine = group >= kWave ? mid : (mid >> (lane & ~(group - 1))) & ((1ull << group) - 1ull);
-            const int limit = natural_long_limit(__builtin_popcountll(mine), group);
+            const unsigned long long far = __ballot(len > kNaturalLong);
+            const unsigned long long mine_far = group >= kWave ? far : (far >> (lane & ~(group - 1))) & ((1ull << group) - 1ull);
+            const int limit = natural_long_limit(__builtin_popcountll(mine), __builtin_popcountll(mine_far), group);
             unsigned long long todo = __ballot(len > limit);
             while (todo != 0ull) {  // the same for the whole workgroup
                 const int r = __builtin_ctzll(todo);
@@ -625,9 +631,10 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
     const int rpv = nr > 0 ? a.rowptr[r0 + min(lane, nr)] : 0;
     const int rnext = __shfl_down(rpv, 1, kWave);  // lanes past the run hold the last pointer; lane 63 is never a row
     const int nmid = (int)__builtin_popcountll(__ballot(lane < nr && rnext - rpv > kNaturalMid));
-    if (lane == 0 && nmid > 0) atomicAdd(&s_nmid, nmid);
+    const int nfar = (int)__builtin_popcountll(__ballot(lane < nr && rnext - rpv > kNaturalLong));
+    if (lane == 0 && nmid > 0) atomicAdd(&s_nmid, nmid + (nfar << 16));  // 64 rows at most: two counts in one word
     __syncthreads();
-    const int long_limit = natural_long_limit(s_nmid, kWavesPerBlock * NR);  // as the scouts decide
+    const int long_limit = natural_long_limit(s_nmid & 0xffff, s_nmid >> 16, kWavesPerBlock * NR);  // as the scouts decide
     if (nr <= 0) return;
     lrp[lane] = rpv;
     wave_lds_sync();
@@ -1013,7 +1020,9 @@ scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *r
     const int64_t rows_cap = std::max(4, std::min(kNaturalRowsMax, kWave / mp.G));
     a.rows_per_wave = 1;
     while (a.rows_per_wave < rows_cap && (int64_t)m >= 8192 * (int64_t)a.rows_per_wave) a.rows_per_wave *= 2;
-    while (a.rows_per_wave < kNaturalRowsMax && (int64_t)m * mp.ncoltiles > (int64_t)12288 * kWavesPerBlock * a.rows_per_wave)
+    // Not where column tiles make the many workgroups out of few (long) rows: 4096 rows of 1638 entries, 16 tiles.
+    while (a.rows_per_wave < kNaturalRowsMax && (int64_t)m * mp.ncoltiles > (int64_t)12288 * kWavesPerBlock * a.rows_per_wave &&
+           (int64_t)m >= 8192 * (int64_t)a.rows_per_wave)
         a.rows_per_wave *= 2;
     a.nb_wave = (int32_t)ceil_div64(m, (int64_t)kWavesPerBlock * a.rows_per_wave);
     a.scout_rows = kWave;

@@ -24,3 +24,15 @@ def test_long_rows(m, n):
     for q, exact in ((p, False), (integer_valued(p, seed=n), True)):
         d = DeviceProblem(q)
         check_against_oracle(q, d.run_natural(), d.ldc, exact=exact, label=f"m={m} n={n}")
+
+
+@pytest.mark.parametrize("m,n", [(600, 256), (2048, 64), (9000, 36)])
+def test_rows_beyond_the_long_limit_are_the_normal_case(m, n):
+    """Every wavefront takes its own rows then; a stretch of short rows beside them, and one of a few long rows, stay as they were."""
+    rng = np.random.default_rng(m)
+    lens = rng.integers(2049, 2500, size=m) if m < 5000 else rng.integers(0, 30, size=m)
+    lens[m // 3:m // 3 + 100] = rng.integers(0, 40, size=100)
+    lens[m // 2:m // 2 + 40] = 2100
+    p = csr_from_row_lengths(lens, 3000, n, seed=n, duplicates=False)
+    d = DeviceProblem(p)
+    check_against_oracle(p, d.run_natural(), d.ldc, label=f"long rows m={m} n={n}")
