@@ -876,7 +876,7 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
                                const float *bias, int32_t act, hipStream_t stream) {
     if (plan->params.PANEL && panel_operands_ok(plan->n, B, ldb, C, ldc))
         return launch_panel(plan, rowptr, colidx, vals, B, ldb, C, ldc, bias, act, stream);
-    if (plan->params.RES) return launch_resident(plan, rowptr, colidx, vals, B, ldb, C, ldc, bias, act, stream);
+    if (plan->params.RES) return launch_resident(plan, colidx, vals, B, ldb, C, ldc, bias, act, stream);
     const Mapping mp = pick_mapping(plan->n, B, ldb, C, ldc, plan->params.SLICED);
     ExecArgs a{};
     a.rowptr = rowptr;

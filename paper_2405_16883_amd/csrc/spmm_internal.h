@@ -115,7 +115,6 @@ struct PanelArgs {
 };
 
 struct ResidentArgs {
-    const int32_t *rowptr;
     const int32_t *ptr;  // [nchunks + 1][m]: a row's first entry of chunk p or later, for the columns that the planner saw
     const int32_t *colidx;
     const float *vals;
@@ -200,8 +199,8 @@ scorch_status_t launch_panel(const scorch_spmm_plan_t *plan, const int32_t *rowp
 // spmm_resident.hip
 scorch_status_t launch_plan_resident(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int32_t *flag,
                                      hipStream_t stream);
-scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
-                                const float *vals, const float *B, int64_t ldb, float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream);
+scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *colidx, const float *vals, const float *B, int64_t ldb,
+                                float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream);
 
 // sddmm_exec.hip (plan == nullptr: plan-free, one wavefront per row)
 scorch_status_t launch_sddmm(const scorch_spmm_plan_t *plan, int32_t m, int32_t d, const int32_t *rowptr,

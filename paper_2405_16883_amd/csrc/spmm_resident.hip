@@ -5,9 +5,11 @@
 // requests, not by their bytes: a die's L2 serves 250 G requests/s over the chip, 128 bytes each at most, so 64-byte rows
 // arrive at 16 TB/s.  Here every workgroup keeps a chunk of the rows of B in LDS for its whole life (158 KB: 158 * 256 / W
 // rows of W columns) and takes, of every row of A in its block of rows, the entries that fall into the chunk.  Where
-// they start is in the plan and checked against the columns of the call (increasing, as the planner saw them).  B enters a CU once,
-// A is read once, and each chunk leaves partial rows that a second launch adds in chunk order (none if B fits one
-// chunk).
+// they start is in the plan.  The plan is bound to the row pointers, not to the columns: where one of a row's entries turns
+// out to lie outside the chunk, they are all gathered from B instead (resident_gather), so that other columns, in any
+// order and repeated, are added up as well (4096 x 16 384, 10 % stored, n = 16: 21.5 us for the planner's columns, 51 for shuffled
+// ones; the gather kernel 42).  B enters a CU once, A is read once, and each chunk leaves partial rows that a second
+// launch adds in chunk order (none if B fits one chunk).
 //
 //   workgroup   16 wavefronts on a CU of its own: one chunk x a block of rows
 //   wavefront   one row at a time: 64 entries per window, one per lane, requested a row ahead
@@ -79,37 +81,48 @@ template <int G> __device__ __forceinline__ float sum_groups(float x) {
     return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
-// Eight lanes per row, four per bound: lane 8 i of the result holds row i's first entry of this chunk or later (column k0 or
-// more), lane 8 i + 4 that of the next chunk (column k1).  The plan's answer is compared with the columns at hand, which may be
-// others than the planner saw, and searched for anew where it does not fit: four probes cut a range into five.  Whatever the
-// columns are, the result lies in the row.  Measured, 4096 x 16 384, 10 % stored, n = 16: searched at every call 27.5 us
-// (5 rounds of dependent reads), compared 21.6, taken from the plan unchecked 20.9.
-__device__ __forceinline__ int resident_bounds(const ResidentArgs &a, int64_t row0, int row_end, int chunk, int k0, int k1, int lane) {
-    const int64_t row = row0 + (lane >> 3) * kResidentWaves;
-    const int target = (lane & 4) ? k1 : k0;
-    const int j = lane & 3;
-    int lo = 0, hi = 0, at = 0;
-    if (row < row_end) {
-        lo = a.rowptr[row];
-        hi = a.rowptr[row + 1];
-        at = a.ptr[(int64_t)(chunk + ((lane >> 2) & 1)) * a.m + row];
+// Entry ranges of this chunk in 32 rows of a wavefront: lane i holds row i's first entry of the chunk, lane 32 + i its
+// first entry after it.  They are the plan's: for the columns that the planner saw, every entry of a range lies in the
+// chunk; whatever the columns of the call are, the ranges of all chunks cover each entry of the row once.
+__device__ __forceinline__ int resident_bounds(const ResidentArgs &a, int64_t row0, int row_end, int chunk, int lane) {
+    const int64_t row = row0 + (lane & 31) * kResidentWaves;
+    return row < row_end ? a.ptr[(int64_t)(chunk + (lane >> 5)) * a.m + row] : 0;
+}
+
+// Four columns c ... c+3 of a row of B; those past column n are never stored and may hold anything.
+template <bool A16> __device__ __forceinline__ f4 resident_load_b(const ResidentArgs &a, int row, int c) {
+    const float *src = a.B + (int64_t)row * a.ldb;
+    if constexpr (A16) return *reinterpret_cast<const f4 *>(src + (c < a.n ? c : 0));
+    f4 x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = src[min(c + i, a.n - 1)];
+    return x;
+}
+
+template <int G, int T, bool A16, int J, int N, int U = 0>
+__device__ __forceinline__ void resident_gather_batch(f4 (&acc)[T], const ResidentArgs &a, int col, int val, int lig) {
+    if constexpr (U < N) {
+        const int c = group_lane<G, J + U>(col);
+        const float v = __int_as_float(group_lane<G, J + U>(val));
+        const bool there = (uint32_t)c < (uint32_t)a.k;
+        f4 x[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) x[t] = resident_load_b<A16>(a, there ? c : 0, t * 4 * G + lig * 4);
+        resident_gather_batch<G, T, A16, J, N, U + 1>(acc, a, col, val, lig);  // the loads of the batch before its multiply-adds
+#pragma unroll
+        for (int t = 0; t < T; ++t) vfma<4>(acc[t], there ? v : 0.f, there ? x[t] : f4{0.f, 0.f, 0.f, 0.f});
     }
-    bool fits = at >= lo && at <= hi;
-    if (fits && j == 0 && at > lo) fits = a.colidx[at - 1] < target;
-    if (fits && j == 1 && at < hi) fits = a.colidx[at] >= target;
-    if (__ballot(fits) == ~0ull) return at;
-    while (__ballot(lo < hi) != 0ull) {
-        const uint32_t len = lo < hi ? (uint32_t)(hi - lo) : 0u;
-        const auto probe = [&](uint32_t i) { return lo + (int)((uint64_t)len * (i + 1) / 5u); };
-        const bool below = len > 0 && a.colidx[probe((uint32_t)j)] < target;
-        const int c = __builtin_popcountll((__ballot(below) >> (lane & ~3)) & 0xFull);
-        if (len > 0) {
-            const int nlo = c > 0 ? probe((uint32_t)c - 1) + 1 : lo;
-            hi = c < 4 ? probe((uint32_t)c) : hi;
-            lo = nlo;
-        }
+}
+
+// The first `steps` entries of every group's window, gathered from B.  `col` is -1 in the lanes past the row's entries.
+// An entry that is not there, or not a column, adds nothing, whatever row 0 of B holds.
+template <int G, int T, bool A16, int J = 0>
+__device__ __forceinline__ void resident_gather(f4 (&acc)[T], const ResidentArgs &a, int col, int val, int steps, int lig) {
+    constexpr int N = G < 4 ? G : 4;
+    if constexpr (J < G) {
+        resident_gather_batch<G, T, A16, J, N>(acc, a, col, val, lig);
+        if (J + N < G && steps > J + N) resident_gather<G, T, A16, J + N>(acc, a, col, val, steps, lig);
     }
-    return lo;
 }
 
 struct ResidentWindows {
@@ -156,7 +169,6 @@ __global__ __launch_bounds__(kResidentThreads) void spmm_resident_kernel(const R
 
     resident_fetch<W, A16>(a, k0, s_b, wv, lane);
     if (tid < W) s_b[kResidentFloats + tid] = 0.f;
-    const int k1 = (int)min((int64_t)a.k, (int64_t)k0 + KR);
     // lanes past the row's entries of the chunk read the last of them once more (no further cache lines), unused
     const auto entry = [&](uint32_t at, uint32_t end) { return min(at + (uint32_t)lane_entry, max(end, 1u) - 1u); };
     const auto request = [&](ResidentWindows &w, uint32_t s, uint32_t e) {
@@ -169,8 +181,8 @@ __global__ __launch_bounds__(kResidentThreads) void spmm_resident_kernel(const R
             }
     };
     int64_t row = (int64_t)blk * a.rows_per_block + wv;
-    int bounds = resident_bounds(a, row, row_end, chunk, k0, k1, lane);
-    const auto bound = [&](int i, int which) { return (uint32_t)__builtin_amdgcn_readlane(bounds, (i & 7) * 8 + which * 4); };
+    int bounds = resident_bounds(a, row, row_end, chunk, lane);
+    const auto bound = [&](int i, int which) { return (uint32_t)__builtin_amdgcn_readlane(bounds, (i & 31) + which * 32); };
     uint32_t s = bound(0, 0), e = bound(0, 1);
     ResidentWindows next{};
     request(next, s, e);
@@ -178,24 +190,43 @@ __global__ __launch_bounds__(kResidentThreads) void spmm_resident_kernel(const R
     __syncthreads();
     for (int i = 1; row < row_end; row += kResidentWaves, ++i) {
         const ResidentWindows cur = next;
-        if ((i & 7) == 0) bounds = resident_bounds(a, row + kResidentWaves, row_end, chunk, k0, k1, lane);
+        if ((i & 31) == 0) bounds = resident_bounds(a, row + kResidentWaves, row_end, chunk, lane);
         const uint32_t s2 = bound(i, 0), e2 = bound(i, 1);
         request(next, s2, e2);
         f4 acc[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+        const auto steps = [&](uint32_t at) { return (int)((e - at + S - 1) / S); };
+        const auto valid = [&](uint32_t at) { return at + (uint32_t)lane_entry < e; };
+        const auto inside = [&](int col) { return (uint32_t)(col - k0) < (uint32_t)KR; };
         const auto work = [&](int col, float value, uint32_t at) {
-            const bool in = at + (uint32_t)lane_entry < e && (uint32_t)(col - k0) < (uint32_t)KR;
+            const bool in = valid(at) && inside(col);
             const int off = in ? (col - k0) * (W * 4) : zero_off;
-            resident_window<G, T>(acc, off, __float_as_int(in ? value : 0.f), (int)((e - at + S - 1) / S), lds, lig16);
+            resident_window<G, T>(acc, off, __float_as_int(in ? value : 0.f), steps(at), lds, lig16);
         };
         uint32_t at = s;
+        bool outside = false;
 #pragma unroll
         for (int i = 0; i < kResidentWindows; ++i, at += kWave)
-            if (at < e) work(cur.c[i], cur.v[i], at);
+            if (at < e) {
+                outside |= valid(at) && !inside(cur.c[i]);
+                work(cur.c[i], cur.v[i], at);
+            }
         for (; at < e; at += kWave) {
             const uint32_t p = entry(at, e);
-            work(a.colidx[p], a.vals[p], at);
+            const int col = a.colidx[p];
+            float value = a.vals[p];
+            asm volatile("" : "+v"(value));  // requested together with the index, not once it is known
+            outside |= valid(at) && !inside(col);
+            work(col, value, at);
+        }
+        if (__ballot(outside) != 0ull) {  // the row once more, wherever its columns are
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+            for (at = s; at < e; at += kWave) {
+                const uint32_t p = entry(at, e);
+                resident_gather<G, T, A16>(acc, a, valid(at) ? a.colidx[p] : -1, __float_as_int(a.vals[p]), steps(at), lig);
+            }
         }
 #pragma unroll
         for (int t = 0; t < T; ++t)
@@ -292,11 +323,10 @@ template <bool A16> static resident_fn pick_resident(int W) {
     }
 }
 
-scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, const float *vals, const float *B,
-                                int64_t ldb, float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream) {
+scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *colidx, const float *vals, const float *B, int64_t ldb,
+                                float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream) {
     const int W = plan->params.RES;
     ResidentArgs a{};
-    a.rowptr = rowptr;
     a.ptr = reinterpret_cast<const int32_t *>(plan->workspace + plan->layout.off_res_ptr);
     a.colidx = colidx;
     a.vals = vals;

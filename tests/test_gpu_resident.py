@@ -1,5 +1,8 @@
 """The resident kernel (narrow B kept in LDS in chunks) against the oracle: one chunk and several, the last of one row,
-every padded width, rows of no, one and many windows of a chunk, and rows whose columns are not increasing."""
+every padded width, rows of no, one and many windows of a chunk, rows whose columns are not increasing, and other columns
+at the call than at the plan."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -82,4 +85,29 @@ def test_a_plan_serves_other_columns_of_the_same_row_pointers(m, n):
         assert plan.info().mode == 3
         check_against_oracle(e.p, e.run_planned(plan), e.ldc, exact=True, label="other columns")
         check_against_oracle(p, d.run_planned(plan), d.ldc, label="the planner's columns")
+        plan.destroy()
+
+
+@pytest.mark.parametrize("n", [3, 8, 15, 20, 64])  # every padded width
+@pytest.mark.parametrize("m", [40, 2500])
+def test_a_plan_serves_columns_in_any_order_and_repeated(m, n):
+    """The columns of the call need not be increasing either: entries in any chunk's place, repeated ones, a row left as it
+    was planned beside them, and rows of B that no entry names are never added (here they are not numbers)."""
+    k = 2 * chunk_rows(n) + 50
+    lens = np.random.default_rng(m).integers(0, 300, size=m)
+    lens[3] = 0
+    p = csr_from_row_lengths(lens, k, n, seed=1, duplicates=False)
+    q = integer_valued(csr_from_row_lengths(lens, k - 2, n, seed=2, sorted_cols=False, duplicates=True), seed=3)
+    cols = q.colidx + 1  # columns 0 and k - 1 are named by no entry
+    some = p.rowptr[m // 2]  # wavefronts meet both kinds of rows
+    cols[:some] = np.clip(p.colidx[:some], 1, k - 2)
+    B = np.full((k, n), np.nan, dtype=np.float32)
+    B[1:k - 1] = q.B
+    q = dataclasses.replace(q, k=k, colidx=cols, B=B)
+    with tuning("res=1"):
+        plan = DeviceProblem(p).make_plan()
+        assert plan.info().mode == 3
+        for r in (q, with_padding(q, n + 3)):
+            e = DeviceProblem(r)
+            check_against_oracle(r, e.run_planned(plan), e.ldc, exact=True, label=f"any order m={m} n={n} ldb={r.ldb}")
         plan.destroy()
