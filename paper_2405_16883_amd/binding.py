@@ -131,12 +131,6 @@ def _dev_ptr(t: Optional[torch.Tensor], dtype: torch.dtype, name: str) -> Option
     return t.data_ptr() if t.numel() else None
 
 
-def _ld(t: torch.Tensor, name: str) -> int:
-    if t.dim() != 2 or (t.numel() and t.stride(1) != 1):
-        raise ValueError(f"{name} must be 2-D with unit column stride")
-    return int(t.stride(0)) if t.shape[0] > 1 else max(int(t.stride(0)), int(t.shape[1]))
-
-
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
     s = stream if stream is not None else torch.cuda.current_stream()
     return int(s.cuda_stream)

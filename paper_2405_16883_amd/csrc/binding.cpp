@@ -6,9 +6,11 @@
 #include <Python.h>
 
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
+#include <exception>
 
 #include "scorch_spmm.h"
 
@@ -40,7 +42,7 @@ struct Args {
             ok = false;
         } else if (t.scalar_type() != type) {
             PyObject *got = PyObject_GetAttrString(v[i], "dtype");
-            PyErr_Format(PyExc_ValueError, "%s must be %s, got %S", name, type == at::kInt ? "torch.int32" : "torch.float32", got);
+            if (got) PyErr_Format(PyExc_ValueError, "%s must be %s, got %S", name, type == at::kInt ? "torch.int32" : "torch.float32", got);
             Py_XDECREF(got);
             ok = false;
         }
@@ -218,15 +220,30 @@ PyObject *coo_to_csr_rowptr(PyObject *, PyObject *const *v, Py_ssize_t nargs) {
     return status_of(a, [&] { return scorch_coo_to_csr_rowptr(m, nnz, rows, out, bad, s); });
 }
 
+// What the interpreter calls.  A tensor without plain memory (sparse, fake, wrapped by a transform) and a missing GPU make torch
+// throw; the exception becomes a Python error here, it must not reach the interpreter's C frames.
+typedef PyObject *(*method)(PyObject *, PyObject *const *, Py_ssize_t);
+template <method F> PyObject *guarded(PyObject *self, PyObject *const *v, Py_ssize_t nargs) {
+    try {
+        return F(self, v, nargs);
+    } catch (...) {
+        torch::translate_exception_to_python(std::current_exception());
+        return nullptr;
+    }
+}
+template <method F> PyMethodDef entry(const char *name) {
+    return {name, (PyCFunction)(void (*)(void))guarded<F>, METH_FASTCALL, nullptr};
+}
+
 PyMethodDef kMethods[] = {
-    {"spmm_csr", (PyCFunction)(void (*)(void))spmm<scorch_spmm_csr>, METH_FASTCALL, nullptr},
-    {"spmm_csr_static", (PyCFunction)(void (*)(void))spmm<scorch_spmm_csr_static>, METH_FASTCALL, nullptr},
-    {"spmm_csr_planned", (PyCFunction)(void (*)(void))spmm_planned, METH_FASTCALL, nullptr},
-    {"spmm_csr_planned_epilogue", (PyCFunction)(void (*)(void))spmm_planned_epilogue, METH_FASTCALL, nullptr},
-    {"sddmm_csr", (PyCFunction)(void (*)(void))sddmm, METH_FASTCALL, nullptr},
-    {"sddmm_csr_planned", (PyCFunction)(void (*)(void))sddmm_planned, METH_FASTCALL, nullptr},
-    {"dense_layer", (PyCFunction)(void (*)(void))dense_layer, METH_FASTCALL, nullptr},
-    {"coo_to_csr_rowptr", (PyCFunction)(void (*)(void))coo_to_csr_rowptr, METH_FASTCALL, nullptr},
+    entry<spmm<scorch_spmm_csr>>("spmm_csr"),
+    entry<spmm<scorch_spmm_csr_static>>("spmm_csr_static"),
+    entry<spmm_planned>("spmm_csr_planned"),
+    entry<spmm_planned_epilogue>("spmm_csr_planned_epilogue"),
+    entry<sddmm>("sddmm_csr"),
+    entry<sddmm_planned>("sddmm_csr_planned"),
+    entry<dense_layer>("dense_layer"),
+    entry<coo_to_csr_rowptr>("coo_to_csr_rowptr"),
     {nullptr, nullptr, 0, nullptr},
 };
 
