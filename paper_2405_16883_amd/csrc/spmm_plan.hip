@@ -177,7 +177,8 @@ __global__ __launch_bounds__(kBlock) void plan_build_kernel(const PlanArgs a) {
     // workgroups before this one, the row pointers of the first tile
     const int32_t nnz = a.m > 0 ? a.rowptr[a.m] : 0;
     int run[kQ] = {0, 0, 0, 0, 0};
-    if (a.counted)
+    // a workspace that does not even hold the counts is not read; that nothing fits it is found below
+    if (a.counted && a.workspace_bytes >= (uint64_t)kQ * nblk * sizeof(int32_t))
         for (int j = tid; j < blk; j += kBlock)
 #pragma unroll
             for (int k = 0; k < kQ; ++k) run[k] += counts[k * nblk + j];

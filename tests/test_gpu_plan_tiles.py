@@ -1,7 +1,10 @@
 """Plan lists against the plan oracle, bit for bit, at the edges of the planning kernels' tiles of 256 rows, of the
-workgroups that count the rows before their own (up to 8), and of windows that reach past a tile."""
+workgroups that count the rows before their own (up to 8), and of windows that reach past a tile; workspaces that are too small."""
 import numpy as np
 import pytest
+import torch
+
+import paper_2405_16883_amd as sp
 
 from oracle.plan import plan_oracle
 from workloads import csr_from_row_lengths
@@ -27,3 +30,16 @@ def test_lists_at_tile_edges(m, tune):
         for key in ("win_row_start", "win_stage", "wave_rows", "wave_span", "items", "split"):
             assert np.array_equal(got[key], want[key]), key
         plan.destroy()
+
+
+@pytest.mark.parametrize("m", [300, 2049, 100000, 600000])  # without a count per workgroup and with one, up to 20 KB of them
+def test_a_workspace_that_is_too_small_is_refused_and_left_alone(m):
+    dev = torch.device("cuda")
+    rowptr = torch.arange(0, 3 * m + 1, 3, dtype=torch.int32, device=dev)
+    need = sp.scorch_spmm_plan_workspace_bytes(m, m, 64, 3 * m)
+    for size in (256, need // 2, need - 1):
+        whole = torch.full((need + 256,), 90, dtype=torch.uint8, device=dev)
+        with pytest.raises(sp.ScorchError, match=f"workspace of {size} bytes is smaller than the {need} needed"):
+            sp.scorch_spmm_plan(m, m, 64, rowptr, 3 * m, workspace=whole[:size])
+        assert bool((whole == 90).all())
+    sp.scorch_spmm_plan(m, m, 64, rowptr, 3 * m, workspace=torch.empty(need, dtype=torch.uint8, device=dev)).destroy()
