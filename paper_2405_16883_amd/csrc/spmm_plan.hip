@@ -529,6 +529,7 @@ __host__ __device__ static int32_t want_resident(int32_t m, int32_t k, int64_t n
     if (m <= 0 || k <= 0 || n < 3 || n > 64) return 0;
     const int32_t W = resident_width(n);
     const int64_t chunks = resident_chunks(k, W);
+    if ((int64_t)m * chunks > nnz) return 0;  // never pays: a row of a chunk costs 2930, an entry saves 110 at most (and the rest fits 64 bits)
     const int64_t per_entry = n > 32 ? 110 : n % 4 != 0 ? 75 : n > 8 ? 57 : n > 4 ? 50 : 35;
     const int64_t entries = nnz * (W > 32 ? 30 : W > 16 ? 26 : 20), rows = (int64_t)m * chunks * 2930;
     int64_t resident = 40000000 + (entries > rows ? entries : rows);

@@ -49,3 +49,18 @@ def test_binding_refuses_cpu_tensors():
     z = torch.zeros(3, dtype=torch.int32)
     with pytest.raises(ValueError):
         sp.scorch_spmm_csr(2, 2, 2, z, z, torch.zeros(3), torch.zeros(2, 2), torch.zeros(2, 2))
+
+
+@pytest.mark.parametrize("n", [3, 16, 33, 64])
+@pytest.mark.parametrize("m,k", [(370_000_000, 370_000_000), (2**31 - 1, 2**31 - 1), (2**31 - 1, 1000), (1000, 2**31 - 1)])
+@pytest.mark.parametrize("nnz", [0, 1_000_000_000, 2**31 - 1])
+def test_sizes_at_which_chunks_times_rows_exceed_64_bits_stay_with_the_gather_kernels(monkeypatch, m, k, nnz, n):
+    """The workspace of a matrix that no chunk of B in LDS can pay for (fewer than 1000 entries per row) is the gather kernels'."""
+    if not os.path.exists(sp.LIB_PATH):
+        pytest.skip("library not built")
+    if nnz >= 1000 * m:
+        pytest.skip("dense rows")
+    monkeypatch.delenv("SCORCH_SPMM_TUNE", raising=False)
+    chosen = sp.scorch_spmm_plan_workspace_bytes(m, k, n, nnz)
+    monkeypatch.setenv("SCORCH_SPMM_TUNE", "res=0")
+    assert chosen == sp.scorch_spmm_plan_workspace_bytes(m, k, n, nnz)
