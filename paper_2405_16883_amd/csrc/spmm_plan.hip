@@ -51,6 +51,7 @@ struct RowClass {
 
 __device__ __forceinline__ RowClass classify(int len, int LW, int CH, int BCH) {
     RowClass r{0, 0, 0, 0, 0};
+    if (len < 0) return r;  // of no class: the host finds a row missing
     if (len <= LW) r.is_short = 1;
     else if (len <= CH) r.wave = 1;
     else {
@@ -747,9 +748,14 @@ scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, cons
     plan->n_split = got.totals[2];
     plan->n_slots = got.totals[3];
     plan->n_short = got.totals[4];
+    // Every row is of one class.  Where one is not, its pointers decrease, and windows may be missing from the table.
+    if ((int64_t)plan->n_wave + plan->n_short + plan->n_split + (plan->n_items - plan->n_slots) != plan->m) {
+        set_error("rowptr decreases (or changed while it was read)");
+        return SCORCH_ERR_INVALID_ARG;
+    }
     if (plan->n_wave > L.cap_wave || plan->n_items > L.cap_items || plan->n_split > L.cap_split ||
         plan->n_slots > L.cap_slots) {
-        set_error("plan lists exceed the workspace bound (rowptr changed or is not non-decreasing?)");
+        set_error("plan lists exceed the workspace bound (rowptr changed while it was read?)");
         return SCORCH_ERR_INVALID_ARG;
     }
     // The panel and resident kernels need every row's columns in strictly increasing order; without colidx this cannot be

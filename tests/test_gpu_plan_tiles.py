@@ -43,3 +43,15 @@ def test_a_workspace_that_is_too_small_is_refused_and_left_alone(m):
             sp.scorch_spmm_plan(m, m, 64, rowptr, 3 * m, workspace=whole[:size])
         assert bool((whole == 90).all())
     sp.scorch_spmm_plan(m, m, 64, rowptr, 3 * m, workspace=torch.empty(need, dtype=torch.uint8, device=dev)).destroy()
+
+
+@pytest.mark.parametrize("m", [4, 300, 5000, 600000])
+def test_row_pointers_that_decrease_are_refused(m):
+    """A plan of them would lack windows, which an execution would then read."""
+    dev = torch.device("cuda")
+    for at in (1, m // 2, m - 1):
+        rowptr = torch.arange(0, 5 * m + 1, 5, dtype=torch.int32, device=dev)
+        rowptr[at] += 7
+        with pytest.raises(sp.ScorchError, match="rowptr decreases") as e:
+            sp.scorch_spmm_plan(m, 100, 8, rowptr, 5 * m)
+        assert e.value.status == sp.binding.SCORCH_ERR_INVALID_ARG
