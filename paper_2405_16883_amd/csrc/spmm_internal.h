@@ -64,6 +64,7 @@ struct alignas(64) PlanResult {
     int32_t nnz;
     int32_t totals[5];  // wave rows, items, split rows, slots, short rows
     int32_t done;       // written last
+    PlanResult *next;   // host side only: the next slot that no call is using
 };
 
 // Everything the execution kernels need, passed by value.

@@ -17,7 +17,6 @@
 #include <algorithm>
 #include <cstdlib>
 #include <mutex>
-#include <vector>
 
 namespace scorch {
 
@@ -666,25 +665,30 @@ constexpr int32_t kPlanRecount = 8;
 // Slots of host memory that the planning kernels write their result to: taken for the length of one call and given back
 // (as many as calls were in flight at once, 64 bytes each).
 static std::mutex g_result_mutex;
-static std::vector<PlanResult *> g_result_free;
+static PlanResult *g_result_free;  // linked through the slots themselves: nothing here can throw
 
 static scorch_status_t take_result(PlanResult **out) {
     std::lock_guard<std::mutex> lock(g_result_mutex);
-    if (g_result_free.empty()) {
+    if (!g_result_free) {
         constexpr size_t kSlots = 4096 / sizeof(PlanResult);
         void *page = nullptr;
         hipError_t e = hipHostMalloc(&page, kSlots * sizeof(PlanResult), hipHostMallocPortable | hipHostMallocMapped);
         if (e != hipSuccess) return hip_fail(e, "allocate host memory for the plan's result");
-        for (size_t i = 0; i < kSlots; ++i) g_result_free.push_back(static_cast<PlanResult *>(page) + i);
+        PlanResult *slots = static_cast<PlanResult *>(page);
+        for (size_t i = 0; i < kSlots; ++i) {
+            slots[i].next = g_result_free;
+            g_result_free = slots + i;
+        }
     }
-    *out = g_result_free.back();
-    g_result_free.pop_back();
+    *out = g_result_free;
+    g_result_free = g_result_free->next;
     return SCORCH_OK;
 }
 
 static void give_result_back(PlanResult *r) {
     std::lock_guard<std::mutex> lock(g_result_mutex);
-    g_result_free.push_back(r);
+    r->next = g_result_free;
+    g_result_free = r;
 }
 
 // The result once it has arrived.  wait_all: everything enqueued on the stream so far has finished as well.  Otherwise
