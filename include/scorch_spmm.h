@@ -28,7 +28,7 @@
  *   - Arithmetic: fp32 products and fp32 accumulation (fused multiply-add), summation order
  *     fixed by the plan, so repeated calls give bit-identical results.
  *   - Return value: SCORCH_OK or a negative status; nothing throws across this boundary.
- *     On error nothing has been enqueued unless the status is SCORCH_ERR_HIP.
+ *     On error no work is left on the stream, and no result is written, unless the status is SCORCH_ERR_HIP.
  *     scorch_last_error() gives a thread-local description of the last failure.
  *   - m == 0 or n == 0 is valid and does no work.
  */
@@ -162,9 +162,11 @@ scorch_status_t scorch_spmm_csr_planned_epilogue(const scorch_spmm_plan_t *plan,
  * of B live in a static device array of SCORCH_STATIC_SCRATCH_BYTES that each GPU the library runs on holds until the
  * process ends.  The call allocates nothing on the device (no hipMalloc, hipFree or allocating library routine).
  *   - A problem whose plan needs more than SCORCH_STATIC_SCRATCH_BYTES (see scorch_spmm_plan_workspace_bytes) is
- *     refused with SCORCH_ERR_UNSUPPORTED and a message naming both sizes; nothing is enqueued then.
- *   - The pattern is analysed at every call (the host waits for the list sizes, once; they are written to host memory
- *     that the library allocates at its first plan), then the
+ *     refused with SCORCH_ERR_UNSUPPORTED and a message naming both sizes; no work is left on the stream then.  Only the
+ *     partial rows of kernels that keep chunks of B in LDS may exceed it: they take turns in the array, block of rows by
+ *     block of rows.
+ *   - The pattern is analysed at every call (the host waits for the list sizes, which are written to host memory
+ *     that the library allocates at its first plan, and where they matter for a look at the columns), then the
  *     execution is enqueued and the call returns without waiting for it.
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two host
  *     threads) race on it and give undefined results; calls on one stream are ordered and safe.  Nothing the previous

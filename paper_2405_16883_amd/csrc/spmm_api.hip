@@ -106,7 +106,7 @@ scorch_status_t scorch_spmm_plan(int32_t m, int32_t k, int32_t n, const int32_t 
     plan->tuning = read_tuning_from_env();
     plan->workspace = static_cast<char *>(workspace);
     if (hipGetDevice(&plan->device) != hipSuccess) plan->device = -1;
-    scorch_status_t st = build_plan(plan, rowptr, colidx, workspace_bytes, true, s);
+    scorch_status_t st = build_plan(plan, rowptr, colidx, workspace_bytes, false, s);
     if (st != SCORCH_OK) {
         if (st == SCORCH_ERR_WORKSPACE_TOO_SMALL)
             set_error("workspace of %zu bytes is smaller than the %llu needed", workspace_bytes,

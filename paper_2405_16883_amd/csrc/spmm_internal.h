@@ -51,7 +51,8 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
 
 struct WorkspaceLayout {
     uint64_t off_counts, off_totals, off_win, off_stage, off_wave, off_wave_span, off_items, off_split, off_partials, off_tickets, off_bpack,
-        off_res_ptr, off_res_partials, off_coldeg, off_hotmask, off_degbins, total;
+        off_res_ptr, off_coldeg, off_hotmask, off_degbins, off_res_partials, total;
+    uint64_t res_row_bytes;  // resident kernel: partial rows of one row of A (0: none, B fits one chunk)
     int64_t ticket_tiles;  // arrival counters per split row: one for every column tile a launch may use
     int64_t n_windows, nblk;
     int64_t cap_wave, cap_items, cap_split, cap_slots;
@@ -63,7 +64,8 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
 struct alignas(64) PlanResult {
     int32_t nnz;
     int32_t totals[5];  // wave rows, items, split rows, slots, short rows
-    int32_t done;       // written last
+    int32_t done;       // written last by the first two kernels
+    int32_t unsorted;   // some row's columns are not strictly increasing
     PlanResult *next;   // host side only: the next slot that no call is using
 };
 
@@ -124,6 +126,7 @@ struct ResidentArgs {
     int64_t ldb, ldc;
     int32_t m, k, n;
     float *partials;     // [nchunks][m][RES], unused with one chunk
+    int64_t ptr_stride;  // rows of the whole matrix; m is those of this launch
     int32_t nchunks;
     int32_t rows_per_block;
     const float *bias;
@@ -147,6 +150,14 @@ struct FixupArgs {
 };
 
 #if defined(__HIPCC__)
+// For a wavefront that looks for rows with columns out of order: true if it has found one.  The first to find one tells
+// the host; `seen` (device memory, 0 before) keeps the others' stores off the bus.
+__device__ __forceinline__ bool report_unsorted(bool bad, int32_t *seen, int32_t *unsorted) {
+    if (__ballot(bad) == 0ull) return false;
+    if ((threadIdx.x & 63) == 0 && atomicExch(seen, 1) == 0) __hip_atomic_store(unsorted, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return true;
+}
+
 __device__ __forceinline__ bool tile_of_workgroup(int32_t xcd_slices, int32_t ncoltiles, uint32_t per_tile, uint32_t &ct,
                                                   uint32_t &b) {
     return tile_of_index(blockIdx.x, xcd_slices, ncoltiles, per_tile, ct, b);
@@ -164,6 +175,8 @@ struct scorch_spmm_plan_s {
     scorch::WorkspaceLayout layout;
     char *workspace;
     int32_t n_short, n_wave, n_items, n_split, n_slots;
+    uint64_t off_res_partials;  // resident kernel: where the partial rows of res_rows rows of A stand, as many as are taken at a time
+    int32_t res_rows;
     int32_t n_hot;    // columns marked hot (0: every gather uses the default cache policy)
     float hot_share;  // share of the stored entries that point at a hot column
 };
@@ -175,10 +188,12 @@ scorch_status_t hip_fail(hipError_t e, const char *what);
 
 // spmm_plan.hip
 // Fills in a plan whose m, k, n, tuning, workspace and device are set.  The number of stored entries is read on the device;
-// SCORCH_ERR_WORKSPACE_TOO_SMALL (nothing written) if the layout needs more than workspace_bytes.  wait_all: all
-// planning work has finished when the call returns; otherwise only what the host needs to know has arrived.
+// SCORCH_ERR_WORKSPACE_TOO_SMALL (nothing written) if the layout needs more than workspace_bytes.
+// one_shot: the plan serves one execution that follows on the stream.  Then only what the host needs to know has arrived when the
+// call returns (on an error everything has finished), and the resident kernel's partial rows may take turns in the
+// workspace.  Otherwise all planning work has finished.
 scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
-                           uint64_t workspace_bytes, bool wait_all, hipStream_t stream);
+                           uint64_t workspace_bytes, bool one_shot, hipStream_t stream);
 
 scorch_status_t launch_rowptr_from_keys(int32_t m, int64_t count, const int32_t *keys, const int32_t *pos,
                                         bool strictly_increasing, int32_t *rowptr, int32_t *bad_flag,
@@ -198,8 +213,8 @@ scorch_status_t launch_panel(const scorch_spmm_plan_t *plan, const int32_t *rowp
                              const float *bias, int32_t act, hipStream_t stream);
 
 // spmm_resident.hip
-scorch_status_t launch_plan_resident(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int32_t *flag,
-                                     hipStream_t stream);
+scorch_status_t launch_plan_resident(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int32_t *seen,
+                                     int32_t *unsorted, hipStream_t stream);
 scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *colidx, const float *vals, const float *B, int64_t ldb,
                                 float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream);
 

@@ -33,6 +33,7 @@ struct PlanArgs {
     uint64_t workspace_bytes;
     int32_t tiles_per_block;  // a workgroup takes this many tiles of kBlock rows
     int32_t counted;          // 1: plan_count_kernel has run; 0: every workgroup counts the rows before its own
+    int32_t one_shot;         // see build_plan
     PlanResult *result;       // host memory
 };
 
@@ -43,6 +44,8 @@ __host__ __device__ static inline int64_t div_pos(int64_t a, int64_t b) {
     if ((((uint64_t)a | (uint64_t)b) >> 32) == 0) return (uint32_t)a / (uint32_t)b;
     return a / b;
 }
+
+__host__ __device__ static uint64_t bytes_needed(const WorkspaceLayout &L, bool one_shot);
 
 struct RowClass {
     int wave, items, split, slots, is_short;
@@ -133,7 +136,7 @@ __global__ __launch_bounds__(kBlock) void plan_count_kernel(const PlanArgs a) {
     const int32_t nnz = a.rowptr[a.m];
     if (nnz < 0) return;
     const PlanParams p = choose_params(a.m, a.k, nnz, a.n, a.tuning);
-    if (layout_workspace(a.m, a.k, nnz, a.n, p).total > a.workspace_bytes) return;  // the host reports it
+    if (bytes_needed(layout_workspace(a.m, a.k, nnz, a.n, p), a.one_shot) > a.workspace_bytes) return;  // the host reports it
     int32_t *counts = reinterpret_cast<int32_t *>(a.workspace);  // the first section of the layout
     int q[kQ] = {0, 0, 0, 0, 0};
     const int64_t row0 = (int64_t)blockIdx.x * a.tiles_per_block * kBlock + threadIdx.x;
@@ -190,7 +193,7 @@ __global__ __launch_bounds__(kBlock) void plan_build_kernel(const PlanArgs a) {
     if (fits) {
         p = choose_params(a.m, a.k, nnz, a.n, a.tuning);
         L = layout_workspace(a.m, a.k, nnz, a.n, p);
-        fits = L.total <= a.workspace_bytes;
+        fits = bytes_needed(L, a.one_shot) <= a.workspace_bytes;
     }
     if (fits) {
         int32_t *win_row_start = reinterpret_cast<int32_t *>(a.workspace + L.off_win);
@@ -286,6 +289,7 @@ __global__ __launch_bounds__(kBlock) void plan_build_kernel(const PlanArgs a) {
         }
     }
     if (last_block && tid == 0) {
+        if (fits) *reinterpret_cast<int32_t *>(a.workspace + L.off_totals) = 0;  // for the kernels that look at the columns
         a.result->nnz = nnz;
 #pragma unroll
         for (int k = 0; k < kQ; ++k) a.result->totals[k] = run[k];
@@ -293,16 +297,16 @@ __global__ __launch_bounds__(kBlock) void plan_build_kernel(const PlanArgs a) {
     }
 }
 
-// Sets *flag when some row's column indices are not strictly increasing (one wavefront per row).
+// Sets *unsorted (host memory) when some row's column indices are not strictly increasing (one wavefront per row).
 __global__ __launch_bounds__(kBlock) void plan_sorted_kernel(const int32_t *rowptr, const int32_t *colidx, int32_t m,
-                                                             int32_t *flag) {
+                                                             int32_t *seen, int32_t *unsorted) {
     const int lane = threadIdx.x & 63;
     for (int64_t row = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6); row < m;
          row += (int64_t)gridDim.x * kWavesPerBlock) {
         const int p0 = rowptr[row], p1 = rowptr[row + 1];
         bool bad = false;
         for (int p = p0 + 1 + lane; p < p1; p += kWave) bad |= colidx[p] <= colidx[p - 1];
-        if (bad) *flag = 1;
+        if (report_unsorted(bad, seen, unsorted)) break;
     }
 }
 
@@ -374,7 +378,7 @@ __global__ __launch_bounds__(kBlock) void plan_hotmask_kernel(const int32_t *deg
     }
 }
 
-static scorch_status_t mark_hot_columns(scorch_spmm_plan_t *plan, const int32_t *colidx, bool forced, bool wait_all,
+static scorch_status_t mark_hot_columns(scorch_spmm_plan_t *plan, const int32_t *colidx, bool forced, bool one_shot,
                                         hipStream_t stream) {
     const WorkspaceLayout &L = plan->layout;
     char *ws = plan->workspace;
@@ -420,7 +424,7 @@ static scorch_status_t mark_hot_columns(scorch_spmm_plan_t *plan, const int32_t 
     hipLaunchKernelGGL(plan_hotmask_kernel, dim3(g3), dim3(kBlock), 0, stream, deg, plan->k, min_bin, nwords, mask);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "launch plan_hotmask_kernel");
-    if (wait_all && (e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e, "wait for plan_hotmask_kernel");
+    if (!one_shot && (e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e, "wait for plan_hotmask_kernel");
     plan->n_hot = (int32_t)std::min<int64_t>(rows, 0x7fffffff);
     return SCORCH_OK;
 }
@@ -537,6 +541,23 @@ __host__ __device__ static int32_t want_resident(int32_t m, int32_t k, int64_t n
     return resident * 10 < nnz * per_entry * 9 ? W : 0;
 }
 
+// Bytes that a plan cannot do without.
+__host__ __device__ static uint64_t bytes_needed(const WorkspaceLayout &L, bool one_shot) {
+    return one_shot ? L.off_res_partials : L.total;
+}
+
+// Rows of A whose partial rows fit at a time, and where they stand (`off`), in a workspace of `bytes` that only a one-shot plan
+// uses: behind everything else, or over the lists of the gather kernels, which the resident kernel does not read.
+__host__ __device__ static int32_t partial_rows_in(const WorkspaceLayout &L, int32_t m, uint64_t bytes, uint64_t &off) {
+    off = L.off_res_partials;
+    uint64_t room = bytes - off;
+    if (room < L.res_row_bytes * m && room < L.off_res_ptr) {
+        off = 0;
+        room = L.off_res_ptr;
+    }
+    return room >= L.res_row_bytes * m ? m : (int32_t)(room / L.res_row_bytes);
+}
+
 __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t) {
     PlanParams p;
     p.ALPHA = 4;
@@ -598,6 +619,18 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     p.BCH = std::max(p.BCH, 64);
     p.U = p.U >= 8 ? 8 : 4;
     p.NT &= 1;
+    // scorch_spmm_csr_static takes what the gather kernels need no more than its scratch for, and gives the planned call's
+    // bits: where the resident kernel does not run in the scratch either, it runs nowhere.
+    if (p.RES) {
+        PlanParams gather = p;
+        gather.RES = 0;
+        if (layout_workspace(m, k, nnz, n, gather).total <= SCORCH_STATIC_SCRATCH_BYTES) {
+            const WorkspaceLayout L = layout_workspace(m, k, nnz, n, p);
+            uint64_t off;
+            if (L.off_res_partials > SCORCH_STATIC_SCRATCH_BYTES || partial_rows_in(L, m, SCORCH_STATIC_SCRATCH_BYTES, off) < std::min(m, 64))
+                p.RES = 0;
+        }
+    }
     return p;
 }
 
@@ -638,12 +671,11 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
     off = align_up(off + (uint64_t)L.cap_slots * L.ticket_tiles * 4, 256);  // indexed by a split row's first slot
     L.off_bpack = off;
     if (p.PACK || (p.PANEL && !p.PDIRECT)) off = align_up(off + (uint64_t)k * ((n + 2 * kPanelCols - 1) / (2 * kPanelCols)) * (2 * kPanelCols) * 4, 256);
-    L.off_res_ptr = L.off_res_partials = off;
+    L.off_res_ptr = off;
     if (p.RES) {
         const int64_t chunks = resident_chunks(k, p.RES);
         off = align_up(off + (uint64_t)(chunks + 1) * m * 4, 256);
-        L.off_res_partials = off;
-        if (chunks > 1) off = align_up(off + (uint64_t)chunks * m * p.RES * 4, 256);
+        if (chunks > 1) L.res_row_bytes = (uint64_t)chunks * p.RES * 4;
     }
     L.off_coldeg = off;
     if (p.HOT) off = align_up(off + (uint64_t)k * 4, 256);
@@ -651,6 +683,8 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
     if (p.HOT) off = align_up(off + ((uint64_t)k / 32 + 2) * 4, 256);
     L.off_degbins = off;
     if (p.HOT) off = align_up(off + (uint64_t)kDegBins * 16, 256);
+    L.off_res_partials = off;  // last: a one-shot plan has fewer of them
+    off = align_up(off + L.res_row_bytes * m, 256);
     L.total = std::max<uint64_t>(off, 256);
     return L;
 }
@@ -691,11 +725,11 @@ static void give_result_back(PlanResult *r) {
     g_result_free = r;
 }
 
-// The result once it has arrived.  wait_all: everything enqueued on the stream so far has finished as well.  Otherwise
+// The result once it has arrived.  Everything enqueued on the stream so far has finished as well, except for a one-shot plan: there
 // the host only watches for the result itself, which arrives some microseconds before a wait on the stream returns; after
 // about a millisecond (the stream was busy with something else) it waits for the stream.
-static scorch_status_t wait_for_result(PlanResult *r, bool wait_all, hipStream_t stream) {
-    if (!wait_all) {
+static scorch_status_t wait_for_result(PlanResult *r, bool one_shot, hipStream_t stream) {
+    if (one_shot) {
         for (int i = 0; i < 20000; ++i) {
             if (__atomic_load_n(&r->done, __ATOMIC_ACQUIRE)) return SCORCH_OK;
             __builtin_ia32_pause();
@@ -710,12 +744,11 @@ static scorch_status_t wait_for_result(PlanResult *r, bool wait_all, hipStream_t
     return SCORCH_OK;
 }
 
-scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
-                           uint64_t workspace_bytes, bool wait_all, hipStream_t stream) {
-    PlanResult *result = nullptr;
-    scorch_status_t st = take_result(&result);
-    if (st != SCORCH_OK) return st;
+// build_plan once a slot for the result has been taken.  `lost`: a wait failed, so a kernel may still write to the slot.
+static scorch_status_t build_plan_in(PlanResult *result, bool *lost, scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
+                                     uint64_t workspace_bytes, bool one_shot, hipStream_t stream) {
     result->done = 0;
+    result->unsorted = 0;
     const int64_t tiles = std::max<int64_t>(1, ((int64_t)plan->m + kBlock - 1) / kBlock);
     PlanArgs a{};
     a.rowptr = rowptr;
@@ -728,15 +761,17 @@ scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, cons
     a.tiles_per_block = (int32_t)((tiles + kPlanBlocksMax - 1) / kPlanBlocksMax);
     const uint32_t nblk = (uint32_t)((tiles + a.tiles_per_block - 1) / a.tiles_per_block);
     a.counted = nblk > (uint32_t)kPlanRecount;
+    a.one_shot = one_shot;
     a.result = result;
     if (a.counted) hipLaunchKernelGGL(plan_count_kernel, dim3(nblk), dim3(kBlock), 0, stream, a);
     hipLaunchKernelGGL(plan_build_kernel, dim3(nblk), dim3(kBlock), 0, stream, a);
     hipError_t e = hipGetLastError();
-    st = e != hipSuccess ? hip_fail(e, "launch plan kernels") : wait_for_result(result, wait_all, stream);
+    scorch_status_t st = e != hipSuccess ? hip_fail(e, "launch plan kernels") : wait_for_result(result, one_shot, stream);
     const PlanResult got = *result;
-    // after a failed wait the kernel may still be running: its slot is not used again
-    if (st != SCORCH_OK) return st;
-    give_result_back(result);
+    if (st != SCORCH_OK) {
+        *lost = true;
+        return st;
+    }
     if (got.nnz < 0) {
         set_error("rowptr[m] = %d is negative", got.nnz);
         return SCORCH_ERR_INVALID_ARG;
@@ -745,7 +780,7 @@ scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, cons
     plan->params = choose_params(plan->m, plan->k, plan->nnz, plan->n, plan->tuning);
     plan->layout = layout_workspace(plan->m, plan->k, plan->nnz, plan->n, plan->params);
     const WorkspaceLayout &L = plan->layout;
-    if (L.total > workspace_bytes) return SCORCH_ERR_WORKSPACE_TOO_SMALL;  // the caller words the message
+    if (bytes_needed(L, one_shot) > workspace_bytes) return SCORCH_ERR_WORKSPACE_TOO_SMALL;  // the caller words the message
     char *ws = plan->workspace;
     plan->n_wave = got.totals[0];
     plan->n_items = got.totals[1];
@@ -766,35 +801,51 @@ scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, cons
     // verified, so the mode is dropped.
     if (!colidx || plan->m == 0 || plan->nnz == 0) plan->params.PANEL = plan->params.RES = 0;
     if (plan->params.PANEL || plan->params.RES) {
-        int32_t unsorted = 0;
-        int32_t *flag = reinterpret_cast<int32_t *>(ws + L.off_totals);
-        e = hipMemsetAsync(flag, 0, sizeof(int32_t), stream);
-        if (e != hipSuccess) return hip_fail(e, "clear sortedness flag");
+        int32_t *seen = reinterpret_cast<int32_t *>(ws + L.off_totals);  // cleared by plan_build_kernel
         const uint32_t g = (uint32_t)std::min<int64_t>(((int64_t)plan->m + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 16);
         if (plan->params.RES) {
-            st = launch_plan_resident(plan, rowptr, colidx, flag, stream);
+            st = launch_plan_resident(plan, rowptr, colidx, seen, &result->unsorted, stream);
             if (st != SCORCH_OK) return st;
         } else {
-            hipLaunchKernelGGL(plan_sorted_kernel, dim3(g), dim3(kBlock), 0, stream, rowptr, colidx, plan->m, flag);
+            hipLaunchKernelGGL(plan_sorted_kernel, dim3(g), dim3(kBlock), 0, stream, rowptr, colidx, plan->m, seen, &result->unsorted);
         }
-        e = hipMemcpyAsync(&unsorted, flag, sizeof(int32_t), hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
-        if (e != hipSuccess) return hip_fail(e, "read the sortedness flag");
-        if (unsorted) plan->params.PANEL = plan->params.RES = 0;
+        e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) {
+            *lost = true;
+            return hip_fail(e, "wait for the look at the columns");
+        }
+        if (__atomic_load_n(&result->unsorted, __ATOMIC_ACQUIRE)) plan->params.PANEL = plan->params.RES = 0;
+    }
+    if (plan->params.RES) {
+        plan->off_res_partials = L.off_res_partials;
+        plan->res_rows = one_shot ? partial_rows_in(L, plan->m, workspace_bytes, plan->off_res_partials) : plan->m;
     }
     plan->n_hot = 0;
     plan->hot_share = 0.f;
     if (plan->params.HOT && colidx && plan->nnz > 0 && plan->k > 0) {
-        st = mark_hot_columns(plan, colidx, plan->tuning.hot > 0, wait_all, stream);
+        st = mark_hot_columns(plan, colidx, plan->tuning.hot > 0, one_shot, stream);
         if (st != SCORCH_OK) return st;
     }
     // the arrival counters of split rows (only used with fix=1) start at zero; every launch leaves them at zero again
     if (L.cap_slots > 0 && plan->tuning.fix > 0) {
         e = hipMemsetAsync(ws + L.off_tickets, 0, (size_t)L.cap_slots * L.ticket_tiles * 4, stream);
-        if (e == hipSuccess && wait_all) e = hipStreamSynchronize(stream);
+        if (e == hipSuccess && !one_shot) e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return hip_fail(e, "clear arrival counters");
     }
     return SCORCH_OK;
+}
+
+scorch_status_t build_plan(scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx,
+                           uint64_t workspace_bytes, bool one_shot, hipStream_t stream) {
+    PlanResult *result = nullptr;
+    scorch_status_t st = take_result(&result);
+    if (st != SCORCH_OK) return st;
+    bool lost = false;
+    st = build_plan_in(result, &lost, plan, rowptr, colidx, workspace_bytes, one_shot, stream);
+    if (!lost) give_result_back(result);  // otherwise it is not used again
+    // an error leaves nothing behind that still reads the caller's arrays
+    if (st != SCORCH_OK && one_shot) (void)hipStreamSynchronize(stream);
+    return st;
 }
 
 }  // namespace scorch

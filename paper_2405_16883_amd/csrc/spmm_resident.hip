@@ -86,7 +86,7 @@ template <int G> __device__ __forceinline__ float sum_groups(float x) {
 // chunk; whatever the columns of the call are, the ranges of all chunks cover each entry of the row once.
 __device__ __forceinline__ int resident_bounds(const ResidentArgs &a, int64_t row0, int row_end, int chunk, int lane) {
     const int64_t row = row0 + (lane & 31) * kResidentWaves;
-    return row < row_end ? a.ptr[(int64_t)(chunk + (lane >> 5)) * a.m + row] : 0;
+    return row < row_end ? a.ptr[(int64_t)(chunk + (lane >> 5)) * a.ptr_stride + row] : 0;
 }
 
 // Four columns c ... c+3 of a row of B; those past column n are never stored and may hold anything.
@@ -277,10 +277,11 @@ __global__ __launch_bounds__(kBlock) void spmm_resident_sum_kernel(const Residen
         }
 }
 
-// Checks that every row's columns are strictly increasing (sets *flag otherwise) and writes ptr[p][row] = the row's
+// Checks that every row's columns are strictly increasing (sets *unsorted otherwise) and writes ptr[p][row] = the row's
 // first entry of chunk p or later, p = 0 ... nchunks.  One wavefront per row.
 __global__ __launch_bounds__(kBlock) void plan_resident_kernel(const int32_t *rowptr, const int32_t *colidx, int32_t m,
-                                                               uint32_t chunk_rows, int32_t nchunks, int32_t *ptr, int32_t *flag) {
+                                                               uint32_t chunk_rows, int32_t nchunks, int32_t *ptr, int32_t *seen,
+                                                               int32_t *unsorted) {
     const int lane = threadIdx.x & 63;
     for (int64_t row = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6); row < m;
          row += (int64_t)gridDim.x * kWavesPerBlock) {
@@ -295,17 +296,17 @@ __global__ __launch_bounds__(kBlock) void plan_resident_kernel(const int32_t *ro
             const int hi = p < p1 ? min((int)((uint32_t)c / chunk_rows), nchunks) : nchunks;
             for (int q = lo; q <= hi; ++q) ptr[(int64_t)q * m + row] = (int)p;
         }
-        if (bad) *flag = 1;
+        if (report_unsorted(bad, seen, unsorted)) break;
     }
 }
 
-scorch_status_t launch_plan_resident(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int32_t *flag,
-                                     hipStream_t stream) {
+scorch_status_t launch_plan_resident(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int32_t *seen,
+                                     int32_t *unsorted, hipStream_t stream) {
     const int W = plan->params.RES;
     const uint32_t g = (uint32_t)std::min<int64_t>(((int64_t)plan->m + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 16);
     hipLaunchKernelGGL(plan_resident_kernel, dim3(g), dim3(kBlock), 0, stream, rowptr, colidx, plan->m,
                        (uint32_t)(kResidentFloats / W), resident_chunks(plan->k, W),
-                       reinterpret_cast<int32_t *>(plan->workspace + plan->layout.off_res_ptr), flag);
+                       reinterpret_cast<int32_t *>(plan->workspace + plan->layout.off_res_ptr), seen, unsorted);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "launch plan_resident_kernel");
     return SCORCH_OK;
@@ -327,35 +328,40 @@ scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *c
                                 float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream) {
     const int W = plan->params.RES;
     ResidentArgs a{};
-    a.ptr = reinterpret_cast<const int32_t *>(plan->workspace + plan->layout.off_res_ptr);
     a.colidx = colidx;
     a.vals = vals;
     a.B = B;
     a.ldb = ldb;
-    a.C = C;
     a.ldc = ldc;
-    a.m = plan->m;
+    a.ptr_stride = plan->m;
     a.k = plan->k;
     a.n = plan->n;
-    a.partials = reinterpret_cast<float *>(plan->workspace + plan->layout.off_res_partials);
+    a.partials = reinterpret_cast<float *>(plan->workspace + plan->off_res_partials);
     a.nchunks = resident_chunks(plan->k, W);
     a.bias = bias;
     a.act = act;
-    // as many row blocks as let every workgroup have a CU at once
-    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(kCus / a.nchunks, ((int64_t)plan->m + kResidentWaves - 1) / kResidentWaves));
-    a.rows_per_block = (int32_t)((plan->m + blocks - 1) / blocks);
-    const int64_t nblk = ((int64_t)plan->m + a.rows_per_block - 1) / a.rows_per_block;
     const uintptr_t pb = reinterpret_cast<uintptr_t>(B);
     const bool a16 = plan->n % 4 == 0 && ldb % 4 == 0 && pb % 16 == 0;
-    hipLaunchKernelGGL(a16 ? pick_resident<true>(W) : pick_resident<false>(W), dim3((uint32_t)(nblk * a.nchunks)),
-                       dim3(kResidentThreads), 0, stream, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "launch spmm_resident_kernel");
-    if (a.nchunks > 1) {
-        const int64_t vecs = (int64_t)plan->m * W / 4;
-        hipLaunchKernelGGL(spmm_resident_sum_kernel, dim3((uint32_t)((vecs + kBlock - 1) / kBlock)), dim3(kBlock), 0, stream, a, W);
-        e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "launch spmm_resident_sum_kernel");
+    const int32_t *ptr = reinterpret_cast<const int32_t *>(plan->workspace + plan->layout.off_res_ptr);
+    // all rows at once, or as many as the workspace holds partial rows for (a row's sum is the same either way)
+    for (int64_t row0 = 0; row0 < plan->m; row0 += plan->res_rows) {
+        a.m = (int32_t)std::min<int64_t>(plan->res_rows, plan->m - row0);
+        a.ptr = ptr + row0;
+        a.C = C + row0 * ldc;
+        // as many row blocks as let every workgroup have a CU at once
+        const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(kCus / a.nchunks, ((int64_t)a.m + kResidentWaves - 1) / kResidentWaves));
+        a.rows_per_block = (int32_t)((a.m + blocks - 1) / blocks);
+        const int64_t nblk = ((int64_t)a.m + a.rows_per_block - 1) / a.rows_per_block;
+        hipLaunchKernelGGL(a16 ? pick_resident<true>(W) : pick_resident<false>(W), dim3((uint32_t)(nblk * a.nchunks)),
+                           dim3(kResidentThreads), 0, stream, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail(e, "launch spmm_resident_kernel");
+        if (a.nchunks > 1) {
+            const int64_t vecs = (int64_t)a.m * W / 4;
+            hipLaunchKernelGGL(spmm_resident_sum_kernel, dim3((uint32_t)((vecs + kBlock - 1) / kBlock)), dim3(kBlock), 0, stream, a, W);
+            e = hipGetLastError();
+            if (e != hipSuccess) return hip_fail(e, "launch spmm_resident_sum_kernel");
+        }
     }
     return SCORCH_OK;
 }

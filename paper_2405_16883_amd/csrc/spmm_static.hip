@@ -83,13 +83,9 @@ extern "C" scorch_status_t scorch_spmm_csr_static(int32_t m, int32_t k, int32_t 
     // its own flags and counters and writes every list up to the counts it returns); the partial rows are written
     // by the pieces of a split row before the same launch order reads them.  The host waits until it knows the list sizes;
     // the execution is ordered behind the planning kernels by the stream.
-    st = build_plan(&plan, rowptr, colidx && vals && B ? colidx : nullptr, kStaticScratchBytes, false, s);
-    if (st == SCORCH_ERR_WORKSPACE_TOO_SMALL && plan.params.RES) {
-        // the partial rows of the resident kernel do not fit: the gather kernels need less
-        plan.tuning.res = 0;
-        st = build_plan(&plan, rowptr, colidx && vals && B ? colidx : nullptr, kStaticScratchBytes, false, s);
-    }
+    st = build_plan(&plan, rowptr, colidx && vals && B ? colidx : nullptr, kStaticScratchBytes, true, s);
     if ((st == SCORCH_OK || st == SCORCH_ERR_WORKSPACE_TOO_SMALL) && plan.nnz > 0 && (!colidx || !vals || !B)) {
+        (void)hipStreamSynchronize(s);  // nothing stays enqueued
         set_error("colidx, vals and B must not be NULL when nnz > 0");
         return SCORCH_ERR_INVALID_ARG;
     }

@@ -55,3 +55,22 @@ def test_row_pointers_that_decrease_are_refused(m):
         with pytest.raises(sp.ScorchError, match="rowptr decreases") as e:
             sp.scorch_spmm_plan(m, 100, 8, rowptr, 5 * m)
         assert e.value.status == sp.binding.SCORCH_ERR_INVALID_ARG
+
+
+def test_a_refused_one_shot_call_leaves_nothing_on_the_stream():
+    dev = torch.device("cuda")
+    m, per_row = 1_000_000, 40
+    assert sp.scorch_spmm_plan_workspace_bytes(m, 4, 64, per_row * m) > sp.STATIC_SCRATCH_BYTES
+    rowptr = torch.arange(0, per_row * m + 1, per_row, dtype=torch.int32, device=dev)
+    cols, vals = torch.zeros(per_row * m, dtype=torch.int32, device=dev), torch.zeros(per_row * m, device=dev)
+    B, C = torch.zeros((4, 64), device=dev), torch.full((m, 64), 7.0, device=dev)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with pytest.raises(sp.ScorchError) as e:
+        sp.scorch_spmm_csr_static(m, 4, 64, rowptr, cols, vals, B, C, stream=s)
+    assert e.value.status == sp.binding.SCORCH_ERR_UNSUPPORTED and s.query()
+    with pytest.raises(sp.ScorchError) as e:
+        sp.scorch_spmm_csr_static(m // 100, 4, 64, rowptr, cols[:0], vals, B, C, stream=s)
+    assert e.value.status == sp.binding.SCORCH_ERR_INVALID_ARG and s.query()
+    torch.cuda.synchronize()
+    assert bool((C == 7.0).all())

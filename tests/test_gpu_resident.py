@@ -111,3 +111,38 @@ def test_a_plan_serves_columns_in_any_order_and_repeated(m, n):
             e = DeviceProblem(r)
             check_against_oracle(r, e.run_planned(plan), e.ldc, exact=True, label=f"any order m={m} n={n} ldb={r.ldb}")
         plan.destroy()
+
+
+@pytest.mark.parametrize("m,k,share,n", [(4096, 16384, 0.1, 64), (4096, 16384, 0.1, 33), (16384, 16384, 0.1, 40), (1040, 8192, 0.2, 64)])
+def test_the_one_shot_call_gives_the_planned_bits_when_its_scratch_holds_the_partial_rows_of_some_rows_only(m, k, share, n):
+    """The partial rows take turns there.  Columns that are not increasing leave both calls to the gather kernels."""
+    dev = torch.device("cuda")
+    per_row = int(share * k)
+    g = torch.Generator(device=dev).manual_seed(n)
+    rows = min(m, 512)  # row lengths and columns of 512 rows, over and over
+    lens = torch.randint(per_row // 2, per_row * 3 // 2, (rows,), generator=g, device=dev)
+    keep = torch.rand((rows, k), generator=g, device=dev).argsort(dim=1).argsort(dim=1) < lens[:, None]
+    cols = keep.nonzero()[:, 1].int().repeat((m + rows - 1) // rows)
+    lens = lens.repeat((m + rows - 1) // rows)[:m]
+    rowptr = torch.zeros(m + 1, dtype=torch.int32, device=dev)
+    rowptr[1:] = lens.cumsum(0)
+    nnz = int(rowptr[-1])
+    cols = cols[:nnz].contiguous()
+    vals, B = torch.rand(nnz, generator=g, device=dev) - 0.5, torch.randn((k, n), generator=g, device=dev)
+    swapped = cols.clone()
+    swapped[[5, 6]] = cols[[6, 5]]  # the first row is out of order
+    for c, mode in ((cols, 3), (swapped, None)):
+        planned, static = torch.empty((m, n), device=dev), torch.empty((m, n), device=dev)
+        plan = sp.scorch_spmm_plan(m, k, n, rowptr, nnz, colidx=c)
+        assert (plan.info().mode == 3) == (mode == 3)
+        sp.scorch_spmm_csr_planned(plan, rowptr, c, vals, B, planned)
+        for _ in range(2):  # the second finds what the first left
+            static.fill_(float("nan"))
+            sp.scorch_spmm_csr_static(m, k, n, rowptr, c, vals, B, static)
+            assert torch.equal(static, planned)
+        plan.destroy()
+    # against double precision, from the same operands, on rows of the first and the last turn
+    for r in (0, m // 2 + 1, m - 1):
+        a, b = int(rowptr[r]), int(rowptr[r + 1])
+        terms = vals[a:b].double()[:, None] * B[swapped[a:b].long()].double()
+        assert bool(((planned[r] - terms.sum(0)).abs() <= 1e-5 * terms.abs().sum(0)).all())
