@@ -56,9 +56,9 @@ typedef struct scorch_spmm_plan_s scorch_spmm_plan_t; /* small host-side handle 
 /*
  * Plan-free SpMM: C = A.B in natural row order.  A matrix of few rows (at most 2048 pairs of a row and a 32-column
  * tile) gets a workgroup per pair.  Otherwise a wavefront takes a short run of consecutive rows
- * (up to 4, up to 16 for small n), walks the short ones (up to 32 entries) side by side and streams the longer ones; the
- * four wavefronts of a workgroup work together on rows with more than 2048 entries (more than 256
- * where such rows are rare).  With B of 8 MB or more and n a multiple of 64 (128) the columns are walked in slices of
+ * (1 to 16, by the number of rows and column tiles), walks the short ones (up to 32 entries) side by side and streams the
+ * longer ones; rows of more than 256 entries and more than four times the mean are dealt evenly to workgroups that start
+ * first and whose four wavefronts work together on each.  With B of 8 MB or more and n a multiple of 64 (128) the columns are walked in slices of
  * 64 (128) that are dealt over the accelerator dies, so that each die gathers from a part of B its L2 can keep.
  * Always available and correct for any valid input; no load balancing
  * beyond that, so a row with very many entries still runs on a single workgroup.  (Definition: see

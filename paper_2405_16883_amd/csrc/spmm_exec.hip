@@ -18,6 +18,7 @@
 // No MFMA: the work is a gather, not a dense contraction.  No atomics: summation order is fixed.
 #include "spmm_internal.h"
 #include "device_util.h"
+#include "scouts.h"
 
 #include <algorithm>
 
@@ -515,23 +516,25 @@ __global__ __launch_bounds__(NW * kWave) void spmm_row_kernel(const ExecArgs a) 
 // are staged with coalesced reads and walked one row per lane group, like a window of the planned path; a longer
 // row is streamed through the stage by the whole wavefront, the lane groups taking interleaved entries.
 //
-// Rows of more than kNaturalLong entries (kNaturalMid if at most a quarter of the workgroup's rows are longer than that,
-// i.e. where they are the outliers of a graph and not the normal case of a matrix with long rows) are left to
-// workgroups at the front of the grid, the scouts: each looks for them in a stretch of rows and takes them one after the
-// other, all 4 wavefronts together (interleaved 64-entry chunks, LDS tree, twice the gathers in flight), so that the
-// longest rows start first and run beside everything else.  Measured against leaving them to the end of the workgroup
-// that holds them, with the run length of before: graph of 169 343 rows (longest 10 316 entries), n = 128: 163 -> 138 us in the kernel trace; with longer runs (launch_natural) 124.
-constexpr int kNaturalLong = 2048;
-constexpr int kNaturalMid = 256;
+// Rows that are long beside the others (long_row_limit) are left to scouts: the workgroups at the front of the grid, or, where
+// all workgroups are resident at once, the first ones of those that take the runs, before their own.  A scout looks at rows
+// from all over the matrix (scout_first, scout_place) and takes the long ones one after the other, all 4 wavefronts together
+// (interleaved 64-entry chunks, LDS tree, twice the gathers in flight), so that the longest rows start first and run
+// beside everything else.  Neither the order of the rows nor how many of them are long leaves them to few workgroups.
+// Measured, us, against workgroups that each look through a stretch of 64 to 1024 neighbouring rows: graph of 169 343 rows (longest
+// 10 316 entries), n = 128, random order 140 -> 138, longest rows first 1149 -> 116; 4096 rows, every fourth of 1000 entries, n = 64
+// 66.6 -> 19.8; 5000 rows of 31 in the mean, n = 128 19.9 -> 16.5; 4096 rows, every 64th of 6000 entries 19.8 -> 22.4.
 constexpr int kNaturalRowsMax = 16;
 constexpr int kNaturalShort = 32;
-constexpr int kScoutsMax = 2048;  // per column tile
 
-// Row length beyond which a row is left to the scouts, for a workgroup of `rows` rows of which `mid` are longer than kNaturalMid
-// and `longs` longer than kNaturalLong.  Where such rows are the normal case nothing is left to them: 2048 rows of 3600
-// entries, n = 256, took 1324 us when 64 rows waited for one scout, 314 with every wavefront on rows of its own.
-__device__ __forceinline__ int natural_long_limit(int mid, int longs, int rows) {
-    return mid * 4 <= rows ? kNaturalMid : longs * 4 <= rows ? kNaturalLong : 0x7fffffff;
+// Position of the first bit from `from` on in the 256 bits of a workgroup (256 if there is none).
+__device__ __forceinline__ int next_long(const unsigned long long *bits, int from) {
+    for (int w = from / kWave; w < kWavesPerBlock; ++w) {
+        unsigned long long x = bits[w];
+        if (w == from / kWave) x &= ~0ull << (from % kWave);
+        if (x != 0ull) return __builtin_amdgcn_readfirstlane(w * kWave + __builtin_ctzll(x));
+    }
+    return kBlock;
 }
 
 template <int V, int G, int T, int U, int NT, bool UA>
@@ -543,7 +546,8 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
     constexpr bool NTC = (NT & 1) != 0;
     __shared__ int s_raw[kWavesPerBlock * smem_ints_per_wave()];
     __shared__ float s_red[kWavesPerBlock * TW];
-    __shared__ int s_nmid;
+    __shared__ unsigned long long s_longs[kWavesPerBlock];  // scouts: which rows are long, and their entries
+    __shared__ int2 s_span[kBlock];
     const int tid = threadIdx.x;
     const int wv = tid >> 6;
     const int lane = tid & 63;
@@ -567,24 +571,23 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
     int *lrp = lcol + 2 * kStageMax;
     vec acc[T];
 
-    if (b < (uint32_t)a.nb_items) {
-        // ---- scout: the long rows of a stretch, 64 rows at a time, all wavefronts on each ----
-        const int group = kWavesPerBlock * NR;  // rows of one workgroup of the other kind: 4, 8, ... 64
-        const int64_t end = min((int64_t)a.m, ((int64_t)b + 1) * a.scout_rows);
-        for (int64_t first = (int64_t)b * a.scout_rows; first < end; first += kWave) {
-            const int64_t row = min(first + lane, (int64_t)a.m - 1);
-            const int q0 = a.rowptr[row];
-            const int len = first + lane < a.m ? a.rowptr[row + 1] - q0 : 0;
-            const unsigned long long mid = __ballot(len > kNaturalMid);
-            const unsigned long long mine = group >= kWave ? mid : (mid >> (lane & ~(group - 1))) & ((1ull << group) - 1ull);
-            const unsigned long long far = __ballot(len > kNaturalLong);
-            const unsigned long long mine_far = group >= kWave ? far : (far >> (lane & ~(group - 1))) & ((1ull << group) - 1ull);
-            const int limit = natural_long_limit(__builtin_popcountll(mine), __builtin_popcountll(mine_far), group);
-            unsigned long long todo = __ballot(len > limit);
-            while (todo != 0ull) {  // the same for the whole workgroup
-                const int r = __builtin_ctzll(todo);
-                todo &= todo - 1ull;
-                const int p0 = __shfl(q0, r, kWave), p1 = p0 + __shfl(len, r, kWave);
+    const int long_limit = long_row_limit((uint32_t)a.rowptr[a.m], (uint32_t)a.m);
+    if (b < (uint32_t)a.nb_scouts) {
+        // ---- scout: 256 rows at a time, all wavefronts on each long one ----
+        for (int64_t first = scout_first(b, a.nb_scouts, a.scout_shift); first < a.m; first += kBlock * a.nb_scouts) {
+            const int64_t mine = first + scout_place(tid, a.nb_scouts, a.scout_shift);
+            int q0 = 0, q1 = 0;
+            if (mine < a.m) {
+                q0 = a.rowptr[mine];
+                q1 = a.rowptr[mine + 1];
+            }
+            const unsigned long long longs = __ballot(q1 - q0 > long_limit);
+            if (lane == 0) s_longs[wv] = longs;
+            if (q1 - q0 > long_limit) s_span[tid] = make_int2(q0, q1);
+            __syncthreads();
+            for (int i = next_long(s_longs, 0); i < kBlock; i = next_long(s_longs, i + 1)) {  // the same for the whole workgroup
+                const int2 span = s_span[i];
+                const int p0 = span.x, p1 = span.y;
 #pragma unroll
                 for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
                 row_accumulate<V, G, T, 2 * U, false, UA>(acc, lcol, lval, lane, grp, p0 + wv * kWave, p1, kBlock, a.colidx,
@@ -602,40 +605,34 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
                 }
                 __syncthreads();
                 if (wv == 0 && grp == 0) {
-                    float *dst = a.C + (first + r) * a.ldc;
+                    float *dst = a.C + (first + scout_place(i, a.nb_scouts, a.scout_shift)) * a.ldc;
 #pragma unroll
                     for (int t = 0; t < T; ++t) {
                         if (!colok[t]) continue;
                         vec out;
 #pragma unroll
-                        for (int i = 0; i < V; ++i) {
-                            const int o = t * GV + lig * V + i;
+                        for (int j = 0; j < V; ++j) {
+                            const int o = t * GV + lig * V + j;
                             float sum = s_red[o];
 #pragma unroll
                             for (int x = 1; x < kWavesPerBlock; ++x) sum += s_red[x * TW + o];
                             if constexpr (V == 1) out = sum;
-                            else out[i] = sum;
+                            else out[j] = sum;
                         }
                         vstore<V, NTC, UA>(dst + coff[t], out);
                     }
                 }
             }
+            __syncthreads();  // the list has been read
         }
-        return;
+        if (a.nb_items > 0) return;
     }
 
     const int64_t r0 = ((int64_t)(b - (uint32_t)a.nb_items) * kWavesPerBlock + wv) * NR;
     const int nr = (int)max((int64_t)0, min((int64_t)NR, (int64_t)a.m - r0));
-    if (tid == 0) s_nmid = 0;
-    __syncthreads();
-    const int rpv = nr > 0 ? a.rowptr[r0 + min(lane, nr)] : 0;
-    const int rnext = __shfl_down(rpv, 1, kWave);  // lanes past the run hold the last pointer; lane 63 is never a row
-    const int nmid = (int)__builtin_popcountll(__ballot(lane < nr && rnext - rpv > kNaturalMid));
-    const int nfar = (int)__builtin_popcountll(__ballot(lane < nr && rnext - rpv > kNaturalLong));
-    if (lane == 0 && nmid > 0) atomicAdd(&s_nmid, nmid + (nfar << 16));  // 64 rows at most: two counts in one word
-    __syncthreads();
-    const int long_limit = natural_long_limit(s_nmid & 0xffff, s_nmid >> 16, kWavesPerBlock * NR);  // as the scouts decide
     if (nr <= 0) return;
+    const int rpv = a.rowptr[r0 + min(lane, nr)];
+    const int rnext = __shfl_down(rpv, 1, kWave);  // lanes past the run hold the last pointer; lane 63 is never a row
     lrp[lane] = rpv;
     wave_lds_sync();
     int i = 0;
@@ -1025,9 +1022,10 @@ scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *r
            (int64_t)m >= 8192 * (int64_t)a.rows_per_wave)
         a.rows_per_wave *= 2;
     a.nb_wave = (int32_t)ceil_div64(m, (int64_t)kWavesPerBlock * a.rows_per_wave);
-    a.scout_rows = kWave;
-    while (ceil_div64(m, a.scout_rows) > kScoutsMax) a.scout_rows *= 2;
-    a.nb_items = (int32_t)ceil_div64(m, a.scout_rows);
+    const Scouts scouts = scouts_for(m, a.nb_wave, mp.ncoltiles);
+    a.nb_scouts = scouts.count;
+    a.scout_shift = scouts.shift;
+    a.nb_items = scouts.beside ? scouts.count : 0;
     a.ncoltiles = mp.ncoltiles;
     const int64_t grid = grid_size(mp, (int64_t)a.nb_items + a.nb_wave);
     if (grid > 0x7fffffffLL) {

@@ -1,6 +1,6 @@
-"""Host-side logic of the library that needs no GPU.  Three pieces of plain integer or text handling live in headers
-without HIP dependencies -- the workgroup -> (column tile, row work) mapping of the XCD-sliced launches, the range of
-row pointers a key of a coordinate list fills, and the parser of the tuning text -- and small C++ checkers under
+"""Host-side logic of the library that needs no GPU.  Four pieces of plain integer or text handling live in headers
+without HIP dependencies -- the workgroup -> (column tile, row work) mapping of the XCD-sliced launches, the dealing of
+long rows to workgroups of the plan-free kernel, the range of row pointers a key of a coordinate list fills, and the parser of the tuning text -- and small C++ checkers under
 tests/host/ are compiled with the host compiler and run on the CPU, once plainly and once under the address and
 undefined-behaviour sanitizers.  The C oracles get the same sanitizer pass through a driver that hands them every
 operand in a heap block of exactly its size."""
@@ -50,6 +50,11 @@ def test_row_pointer_fill_ranges_stay_inside_rowptr(repo_root, tmp_path, sanitiz
     out = run_checker(build_checker(repo_root, tmp_path, "rowptr_keys_check", sanitize), sanitize)
     # sum over m = 0..4 of 2 * sum_{len=0..4} (m + 8)^len key lists
     assert int(out.split()[1]) == sum(2 * sum((m + 8) ** n for n in range(5)) for m in range(5))
+
+
+@pytest.mark.parametrize("sanitize", [False, True])
+def test_long_rows_are_dealt_evenly_and_every_row_is_looked_at_once(repo_root, tmp_path, sanitize):
+    run_checker(build_checker(repo_root, tmp_path, "scouts_check", sanitize), sanitize)
 
 
 @pytest.mark.parametrize("sanitize", [False, True])
