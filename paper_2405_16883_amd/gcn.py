@@ -62,18 +62,22 @@ class GcnLayer:
 
     def forward(self, H: torch.Tensor, W: torch.Tensor, bias: Optional[torch.Tensor] = None, relu: bool = True,
                 stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
+        """All of it runs on ``stream`` (default: the current one): what it reads has to be there, as for any call on a stream."""
         n_in, n_out = int(W.shape[0]), int(W.shape[1])
         if H.shape != (self.m, n_in):
             raise ValueError(f"H must be {self.m} x {n_in}")
+        if stream is not None:
+            self._plan(min(n_in, n_out))  # on the current stream, as the adjacency
+            with torch.cuda.stream(stream):
+                return self.forward(H, W, bias, relu)
         act = _b.ACT_RELU if relu else _b.ACT_IDENTITY
         if not self.aggregates_first(n_in, n_out):
             Z = torch.mm(H, W)
             out = torch.empty((self.m, n_out), dtype=torch.float32, device=H.device)
-            _b.scorch_spmm_csr_planned_epilogue(self._plan(n_out), self.rowptr, self.colidx, self.vals, Z, bias, act, out,
-                                                stream=stream)
+            _b.scorch_spmm_csr_planned_epilogue(self._plan(n_out), self.rowptr, self.colidx, self.vals, Z, bias, act, out)
             return out
         Y = torch.empty((self.m, n_in), dtype=torch.float32, device=H.device)
-        _b.scorch_spmm_csr_planned(self._plan(n_in), self.rowptr, self.colidx, self.vals, H, Y, stream=stream)
+        _b.scorch_spmm_csr_planned(self._plan(n_in), self.rowptr, self.colidx, self.vals, H, Y)
         # With an activation the dense library makes one more pass over the result (addmm adds the bias inside the product,
         # relu_ runs on what it wrote): one kernel for all three takes 0.2 to 0.85 of the time.  Without one, the product alone
         # is between 1.6 times faster and 1.35 times slower than the library's, so that case stays there.

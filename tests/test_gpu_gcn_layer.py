@@ -74,3 +74,24 @@ def test_weight_gradient_of_a_widening_layer_still_flows():
         on = (out > 0).double()
     assert bool(((W.grad.double() - Y.double().T @ on).abs() <= p.m * 2.0 ** -24 * (Y.double().abs().T @ on)).all())
     layer.close()
+
+
+@pytest.mark.parametrize("n_in,n_out,relu", [(16, 32, True), (16, 32, False), (32, 16, True), (160, 200, True)])
+def test_a_layer_runs_on_the_stream_it_is_given(n_in, n_out, relu):
+    """Both products, the epilogue and the memory between them: work queued on that stream before the call holds all of them back."""
+    p = make_scaled_config(3, 0.02, seed=3)
+    layer = GcnLayer(p.m, torch.from_numpy(p.rowptr).to(DEV), torch.from_numpy(p.colidx).to(DEV), torch.from_numpy(p.vals).to(DEV), p.nnz)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    H, W, b = (torch.randn(size, generator=g, device=DEV) for size in ((p.m, n_in), (n_in, n_out), (n_out,)))
+    want = layer.forward(H, W, b, relu=relu)
+    late = torch.zeros_like(H)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        torch.cuda._sleep(20_000_000)
+        late.copy_(H)  # the operand is there only once the stream gets to it
+    got = layer.forward(late, W, b, relu=relu, stream=s)
+    assert torch.cuda.current_stream() != s
+    s.synchronize()
+    assert torch.equal(got, want)
+    layer.close()
