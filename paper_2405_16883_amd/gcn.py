@@ -38,9 +38,16 @@ def _native_product(X: torch.Tensor, W: torch.Tensor, bias: Optional[torch.Tenso
         return False
     if bias is not None and (bias.device != X.device or bias.dim() != 1 or bias.shape[0] != n or bias.stride(0) != 1):
         return False
-    return not (torch._C._len_torch_dispatch_stack() or torch._C._len_torch_function_stack()
-                or torch._C._functorch.peek_interpreter_stack() is not None or torch.is_autocast_enabled("cuda")
-                or torch.autograd.forward_ad._current_level >= 0)
+    return _unwatched()
+
+
+def _unwatched() -> bool:
+    try:
+        return not (torch._C._len_torch_dispatch_stack() or torch._C._len_torch_function_stack()
+                    or torch._C._functorch.peek_interpreter_stack() is not None or torch.is_autocast_enabled("cuda")
+                    or torch.autograd.forward_ad._current_level >= 0)
+    except AttributeError:  # a torch that keeps these elsewhere: its own operations are right in any case
+        return False
 
 
 class GcnLayer:

@@ -1,0 +1,27 @@
+"""Which torch states leave the dense product of a layer to torch; needs no GPU."""
+import pytest
+import torch
+from torch.utils._python_dispatch import TorchDispatchMode
+
+from paper_2405_16883_amd import gcn
+
+
+def test_modes_and_transforms_are_seen():
+    class Watch(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    assert gcn._unwatched()
+    with Watch():
+        assert not gcn._unwatched()
+    with torch.autograd.forward_ad.dual_level():
+        assert not gcn._unwatched()
+    assert torch.vmap(lambda x: x * float(gcn._unwatched()))(torch.ones(2)).sum() == 0
+    assert gcn._unwatched()
+
+
+@pytest.mark.parametrize("owner,name", [(torch._C, "_len_torch_dispatch_stack"), (torch._C, "_len_torch_function_stack"),
+                                        (torch._C._functorch, "peek_interpreter_stack"), (torch.autograd.forward_ad, "_current_level")])
+def test_a_torch_without_one_of_these_names_keeps_the_product(monkeypatch, owner, name):
+    monkeypatch.delattr(owner, name)
+    assert not gcn._unwatched()
