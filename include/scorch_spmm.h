@@ -94,7 +94,8 @@ scorch_status_t scorch_spmm_plan_workspace_bytes(int32_t m, int32_t k, int32_t n
  * lives.  `colidx` may be NULL; when given (device, nnz entries) it is only inspected to see whether
  * every row stores its columns in strictly increasing order, which is what the panel kernel for
  * dense-ish matrices needs (with NULL, or with unsorted or repeated columns in a row, the gather
- * kernels are used).  The
+ * kernels are used).  The panel kernel (n >= 256) takes the columns of a call to be increasing as they were here; the others
+ * take any.  The
  * call enqueues on `stream` and WAITS for it (it reads nnz and the list sizes back).  The plan is valid for exactly this rowptr content
  * and this n, on the device that was current.
  * When B is more than three times the 256 MB memory-side cache, n >= 96 and colidx is given, the plan also counts how often

@@ -131,7 +131,7 @@ __device__ __forceinline__ void panel_compute(PanelRows<RW, kBatch, Q> &st, cons
 #pragma unroll
     for (int r = 0; r < RW; ++r) {
         // Whole batches first, without a test per entry (all branches here are wave-uniform, and the scalar
-        // instructions of such tests cost issue slots like vector ones: this loop is bound by instruction issue), then
+        // instructions of such tests cost issue slots like vector ones), then
         // half a batch if that many entries are left, then the remaining entries one at a time.
         int jj = j[r];
         for (; jj + kBatch <= lim[r]; jj += kBatch) panel_visits<kBatch, Q, KR>(st.acc[r], st.colreg[r], st.valreg[r], jj, sbuf, k0, lane);

@@ -526,8 +526,8 @@ __host__ __device__ static int32_t resident_width(int32_t n) {
 // 16 384, k = 1024 ... 16 384, 1 ... 50 % stored, n = 1 ... 64, in units of 0.1 ps (integers: host and device have to
 // decide alike).  Gathers: 2.3 ps (n = 1) to 11 ps (n = 64) per entry.  Resident: 2 to 3 ps per entry, but at least
 // 1.2 us per row and chunk that a wavefront goes through (4096 wavefronts), 4 us to fill LDS, and the second launch over the partial
-// rows.  Measured, gather / resident in us, 4096 x 16 384 with 10 % stored: n = 4 25.0 / 18.8, 8 38.8 / 19.8, 16 42.0 / 19.8,
-// 32 45.9 / 31.2, 64 78.4 / 47.5; with 1 %: 5.0 / 7.6, 5.3 / 9.7, 5.6 / 13.0, 5.9 / 24.8, 10.8 / 34.1; 16 384 x 4096 with 26 %: n = 16
+// rows.  Measured, gather / resident in us, 4096 x 16 384 with 10 % stored: n = 4 25.0 / 19.8, 8 38.8 / 21.6, 16 42.0 / 21.5,
+// 32 45.9 / 33.4, 64 78.4 / 53.0; with 1 %: 5.0 / 7.6, 5.3 / 9.7, 5.6 / 13.0, 5.9 / 24.8, 10.8 / 34.1; 16 384 x 4096 with 26 %: n = 16
 // 72.3 / 43.3, n = 64 153 / 80.
 __host__ __device__ static int32_t want_resident(int32_t m, int32_t k, int64_t nnz, int32_t n) {
     if (m <= 0 || k <= 0 || n < 3 || n > 64) return 0;

@@ -2,14 +2,16 @@
 // weight times a small batch, C_ik = sum_j A_ij * B_jk (paper, Section 4.2).
 //
 // The gather kernels fetch one row of B per stored entry from L2.  For narrow rows that is bound by the number of
-// requests, not by their bytes: a die's L2 serves 250 G requests/s over the chip, 128 bytes each at most, so 64-byte rows
-// arrive at 16 TB/s.  Here every workgroup keeps a chunk of the rows of B in LDS for its whole life (158 KB: 158 * 256 / W
+// requests, not by their bytes: the dies' L2s serve 226 G requests/s at most (probe of 512-byte rows), 128 bytes each, so
+// 64-byte rows arrive at 14 to 16 TB/s.  Here every workgroup keeps a chunk of the rows of B in LDS for its whole life (158 KB: 158 * 256 / W
 // rows of W columns) and takes, of every row of A in its block of rows, the entries that fall into the chunk.  Where
 // they start is in the plan.  The plan is bound to the row pointers, not to the columns: where one of a row's entries turns
 // out to lie outside the chunk, they are all gathered from B instead (resident_gather), so that other columns, in any
 // order and repeated, are added up as well (4096 x 16 384, 10 % stored, n = 16: 21.5 us for the planner's columns, 51 for shuffled
 // ones; the gather kernel 42).  B enters a CU once, A is read once, and each chunk leaves partial rows that a second
 // launch adds in chunk order (none if B fits one chunk).
+//
+// Now no unit is saturated (n = 16: VALU busy 48 %, LDS 24 %, half of that bank conflicts): with LDS full a SIMD has four wavefronts.
 //
 //   workgroup   16 wavefronts on a CU of its own: one chunk x a block of rows
 //   wavefront   one row at a time: 64 entries per window, one per lane, requested a row ahead

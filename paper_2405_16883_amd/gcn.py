@@ -86,8 +86,8 @@ class GcnLayer:
         Y = torch.empty((self.m, n_in), dtype=torch.float32, device=H.device)
         _b.scorch_spmm_csr_planned(self._plan(n_in), self.rowptr, self.colidx, self.vals, H, Y)
         # With an activation the dense library makes one more pass over the result (addmm adds the bias inside the product,
-        # relu_ runs on what it wrote): one kernel for all three takes 0.2 to 0.85 of the time.  Without one, the product alone
-        # is between 1.6 times faster and 1.35 times slower than the library's, so that case stays there.
+        # relu_ runs on what it wrote): one kernel for all three takes 0.15 to 0.85 of the time.  Without one, the product alone
+        # takes 0.17 to 1.35 of the library's time, more than all of it on 20 000 to 60 000 rows, so that case stays there.
         if relu and _native_product(Y, W, bias):
             out = torch.empty((self.m, n_out), dtype=torch.float32, device=H.device)
             _b.scorch_dense_layer(Y, W, bias, act, out)
