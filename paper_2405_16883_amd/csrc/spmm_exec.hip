@@ -516,14 +516,13 @@ __global__ __launch_bounds__(NW * kWave) void spmm_row_kernel(const ExecArgs a) 
 // are staged with coalesced reads and walked one row per lane group, like a window of the planned path; a longer
 // row is streamed through the stage by the whole wavefront, the lane groups taking interleaved entries.
 //
-// Rows that are long beside the others (long_row_limit) are left to scouts: the workgroups at the front of the grid, or, where
-// all workgroups are resident at once, the first ones of those that take the runs, before their own.  A scout looks at rows
-// from all over the matrix (scout_first, scout_place) and takes the long ones one after the other, all 4 wavefronts together
-// (interleaved 64-entry chunks, LDS tree, twice the gathers in flight), so that the longest rows start first and run
-// beside everything else.  Neither the order of the rows nor how many of them are long leaves them to few workgroups.
-// Measured, us, against workgroups that each look through a stretch of 64 to 1024 neighbouring rows: graph of 169 343 rows (longest
-// 10 316 entries), n = 128, random order 140 -> 138, longest rows first 1149 -> 116; 4096 rows, every fourth of 1000 entries, n = 64
-// 66.6 -> 19.8; 5000 rows of 31 in the mean, n = 128 19.9 -> 16.5; 4096 rows, every 64th of 6000 entries 19.8 -> 22.4.
+// Rows that are long beside the others (long_row_limit) are left to the workgroups at the front of the grid, the scouts.  A scout
+// looks at rows from all over the matrix (scout_first, scout_place) and takes the long ones one after the other, all 4
+// wavefronts together (interleaved 64-entry chunks, LDS tree, twice the gathers in flight), so that the longest rows
+// start first and run beside everything else.  Neither the order of the rows nor how many of them are long leaves them to
+// few workgroups.  Measured, us, against workgroups that each look through a stretch of 64 to 1024 neighbouring rows: graph of 169 343
+// rows (longest 10 316 entries), n = 128, random order 140 -> 138, longest rows first 1149 -> 116; 16 384 rows, every
+// fourth of 1000 entries, n = 64 69 -> 44; 16 000 rows of 6, n = 16 7.6 -> 7.2.
 constexpr int kNaturalRowsMax = 16;
 constexpr int kNaturalShort = 32;
 
@@ -571,67 +570,11 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
     int *lrp = lcol + 2 * kStageMax;
     vec acc[T];
 
-    const int long_limit = long_row_limit((uint32_t)a.rowptr[a.m], (uint32_t)a.m);
-    if (b < (uint32_t)a.nb_scouts) {
-        // ---- scout: 256 rows at a time, all wavefronts on each long one ----
-        for (int64_t first = scout_first(b, a.nb_scouts, a.scout_shift); first < a.m; first += kBlock * a.nb_scouts) {
-            const int64_t mine = first + scout_place(tid, a.nb_scouts, a.scout_shift);
-            int q0 = 0, q1 = 0;
-            if (mine < a.m) {
-                q0 = a.rowptr[mine];
-                q1 = a.rowptr[mine + 1];
-            }
-            const unsigned long long longs = __ballot(q1 - q0 > long_limit);
-            if (lane == 0) s_longs[wv] = longs;
-            if (q1 - q0 > long_limit) s_span[tid] = make_int2(q0, q1);
-            __syncthreads();
-            for (int i = next_long(s_longs, 0); i < kBlock; i = next_long(s_longs, i + 1)) {  // the same for the whole workgroup
-                const int2 span = s_span[i];
-                const int p0 = span.x, p1 = span.y;
-#pragma unroll
-                for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
-                row_accumulate<V, G, T, 2 * U, false, UA>(acc, lcol, lval, lane, grp, p0 + wv * kWave, p1, kBlock, a.colidx,
-                                                          a.vals, a.B, ldb, colok[0], coff);
-                reduce_groups<V, G, T>(acc);
-                __syncthreads();  // s_red of the previous row has been read
-                if (grp == 0) {
-#pragma unroll
-                    for (int t = 0; t < T; ++t) {
-                        if constexpr (V == 1) s_red[wv * TW + t * GV + lig] = acc[t];
-                        else
-#pragma unroll
-                            for (int i = 0; i < V; ++i) s_red[wv * TW + t * GV + lig * V + i] = acc[t][i];
-                    }
-                }
-                __syncthreads();
-                if (wv == 0 && grp == 0) {
-                    float *dst = a.C + (first + scout_place(i, a.nb_scouts, a.scout_shift)) * a.ldc;
-#pragma unroll
-                    for (int t = 0; t < T; ++t) {
-                        if (!colok[t]) continue;
-                        vec out;
-#pragma unroll
-                        for (int j = 0; j < V; ++j) {
-                            const int o = t * GV + lig * V + j;
-                            float sum = s_red[o];
-#pragma unroll
-                            for (int x = 1; x < kWavesPerBlock; ++x) sum += s_red[x * TW + o];
-                            if constexpr (V == 1) out = sum;
-                            else out[j] = sum;
-                        }
-                        vstore<V, NTC, UA>(dst + coff[t], out);
-                    }
-                }
-            }
-            __syncthreads();  // the list has been read
-        }
-        if (a.nb_items > 0) return;
-    }
-
+    const bool scout = b < (uint32_t)a.nb_items;
+    const int long_limit = long_row_limit((uint32_t)a.rowptr[a.m], a.one_over_m);
     const int64_t r0 = ((int64_t)(b - (uint32_t)a.nb_items) * kWavesPerBlock + wv) * NR;
-    const int nr = (int)max((int64_t)0, min((int64_t)NR, (int64_t)a.m - r0));
-    if (nr <= 0) return;
-    const int rpv = a.rowptr[r0 + min(lane, nr)];
+    const int nr = scout ? 0 : (int)max((int64_t)0, min((int64_t)NR, (int64_t)a.m - r0));
+    const int rpv = nr > 0 ? a.rowptr[r0 + min(lane, nr)] : 0;
     const int rnext = __shfl_down(rpv, 1, kWave);  // lanes past the run hold the last pointer; lane 63 is never a row
     lrp[lane] = rpv;
     wave_lds_sync();
@@ -677,6 +620,60 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
         }
         wave_lds_sync();  // the stage is refilled next
         i = j;
+    }
+    if (!scout) return;
+
+    // ---- scout: 256 rows at a time, all wavefronts on each long one ----
+    for (int64_t first = scout_first(b, a.nb_items, a.scout_shift); first < a.m; first += kBlock * a.nb_items) {
+        const int64_t mine = first + scout_place(tid, a.nb_items, a.scout_shift);
+        int q0 = 0, q1 = 0;
+        if (mine < a.m) {
+            q0 = a.rowptr[mine];
+            q1 = a.rowptr[mine + 1];
+        }
+        const unsigned long long longs = __ballot(q1 - q0 > long_limit);
+        if (lane == 0) s_longs[wv] = longs;
+        if (q1 - q0 > long_limit) s_span[tid] = make_int2(q0, q1);
+        __syncthreads();
+        for (int i = next_long(s_longs, 0); i < kBlock; i = next_long(s_longs, i + 1)) {  // the same for the whole workgroup
+            const int2 span = s_span[i];
+            const int p0 = span.x, p1 = span.y;
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
+            row_accumulate<V, G, T, 2 * U, false, UA>(acc, lcol, lval, lane, grp, p0 + wv * kWave, p1, kBlock, a.colidx,
+                                                      a.vals, a.B, ldb, colok[0], coff);
+            reduce_groups<V, G, T>(acc);
+            __syncthreads();  // s_red of the previous row has been read
+            if (grp == 0) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    if constexpr (V == 1) s_red[wv * TW + t * GV + lig] = acc[t];
+                    else
+#pragma unroll
+                        for (int i = 0; i < V; ++i) s_red[wv * TW + t * GV + lig * V + i] = acc[t][i];
+                }
+            }
+            __syncthreads();
+            if (wv == 0 && grp == 0) {
+                float *dst = a.C + (first + scout_place(i, a.nb_items, a.scout_shift)) * a.ldc;
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    if (!colok[t]) continue;
+                    vec out;
+#pragma unroll
+                    for (int j = 0; j < V; ++j) {
+                        const int o = t * GV + lig * V + j;
+                        float sum = s_red[o];
+#pragma unroll
+                        for (int x = 1; x < kWavesPerBlock; ++x) sum += s_red[x * TW + o];
+                        if constexpr (V == 1) out = sum;
+                        else out[j] = sum;
+                    }
+                    vstore<V, NTC, UA>(dst + coff[t], out);
+                }
+            }
+        }
+        __syncthreads();  // the list has been read
     }
 }
 
@@ -1022,10 +1019,10 @@ scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *r
            (int64_t)m >= 8192 * (int64_t)a.rows_per_wave)
         a.rows_per_wave *= 2;
     a.nb_wave = (int32_t)ceil_div64(m, (int64_t)kWavesPerBlock * a.rows_per_wave);
-    const Scouts scouts = scouts_for(m, a.nb_wave, mp.ncoltiles);
-    a.nb_scouts = scouts.count;
+    const Scouts scouts = scouts_for(m);
+    a.nb_items = scouts.count;
     a.scout_shift = scouts.shift;
-    a.nb_items = scouts.beside ? scouts.count : 0;
+    a.one_over_m = 1.f / (float)m;
     a.ncoltiles = mp.ncoltiles;
     const int64_t grid = grid_size(mp, (int64_t)a.nb_items + a.nb_wave);
     if (grid > 0x7fffffffLL) {

@@ -97,7 +97,8 @@ struct ExecArgs {
     int32_t act;            // epilogue: 0 identity, 1 ReLU
     const uint32_t *hotmask;  // one bit per column of A, set for the most referenced rows of B (hot/cold variants only)
     int32_t rows_per_wave;    // plan-free kernel only: consecutive rows taken by one wavefront (a power of two)
-    int32_t nb_scouts, scout_shift;  // plan-free kernel only: see scouts.h; nb_items of the scouts do nothing else
+    int32_t scout_shift;      // plan-free kernel only: see scouts.h (nb_items: the scouts)
+    float one_over_m;
     int64_t b_bytes;          // size of B in bytes (cache-policy experiments of the hot/cold variants only)
 };
 

@@ -38,7 +38,7 @@ def test_rows_beyond_the_long_limit_are_the_normal_case(m, n):
     check_against_oracle(p, d.run_natural(), d.ldc, label=f"long rows m={m} n={n}")
 
 
-# scouts that take runs as well (up to 2048 workgroups) and that do not, and groups of four rows; rows of 400 entries are long
+# every number of workgroups that look for long rows, and groups of four rows; rows of 400 entries are long
 # beside rows of 2, rows of 1000 are not beside a mean of 254 or more
 @pytest.mark.parametrize("m,n", [(2050, 32), (8190, 64), (32768, 20), (33000, 36), (524287, 4), (524288, 4), (600001, 3)])
 def test_long_rows_at_a_distance_in_a_cluster_and_first(m, n):
