@@ -91,9 +91,9 @@ scorch_status_t scorch_spmm_plan_workspace_bytes(int32_t m, int32_t k, int32_t n
  *                               fixed order (no floating-point atomics)
  * `workspace` (device, 256-byte aligned, at least the bound above) receives the row lists and
  * holds the partial rows at execution; it must stay allocated and unmodified while the plan
- * lives.  `colidx` may be NULL; when given (device, nnz entries) it is only inspected to see whether
+ * lives.  `colidx` may be NULL; when given (device, nnz entries) it is inspected to see whether
  * every row stores its columns in strictly increasing order, which is what the panel kernel for
- * dense-ish matrices needs (with NULL, or with unsorted or repeated columns in a row, the gather
+ * dense-ish matrices needs, and, for large B, to cut long rows by ranges of columns, one per accelerator die (with NULL, or with unsorted or repeated columns in a row, the gather
  * kernels are used).  The panel kernel (n >= 256) takes the columns of a call to be increasing as they were here; the others
  * take any.  The
  * call enqueues on `stream` and WAITS for it (it reads nnz and the list sizes back).  The plan is valid for exactly this rowptr content
@@ -102,12 +102,12 @@ scorch_status_t scorch_spmm_plan_workspace_bytes(int32_t m, int32_t k, int32_t n
  * each column occurs and marks the most referenced columns (up to 64 MB of rows of B) as hot; execution then
  * reads only those rows of B with the default cache policy and the others with the streaming policy.
  * This changes no result bit.
- * Optional environment variable SCORCH_SPMM_TUNE="bn=..,alpha=..,lw=..,ch=..,bch=..,u=..,nt=..,sliced=..,pack=..,panel=..,hot=<KB>,sdblk=..,fix=..,cold=..,res=.."
+ * Optional environment variable SCORCH_SPMM_TUNE="bn=..,alpha=..,lw=..,ch=..,bch=..,u=..,nt=..,sliced=..,pack=..,panel=..,hot=<KB>,sdblk=..,fix=..,cold=..,res=..,cut=..,cutj=.."
  * overrides the built-in parameter choice (for experiments; sliced = 0, 1 (= 32), 32, 64 or 128 columns of B per
  * accelerator-die slice, panel = 0, 1 or 2; sdblk = blocks of columns of A per accelerator die in the planned
  * SDDMM, 0 = row-wise kernel; fix = 1: partial rows are added inside the fused launch, by the piece that finishes last, instead
  * of by a second launch; cold = 1, 2, 3: cache-policy bits of the loads of the rows of B outside the hot set; res = 0, 1: narrow B
- * gathered, or kept in LDS in chunks).
+ * gathered, or kept in LDS in chunks; cut = 0, 1: long rows whole, or cut by columns, into up to 2^cutj pieces per die).
  * The variable is read when a plan is made (and by scorch_spmm_plan_workspace_bytes), never by an execution call.
  */
 scorch_status_t scorch_spmm_plan(int32_t m, int32_t k, int32_t n,
@@ -119,7 +119,7 @@ scorch_status_t scorch_spmm_plan(int32_t m, int32_t k, int32_t n,
 /*
  * Planned SpMM: the operation at the top of this file (paper, Section 4.2), i.e. the same result contract as
  * scorch_spmm_csr, executed through the plan's row lists (the plan itself has no counterpart in the paper):
- * one fused launch, plus one small fix-up launch when rows were split across workgroups (the pieces
+ * one fused launch, plus one small launch when rows were split across workgroups or cut by columns (the pieces
  * leave partial rows in the workspace, which are added in piece order); for wide
  * B with few rows a pre-pass first copies B into column-slice-major order so that each accelerator
  * die keeps its slice of B in its own L2; matrices with a few percent of their entries stored and

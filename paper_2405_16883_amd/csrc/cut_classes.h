@@ -1,0 +1,73 @@
+// How long rows are cut by columns (spmm_cut.hip): which rows, into how many pieces, and where a piece's partial row
+// stands.  Plain integer arithmetic with no HIP dependency, so that the host tests can compile and check it on the CPU.
+#pragma once
+
+#include <stdint.h>
+
+#include "xcd_map.h"
+
+namespace scorch {
+
+constexpr int kCutMinLen = 64;   // shorter rows are never cut
+constexpr int kCutBuckets = 17;  // row lengths from kCutMinLen on, two buckets per power of two; the last holds 16 384 and more
+constexpr int kCutClasses = 5;   // class j: 2^j pieces per XCD
+constexpr int kCutBounds = kXcds << (kCutClasses - 1);  // finest division of the columns
+constexpr int kCutBins = 2048;   // column histogram that the division is read off
+
+// Bucket of a row of `len` >= kCutMinLen entries, and the shortest row of a bucket.
+SCORCH_HOST_DEVICE inline int cut_bucket(int32_t len) {
+    const int e = 31 - __builtin_clz((unsigned)len);
+    const int b = 2 * (e - 6) + ((len >> (e - 1)) & 1);
+    return b < kCutBuckets ? b : kCutBuckets - 1;
+}
+SCORCH_HOST_DEVICE inline int32_t cut_bucket_len(int b) { return (2 + (b & 1)) << (5 + b / 2); }
+
+// A row is cut into 2^class pieces per XCD: as many as leave 16 entries per piece in the mean, 2^finest at most, but enough
+// for pieces of 256 entries in the mean (a piece is one wavefront's chain).
+SCORCH_HOST_DEVICE inline int cut_class(int b, int finest) {
+    const int by_reuse = b / 2 - 1 < finest ? b / 2 - 1 : finest;
+    const int by_chain = b / 2 - 4;
+    const int j = by_reuse > by_chain ? by_reuse : by_chain;
+    return j < 0 ? 0 : (j < kCutClasses ? j : kCutClasses - 1);
+}
+
+// What the planner found, in the workspace.  Piece (x, s, i) of class j -- XCD x, s-th part of its columns, i-th row of the
+// class -- has the index x * pieces + piece_off[j] + s * rows[j] + i, in the order in which the XCDs take them: longest rows first,
+// one part of the columns after the other.
+struct CutHead {
+    int32_t len;      // rows of at least this many entries are cut (INT32_MAX: none)
+    int32_t pieces;   // per XCD
+    int32_t n_rows;
+    int32_t longest;  // longest piece; beyond `limit` the pieces are not used
+    int32_t limit;
+};
+struct CutInfo : CutHead {
+    int32_t rows[kCutClasses], row_off[kCutClasses], piece_off[kCutClasses];
+    int32_t bound[kCutBounds];  // first column of every part of the finest division
+};
+
+// Where the rows are not cut, or one piece came out too long to be one wavefront's work, nothing is.
+SCORCH_HOST_DEVICE inline int32_t cut_len_in_use(const CutHead &c) { return c.longest <= c.limit ? c.len : INT32_MAX; }
+
+// Chooses the shortest rows to cut so that their pieces fit `cap_pieces` (over all XCDs), and lays the classes out.
+SCORCH_HOST_DEVICE inline void cut_layout(const int32_t (&rows_in)[kCutBuckets], int finest, int64_t cap_pieces, CutInfo &c) {
+    int64_t pieces = 0;
+    int first = kCutBuckets;
+    for (int b = kCutBuckets - 1; b >= 0; --b) {
+        pieces += (int64_t)rows_in[b] << cut_class(b, finest);
+        if (pieces * kXcds > cap_pieces) break;
+        first = b;
+    }
+    for (int j = 0; j < kCutClasses; ++j) c.rows[j] = 0;
+    for (int b = first; b < kCutBuckets; ++b) c.rows[cut_class(b, finest)] += rows_in[b];
+    c.len = first < kCutBuckets ? cut_bucket_len(first) : INT32_MAX;
+    c.n_rows = c.pieces = 0;
+    for (int j = kCutClasses - 1; j >= 0; --j) {
+        c.row_off[j] = c.n_rows;
+        c.piece_off[j] = c.pieces;
+        c.n_rows += c.rows[j];
+        c.pieces += c.rows[j] << j;
+    }
+}
+
+}  // namespace scorch

@@ -198,7 +198,7 @@ __device__ __forceinline__ void row_accumulate(typename Vec<V>::type (&acc)[T], 
 
 constexpr int smem_ints_per_wave() { return 2 * kStageMax + kWindowRowsMax + 2; }
 
-template <int V, int G, int T, int U, int NT, bool UA, bool HOT = false, int COLD = 0>
+template <int V, int G, int T, int U, int NT, bool UA, bool HOT = false, int COLD = 0, bool CUT = false>
 __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
     using vec = typename Vec<V>::type;
     constexpr int S = kWave / G;
@@ -223,8 +223,20 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
     const int lig = lane % G;
 
     const uint32_t per_tile = (uint32_t)a.nb_items + (uint32_t)a.nb_wave + (uint32_t)a.nb_win;
+    // rows cut by columns come first: workgroup = (column tile * cut_wgs + group of pieces) * 8 + XCD
+    const uint32_t cut_grid = CUT ? (uint32_t)a.cut_wgs * (uint32_t)a.ncoltiles * kXcds : 0;
+    const bool cut_piece = CUT && blockIdx.x < cut_grid;
     uint32_t ct, b;
-    if (!tile_of_workgroup(a.xcd_slices, a.ncoltiles, per_tile, ct, b)) return;
+    if (cut_piece) {
+        b = blockIdx.x / kXcds;
+        ct = b / (uint32_t)a.cut_wgs;
+        b -= ct * (uint32_t)a.cut_wgs;
+        // the XCDs start at different tiles: rows of B are 256-byte blocks of different memory channels side by side, and one tile
+        // at a time on all XCDs would use a part of the channels
+        ct = (ct + (blockIdx.x & (kXcds - 1))) % (uint32_t)a.ncoltiles;
+    } else if (!tile_of_workgroup(a.xcd_slices, a.ncoltiles, per_tile, ct, b, cut_grid)) {
+        return;
+    }
 
     // coff[t]: first column of the lane's t-th vector.  With unaligned rows (UA) n need not be a multiple of V:
     // the vector that would run past column n is moved back to end at n, so it overlaps its neighbour and both
@@ -257,9 +269,75 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
 #pragma unroll
     for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
 
+    if constexpr (CUT) if (cut_piece) {
+        // ---- pieces of rows cut by columns: kCutRun of them per wavefront, each to its partial row ----
+        // Rows of B are read with the default cache policy here whatever the variant: they are used again.
+        const int x = (int)(blockIdx.x & (kXcds - 1));
+        const int pieces = cut_len_in_use(*a.cut) == INT32_MAX ? 0 : a.cut->pieces;
+        const int q0 = ((int)b * kWavesPerBlock + wv) * kCutRun;
+        const int nq = min(kCutRun, pieces - q0);
+        if (nq <= 0) return;
+        const int64_t first = (int64_t)x * pieces + q0;
+        const int2 span = a.cut_spans[first + min(lane, nq - 1)];
+        const int len = lane < nq ? span.y - span.x : 0;
+        int end = len;  // of the piece's entries in the stage
+#pragma unroll
+        for (int off = 1; off < kCutRun; off <<= 1) {
+            const int o = __shfl_up(end, off, kWave);
+            if (lane >= off) end += o;
+        }
+        const int total = __shfl(end, kCutRun - 1, kWave);
+        float *dst0 = a.cut_partials + first * a.partial_stride;
+        if (total <= kCutStage) {
+            // short pieces: staged together, one lane group per piece
+            const int shift = span.x - (end - len);  // from the place in the stage to the entry
+            int ends[kCutRun], shifts[kCutRun];
+#pragma unroll
+            for (int i = 0; i < kCutRun; ++i) {
+                ends[i] = __builtin_amdgcn_readlane(end, i);
+                shifts[i] = __builtin_amdgcn_readlane(shift, i);
+            }
+            for (int e = lane; e < total; e += kWave) {
+                int sh = shifts[0];
+#pragma unroll
+                for (int i = 1; i < kCutRun; ++i)
+                    if (e >= ends[i - 1]) sh = shifts[i];
+                lcol[e] = ld_idx<NTA>(a.colidx + e + sh);
+                lval[e] = ld_val<NTA>(a.vals + e + sh);
+            }
+            if (lane < kCutRun) lrp[lane + 1] = end;
+            if (lane == 0) lrp[0] = 0;
+            wave_lds_sync();
+            for (int i = grp; i < nq; i += S) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
+                gather_fma<V, T, U, UA>(acc, lcol, lval, lrp[i], lrp[i + 1], 1, Bc, ldb, colok[0], boff);
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    if (colok[t]) vstore<V, HOT, UA>(dst0 + (int64_t)i * a.partial_stride + coff[t], acc[t]);
+            }
+            return;
+        }
+        for (int i = 0; i < nq; ++i) {
+            const int p0 = __builtin_amdgcn_readlane(span.x, i), p1 = __builtin_amdgcn_readlane(span.y, i);
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
+            row_accumulate<V, G, T, U, NTA, UA>(acc, lcol, lval, lane, grp, p0, p1, kWave, a.colidx, a.vals, Bc, ldb, colok[0], boff);
+            reduce_groups<V, G, T>(acc);
+            if (grp == 0) {
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    if (colok[t]) vstore<V, HOT, UA>(dst0 + (int64_t)i * a.partial_stride + coff[t], acc[t]);
+            }
+        }
+        return;
+    }
+    const int cut_len = CUT ? cut_len_in_use(*a.cut) : INT32_MAX;
+
     if (b < (uint32_t)a.nb_items) {
         // ---- piece of a long row: 4 wavefronts, LDS tree, then C or a partial row ----
         const int4 it = a.items[b];
+        if (CUT && a.rowptr[it.x + 1] - a.rowptr[it.x] >= cut_len) return;
         row_accumulate<V, G, T, U, NTA, UA, HOT, COLD>(acc, lcol, lval, lane, grp, it.y + wv * kWave, it.z, kBlock, a.colidx,
                                                        a.vals, Bc, ldb, colok[0], boff, a.hotmask, cp);
         reduce_groups<V, G, T>(acc);
@@ -341,6 +419,7 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
         const int row = a.wave_rows[idx];
         const int2 span = a.wave_span[idx];  // the row's entry range, kept in the plan beside its id
         const int p0 = span.x, p1 = span.y;
+        if (CUT && p1 - p0 >= cut_len) return;
         row_accumulate<V, G, T, U, NTA, UA, HOT, COLD>(acc, lcol, lval, lane, grp, p0, p1, kWave, a.colidx, a.vals, Bc, ldb,
                                                        colok[0], boff, a.hotmask, cp);
         reduce_groups<V, G, T>(acc);
@@ -711,6 +790,7 @@ __global__ __launch_bounds__(kBlock) void spmm_fixup_kernel(const FixupArgs a) {
     const int s = blockIdx.x;
     if (s >= a.n_split) return;
     const int4 d = a.split[s];
+    if (a.cut && a.rowptr[d.x + 1] - a.rowptr[d.x] >= cut_len_in_use(*a.cut)) return;
     const float *src = a.partials + (int64_t)d.y * a.partial_stride;
     float *dst = a.C + (int64_t)d.x * a.ldc;
     for (int c = threadIdx.x; c < a.n; c += kBlock) {
@@ -818,6 +898,20 @@ static kernel_fn pick_fused_hot(int G, int T, int cold) {
         default: return spmm_fused_kernel<4, 64, 1, 8, 1, false, true>;
     }
 }
+// With rows cut by columns: groups of 8 lanes and more, one unroll depth, streaming stores, the plain hot/cold variant.
+static kernel_fn pick_fused_cut(int G, int T, bool UA, bool hot) {
+#define SCORCH_CUT(G, T)                                                                                                \
+    return hot ? spmm_fused_kernel<4, G, T, 8, 1, false, true, 0, true>                                                 \
+               : (UA ? spmm_fused_kernel<4, G, T, 8, 1, true, false, 0, true> : spmm_fused_kernel<4, G, T, 8, 1, false, false, 0, true>);
+    if (T == 2) { SCORCH_CUT(64, 2) }
+    switch (G) {
+        case 8: SCORCH_CUT(8, 1)
+        case 16: SCORCH_CUT(16, 1)
+        case 32: SCORCH_CUT(32, 1)
+        default: SCORCH_CUT(64, 1)
+    }
+#undef SCORCH_CUT
+}
 // The plan-free path is compiled for one unroll depth (8) and streaming stores only.
 #define SCORCH_NATURAL(V, G, T, UA) return spmm_natural_kernel<V, G, T, 8, 1, UA>;
 #define SCORCH_NATURAL_G4(UA)                                               \
@@ -910,8 +1004,17 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
     a.xcd_slices = mp.xcd_slices;
     a.bias = bias;
     a.act = act;
+    // every row that the plan keeps among the pieces is cut by columns instead
+    const bool no_items = plan->cut_pieces > 0 && plan->cut_len > 0 && plan->cut_len <= plan->params.CH + 1;
+    if (plan->cut_pieces > 0) {
+        a.cut = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_info);
+        a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->layout.off_cut_spans);
+        a.cut_partials = reinterpret_cast<float *>(ws + plan->layout.off_cut_partials);
+        a.cut_wgs = (int32_t)ceil_div64(plan->cut_pieces, kWavesPerBlock * kCutRun);
+        if (no_items) a.nb_items = 0;
+    }
     const int64_t per_tile = (int64_t)a.nb_items + a.nb_wave + a.nb_win;
-    const int64_t grid = grid_size(mp, per_tile);
+    const int64_t grid = grid_size(mp, per_tile) + (int64_t)a.cut_wgs * mp.ncoltiles * kXcds;
     if (grid > 0x7fffffffLL) {
         set_error("launch grid of %lld workgroups exceeds the HIP limit", (long long)grid);
         return SCORCH_ERR_UNSUPPORTED;
@@ -925,20 +1028,27 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
         a.b_tile_stride = (int64_t)plan->k * kSliceCols;
     }
     if (grid > 0) {
-        kernel_fn fn = pick_fused(mp.V, mp.G, mp.T, plan->params.U, plan->params.NT, mp.UA);
+        kernel_fn fn = a.cut ? pick_fused_cut(mp.G, mp.T, mp.UA, false)
+                             : pick_fused(mp.V, mp.G, mp.T, plan->params.U, plan->params.NT, mp.UA);
         if (plan->n_hot > 0 && mp.V == 4 && !mp.UA && mp.xcd_slices == 0 && mp.G >= 8 && plan->params.U >= 8 &&
             (plan->params.NT & 1)) {
             // hot/cold variant: rows of B outside the plan's hot set are read with the streaming policy
             a.hotmask = reinterpret_cast<const uint32_t *>(ws + plan->layout.off_hotmask);
             a.b_bytes = (int64_t)plan->k * ldb * 4;
-            fn = pick_fused_hot(mp.G, mp.T, a.b_bytes < (1ll << 32) ? plan->tuning.cold : 0);
+            fn = a.cut ? pick_fused_cut(mp.G, mp.T, false, true) : pick_fused_hot(mp.G, mp.T, a.b_bytes < (1ll << 32) ? plan->tuning.cold : 0);
         }
         hipLaunchKernelGGL(fn, dim3((uint32_t)grid), dim3(kBlock), 0, stream, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "launch spmm_fused_kernel");
     }
-    if (plan->n_split > 0 && !fold) {
+    if (plan->cut_pieces > 0) {
+        scorch_status_t st = launch_cut_sum(plan, C, ldc, bias, act, stream);
+        if (st != SCORCH_OK) return st;
+    }
+    if (plan->n_split > 0 && !fold && !no_items) {
         FixupArgs f{};
+        f.rowptr = rowptr;
+        f.cut = a.cut;
         f.split = reinterpret_cast<const int4 *>(ws + plan->layout.off_split);
         f.partials = a.partials;
         f.C = C;

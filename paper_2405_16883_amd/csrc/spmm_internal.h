@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "scorch_spmm.h"
+#include "cut_classes.h"
 #include "tuning.h"
 #include "xcd_map.h"
 
@@ -42,6 +43,8 @@ struct PlanParams {
     int32_t PANEL;  // dense-ish sorted rows: stream B through LDS in k-panels (spmm_panel.hip); 1: 256-column tiles, 2: 512
     int32_t PDIRECT; // panel kernel: 1 = fetch the panels from the caller's row-major B instead of a tile-major copy
     int32_t RES;    // >0: narrow B kept in LDS in chunks (spmm_resident.hip), rows padded to this many columns
+    int32_t CUT;    // 1: long rows are cut by columns, a range of columns per XCD (spmm_cut.hip)
+    int32_t CUTJ;   // finest class for the sake of reuse (see cut_class)
     int32_t HOT;    // >0: budget in KB for the most referenced rows of B, which alone keep the default cache policy
 };
 
@@ -51,11 +54,13 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
 
 struct WorkspaceLayout {
     uint64_t off_counts, off_totals, off_win, off_stage, off_wave, off_wave_span, off_items, off_split, off_partials, off_tickets, off_bpack,
-        off_res_ptr, off_coldeg, off_hotmask, off_degbins, off_res_partials, total;
+        off_res_ptr, off_coldeg, off_hotmask, off_degbins, off_res_partials,
+        off_cut_info, off_cut_counts, off_cut_hist, off_cut_rows, off_cut_spans, off_cut_partials, total;
     uint64_t res_row_bytes;  // resident kernel: partial rows of one row of A (0: none, B fits one chunk)
     int64_t ticket_tiles;  // arrival counters per split row: one for every column tile a launch may use
     int64_t n_windows, nblk;
     int64_t cap_wave, cap_items, cap_split, cap_slots;
+    int64_t cap_cut;  // pieces of rows cut by columns, over all XCDs
     int32_t partial_stride;
 };
 __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64_t nnz, int32_t n, const PlanParams &p);
@@ -65,6 +70,7 @@ struct alignas(64) PlanResult {
     int32_t nnz;
     int32_t totals[5];  // wave rows, items, split rows, slots, short rows
     int32_t done;       // written last by the first two kernels
+    CutHead cut;        // rows cut by columns
     int32_t unsorted;   // some row's columns are not strictly increasing
     PlanResult *next;   // host side only: the next slot that no call is using
 };
@@ -99,6 +105,10 @@ struct ExecArgs {
     int32_t rows_per_wave;    // plan-free kernel only: consecutive rows taken by one wavefront (a power of two)
     int32_t scout_shift;      // plan-free kernel only: see scouts.h (nb_items: the scouts)
     float one_over_m;
+    const CutInfo *cut;       // rows cut by columns (nullptr: none)
+    const int2 *cut_spans;    // entry range of every piece
+    float *cut_partials;
+    int32_t cut_wgs;          // workgroups for them, per XCD and column tile (a multiple of 8 in all: they are the first of the grid)
     int64_t b_bytes;          // size of B in bytes (cache-policy experiments of the hot/cold variants only)
 };
 
@@ -148,6 +158,8 @@ struct FixupArgs {
     int32_t n, n_split, partial_stride;
     const float *bias;
     int32_t act;
+    const int32_t *rowptr;
+    const CutInfo *cut;  // rows cut by columns are left out (nullptr: there are none)
 };
 
 #if defined(__HIPCC__)
@@ -160,8 +172,8 @@ __device__ __forceinline__ bool report_unsorted(bool bad, int32_t *seen, int32_t
 }
 
 __device__ __forceinline__ bool tile_of_workgroup(int32_t xcd_slices, int32_t ncoltiles, uint32_t per_tile, uint32_t &ct,
-                                                  uint32_t &b) {
-    return tile_of_index(blockIdx.x, xcd_slices, ncoltiles, per_tile, ct, b);
+                                                  uint32_t &b, uint32_t first = 0) {
+    return tile_of_index(blockIdx.x - first, xcd_slices, ncoltiles, per_tile, ct, b);
 }
 #endif
 
@@ -179,6 +191,8 @@ struct scorch_spmm_plan_s {
     uint64_t off_res_partials;  // resident kernel: where the partial rows of res_rows rows of A stand, as many as are taken at a time
     int32_t res_rows;
     int32_t n_hot;    // columns marked hot (0: every gather uses the default cache policy)
+    int32_t cut_pieces, cut_rows;  // rows cut by columns: pieces per XCD and rows, or upper bounds (one-shot plan); 0: none
+    int32_t cut_len;               // shortest of them (one-shot plan: not known)
     float hot_share;  // share of the stored entries that point at a hot column
 };
 
@@ -218,6 +232,14 @@ scorch_status_t launch_plan_resident(const scorch_spmm_plan_t *plan, const int32
                                      int32_t *unsorted, hipStream_t stream);
 scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *colidx, const float *vals, const float *B, int64_t ldb,
                                 float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream);
+
+// spmm_cut.hip
+constexpr int kPlanBlocksMax = 1024;  // workgroups of a planning kernel
+constexpr int kCutRun = 4;            // pieces per wavefront
+constexpr int kCutStage = 32 * kCutRun;
+scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, PlanResult *result,
+                                hipStream_t stream);
+scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream);
 
 // sddmm_exec.hip (plan == nullptr: plan-free, one wavefront per row)
 scorch_status_t launch_sddmm(const scorch_spmm_plan_t *plan, int32_t m, int32_t d, const int32_t *rowptr,

@@ -288,6 +288,8 @@ __global__ __launch_bounds__(kBlock) void plan_build_kernel(const PlanArgs a) {
             if (last_tile && tid == 0) win_row_start[L.n_windows] = a.m;
         }
     }
+    if (last_block && fits && L.cap_cut > 0)
+        for (int i = tid; i < kCutBins; i += kBlock) reinterpret_cast<int32_t *>(a.workspace + L.off_cut_hist)[i] = 0;
     if (last_block && tid == 0) {
         if (fits) *reinterpret_cast<int32_t *>(a.workspace + L.off_totals) = 0;  // for the kernels that look at the columns
         a.result->nnz = nnz;
@@ -541,6 +543,17 @@ __host__ __device__ static int32_t want_resident(int32_t m, int32_t k, int64_t n
     return resident * 10 < nnz * per_entry * 9 ? W : 0;
 }
 
+constexpr int64_t kCutNnzMin = 1 << 20;
+
+// Cutting long rows by columns (spmm_cut.hip) pays where B is much larger than the 8 L2s (32 MB) together and rows are skewed.  Measured
+// without / with, us: graph of 2.4 M nodes, degree 50, n = 100 7960 / 6600; 1 M, 50, n = 64 1703 / 1336; 100 000, 50, n = 100 253 / 212;
+// 300 000, 20, n = 33 169 / 148; 169 343, 15, n = 128 121 / 111 (operands that change from call to call: 125 / 125), n = 100 126 / 113,
+// n = 48 (32 MB) 62.5 / 60.9; n = 32 (21 MB) 39.8 / 46.2, n = 16 32.2 / 39.0.  With 32-column slices (SLICED = 32) 121 / 145.  Plans get
+// dearer by 0.1 ms (2.5 M entries) to 0.7 ms (122 M); below a million entries nobody waits for that.
+__host__ __device__ static bool want_cut(int32_t k, int32_t n, int32_t sliced) {
+    return n >= 32 && (sliced == 0 || sliced == 64) && (int64_t)k * n * 4 >= 32ll << 20;
+}
+
 // Bytes that a plan cannot do without.
 __host__ __device__ static uint64_t bytes_needed(const WorkspaceLayout &L, bool one_shot) {
     return one_shot ? L.off_res_partials : L.total;
@@ -588,6 +601,16 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     p.PDIRECT = (p.PANEL && (t.pack != 1 || p.PANEL == 3)) ? 1 : 0;
     p.RES = p.PANEL == 0 ? want_resident(m, k, nnz, n) : 0;
     if (t.res >= 0) p.RES = (t.res > 0 && n <= 64 && k > 0 && m > 0 && p.PANEL == 0) ? resident_width(n) : 0;
+    p.CUT = p.CUTJ = 0;
+    if ((nnz >= kCutNnzMin && t.cut != 0) || t.cut > 0) {  // the planning kernels evaluate this: one comparison for small matrices
+        const bool possible = m > 0 && k > 0 && n > 16 && p.PANEL == 0 && p.RES == 0 && p.PACK == 0 && t.fix <= 0 && t.u <= 0 && t.nt < 0;
+        p.CUT = possible && (t.cut > 0 || want_cut(k, n, p.SLICED)) ? 1 : 0;
+        // parts of the columns of an XCD, up to 16 MB of B each: 122 MB in 1 / 4 / 8 / 16 parts 7100 / 6690 / 6600 / 6720 us,
+        // 32 MB in 1 / 2 / 4 / 8 1356 / 1336 / 1356 / 1391, 5 MB in 1 / 2 / 4 212 / 226 / 237
+        const int64_t xcd_bytes = (int64_t)k * (p.SLICED ? p.SLICED : n) * 4 / kXcds;
+        while (p.CUTJ < kCutClasses - 1 && (xcd_bytes >> p.CUTJ) > (16ll << 20)) ++p.CUTJ;
+        if (t.cutj >= 0) p.CUTJ = std::min(t.cutj, kCutClasses - 1);
+    }
     // Enough independent wavefront tasks to fill 256 CUs several times over, but pieces long
     // enough that the per-piece overhead stays small.
     const int64_t coltiles = p.SLICED ? (n + p.SLICED - 1) / p.SLICED : std::max<int64_t>(1, (n + 511) / 512);
@@ -636,6 +659,16 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
 
 __host__ __device__ static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) & ~(a - 1); }  // a: a power of two
 
+// Pieces of rows cut by columns that a workspace has room for, `off` bytes of which are taken: one for 40 stored entries, fewer where
+// that keeps the workspace within what scorch_spmm_csr_static has.
+__host__ __device__ static int64_t cut_capacity(int64_t nnz, int64_t partial_stride, uint64_t off) {
+    const int64_t cap = nnz / 40;
+    if (off > SCORCH_STATIC_SCRATCH_BYTES) return cap;
+    const uint64_t fixed = off + sizeof(CutInfo) + (kCutBuckets * kPlanBlocksMax + kCutBins) * 4 + 6 * 256;
+    if (fixed >= SCORCH_STATIC_SCRATCH_BYTES) return 0;
+    return std::min<int64_t>(cap, (int64_t)((SCORCH_STATIC_SCRATCH_BYTES - fixed) / (uint64_t)(partial_stride * 4 + 9)));
+}
+
 __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64_t nnz, int32_t n, const PlanParams &p) {
     WorkspaceLayout L{};
     L.nblk = ((int64_t)m + kBlock - 1) / kBlock;
@@ -683,6 +716,20 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
     if (p.HOT) off = align_up(off + ((uint64_t)k / 32 + 2) * 4, 256);
     L.off_degbins = off;
     if (p.HOT) off = align_up(off + (uint64_t)kDegBins * 16, 256);
+    L.off_cut_info = off;
+    if (p.CUT && (L.cap_cut = cut_capacity(nnz, L.partial_stride, off)) > 0) {
+        off = align_up(off + sizeof(CutInfo), 256);
+        L.off_cut_counts = off;
+        off = align_up(off + (uint64_t)kCutBuckets * kPlanBlocksMax * 4, 256);
+        L.off_cut_hist = off;
+        off = align_up(off + (uint64_t)kCutBins * 4, 256);
+        L.off_cut_rows = off;
+        off = align_up(off + (uint64_t)L.cap_cut / kXcds * 4, 256);
+        L.off_cut_spans = off;
+        off = align_up(off + (uint64_t)L.cap_cut * 8, 256);
+        L.off_cut_partials = off;
+        off = align_up(off + (uint64_t)L.cap_cut * L.partial_stride * 4, 256);
+    }
     L.off_res_partials = off;  // last: a one-shot plan has fewer of them
     off = align_up(off + L.res_row_bytes * m, 256);
     L.total = std::max<uint64_t>(off, 256);
@@ -693,7 +740,6 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
 // counts of all workgroups before one are few enough to be added up by each.  Up to kPlanRecount workgroups the counting launch
 // is left out and every workgroup counts the rows before its own, 8 batches of row pointers at most; with 78 of them the
 // build kernel took 30 us instead of 7.7 + 4.3 for the counts.
-constexpr int32_t kPlanBlocksMax = 1024;
 constexpr int32_t kPlanRecount = 8;
 
 // Slots of host memory that the planning kernels write their result to: taken for the length of one call and given back
@@ -799,7 +845,7 @@ static scorch_status_t build_plan_in(PlanResult *result, bool *lost, scorch_spmm
     }
     // The panel and resident kernels need every row's columns in strictly increasing order; without colidx this cannot be
     // verified, so the mode is dropped.
-    if (!colidx || plan->m == 0 || plan->nnz == 0) plan->params.PANEL = plan->params.RES = 0;
+    if (!colidx || plan->m == 0 || plan->nnz == 0) plan->params.PANEL = plan->params.RES = plan->params.CUT = 0;
     if (plan->params.PANEL || plan->params.RES) {
         int32_t *seen = reinterpret_cast<int32_t *>(ws + L.off_totals);  // cleared by plan_build_kernel
         const uint32_t g = (uint32_t)std::min<int64_t>(((int64_t)plan->m + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 16);
@@ -819,6 +865,27 @@ static scorch_status_t build_plan_in(PlanResult *result, bool *lost, scorch_spmm
     if (plan->params.RES) {
         plan->off_res_partials = L.off_res_partials;
         plan->res_rows = one_shot ? partial_rows_in(L, plan->m, workspace_bytes, plan->off_res_partials) : plan->m;
+    }
+    plan->cut_pieces = plan->cut_rows = 0;
+    plan->cut_len = 0;
+    if (plan->params.CUT && L.cap_cut > 0) {
+        st = launch_plan_cut(plan, rowptr, colidx, one_shot ? nullptr : result, stream);
+        if (st != SCORCH_OK) return st;
+        if (one_shot) {  // what the planner finds stays on the device
+            plan->cut_pieces = (int32_t)(L.cap_cut / kXcds);
+            plan->cut_rows = (int32_t)(L.cap_cut / kXcds);
+        } else {
+            e = hipStreamSynchronize(stream);
+            if (e != hipSuccess) {
+                *lost = true;
+                return hip_fail(e, "wait for the kernels that cut rows");
+            }
+            if (cut_len_in_use(result->cut) != INT32_MAX) {
+                plan->cut_pieces = result->cut.pieces;
+                plan->cut_rows = result->cut.n_rows;
+                plan->cut_len = result->cut.len;
+            }
+        }
     }
     plan->n_hot = 0;
     plan->hot_share = 0.f;

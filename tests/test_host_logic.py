@@ -58,6 +58,11 @@ def test_long_rows_are_dealt_evenly_and_every_row_is_looked_at_once(repo_root, t
 
 
 @pytest.mark.parametrize("sanitize", [False, True])
+def test_pieces_of_rows_cut_by_columns_fit_and_have_places_of_their_own(repo_root, tmp_path, sanitize):
+    run_checker(build_checker(repo_root, tmp_path, "cut_classes_check", sanitize), sanitize)
+
+
+@pytest.mark.parametrize("sanitize", [False, True])
 def test_tuning_text_parser(repo_root, tmp_path, sanitize):
     run_checker(build_checker(repo_root, tmp_path, "tuning_check", sanitize, extra=("-pthread",)), sanitize)
 
