@@ -43,6 +43,11 @@ struct SddmmArgs {
     int32_t k;              // column-block kernel: rows of Ct
     int32_t block_rows;     // column-block kernel: rows of Ct per block
     int32_t rounds;         // column-block kernel: blocks per XCD (block = round * 8 + XCD)
+    const CutInfo *cut;     // rows cut by columns (nullptr: none), see spmm_cut.hip
+    const int2 *cut_spans;
+    const int32_t *cut_rows;
+    uint32_t cut_grid;      // workgroups for them, the first of the grid
+    int32_t cut_len;        // rows of at least this many entries are cut
 };
 
 // Plan-free path: row lengths up to which a lane group walks a row alone / a wavefront streams a row alone (the larger
@@ -170,7 +175,7 @@ __device__ __forceinline__ void load_x(typename Vec<V>::type (&x)[T], const floa
 
 constexpr int sddmm_smem_ints_per_wave() { return 2 * kStageMax + kWindowRowsMax + 2; }
 
-template <int V, int G, int T, bool PLANNED, bool UA>
+template <int V, int G, int T, bool PLANNED, bool UA, bool CUT = false>
 __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a) {
     using vec = typename Vec<V>::type;
     constexpr int S = kWave / G;
@@ -195,7 +200,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a) {
     float *lval = reinterpret_cast<float *>(lcol + kStageMax);
     int *lrp = lcol + 2 * kStageMax;
     vec x[T];
-    const uint32_t b = blockIdx.x;
+    uint32_t b = blockIdx.x;
 
     if constexpr (!PLANNED) {
         // Plan-free: rows in natural order, a run of consecutive rows per wavefront.  The wavefront reads the run's row
@@ -267,9 +272,30 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a) {
         return;
     }
 
+    if constexpr (CUT) if (b < a.cut_grid) {
+        // pieces of rows cut by columns: kCutRun of them per wavefront, so that an XCD's gathers stay within its range of Ct
+        const int q0 = ((int)(b / kXcds) * kWavesPerBlock + wv) * kCutRun;
+        const int nq = min(kCutRun, a.cut->pieces - q0);
+        if (nq <= 0) return;
+        const int q = q0 + min(lane, nq - 1);
+        int j = kCutClasses - 1;
+        while (j > 0 && q >= a.cut->piece_off[j] + (a.cut->rows[j] << j)) --j;
+        const int row_of_lane = a.cut_rows[a.cut->row_off[j] + (q - a.cut->piece_off[j]) % max(1, a.cut->rows[j])];
+        const int2 span = a.cut_spans[(int64_t)(b & (kXcds - 1)) * a.cut->pieces + q];
+        for (int i = 0; i < nq; ++i) {
+            const int p0 = __builtin_amdgcn_readlane(span.x, i), p1 = __builtin_amdgcn_readlane(span.y, i);
+            if (p0 == p1) continue;
+            const int row = __builtin_amdgcn_readlane(row_of_lane, i);
+            load_x<V, T, UA>(x, a.B + (int64_t)row * a.ldb, colok, coff, nmask);
+            sddmm_row<V, G, T, false, UA>(x, lcol, lval, lane, grp, lig, p0, p1, kWave, a, Yc, colok, coff, nmask);
+        }
+        return;
+    }
+    if constexpr (CUT) b -= a.cut_grid;
     if (b < (uint32_t)a.nb_items) {
         // piece of a long row: the 4 wavefronts take interleaved chunks; entries are independent
         const int4 it = a.items[b];
+        if (CUT && a.rowptr[it.x + 1] - a.rowptr[it.x] >= a.cut_len) return;
         load_x<V, T, UA>(x, a.B + (int64_t)it.x * a.ldb, colok, coff, nmask);
         sddmm_row<V, G, T, false, UA>(x, lcol, lval, lane, grp, lig, it.y + wv * kWave, it.z, kBlock, a, Yc, colok, coff,
                                       nmask);
@@ -280,6 +306,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a) {
         if (idx >= a.n_wave_rows) return;
         const int row = a.wave_rows[idx];
         const int2 span = a.wave_span[idx];  // the row's entry range, kept in the plan beside its id
+        if (CUT && span.y - span.x >= a.cut_len) return;
         load_x<V, T, UA>(x, a.B + (int64_t)row * a.ldb, colok, coff, nmask);
         sddmm_row<V, G, T, false, UA>(x, lcol, lval, lane, grp, lig, span.x, span.y, kWave, a, Yc, colok, coff, nmask);
         return;
@@ -412,6 +439,20 @@ template <bool PLANNED> static sddmm_fn pick_sddmm(int V, int G, int T, bool UA)
 #undef SCORCH_SD
 }
 
+// With rows cut by columns: V = 4 only.
+static sddmm_fn pick_sddmm_cut(int G, int T, bool UA) {
+#define SCORCH_SDC(Gg, Tt) return UA ? sddmm_kernel<4, Gg, Tt, true, true, true> : sddmm_kernel<4, Gg, Tt, true, false, true>;
+    if (T == 4) { SCORCH_SDC(64, 4) }
+    if (T == 2) { SCORCH_SDC(64, 2) }
+    switch (G) {
+        case 8: SCORCH_SDC(8, 1)
+        case 16: SCORCH_SDC(16, 1)
+        case 32: SCORCH_SDC(32, 1)
+        default: SCORCH_SDC(64, 1)
+    }
+#undef SCORCH_SDC
+}
+
 static sddmm_fn pick_sddmm_colblock(int V, int G, int T, bool UA) {
 #define SCORCH_SDB(Vv, Gg, Tt, Uu) return sddmm_colblock_kernel<Vv, Gg, Tt, Uu>;
 #define SCORCH_SDB_G4(Uu)                                 \
@@ -515,8 +556,17 @@ scorch_status_t launch_sddmm(const scorch_spmm_plan_t *plan, int32_t m, int32_t 
         a.nb_wave = (plan->n_wave + kWavesPerBlock - 1) / kWavesPerBlock;
         a.nb_win = plan->n_short > 0 ? (int32_t)((plan->layout.n_windows + kWavesPerBlock - 1) / kWavesPerBlock) : 0;
         a.LW = plan->params.LW;
-        grid = (int64_t)a.nb_items + a.nb_wave + a.nb_win;
         fn = pick_sddmm<true>(V, G, T, UA);
+        if (plan->cut_pieces > 0 && V == 4) {
+            fn = pick_sddmm_cut(G, T, UA);
+            a.cut = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_info);
+            a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->layout.off_cut_spans);
+            a.cut_rows = reinterpret_cast<const int32_t *>(ws + plan->layout.off_cut_rows);
+            a.cut_len = plan->cut_len;
+            a.cut_grid = (uint32_t)((plan->cut_pieces + kWavesPerBlock * kCutRun - 1) / (kWavesPerBlock * kCutRun)) * kXcds;
+            if (a.cut_len <= plan->params.CH + 1) a.nb_items = 0;
+        }
+        grid = (int64_t)a.cut_grid + a.nb_items + a.nb_wave + a.nb_win;
     } else {
         // rows per wavefront: 4 (up to one per lane group, 16 at most, when the groups are narrow) once that leaves a
         // workgroup for every compute unit
