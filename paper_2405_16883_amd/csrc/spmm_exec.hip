@@ -210,10 +210,12 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
     // displace them (workload 4: another 2.7 % less time)
     constexpr bool NTA = HOT;
 
-    __shared__ int s_raw[kWavesPerBlock * smem_ints_per_wave()];
+    constexpr bool kOneLane = G == 1 && T == 1 && !HOT;
+    __shared__ int s_raw[kOneLane ? 1 : kWavesPerBlock * smem_ints_per_wave()];
     __shared__ float s_red[kWavesPerBlock * TW];
     // one-lane groups (n <= 4) only: the products of a window's entries, summed per row afterwards
-    __shared__ __attribute__((aligned(16))) float s_prod[G == 1 ? kWavesPerBlock * kStageMax * V : 1];
+    constexpr int kProducts = V <= 2 ? kBNMax + kWholeMax : kStageMax;
+    __shared__ __attribute__((aligned(16))) float s_prod[G == 1 ? kWavesPerBlock * kProducts * V : 1];
     __shared__ int s_flag;  // piece of a split row: this workgroup drew the row's last ticket
 
     const int tid = threadIdx.x;
@@ -261,7 +263,7 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
     }
     const ColdPath *cp = COLD != 0 ? &cold : nullptr;
 
-    int *lcol = s_raw + wv * smem_ints_per_wave();
+    int *lcol = kOneLane ? s_raw : s_raw + wv * smem_ints_per_wave();
     float *lval = reinterpret_cast<float *>(lcol + kStageMax);
     int *lrp = lcol + 2 * kStageMax;
 
@@ -437,11 +439,58 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
     if (w >= a.n_windows) return;
     const int r0 = a.win_row_start[w];
     const int r1 = a.win_row_start[w + 1];
+    const int nr = min(r1 - r0, kWindowRowsMax);
+    if constexpr (G == 1 && V <= 2) if (a.whole_rows) {
+        // One or two columns: a row of up to kWholeMax entries is walked here whatever its class, so that no entry between two short
+        // rows is gathered in vain and medium rows need no wavefronts of their own.  A longer row can only be the last of its window
+        // (rows start within kBNMax entries of each other).  A lane adds up a row of up to kLaneRow entries, the wavefront the others.
+        if (nr <= 0) return;
+        const int rp = a.rowptr[r0 + min(lane, nr)];
+        const int next = __shfl_down(rp, 1, kWave), end = a.rowptr[r0 + nr];
+        const int len = (lane == kWave - 1 ? end : next) - rp;
+        const int first = __builtin_amdgcn_readlane(rp, 0);
+        const int last = __builtin_amdgcn_readlane(rp, nr - 1);
+        const int count = (end - last <= kWholeMax ? end : last) - first;
+        vec *prod = reinterpret_cast<vec *>(s_prod) + wv * kProducts;
+        constexpr int kSteps = kProducts / kWave;
+        vec x[kSteps];
+        float v[kSteps];
+        int c[kSteps];
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) {
+            const int e = lane + i * kWave;
+            c[i] = e < count ? a.colidx[first + e] : 0;
+            v[i] = e < count ? a.vals[first + e] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) x[i] = lane + i * kWave < count ? vload<V, UA>(b_row(Bc, c[i], ldb) + boff[0]) : vzero<V>();
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) {
+            vec pr = vzero<V>();
+            vfma<V>(pr, v[i], x[i]);
+            if (lane + i * kWave < count) prod[lane + i * kWave] = pr;
+        }
+        wave_lds_sync();
+        const float *bias = a.bias ? a.bias + coff[0] : nullptr;
+        if (lane < nr && len <= kLaneRow) {
+            vec sum = vzero<V>();
+            for (const vec *q = prod + (rp - first), *e = q + len; q < e; ++q) vadd<V>(sum, *q);
+            vstore<V, NTC, UA>(a.C + (int64_t)(r0 + lane) * a.ldc + coff[0], apply_epilogue<V>(sum, bias, a.act));
+        }
+        for (unsigned long long todo = __ballot(lane < nr && len > kLaneRow && len <= kWholeMax); todo != 0ull; todo &= todo - 1ull) {
+            const int i = __builtin_ctzll(todo);
+            const int q0 = __builtin_amdgcn_readlane(rp, i) - first, n = __builtin_amdgcn_readlane(len, i);
+            vec sum[1] = {vzero<V>()};
+            for (int e = lane; e < n; e += kWave) vadd<V>(sum[0], prod[q0 + e]);
+            reduce_groups<V, G, 1>(sum);
+            if (lane == 0) vstore<V, NTC, UA>(a.C + (int64_t)(r0 + i) * a.ldc + coff[0], apply_epilogue<V>(sum[0], bias, a.act));
+        }
+        return;
+    }
     // which entries the window stages is known from the plan, so colidx/vals are requested together with the row
     // pointers instead of after them
     const int2 stg = a.win_stage[w];
     if (stg.y < 0) return;  // no short row in this window
-    const int nr = min(r1 - r0, kWindowRowsMax);
     const int sbeg = stg.x, cnt = stg.y;
     const int rpv = a.rowptr[r0 + min(lane, nr)];
     const int rlast = a.rowptr[r0 + nr];
@@ -453,7 +502,7 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
         // lanes, so the lanes split the window's *entries* instead of its rows: every lane reads its entries
         // (coalesced), gathers the V values of B they point at, and parks the products in LDS; then the lane of
         // each short row adds up that row's products in stored order.
-        vec *prod = reinterpret_cast<vec *>(s_prod) + wv * kStageMax;
+        vec *prod = reinterpret_cast<vec *>(s_prod) + wv * kProducts;
         constexpr int kSteps = (kStageMax + kWave - 1) / kWave;
         vec x[kSteps];
         float v[kSteps];
@@ -998,6 +1047,15 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
     a.nb_items = plan->n_items;
     a.nb_wave = (int32_t)ceil_div64(plan->n_wave, kWavesPerBlock);
     a.nb_win = plan->n_short > 0 ? (int32_t)ceil_div64(plan->layout.n_windows, kWavesPerBlock) : 0;
+    // One or two columns, mean row of up to 32 entries: medium rows stay with their windows.  Bound by L2 requests, one per entry, and the
+    // chain of reads of every wavefront: fewer of both.  us before / after, n = 1: 169 343 rows, 2.5 M entries 19.2 / 16.7; 600 000 rows of 8
+    // 35.2 / 29.2, of 25 115 / 97; 1.5 M rows of 4 56 / 47; 20 000 of 5 5.2 / 5.1.  Rows of 164 (all medium) 11.2 / 15.8, 600 000 of 40 even,
+    // hence the mean.
+    a.whole_rows = mp.G == 1 && mp.V <= 2 && plan->params.CH <= kWholeMax && plan->nnz <= kLaneRow * (int64_t)plan->m;
+    if (a.whole_rows) {
+        a.nb_wave = 0;
+        a.nb_win = (int32_t)ceil_div64(plan->layout.n_windows, kWavesPerBlock);
+    }
     a.partial_stride = plan->layout.partial_stride;
     a.LW = plan->params.LW;
     a.ncoltiles = mp.ncoltiles;

@@ -19,6 +19,8 @@ constexpr int kBlock = kWave * kWavesPerBlock;
 constexpr int kBNMax = 256;
 constexpr int kLWMax = 64;
 constexpr int kStageMax = kBNMax + kLWMax;
+constexpr int kWholeMax = 256;  // one or two columns: rows that a window's wavefront walks whole
+constexpr int kLaneRow = 32;
 constexpr int kWindowRowsMax = 64;  // one lane per row when reading rowptr
 constexpr int kPanelCols = 256; // panel kernel: one wavefront covers 256 columns (64 lanes x float4)
 constexpr int kResidentFloats = 158 * 256;  // resident kernel: floats of B a workgroup keeps; with a row of zeros 160 KB of LDS
@@ -102,6 +104,7 @@ struct ExecArgs {
     const float *bias;      // epilogue: n floats added to every row of C, or nullptr
     int32_t act;            // epilogue: 0 identity, 1 ReLU
     const uint32_t *hotmask;  // one bit per column of A, set for the most referenced rows of B (hot/cold variants only)
+    bool whole_rows;          // one-lane groups: windows hold all rows of up to kWholeMax entries
     int32_t rows_per_wave;    // plan-free kernel only: consecutive rows taken by one wavefront (a power of two)
     int32_t scout_shift;      // plan-free kernel only: see scouts.h (nb_items: the scouts)
     float one_over_m;

@@ -1,0 +1,46 @@
+"""One and two columns: rows of every length a window's wavefront may meet, and means on either side of the rule."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2405_16883_amd as sp
+from workloads import csr_from_row_lengths, integer_valued, with_padding
+
+from gpu_util import DeviceProblem, check_against_oracle, tuning
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4])
+@pytest.mark.parametrize("spec", [None, "bn=16", "bn=256", "bn=256,alpha=1", "ch=512"])
+@pytest.mark.parametrize("many", [0, 7, 40])  # of the longer lengths: none, among short rows, most rows (mean above 32)
+def test_rows_of_every_length(n, spec, many):
+    rng = np.random.default_rng(many)
+    m = 700
+    lens = rng.integers(0, 12, size=m)
+    edges = [31, 32, 33, 63, 64, 65, 128, 255, 256, 257, 300, 700]
+    at = rng.permutation(m)[:many * len(edges)]
+    lens[at] = np.resize(edges, at.size)
+    lens[[0, m - 1]] = [256, 257] if many else [32, 31]
+    p = csr_from_row_lengths(lens, 900, n, seed=many, duplicates=True)
+    with tuning(spec):
+        for q, exact, pad in ((p, False, 0), (with_padding(p, n + 3), False, 1), (integer_valued(p, seed=n), True, 0)):
+            d = DeviceProblem(q, ldc=n + pad)
+            plan = d.make_plan()
+            plain = d.run_planned(plan)
+            check_against_oracle(q, plain, d.ldc, exact=exact, label=f"n={n} {spec} {many}")
+            bias = torch.arange(1, n + 1, dtype=torch.float32, device=d.dev) - 2
+            sp.scorch_spmm_csr_planned_epilogue(plan, d.rowptr, d.colidx, d.vals, d._B_arg(), bias, sp.ACT_RELU, d._C_arg())
+            torch.cuda.synchronize()
+            if exact:
+                assert np.array_equal(d.Cfull.cpu().numpy()[:, :n], np.maximum(plain[:, :n] + bias.cpu().numpy(), 0))
+            plan.destroy()
+
+
+@pytest.mark.parametrize("lens", [[0] * 130, [1] * 64 + [0] * 64 + [256], [257], [256], [0, 300, 0], [255, 256, 255, 256] + [0] * 60])
+def test_few_rows(lens):
+    p = integer_valued(csr_from_row_lengths(lens, 400, 1, seed=1), seed=2)
+    d = DeviceProblem(p)
+    plan = d.make_plan()
+    check_against_oracle(p, d.run_planned(plan), d.ldc, exact=True, label=str(lens[:4]))
+    plan.destroy()
