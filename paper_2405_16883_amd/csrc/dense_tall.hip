@@ -7,11 +7,14 @@
 // parts of up to 128 columns.  X goes straight from memory into the operand registers, a step of 16 columns ahead, once
 // per part.  The product is formed as Y^T = W^T X^T: the first operand of the instruction is W^T, so that a lane ends with four
 // consecutive columns of one row of Y and stores them as one vector.  Bias and activation are applied on the way out:
-// left to passes of their own they read and write Y once more.  Measured against torch.addmm + relu_, us: 169 343 rows, 64 -> 128
-// 88 / 42, 100 -> 128 98 / 60, 128 -> 256 167 / 108; 1 M rows, 64 -> 128 412 / 212 (3.7 TB/s), 16 -> 200 607 / 282; 20 000 rows,
-// 128 -> 256 29 / 25; 2000 rows 22 / 4 to 12.  Scalar loads of X instead of vectors: 5-35 % more.
-// Lane l of a wavefront holds, of 16 columns of X, the four from 4 (l / 16) onwards, i.e. instruction s of 4 adds up columns
-// s, 4 + s, 8 + s, 12 + s of the 16: any assignment will do as long as both operands follow it, and this one reads vectors.
+// left to passes of their own they read and write Y once more.  The first rows of X are requested before W is staged, four rounds of
+// W at a time: 169 343 rows, 128 -> 128 72.5 -> 63.6 us, 128 -> 64 46 -> 38, 64 -> 128 47 -> 42.  What is left there: one or two units per
+// wavefront, so that start, product and store hardly overlap (1 M rows: 104 TFLOP/s, the dense library 94).  Column parts of 64
+// instead of 128 (1 M rows 315 -> 330 us) and three or four workgroups per CU are no faster.  Scalar loads of X instead of vectors: 5-35 % more.
+// Lane l of a wavefront reads, of 16 columns of X, the four from 4 (l / 16) onwards, one vector; two exchanges between the
+// 16-lane rows of the wavefront (order_x) then give it columns 2 (l / 16) and the next, of each half of the 16, so that every
+// instruction adds up the even or the odd columns of 8 in ascending order.  That is the order in which the dense library adds up
+// (each instruction is a chain of fused multiply-adds): the same bits wherever it takes its usual kernel, so that a layer may take either.
 #include "device_util.h"
 #include "spmm_internal.h"
 
@@ -48,6 +51,25 @@ __device__ __forceinline__ f4 dense_load_x(const float *row, int c, int k) {
     return x;
 }
 
+// From columns 4 q ... 4 q + 3 of 16 in the lanes of row q to columns 2 q, 2 q + 1, 8 + 2 q, 9 + 2 q.
+__device__ __forceinline__ f4 order_x(f4 x) {
+    auto exchange = [](float a, float b, float &lo, float &hi) {
+        const auto odd = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        const auto half = __builtin_amdgcn_permlane32_swap(odd[0], odd[1], false, false);
+        lo = __uint_as_float(half[0]);
+        hi = __uint_as_float(half[1]);
+    };
+    f4 y;
+    float lo, hi;
+    exchange(x[0], x[2], lo, hi);
+    y[0] = lo;
+    y[2] = hi;
+    exchange(x[1], x[3], lo, hi);
+    y[1] = lo;
+    y[3] = hi;
+    return y;
+}
+
 // NT: 16-column tiles of Y per workgroup.  RT: 16-row tiles per wavefront.
 template <int NT, int RT>
 __global__ __launch_bounds__(kDenseThreads, 4) void dense_tall_kernel(const DenseArgs a) {
@@ -62,21 +84,6 @@ __global__ __launch_bounds__(kDenseThreads, 4) void dense_tall_kernel(const Dens
     const int first = (int)(blockIdx.x / kXcds) / a.parts * kXcds + (int)(blockIdx.x % kXcds);
     const int nblk = (int)gridDim.x / a.parts;
     const int n0 = part * (16 * NT);
-    // four rows of W at one column per thread; neighbouring threads read neighbouring columns
-    for (int i = tid; i < 16 * NT * steps * 4; i += kDenseThreads) {
-        const int c = i % (16 * NT), quad = i / (16 * NT);
-        const int k0 = quad * 4;
-        f4 w = {0.f, 0.f, 0.f, 0.f};
-        if (n0 + c < a.n)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (k0 + j < a.k) w[j] = a.W[(int64_t)(k0 + j) * a.ldw + n0 + c];
-        *reinterpret_cast<f4 *>(s_w + c * stride + quad * 4) = w;
-    }
-    float *s_bias = s_w + 16 * NT * stride;
-    if (tid < 16 * NT) s_bias[tid] = a.bias && n0 + tid < a.n ? a.bias[n0 + tid] : 0.f;
-    __syncthreads();
-
     const int q = lane >> 4, r = lane & 15;
     const float *wbase = s_w + r * stride + q * 4;
     const float *xrow[RT];
@@ -95,9 +102,27 @@ __global__ __launch_bounds__(kDenseThreads, 4) void dense_tall_kernel(const Dens
     };
     // units are dealt wavefront by wavefront over the workgroups, so that a last incomplete round is spread over the chip
     const int u0 = wv * nblk + first, du = kDenseWaves * nblk;
-    if (u0 >= a.units) return;
     rows_of(u0);
-    fetch(0);
+    fetch(0);  // on its way while W is staged
+    // four rows of W at one column per thread; neighbouring threads read neighbouring columns
+#pragma unroll 4
+    for (int i = tid; i < 16 * NT * steps * 4; i += kDenseThreads) {
+        const int c = i % (16 * NT), quad = i / (16 * NT);
+        const int k0 = quad / 4 * 16 + quad % 4 * 2;  // rows k0, k0 + 1, k0 + 8, k0 + 9: see order_x
+        f4 w = {0.f, 0.f, 0.f, 0.f};
+        if (n0 + c < a.n)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int kj = k0 + j % 2 + j / 2 * 8;
+                if (kj < a.k) w[j] = a.W[(int64_t)kj * a.ldw + n0 + c];
+            }
+        *reinterpret_cast<f4 *>(s_w + c * stride + quad * 4) = w;
+    }
+    float *s_bias = s_w + 16 * NT * stride;
+    if (tid < 16 * NT) s_bias[tid] = a.bias && n0 + tid < a.n ? a.bias[n0 + tid] : 0.f;
+    __syncthreads();
+
+    if (u0 >= a.units) return;
     for (int64_t u = u0; u < a.units; u += du) {
 #pragma unroll
         for (int c = 0; c < NT; ++c)
@@ -105,7 +130,7 @@ __global__ __launch_bounds__(kDenseThreads, 4) void dense_tall_kernel(const Dens
             for (int t = 0; t < RT; ++t) acc[c][t] = f4{0.f, 0.f, 0.f, 0.f};
         for (int s = 0; s < steps; ++s) {
 #pragma unroll
-            for (int t = 0; t < RT; ++t) x[t] = xn[t];
+            for (int t = 0; t < RT; ++t) x[t] = order_x(xn[t]);
             // the next 16 columns, of the next unit at the end of this one
             if (s + 1 < steps) {
                 fetch(s + 1);
@@ -183,8 +208,12 @@ scorch_status_t launch_dense_tall(int32_t m, int32_t k, int32_t n, const float *
     const int32_t all_tiles = (int32_t)(((int64_t)n + 15) / 16);
     a.parts = (all_tiles + kDenseTilesMax - 1) / kDenseTilesMax;
     const int32_t tiles = (all_tiles + a.parts - 1) / a.parts;
-    // two 16-row tiles per wavefront (each fragment of W out of LDS feeds both) unless that leaves SIMDs without work
-    const int rt = ((int64_t)m + 31) / 32 * a.parts >= 4 * kCus ? 2 : 1;
+    // Two 16-row tiles per wavefront (each fragment of W out of LDS feeds both) unless one gives fewer rounds of the resident
+    // wavefronts, with 4 % for the second reading of W: 169 343 x 128 -> 128, 1.3 rounds of two or 2.6 of one: 71.1 / 68.9 us, 1 M rows
+    // 337 / 342.
+    const int64_t waves = (int64_t)2 * kCus / a.parts * kDenseWaves;
+    auto rounds = [&](int t) { return (((int64_t)m + 16 * t - 1) / (16 * t) + waves - 1) / std::max<int64_t>(1, waves) * t; };
+    const int rt = 100 * rounds(2) <= 104 * rounds(1) ? 2 : 1;
     a.units = (int32_t)(((int64_t)m + 16 * rt - 1) / (16 * rt));
     const uint32_t lds = (uint32_t)(16 * tiles * (((k + 15) / 16) * 16 + 4 + 1) * 4);  // one more per column: the bias
     // as many workgroups as are resident at once, in whole rounds of 8 per part

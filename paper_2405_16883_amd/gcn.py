@@ -1,9 +1,9 @@
 """One graph-convolution layer  H' = act(A_hat H W + b)  on top of the C ABI (paper, Section 5.1).
 
-The neighbourhood aggregation runs in scorch_spmm_csr_planned_epilogue.  The dense product is left to the dense library
-(torch.mm), as the paper leaves dense work to PyTorch, except where it comes last and an activation follows: then product,
-bias and activation are one call of scorch_dense_layer, where that applies (see _native_product).  The order of the two products is chosen by width: the aggregation costs 2*nnz*n flops and gathers n floats per stored entry, so it is done
-at the narrower of the two feature widths:
+The neighbourhood aggregation runs in scorch_spmm_csr_planned_epilogue.  The dense product is one call of scorch_dense_layer
+where that applies (see _native_product) and is the faster one, otherwise the dense library's (torch.mm), to which the paper
+leaves dense work.  The order of the two products is chosen by width: the aggregation costs 2*nnz*n flops and gathers n floats per
+stored entry, so it is done at the narrower of the two feature widths:
 
     n_out <= n_in :  H' = act(A_hat (H W) + b)      dense product first, epilogue fused into the aggregation
     n_out >  n_in :  H' = act((A_hat H) W + b)      aggregation first, epilogue fused into the dense product
@@ -39,6 +39,15 @@ def _native_product(X: torch.Tensor, W: torch.Tensor, bias: Optional[torch.Tenso
     if bias is not None and (bias.device != X.device or bias.dim() != 1 or bias.shape[0] != n or bias.stride(0) != 1):
         return False
     return _unwatched()
+
+
+def _native_first(m: int, k: int, n: int) -> bool:
+    """Whether the dense product alone, m x k times k x n, is better made by scorch_dense_layer.  With k in multiples of 16 it adds up
+    in the dense library's usual order (the same bits as torch.mm on nearly all shapes tried), and over 13 widths, 3000 to 2.4 M rows,
+    it takes 0.2 to 1.0 of the time, us own / library: 64 -> 64 20 000 rows 7 / 18, 169 343 22 / 48, 1 M 122 / 167; 128 -> 128 16 / 23, 60 / 78,
+    312 / 341.  Not so where the library's tiles of a wide product come out in whole rounds over the chip: 128 -> 128 60 000 rows 26 / 24,
+    80 000 35 / 33, 131 072 48 / 46; 144 -> 128 60 000 28 / 25."""
+    return k % 16 == 0 and not (k * n >= 128 * 128 and 50000 <= m < 150000)
 
 
 def _unwatched() -> bool:
@@ -79,7 +88,11 @@ class GcnLayer:
                 return self.forward(H, W, bias, relu)
         act = _b.ACT_RELU if relu else _b.ACT_IDENTITY
         if not self.aggregates_first(n_in, n_out):
-            Z = torch.mm(H, W)
+            if _native_first(self.m, n_in, n_out) and _native_product(H, W, None):
+                Z = torch.empty((self.m, n_out), dtype=torch.float32, device=H.device)
+                _b.scorch_dense_layer(H, W, None, _b.ACT_IDENTITY, Z)
+            else:
+                Z = torch.mm(H, W)
             out = torch.empty((self.m, n_out), dtype=torch.float32, device=H.device)
             _b.scorch_spmm_csr_planned_epilogue(self._plan(n_out), self.rowptr, self.colidx, self.vals, Z, bias, act, out)
             return out

@@ -39,3 +39,18 @@ def test_dense_layer_keeps_nan_and_refuses_wide_x():
     k = sp.DENSE_LAYER_K_MAX + 1
     with pytest.raises(sp.ScorchError):
         sp.scorch_dense_layer(torch.zeros((4, k), device=DEV), torch.zeros((k, 5), device=DEV), None, sp.ACT_RELU, Y)
+
+
+@pytest.mark.parametrize("k", [1, 8, 9, 16, 24, 33, 64])
+def test_dense_layer_adds_up_the_even_then_the_odd_columns_of_eight(k):
+    """The order of the sums, which the dense library shares: each a fused multiply-add, here in float64 rounded to float32."""
+    m, n = 100, 20
+    g = torch.Generator(device=DEV).manual_seed(k)
+    X, W = torch.randn((m, k), generator=g, device=DEV), torch.randn((k, n), generator=g, device=DEV)
+    Y = torch.empty((m, n), device=DEV)
+    sp.scorch_dense_layer(X, W, None, sp.ACT_IDENTITY, Y)
+    acc = torch.zeros((m, n), device=DEV)
+    for c in [b + 2 * q + s for b in range(0, k, 8) for s in range(2) for q in range(4) if b + 2 * q + s < k]:
+        acc = (acc.double() + X[:, c:c + 1].double() * W[c:c + 1].double()).float()
+    # rounded twice (the sum to 53 bits first) only where 29 bits below the last one read 10...0: one sum in 2^28
+    assert torch.equal(acc, Y)
