@@ -664,7 +664,7 @@ __device__ __forceinline__ int next_long(const unsigned long long *bits, int fro
     return kBlock;
 }
 
-template <int V, int G, int T, int U, int NT, bool UA>
+template <int V, int G, int T, int U, int NT, bool UA, int SU>
 __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) {
     using vec = typename Vec<V>::type;
     constexpr int S = kWave / G;
@@ -768,7 +768,7 @@ __global__ __launch_bounds__(kBlock) void spmm_natural_kernel(const ExecArgs a) 
             const int p0 = span.x, p1 = span.y;
 #pragma unroll
             for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
-            row_accumulate<V, G, T, 2 * U, false, UA>(acc, lcol, lval, lane, grp, p0 + wv * kWave, p1, kBlock, a.colidx,
+            row_accumulate<V, G, T, SU, false, UA>(acc, lcol, lval, lane, grp, p0 + wv * kWave, p1, kBlock, a.colidx,
                                                       a.vals, a.B, ldb, colok[0], coff);
             reduce_groups<V, G, T>(acc);
             __syncthreads();  // s_red of the previous row has been read
@@ -962,7 +962,7 @@ static kernel_fn pick_fused_cut(int G, int T, bool UA, bool hot) {
 #undef SCORCH_CUT
 }
 // The plan-free path is compiled for one unroll depth (8) and streaming stores only.
-#define SCORCH_NATURAL(V, G, T, UA) return spmm_natural_kernel<V, G, T, 8, 1, UA>;
+#define SCORCH_NATURAL(V, G, T, UA) return spmm_natural_kernel<V, G, T, 8, 1, UA, G == 8 ? 8 : 16>;
 #define SCORCH_NATURAL_G4(UA)                                               \
     if (T == 2) { SCORCH_NATURAL(4, 64, 2, UA) }                            \
     switch (G) {                                                            \
@@ -1197,7 +1197,11 @@ scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *r
         set_error("launch grid of %lld workgroups exceeds the HIP limit", (long long)grid);
         return SCORCH_ERR_UNSUPPORTED;
     }
-    kernel_fn fn = pick_natural(mp.V, mp.G, mp.T, mp.UA);
+    // Gathers in flight per group of a scout: 16, which takes 84 to 124 VGPRs, or 8, which leaves room for one or two more wavefronts
+    // per SIMD.  us with 16 / 8: groups of 8 lanes, 169 343 rows, n = 32 49.4 / 40.4; 64-column slices, 30 000 rows, n = 128 31.0 / 28.5,
+    // 169 343 128.6 / 123.6; but n = 192 190.9 / 193.2, 300 000 rows of 30, n = 128 510 / 517; whole rows, 30 000 rows, n = 64 23.2 / 25.9.
+    kernel_fn fn = mp.G == 16 && slice_cols == 64 && (int64_t)m * mp.ncoltiles < 400000 ? spmm_natural_kernel<4, 16, 1, 8, 1, false, 8>
+                                                                                       : pick_natural(mp.V, mp.G, mp.T, mp.UA);
     hipLaunchKernelGGL(fn, dim3((uint32_t)grid), dim3(kBlock), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "launch spmm_natural_kernel");

@@ -59,3 +59,13 @@ def test_long_rows_on_either_side_of_four_times_the_mean(every):
     p = integer_valued(csr_from_row_lengths(lens, 1500, 64, seed=every, duplicates=True), seed=1)
     d = DeviceProblem(p)
     check_against_oracle(p, d.run_natural(), d.ldc, exact=True, label=f"every {every}")
+
+
+@pytest.mark.parametrize("m,n", [(9000, 128), (5000, 192), (199999, 128), (200001, 128), (6000, 32)])
+def test_long_rows_with_column_slices_on_either_side_of_the_scouts_rule(m, n):
+    lens = np.random.default_rng(m).integers(0, 4, size=m)
+    lens[::max(64, m // 100)] = 700
+    lens[5] = 5000
+    p = integer_valued(csr_from_row_lengths(lens, 17000, n, seed=m, duplicates=True), seed=n)
+    d = DeviceProblem(p)
+    check_against_oracle(p, d.run_natural(), d.ldc, exact=True, label=f"m={m} n={n}")
