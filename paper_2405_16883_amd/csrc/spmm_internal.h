@@ -45,6 +45,7 @@ struct PlanParams {
     int32_t PANEL;  // dense-ish sorted rows: stream B through LDS in k-panels (spmm_panel.hip); 1: 256-column tiles, 2: 512
     int32_t PDIRECT; // panel kernel: 1 = fetch the panels from the caller's row-major B instead of a tile-major copy
     int32_t RES;    // >0: narrow B kept in LDS in chunks (spmm_resident.hip), rows padded to this many columns
+    int32_t RESC;   // resident kernel: chunks of B
     int32_t CUT;    // 1: long rows are cut by columns, a range of columns per XCD (spmm_cut.hip)
     int32_t CUTJ;   // finest class for the sake of reuse (see cut_class)
     int32_t HOT;    // >0: budget in KB for the most referenced rows of B, which alone keep the default cache policy
@@ -141,13 +142,13 @@ struct ResidentArgs {
     int32_t m, k, n;
     float *partials;     // [nchunks][m][RES], unused with one chunk
     int64_t ptr_stride;  // rows of the whole matrix; m is those of this launch
-    int32_t nchunks;
+    int32_t nchunks, chunk_rows;
     int32_t rows_per_block;
     const float *bias;
     int32_t act;
 };
 
-// Chunks of the resident kernel for rows padded to W columns.
+// The fewest chunks of the resident kernel for rows padded to W columns.
 __host__ __device__ inline int32_t resident_chunks(int32_t k, int32_t W) {
     const uint32_t rows = (uint32_t)(kResidentFloats / W);
     return (int32_t)(((uint32_t)k + rows - 1) / rows);

@@ -543,6 +543,29 @@ __host__ __device__ static int32_t want_resident(int32_t m, int32_t k, int64_t n
     return resident * 10 < nnz * per_entry * 9 ? W : 0;
 }
 
+// Chunks of the resident kernel: no fewer than B needs, and as many as make the longest wavefront's work shortest.  Every chunk has as many
+// blocks of rows as let all workgroups run at once, and a wavefront of a block takes whole rows, so a few rows more than a multiple
+// of 16 cost as much as 16.  In ns, as fitted for want_resident: 8 per entry of a row's chunk and 400 per row and chunk of a wavefront; 2.7 per
+// 1000 floats of partial rows.  4096 x 16 384 with 10 % stored, n = 16: seven chunks, the last half full, 8 rows of 253 entries per wavefront;
+// eight even ones, 8 rows of 205.
+__host__ __device__ static int32_t resident_balance(int32_t m, int32_t k, int64_t nnz, int32_t W) {
+    const int32_t fewest = resident_chunks(k, W);
+    if (fewest == 1) return 1;  // no partial rows, no second launch
+    int32_t best = fewest;
+    int64_t best_cost = INT64_MAX;
+    for (int32_t c = fewest; c <= fewest + 8; ++c) {
+        const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(kCus / c, ((int64_t)m + 15) / 16));
+        const int64_t rows = (((int64_t)m + blocks - 1) / blocks + 15) / 16;
+        const int64_t rounds = (blocks * c + kCus - 1) / kCus;
+        const int64_t cost = rounds * rows * (8 * (nnz / ((int64_t)m * c)) + 400) + (int64_t)m * c * W / 1000 * 27 / 10;
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = c;
+        }
+    }
+    return best;
+}
+
 constexpr int64_t kCutNnzMin = 1 << 20;
 
 // Cutting long rows by columns (spmm_cut.hip) pays where B is much larger than the 8 L2s (32 MB) together and rows are skewed.  Measured
@@ -642,6 +665,7 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     p.BCH = std::max(p.BCH, 64);
     p.U = p.U >= 8 ? 8 : 4;
     p.NT &= 1;
+    p.RESC = p.RES ? resident_balance(m, k, nnz, p.RES) : 0;
     // scorch_spmm_csr_static takes what the gather kernels need no more than its scratch for, and gives the planned call's
     // bits: where the resident kernel does not run in the scratch either, it runs nowhere.
     if (p.RES) {
@@ -706,7 +730,7 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
     if (p.PACK || (p.PANEL && !p.PDIRECT)) off = align_up(off + (uint64_t)k * ((n + 2 * kPanelCols - 1) / (2 * kPanelCols)) * (2 * kPanelCols) * 4, 256);
     L.off_res_ptr = off;
     if (p.RES) {
-        const int64_t chunks = resident_chunks(k, p.RES);
+        const int64_t chunks = p.RESC;
         off = align_up(off + (uint64_t)(chunks + 1) * m * 4, 256);
         if (chunks > 1) L.res_row_bytes = (uint64_t)chunks * p.RES * 4;
     }

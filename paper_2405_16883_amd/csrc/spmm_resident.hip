@@ -136,13 +136,13 @@ struct ResidentWindows {
 // single floats.  Lanes past row k or column n load nothing, and what they leave only feeds columns that are never
 // stored.
 template <int W, bool A16>
-__device__ __forceinline__ void resident_fetch(const ResidentArgs &a, int k0, float *s_b, int wv, int lane) {
+__device__ __forceinline__ void resident_fetch(const ResidentArgs &a, int k0, int k1, float *s_b, int wv, int lane) {
     constexpr int E = A16 ? 4 : 1;
     constexpr int kPieces = kResidentFloats / (kWave * E);
     for (int i = wv; i < kPieces; i += kResidentWaves) {
         const int f = (i * kWave + lane) * E;
         const int row = f / W, col = f % W;
-        if (k0 + row < a.k && col < a.n) {
+        if (k0 + row < k1 && col < a.n) {
             const float *src = a.B + (int64_t)(k0 + row) * a.ldb + col;
             if constexpr (A16) __builtin_amdgcn_global_load_lds(src, s_b + i * kWave * E, 16, 0, 0);
             else __builtin_amdgcn_global_load_lds(src, s_b + i * kWave * E, 4, 0, 0);
@@ -154,7 +154,6 @@ template <int G, int T, bool A16>
 __global__ __launch_bounds__(kResidentThreads) void spmm_resident_kernel(const ResidentArgs a) {
     constexpr int W = 4 * G * T;
     constexpr int S = kWave / G;
-    constexpr int KR = kResidentFloats / W;
     __shared__ __attribute__((aligned(16))) float s_b[kResidentFloats + W];  // the chunk and a row of zeros
     const int tid = threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -162,14 +161,14 @@ __global__ __launch_bounds__(kResidentThreads) void spmm_resident_kernel(const R
     const int grp = lane / G, lig = lane % G;
     const int chunk = (int)(blockIdx.x % (uint32_t)a.nchunks);
     const int blk = (int)(blockIdx.x / (uint32_t)a.nchunks);
-    const int k0 = chunk * KR;
+    const int k0 = chunk * a.chunk_rows;
     const int row_end = (int)min((int64_t)a.m, ((int64_t)blk + 1) * a.rows_per_block);
     const int lane_entry = S * lig + grp;  // which entry of a window this lane holds
     const char *lds = reinterpret_cast<const char *>(s_b);
     const int zero_off = kResidentFloats * 4;
     const int lig16 = lig * 16;
 
-    resident_fetch<W, A16>(a, k0, s_b, wv, lane);
+    resident_fetch<W, A16>(a, k0, (int)min((int64_t)a.k, (int64_t)k0 + a.chunk_rows), s_b, wv, lane);
     if (tid < W) s_b[kResidentFloats + tid] = 0.f;
     // lanes past the row's entries of the chunk read the last of them once more (no further cache lines), unused
     const auto entry = [&](uint32_t at, uint32_t end) { return min(at + (uint32_t)lane_entry, max(end, 1u) - 1u); };
@@ -200,7 +199,7 @@ __global__ __launch_bounds__(kResidentThreads) void spmm_resident_kernel(const R
         for (int t = 0; t < T; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
         const auto steps = [&](uint32_t at) { return (int)((e - at + S - 1) / S); };
         const auto valid = [&](uint32_t at) { return at + (uint32_t)lane_entry < e; };
-        const auto inside = [&](int col) { return (uint32_t)(col - k0) < (uint32_t)KR; };
+        const auto inside = [&](int col) { return (uint32_t)(col - k0) < (uint32_t)a.chunk_rows; };
         const auto work = [&](int col, float value, uint32_t at) {
             const bool in = valid(at) && inside(col);
             const int off = in ? (col - k0) * (W * 4) : zero_off;
@@ -302,12 +301,17 @@ __global__ __launch_bounds__(kBlock) void plan_resident_kernel(const int32_t *ro
     }
 }
 
+static uint32_t resident_chunk_rows(const scorch_spmm_plan_t *plan) {
+    const uint32_t chunks = (uint32_t)plan->params.RESC;
+    return ((uint32_t)plan->k + chunks - 1) / chunks;
+}
+
 scorch_status_t launch_plan_resident(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int32_t *seen,
                                      int32_t *unsorted, hipStream_t stream) {
     const int W = plan->params.RES;
     const uint32_t g = (uint32_t)std::min<int64_t>(((int64_t)plan->m + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 16);
     hipLaunchKernelGGL(plan_resident_kernel, dim3(g), dim3(kBlock), 0, stream, rowptr, colidx, plan->m,
-                       (uint32_t)(kResidentFloats / W), resident_chunks(plan->k, W),
+                       resident_chunk_rows(plan), plan->params.RESC,
                        reinterpret_cast<int32_t *>(plan->workspace + plan->layout.off_res_ptr), seen, unsorted);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "launch plan_resident_kernel");
@@ -339,7 +343,8 @@ scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *c
     a.k = plan->k;
     a.n = plan->n;
     a.partials = reinterpret_cast<float *>(plan->workspace + plan->off_res_partials);
-    a.nchunks = resident_chunks(plan->k, W);
+    a.nchunks = plan->params.RESC;
+    a.chunk_rows = (int32_t)resident_chunk_rows(plan);
     a.bias = bias;
     a.act = act;
     const uintptr_t pb = reinterpret_cast<uintptr_t>(B);

@@ -146,3 +146,16 @@ def test_the_one_shot_call_gives_the_planned_bits_when_its_scratch_holds_the_par
         a, b = int(rowptr[r]), int(rowptr[r + 1])
         terms = vals[a:b].double()[:, None] * B[swapped[a:b].long()].double()
         assert bool(((planned[r] - terms.sum(0)).abs() <= 1e-5 * terms.abs().sum(0)).all())
+
+
+@pytest.mark.parametrize("m,k,n", [(512, 16384, 16), (250, 3000, 60), (4096, 5200, 32), (17, 10113, 4), (300, 2529, 16)])
+def test_resident_with_more_chunks_than_b_needs(m, k, n):
+    """Chunks are even, and may be more than the fewest so that the workgroups come out in whole rounds."""
+    p = csr_from_row_lengths([300] * m, k, n, seed=m)
+    with tuning("res=1"):
+        for q, exact in ((p, False), (integer_valued(p, seed=n), True)):
+            d = DeviceProblem(q)
+            plan = d.make_plan()
+            assert plan.info().mode == 3
+            check_against_oracle(q, d.run_planned(plan), d.ldc, exact=exact, label=f"m={m} k={k} n={n}")
+            plan.destroy()
