@@ -568,13 +568,15 @@ __host__ __device__ static int32_t resident_balance(int32_t m, int32_t k, int64_
 
 constexpr int64_t kCutNnzMin = 1 << 20;
 
-// Cutting long rows by columns (spmm_cut.hip) pays where B is much larger than the 8 L2s (32 MB) together and rows are skewed.  Measured
-// without / with, us: graph of 2.4 M nodes, degree 50, n = 100 7960 / 6600; 1 M, 50, n = 64 1703 / 1336; 100 000, 50, n = 100 253 / 212;
-// 300 000, 20, n = 33 169 / 148; 169 343, 15, n = 128 121 / 111 (operands that change from call to call: 125 / 125), n = 100 126 / 113,
-// n = 48 (32 MB) 62.5 / 60.9; n = 32 (21 MB) 39.8 / 46.2, n = 16 32.2 / 39.0.  With 32-column slices (SLICED = 32) 121 / 145.  Plans get
-// dearer by 0.1 ms (2.5 M entries) to 0.7 ms (122 M); below a million entries nobody waits for that.
-__host__ __device__ static bool want_cut(int32_t k, int32_t n, int32_t sliced) {
-    return n >= 32 && (sliced == 0 || sliced == 64) && (int64_t)k * n * 4 >= 32ll << 20;
+// Cutting long rows by columns (spmm_cut.hip) pays where B is as large as the 8 L2s (32 MB) together, a row of it is more than one
+// 128-byte line, and the gathers are more than the second launch's 4 us.  Measured without / with, us: graph of 2.4 M nodes, degree 50,
+// n = 100 7960 / 6600; 1 M, 50, n = 64 1703 / 1336; 100 000, 50, n = 100 253 / 212; 400 000, 12, n = 33 141 / 130; 169 343, 15, n = 128
+// 121 / 111 (operands that change from call to call: 125 / 125), n = 100 126 / 113, n = 48 (32 MB) 62.5 / 60.9.  Rows that are all long, where
+// neither slices (n not a multiple of 4) nor panels serve: 4096 x 16 384, 10 % stored, n = 1001 3012 / 1158; 10 000 x 40 000, 3 %,
+// n = 229 1681 / 550.  Not: n = 32, 169 343 (21 MB) 39.8 / 46.2, 2.4 M nodes of degree 3 212 / 225; 1.3 M entries, n = 64 41.1 / 43.7;
+// with 32-column slices (SLICED = 32) 121 / 145.  Plans get dearer by 0.1 ms (2.5 M entries) to 0.7 ms (122 M).
+__host__ __device__ static bool want_cut(int32_t k, int64_t nnz, int32_t n, int32_t sliced) {
+    return n > 32 && nnz * n >= 100000000 && (sliced == 0 || sliced == 64) && (int64_t)k * n * 4 >= 32ll << 20;
 }
 
 // Bytes that a plan cannot do without.
@@ -627,7 +629,7 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     p.CUT = p.CUTJ = 0;
     if ((nnz >= kCutNnzMin && t.cut != 0) || t.cut > 0) {  // the planning kernels evaluate this: one comparison for small matrices
         const bool possible = m > 0 && k > 0 && n > 16 && p.PANEL == 0 && p.RES == 0 && p.PACK == 0 && t.fix <= 0 && t.u <= 0 && t.nt < 0;
-        p.CUT = possible && (t.cut > 0 || want_cut(k, n, p.SLICED)) ? 1 : 0;
+        p.CUT = possible && (t.cut > 0 || want_cut(k, nnz, n, p.SLICED)) ? 1 : 0;
         // parts of the columns of an XCD, up to 16 MB of B each: 122 MB in 1 / 4 / 8 / 16 parts 7100 / 6690 / 6600 / 6720 us,
         // 32 MB in 1 / 2 / 4 / 8 1356 / 1336 / 1356 / 1391, 5 MB in 1 / 2 / 4 212 / 226 / 237
         const int64_t xcd_bytes = (int64_t)k * (p.SLICED ? p.SLICED : n) * 4 / kXcds;

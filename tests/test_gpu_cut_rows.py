@@ -84,6 +84,37 @@ def test_cut_rows_of_any_columns_and_the_one_shot_call(kind):
         plan.destroy()
 
 
+@pytest.mark.parametrize("n", [100, 101])
+def test_cut_rows_by_the_planners_own_choice_in_all_calls_and_graphs(n):
+    """A matrix large enough for it, skewed rows: planned, one-shot and replayed calls agree to the bit."""
+    rng = np.random.default_rng(n)
+    lens = np.minimum(3000, (4.0 / rng.random(90000) ** 0.7).astype(np.int64))
+    p = csr_from_row_lengths(lens, 90000, n, seed=n)
+    assert p.nnz >= 1 << 20
+    d = DeviceProblem(p)
+    plan = d.make_plan()
+    got = d.run_planned(plan)
+    check_against_oracle(p, got, d.ldc, rows=np.argsort(lens)[-300:], label="longest rows")
+    check_against_oracle(p, got, d.ldc, rows=rng.integers(0, p.m, size=500), label="any rows")
+    with tuning("cut=0"):
+        whole = d.make_plan()
+    assert not np.array_equal(d.run_planned(whole), got)
+    whole.destroy()
+    d.reset_C()
+    sp.scorch_spmm_csr_static(p.m, p.k, p.n, d.rowptr, d.colidx, d.vals, d._B_arg(), d._C_arg())
+    torch.cuda.synchronize()
+    assert np.array_equal(d.Cfull.cpu().numpy(), got)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sp.scorch_spmm_csr_planned(plan, d.rowptr, d.colidx, d.vals, d._B_arg(), d._C_arg())
+    for _ in range(3):
+        d.reset_C()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(d.Cfull.cpu().numpy(), got)
+    plan.destroy()
+
+
 @pytest.mark.parametrize("m", [1, 64, 400])
 def test_cut_where_no_or_every_row_is_long(m):
     for length in (0, 63, 64, 3000):
