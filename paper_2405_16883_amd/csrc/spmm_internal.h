@@ -150,7 +150,7 @@ struct ResidentArgs {
 
 // The fewest chunks of the resident kernel for rows padded to W columns.
 __host__ __device__ inline int32_t resident_chunks(int32_t k, int32_t W) {
-    const uint32_t rows = (uint32_t)(kResidentFloats / W);
+    const uint32_t rows = (uint32_t)kResidentFloats >> __builtin_ctz((unsigned)W);  // W: a power of two
     return (int32_t)(((uint32_t)k + rows - 1) / rows);
 }
 

@@ -519,9 +519,7 @@ __host__ __device__ static int32_t want_panel(int32_t m, int32_t k, int64_t nnz,
 
 // Columns a row of B is padded to in LDS by the resident kernel (spmm_resident.hip).
 __host__ __device__ static int32_t resident_width(int32_t n) {
-    int32_t W = 4;
-    while (W < n) W *= 2;
-    return W;
+    return n <= 4 ? 4 : 1 << (32 - __builtin_clz((unsigned)(n - 1)));
 }
 
 // The resident kernel against the gather kernels, for at most 64 columns: both times as fitted to sweeps over m = 1024 ...
@@ -534,6 +532,8 @@ __host__ __device__ static int32_t resident_width(int32_t n) {
 __host__ __device__ static int32_t want_resident(int32_t m, int32_t k, int64_t nnz, int32_t n) {
     if (m <= 0 || k <= 0 || n < 3 || n > 64) return 0;
     const int32_t W = resident_width(n);
+    // as below, without a division: the planning kernels evaluate this, and most matrices end here (both sides alike in float64)
+    if ((double)m * k * W > (double)nnz * kResidentFloats) return 0;
     const int64_t chunks = resident_chunks(k, W);
     if ((int64_t)m * chunks > nnz) return 0;  // never pays: a row of a chunk costs 2930, an entry saves 110 at most (and the rest fits 64 bits)
     const int64_t per_entry = n > 32 ? 110 : n % 4 != 0 ? 75 : n > 8 ? 57 : n > 4 ? 50 : 35;
