@@ -8,8 +8,8 @@
 
 namespace scorch {
 
-constexpr int kCutMinLen = 64;   // shorter rows are never cut
-constexpr int kCutBuckets = 17;  // row lengths from kCutMinLen on, two buckets per power of two; the last holds 16 384 and more
+constexpr int kCutMinLen = 128;  // shorter rows are never cut: a piece per XCD of less than 16 entries costs more than it gives
+constexpr int kCutBuckets = 15;  // row lengths from kCutMinLen on, two buckets per power of two; the last holds 16 384 and more
 constexpr int kCutClasses = 5;   // class j: 2^j pieces per XCD
 constexpr int kCutBounds = kXcds << (kCutClasses - 1);  // finest division of the columns
 constexpr int kCutBins = 2048;   // column histogram that the division is read off
@@ -17,16 +17,16 @@ constexpr int kCutBins = 2048;   // column histogram that the division is read o
 // Bucket of a row of `len` >= kCutMinLen entries, and the shortest row of a bucket.
 SCORCH_HOST_DEVICE inline int cut_bucket(int32_t len) {
     const int e = 31 - __builtin_clz((unsigned)len);
-    const int b = 2 * (e - 6) + ((len >> (e - 1)) & 1);
+    const int b = 2 * (e - 7) + ((len >> (e - 1)) & 1);
     return b < kCutBuckets ? b : kCutBuckets - 1;
 }
-SCORCH_HOST_DEVICE inline int32_t cut_bucket_len(int b) { return (2 + (b & 1)) << (5 + b / 2); }
+SCORCH_HOST_DEVICE inline int32_t cut_bucket_len(int b) { return (2 + (b & 1)) << (6 + b / 2); }
 
 // A row is cut into 2^class pieces per XCD: as many as leave 16 entries per piece in the mean, 2^finest at most, but enough
 // for pieces of 256 entries in the mean (a piece is one wavefront's chain).
 SCORCH_HOST_DEVICE inline int cut_class(int b, int finest) {
-    const int by_reuse = b / 2 - 1 < finest ? b / 2 - 1 : finest;
-    const int by_chain = b / 2 - 4;
+    const int by_reuse = b / 2 < finest ? b / 2 : finest;
+    const int by_chain = b / 2 - 3;
     const int j = by_reuse > by_chain ? by_reuse : by_chain;
     return j < 0 ? 0 : (j < kCutClasses ? j : kCutClasses - 1);
 }
@@ -68,6 +68,32 @@ SCORCH_HOST_DEVICE inline void cut_layout(const int32_t (&rows_in)[kCutBuckets],
         c.n_rows += c.rows[j];
         c.pieces += c.rows[j] << j;
     }
+}
+
+// The rows that take their turn in round `turn` where only `budget` pieces per XCD (at least 2^(kCutClasses - 1)) have room at a time: the
+// next ones of the list, as a layout of their own.  false: there is no such round.
+SCORCH_HOST_DEVICE inline bool cut_turn(const CutInfo &all, int32_t budget, int32_t turn, CutInfo &c) {
+    int j = kCutClasses - 1, i = 0;
+    for (int t = 0; t <= turn; ++t) {
+        c.n_rows = c.pieces = 0;
+        for (int x = 0; x < kCutClasses; ++x) c.rows[x] = c.row_off[x] = c.piece_off[x] = 0;
+        for (; j >= 0; --j, i = 0) {
+            const int32_t left = all.rows[j] - i, fit = (budget - c.pieces) >> j;
+            c.rows[j] = left < fit ? left : fit;
+            c.row_off[j] = all.row_off[j] + i;
+            c.piece_off[j] = c.pieces;
+            c.n_rows += c.rows[j];
+            c.pieces += c.rows[j] << j;
+            i += c.rows[j];
+            if (i < all.rows[j]) break;
+        }
+        if (c.n_rows == 0) return false;
+    }
+    c.len = all.len;
+    c.limit = all.limit;
+    c.longest = 0;
+    for (int b = 0; b < kCutBounds; ++b) c.bound[b] = all.bound[b];
+    return true;
 }
 
 }  // namespace scorch

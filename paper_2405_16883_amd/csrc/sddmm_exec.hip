@@ -560,7 +560,7 @@ scorch_status_t launch_sddmm(const scorch_spmm_plan_t *plan, int32_t m, int32_t 
         if (plan->cut_pieces > 0 && V == 4) {
             fn = pick_sddmm_cut(G, T, UA);
             a.cut = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_info);
-            a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->layout.off_cut_spans);
+            a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->off_cut_spans);
             a.cut_rows = reinterpret_cast<const int32_t *>(ws + plan->layout.off_cut_rows);
             a.cut_len = plan->cut_len;
             a.cut_grid = (uint32_t)((plan->cut_pieces + kWavesPerBlock * kCutRun - 1) / (kWavesPerBlock * kCutRun)) * kXcds;

@@ -27,13 +27,14 @@ struct CutPlanArgs {
     int32_t tiles_per_block;
     int32_t finest;  // see cut_class
     int32_t shift;   // columns per histogram bin (log2)
-    int64_t cap_pieces;
+    int64_t cap_layout, cap_pieces;  // pieces that are laid out at most; room for the ranges of so many
     int32_t *counts;  // [kCutBuckets][workgroups]
     int32_t *hist;
     CutInfo *info;
     int32_t *rows;
     int2 *spans;
     int32_t max_rows;
+    int32_t max_len;  // every row that the plan cuts into pieces of entries is to be cut by columns, or none is
 };
 
 // Rows per bucket and workgroup, and the histogram of the columns of the long rows (64 evenly spaced entries of each stand for all).
@@ -99,11 +100,11 @@ __global__ __launch_bounds__(kBlock) void cut_layout_kernel(const CutPlanArgs a,
         CutInfo c{};
         int rows[kCutBuckets];
         for (int b = 0; b < kCutBuckets; ++b) rows[b] = s_rows[b];
-        cut_layout(rows, a.finest, a.cap_pieces, c);
+        cut_layout(rows, a.finest, a.cap_layout, c);
         int64_t entries = 0;  // of the rows that are cut, about
         for (int b = 0; b < kCutBuckets; ++b)
             if (cut_bucket_len(b) >= c.len) entries += (int64_t)rows[b] * cut_bucket_len(b) * 5 / 4;
-        if (entries * 20 < a.nnz) c.len = INT32_MAX;
+        if (entries * 20 < a.nnz || c.len > a.max_len) c.len = INT32_MAX;
         if (c.len == INT32_MAX) c.n_rows = c.pieces = 0;
         a.info->len = c.len;
         a.info->pieces = c.pieces;
@@ -178,11 +179,11 @@ __global__ __launch_bounds__(kBlock) void cut_list_kernel(const CutPlanArgs a) {
     }
 }
 
-// Class of the r-th row of the list, and its place within the class.
+// Class of the r-th row of a layout, and its place among the layout's rows of the class.
 __device__ __forceinline__ int class_of_row(const CutInfo &c, int r, int &i) {
     int j = kCutClasses - 1;
-    while (j > 0 && r >= c.row_off[j] + c.rows[j]) --j;
-    i = r - c.row_off[j];
+    while (j > 0 && r >= c.rows[j]) r -= c.rows[j--];
+    i = r;
     return j;
 }
 
@@ -190,12 +191,12 @@ __device__ __forceinline__ int class_of_row(const CutInfo &c, int r, int &i) {
 __global__ __launch_bounds__(kBlock) void cut_span_kernel(const CutPlanArgs a) {
     const CutInfo &c = *a.info;
     const int lane = threadIdx.x & 63;
-    const int n_rows = min(c.n_rows, a.max_rows);
+    const int n_rows = c.n_rows;
     int longest = 0;
     for (int r = (int)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6); r < n_rows; r += (int)gridDim.x * kWavesPerBlock) {
         int i;
         const int j = class_of_row(c, r, i);
-        const int row = a.rows[r];
+        const int row = a.rows[c.row_off[j] + i];
         const int p0 = a.rowptr[row], p1 = a.rowptr[row + 1];
         const int parts = 1 << j;
         int before = p0;  // end of the pieces so far: the row's entries are covered once even if the columns are in no order
@@ -234,8 +235,13 @@ __global__ __launch_bounds__(kBlock) void cut_span_kernel(const CutPlanArgs a) {
     if (lane == 0 && longest > 0) atomicMax(&a.info->longest, longest);
 }
 
-scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, PlanResult *result,
-                                hipStream_t stream) {
+// One thread: the layout of the rows of a round.
+__global__ void cut_turn_kernel(const CutInfo *all, int32_t budget, int32_t turn, CutInfo *out) {
+    CutInfo c{};
+    if (cut_turn(*all, budget, turn, c)) *out = c;
+}
+
+static CutPlanArgs cut_plan_args(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx) {
     const WorkspaceLayout &L = plan->layout;
     char *ws = plan->workspace;
     const int64_t tiles = ((int64_t)plan->m + kBlock - 1) / kBlock;
@@ -248,13 +254,22 @@ scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *r
     a.tiles_per_block = (int32_t)((tiles + kPlanBlocksMax - 1) / kPlanBlocksMax);
     a.finest = plan->params.CUTJ;
     while (((int64_t)(plan->k - 1) >> a.shift) >= kCutBins) ++a.shift;
-    a.cap_pieces = L.cap_cut;
+    a.cap_pieces = a.cap_layout = L.cap_cut;
     a.counts = reinterpret_cast<int32_t *>(ws + L.off_cut_counts);
     a.hist = reinterpret_cast<int32_t *>(ws + L.off_cut_hist);
     a.info = reinterpret_cast<CutInfo *>(ws + L.off_cut_info);
     a.rows = reinterpret_cast<int32_t *>(ws + L.off_cut_rows);
-    a.spans = reinterpret_cast<int2 *>(ws + L.off_cut_spans);
+    a.spans = reinterpret_cast<int2 *>(ws + plan->off_cut_spans);
+    a.max_len = plan->params.CH + 1;
     a.max_rows = (int32_t)(L.cap_cut / kXcds);
+    return a;
+}
+
+scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int64_t cap_pieces,
+                                PlanResult *result, hipStream_t stream) {
+    CutPlanArgs a = cut_plan_args(plan, rowptr, colidx);
+    a.cap_pieces = cap_pieces;
+    const int64_t tiles = ((int64_t)plan->m + kBlock - 1) / kBlock;
     const uint32_t nblk = (uint32_t)((tiles + a.tiles_per_block - 1) / a.tiles_per_block);
     const uint32_t g = (uint32_t)std::min<int64_t>(std::max<int64_t>(1, (a.max_rows + kWavesPerBlock - 1) / kWavesPerBlock), 256 * 8);
     hipLaunchKernelGGL(cut_count_kernel, dim3(nblk), dim3(kBlock), 0, stream, a);
@@ -265,6 +280,19 @@ scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *r
     if (e == hipSuccess && result)
         e = hipMemcpyAsync(&result->cut, a.info, sizeof(result->cut), hipMemcpyDeviceToHost, stream);
     if (e != hipSuccess) return hip_fail(e, "launch the kernels that cut rows");
+    return SCORCH_OK;
+}
+
+scorch_status_t launch_cut_turn(const scorch_spmm_plan_t *plan, int32_t turn, const int32_t *rowptr, const int32_t *colidx, hipStream_t stream) {
+    CutPlanArgs a = cut_plan_args(plan, rowptr, colidx);
+    const CutInfo *all = a.info;
+    a.info = reinterpret_cast<CutInfo *>(plan->workspace + plan->layout.off_cut_turn);
+    a.cap_pieces = (int64_t)plan->cut_budget * kXcds;
+    const uint32_t g = (uint32_t)std::min<int64_t>((plan->cut_budget + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 8);
+    hipLaunchKernelGGL(cut_turn_kernel, dim3(1), dim3(1), 0, stream, all, plan->cut_budget, turn, a.info);
+    hipLaunchKernelGGL(cut_span_kernel, dim3(g), dim3(kBlock), 0, stream, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "launch the kernels of a round of cut rows");
     return SCORCH_OK;
 }
 
@@ -294,7 +322,7 @@ __global__ __launch_bounds__(kBlock) void cut_sum_kernel(const CutSumArgs a) {
     const int parts = 1 << j;
     const int64_t part_stride = (int64_t)c.rows[j] * a.stride, xcd_stride = (int64_t)c.pieces * a.stride;
     const float *src = a.partials + ((int64_t)c.piece_off[j] + i) * a.stride;
-    float *dst = a.C + (int64_t)a.rows[r] * a.ldc;
+    float *dst = a.C + (int64_t)a.rows[c.row_off[j] + i] * a.ldc;
     for (int col = ((int)threadIdx.x % a.team) * 4; col < a.n; col += a.team * 4) {
         f4 sum = {0.f, 0.f, 0.f, 0.f};
         auto add = [&](auto count, int q0) {
@@ -332,12 +360,13 @@ __global__ __launch_bounds__(kBlock) void cut_sum_kernel(const CutSumArgs a) {
     }
 }
 
-scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream) {
+scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, const CutInfo *info, int32_t max_rows, float *C, int64_t ldc, const float *bias,
+                               int32_t act, hipStream_t stream) {
     const char *ws = plan->workspace;
     CutSumArgs a{};
-    a.cut = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_info);
+    a.cut = info;
     a.rows = reinterpret_cast<const int32_t *>(ws + plan->layout.off_cut_rows);
-    a.partials = reinterpret_cast<const float *>(ws + plan->layout.off_cut_partials);
+    a.partials = reinterpret_cast<const float *>(ws + plan->off_cut_partials);
     a.C = C;
     a.ldc = ldc;
     a.n = plan->n;
@@ -348,7 +377,7 @@ scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, float *C, int64_t
     a.act = act;
     a.aligned = plan->n % 4 == 0 && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0;
     const int per_block = kBlock / a.team;
-    const uint32_t grid = (uint32_t)((plan->cut_rows + per_block - 1) / per_block);
+    const uint32_t grid = (uint32_t)((max_rows + per_block - 1) / per_block);
     hipLaunchKernelGGL(cut_sum_kernel, dim3(grid), dim3(kBlock), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "launch cut_sum_kernel");

@@ -281,7 +281,9 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
         if (nq <= 0) return;
         const int64_t first = (int64_t)x * pieces + q0;
         const int2 span = a.cut_spans[first + min(lane, nq - 1)];
-        const int len = lane < nq ? span.y - span.x : 0;
+        // a piece of up to kCutShort entries is one lane group's (the sum of a piece depends on nothing but the piece)
+        const int whole = lane < nq ? span.y - span.x : 0;
+        const int len = whole <= kCutShort ? whole : 0;
         int end = len;  // of the piece's entries in the stage
 #pragma unroll
         for (int off = 1; off < kCutRun; off <<= 1) {
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
         }
         const int total = __shfl(end, kCutRun - 1, kWave);
         float *dst0 = a.cut_partials + first * a.partial_stride;
-        if (total <= kCutStage) {
+        {
             // short pieces: staged together, one lane group per piece
             const int shift = span.x - (end - len);  // from the place in the stage to the entry
             int ends[kCutRun], shifts[kCutRun];
@@ -310,7 +312,9 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
             if (lane < kCutRun) lrp[lane + 1] = end;
             if (lane == 0) lrp[0] = 0;
             wave_lds_sync();
+            const unsigned long long longs = __ballot(whole > kCutShort);
             for (int i = grp; i < nq; i += S) {
+                if ((longs >> i) & 1ull) continue;
 #pragma unroll
                 for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
                 gather_fma<V, T, U, UA>(acc, lcol, lval, lrp[i], lrp[i + 1], 1, Bc, ldb, colok[0], boff);
@@ -318,10 +322,12 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
                 for (int t = 0; t < T; ++t)
                     if (colok[t]) vstore<V, HOT, UA>(dst0 + (int64_t)i * a.partial_stride + coff[t], acc[t]);
             }
-            return;
+            if (longs == 0ull) return;
+            wave_lds_sync();  // the stage is used again
         }
         for (int i = 0; i < nq; ++i) {
             const int p0 = __builtin_amdgcn_readlane(span.x, i), p1 = __builtin_amdgcn_readlane(span.y, i);
+            if (p1 - p0 <= kCutShort) continue;
 #pragma unroll
             for (int t = 0; t < T; ++t) acc[t] = vzero<V>();
             row_accumulate<V, G, T, U, NTA, UA>(acc, lcol, lval, lane, grp, p0, p1, kWave, a.colidx, a.vals, Bc, ldb, colok[0], boff);
@@ -1066,9 +1072,9 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
     const bool no_items = plan->cut_pieces > 0 && plan->cut_len > 0 && plan->cut_len <= plan->params.CH + 1;
     if (plan->cut_pieces > 0) {
         a.cut = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_info);
-        a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->layout.off_cut_spans);
-        a.cut_partials = reinterpret_cast<float *>(ws + plan->layout.off_cut_partials);
-        a.cut_wgs = (int32_t)ceil_div64(plan->cut_pieces, kWavesPerBlock * kCutRun);
+        a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->off_cut_spans);
+        a.cut_partials = reinterpret_cast<float *>(ws + plan->off_cut_partials);
+        a.cut_wgs = (int32_t)ceil_div64(plan->cut_turns > 0 ? plan->cut_budget : plan->cut_pieces, kWavesPerBlock * kCutRun);
         if (no_items) a.nb_items = 0;
     }
     const int64_t per_tile = (int64_t)a.nb_items + a.nb_wave + a.nb_win;
@@ -1095,12 +1101,30 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
             a.b_bytes = (int64_t)plan->k * ldb * 4;
             fn = a.cut ? pick_fused_cut(mp.G, mp.T, false, true) : pick_fused_hot(mp.G, mp.T, a.b_bytes < (1ll << 32) ? plan->tuning.cold : 0);
         }
-        hipLaunchKernelGGL(fn, dim3((uint32_t)grid), dim3(kBlock), 0, stream, a);
+        if (plan->cut_turns > 0) {
+            // the pieces round by round: their ranges, the pieces, their sums; then the other rows
+            const CutInfo *info = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_turn);
+            ExecArgs r = a;
+            r.cut = info;
+            r.nb_items = r.nb_wave = r.nb_win = 0;
+            const uint32_t cuts = (uint32_t)((int64_t)a.cut_wgs * mp.ncoltiles * kXcds);
+            for (int32_t turn = 0; turn < plan->cut_turns; ++turn) {
+                scorch_status_t st = launch_cut_turn(plan, turn, rowptr, colidx, stream);
+                if (st != SCORCH_OK) return st;
+                hipLaunchKernelGGL(fn, dim3(cuts), dim3(kBlock), 0, stream, r);
+                hipError_t e = hipGetLastError();
+                if (e != hipSuccess) return hip_fail(e, "launch spmm_fused_kernel");
+                if ((st = launch_cut_sum(plan, info, plan->cut_budget, C, ldc, bias, act, stream)) != SCORCH_OK) return st;
+            }
+            a.cut_wgs = 0;
+        }
+        const int64_t left = per_tile > 0 || a.cut_wgs > 0 ? grid_size(mp, per_tile) + (int64_t)a.cut_wgs * mp.ncoltiles * kXcds : 0;
+        if (left > 0) hipLaunchKernelGGL(fn, dim3((uint32_t)left), dim3(kBlock), 0, stream, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "launch spmm_fused_kernel");
     }
-    if (plan->cut_pieces > 0) {
-        scorch_status_t st = launch_cut_sum(plan, C, ldc, bias, act, stream);
+    if (plan->cut_pieces > 0 && plan->cut_turns == 0) {
+        scorch_status_t st = launch_cut_sum(plan, a.cut, plan->cut_rows, C, ldc, bias, act, stream);
         if (st != SCORCH_OK) return st;
     }
     if (plan->n_split > 0 && !fold && !no_items) {

@@ -58,7 +58,8 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
 struct WorkspaceLayout {
     uint64_t off_counts, off_totals, off_win, off_stage, off_wave, off_wave_span, off_items, off_split, off_partials, off_tickets, off_bpack,
         off_res_ptr, off_coldeg, off_hotmask, off_degbins, off_res_partials,
-        off_cut_info, off_cut_counts, off_cut_hist, off_cut_rows, off_cut_spans, off_cut_partials, total;
+        off_cut_info, off_cut_turn, off_cut_counts, off_cut_hist, off_cut_rows, off_cut_spans, off_cut_partials, total;
+    uint64_t off_turns;      // what a one-shot plan cannot do without ends here: partial rows after it may take turns
     uint64_t res_row_bytes;  // resident kernel: partial rows of one row of A (0: none, B fits one chunk)
     int64_t ticket_tiles;  // arrival counters per split row: one for every column tile a launch may use
     int64_t n_windows, nblk;
@@ -73,7 +74,7 @@ struct alignas(64) PlanResult {
     int32_t nnz;
     int32_t totals[5];  // wave rows, items, split rows, slots, short rows
     int32_t done;       // written last by the first two kernels
-    CutHead cut;        // rows cut by columns
+    CutInfo cut;        // rows cut by columns
     int32_t unsorted;   // some row's columns are not strictly increasing
     PlanResult *next;   // host side only: the next slot that no call is using
 };
@@ -197,6 +198,8 @@ struct scorch_spmm_plan_s {
     int32_t n_hot;    // columns marked hot (0: every gather uses the default cache policy)
     int32_t cut_pieces, cut_rows;  // rows cut by columns: pieces per XCD and rows, or upper bounds (one-shot plan); 0: none
     int32_t cut_len;               // shortest of them (one-shot plan: not known)
+    int32_t cut_budget, cut_turns; // one-shot plan without room for all pieces: pieces per XCD at a time, and rounds (0: all at once)
+    uint64_t off_cut_spans, off_cut_partials;
     float hot_share;  // share of the stored entries that point at a hot column
 };
 
@@ -240,10 +243,14 @@ scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *c
 // spmm_cut.hip
 constexpr int kPlanBlocksMax = 1024;  // workgroups of a planning kernel
 constexpr int kCutRun = 4;            // pieces per wavefront
-constexpr int kCutStage = 32 * kCutRun;
-scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, PlanResult *result,
-                                hipStream_t stream);
-scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream);
+constexpr int kCutShort = 32;         // pieces of up to so many entries are one lane group's
+// spans: room for the pieces (a one-shot plan's: cap_pieces fewer than the layout's); result: where the outcome is to be copied, or nullptr
+scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int64_t cap_pieces,
+                                PlanResult *result, hipStream_t stream);
+scorch_status_t launch_cut_turn(const scorch_spmm_plan_t *plan, int32_t turn, const int32_t *rowptr, const int32_t *colidx, hipStream_t stream);
+// info: the layout the pieces were made for (that of all rows, or of a round), max_rows rows at most
+scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, const CutInfo *info, int32_t max_rows, float *C, int64_t ldc, const float *bias,
+                               int32_t act, hipStream_t stream);
 
 // sddmm_exec.hip (plan == nullptr: plan-free, one wavefront per row)
 scorch_status_t launch_sddmm(const scorch_spmm_plan_t *plan, int32_t m, int32_t d, const int32_t *rowptr,

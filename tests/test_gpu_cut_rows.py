@@ -15,7 +15,7 @@ from gpu_util import ATOL, RTOL_T, DeviceProblem, check_against_oracle, tuning
 pytestmark = pytest.mark.gpu
 
 
-def problem(n, seed=0, duplicates=False, k=9000, m=3000):
+def problem(n, seed=0, duplicates=False, k=9000, m=7000):
     rng = np.random.default_rng(seed)
     lens = rng.integers(0, 30, size=m)
     lens[rng.permutation(m)[:260]] = np.repeat([63, 64, 65, 127, 128, 200, 255, 256, 300, 511, 512, 1023, 1024], 20)
@@ -113,6 +113,29 @@ def test_cut_rows_by_the_planners_own_choice_in_all_calls_and_graphs(n):
         torch.cuda.synchronize()
         assert np.array_equal(d.Cfull.cpu().numpy(), got)
     plan.destroy()
+
+
+@pytest.mark.parametrize("m,k,n,length", [(2500, 6000, 300, 500), (600, 9000, 1001, 2500), (3000, 20000, 90, (64, 3000)),
+                                          (2500, 8000, 333, 1600)])  # the last: in the place of 10 MB of other partial rows
+def test_pieces_that_take_turns_in_the_one_shot_call(m, k, n, length):
+    """Partial rows of more than the static scratch: the one-shot call goes round by round and keeps the planned call's bits."""
+    rng = np.random.default_rng(m)
+    lens = np.full(m, length) if np.isscalar(length) else rng.integers(*length, size=m)
+    lens[rng.integers(0, m, size=m // 10)] = rng.integers(0, 64, size=m // 10)
+    p = csr_from_row_lengths(lens, k, n, seed=n, duplicates=False)
+    for q, exact in ((p, False), (integer_valued(p, seed=1), True)):
+        with tuning("cut=1,res=0,panel=0,sliced=0"):
+            d = DeviceProblem(q)
+            plan = d.make_plan()
+            assert plan.info().workspace_bytes_used > sp.STATIC_SCRATCH_BYTES
+            got = d.run_planned(plan)
+            check_against_oracle(q, got, d.ldc, exact=exact, label=f"m={m} n={n}")
+            for _ in range(2):
+                d.reset_C()
+                sp.scorch_spmm_csr_static(q.m, q.k, q.n, d.rowptr, d.colidx, d.vals, d._B_arg(), d._C_arg())
+                torch.cuda.synchronize()
+                assert np.array_equal(d.Cfull.cpu().numpy(), got)
+            plan.destroy()
 
 
 @pytest.mark.parametrize("m", [1, 64, 400])
