@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kBlock) void cut_count_kernel(const CutPlanArgs a) 
 __global__ __launch_bounds__(kBlock) void cut_layout_kernel(const CutPlanArgs a, int nblk) {
     __shared__ int s_rows[kCutBuckets];
     __shared__ int64_t s_pre[kCutBins + 1];
-    __shared__ int64_t s_part[kBlock + 1];
+    __shared__ int64_t s_wave[kWavesPerBlock];
     constexpr int kPer = kCutBins / kBlock;
     const int tid = threadIdx.x;
     if (tid < kCutBuckets) s_rows[tid] = 0;
@@ -87,16 +87,22 @@ __global__ __launch_bounds__(kBlock) void cut_layout_kernel(const CutPlanArgs a,
         h[i] = a.hist[tid * kPer + i];
         sum += h[i];
     }
-    s_part[tid] = sum;
+    int64_t run = sum;  // of the bins up to and with this thread's
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int64_t o = __shfl_up((long long)run, off, kWave);
+        if ((tid & 63) >= off) run += o;
+    }
+    if ((tid & 63) == kWave - 1) s_wave[tid >> 6] = run;
     __syncthreads();
+    int64_t total = 0;
+    run -= sum;
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) {
+        if (w < (tid >> 6)) run += s_wave[w];
+        total += s_wave[w];
+    }
     if (tid == 0) {
-        int64_t run = 0;
-        for (int i = 0; i < kBlock; ++i) {
-            const int64_t v = s_part[i];
-            s_part[i] = run;
-            run += v;
-        }
-        s_part[kBlock] = run;
         CutInfo c{};
         int rows[kCutBuckets];
         for (int b = 0; b < kCutBuckets; ++b) rows[b] = s_rows[b];
@@ -117,8 +123,6 @@ __global__ __launch_bounds__(kBlock) void cut_layout_kernel(const CutPlanArgs a,
             a.info->piece_off[j] = c.piece_off[j];
         }
     }
-    __syncthreads();
-    int64_t run = s_part[tid];
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
         s_pre[tid * kPer + i] = run;
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void cut_layout_kernel(const CutPlanArgs a,
     if (tid == kBlock - 1) s_pre[kCutBins] = run;
     __syncthreads();
     if (tid < kCutBounds) {
-        const int64_t target = s_part[kBlock] * tid / kCutBounds;
+        const int64_t target = total * tid / kCutBounds;
         int lo = 0, hi = kCutBins - 1;  // the last bin that starts at or before the target
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;

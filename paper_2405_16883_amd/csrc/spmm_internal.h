@@ -244,7 +244,7 @@ scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *c
 constexpr int kPlanBlocksMax = 1024;  // workgroups of a planning kernel
 constexpr int kCutRun = 4;            // pieces per wavefront
 constexpr int kCutShort = 32;         // pieces of up to so many entries are one lane group's
-// spans: room for the pieces (a one-shot plan's: cap_pieces fewer than the layout's); result: where the outcome is to be copied, or nullptr
+// cap_pieces: room for the ranges of so many pieces (0: none are written); result: where the outcome is copied to, or nullptr
 scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int64_t cap_pieces,
                                 PlanResult *result, hipStream_t stream);
 scorch_status_t launch_cut_turn(const scorch_spmm_plan_t *plan, int32_t turn, const int32_t *rowptr, const int32_t *colidx, hipStream_t stream);
