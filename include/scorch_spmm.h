@@ -164,8 +164,8 @@ scorch_status_t scorch_spmm_csr_planned_epilogue(const scorch_spmm_plan_t *plan,
  * process ends.  The call allocates nothing on the device (no hipMalloc, hipFree or allocating library routine).
  *   - A problem whose plan needs more than SCORCH_STATIC_SCRATCH_BYTES (see scorch_spmm_plan_workspace_bytes) is
  *     refused with SCORCH_ERR_UNSUPPORTED and a message naming both sizes; no work is left on the stream then.  Only the
- *     partial rows of kernels that keep chunks of B in LDS may exceed it: they take turns in the array, block of rows by
- *     block of rows.
+ *     partial rows of kernels that keep chunks of B in LDS, and the pieces of rows cut by columns, may exceed it: they take
+ *     turns in the array, some rows at a time.
  *   - The pattern is analysed at every call (the host waits for the list sizes, which are written to host memory
  *     that the library allocates at its first plan, and where they matter for a look at the columns), then the
  *     execution is enqueued and the call returns without waiting for it.
