@@ -18,6 +18,7 @@
 // No MFMA: the work is a gather, not a dense contraction.  No atomics: summation order is fixed.
 #include "spmm_internal.h"
 #include "device_util.h"
+#include "lane_mapping.h"
 #include "scouts.h"
 
 #include <algorithm>
@@ -861,49 +862,6 @@ __global__ __launch_bounds__(kBlock) void spmm_fixup_kernel(const FixupArgs a) {
 // host side: pick the lane mapping from n and the operand alignment, then launch
 // ------------------------------------------------------------------------------------------
 
-struct Mapping {
-    int V, G, T, ncoltiles;
-    bool UA;  // four floats per lane at float alignment, last vector of a row moved back to end at column n
-    int xcd_slices;  // 0: tile-major grid; 1: column slices dealt over the XCDs (see tile_of_workgroup)
-};
-
-static Mapping pick_mapping(int32_t n, const float *B, int64_t ldb, const float *C, int64_t ldc, int slice_cols) {
-    Mapping mp{};
-    const uintptr_t pb = reinterpret_cast<uintptr_t>(B), pc = reinterpret_cast<uintptr_t>(C);
-    if (n % 4 == 0 && ldb % 4 == 0 && ldc % 4 == 0 && pb % 16 == 0 && pc % 16 == 0) mp.V = 4;
-    else if (n >= 4) {
-        // rows that are not 16-byte aligned, or n not a multiple of 4: still four floats per lane
-        mp.V = 4;
-        mp.UA = true;
-    } else if (n % 2 == 0 && ldb % 2 == 0 && ldc % 2 == 0 && pb % 8 == 0 && pc % 8 == 0) mp.V = 2;
-    else mp.V = 1;
-    mp.xcd_slices = 0;
-    if (slice_cols > 0 && mp.V == 4 && !mp.UA) {
-        // column slices of B (32 columns = one 128-byte line of a row, or 64 or 128), one slice per XCD at a time
-        mp.G = slice_cols / 4;
-        mp.T = 1;
-        mp.ncoltiles = (n + slice_cols - 1) / slice_cols;
-        mp.xcd_slices = 1;
-        return mp;
-    }
-    const int lanes = (n + mp.V - 1) / mp.V;
-    if (lanes <= kWave) {
-        // n <= 4 (SpMV and its neighbours): one lane per group, the 64 lanes of a wavefront take 64 entries
-        // of a row (or 64 short rows of a window) per step and are combined by the xor butterfly
-        int g = 1;
-        while (g < lanes) g <<= 1;
-        mp.G = g;
-        mp.T = 1;
-        mp.ncoltiles = 1;
-    } else {
-        mp.G = kWave;
-        mp.T = 2;
-        const int tw = mp.G * mp.V * mp.T;
-        mp.ncoltiles = (n + tw - 1) / tw;
-    }
-    return mp;
-}
-
 static int64_t grid_size(const Mapping &mp, int64_t per_tile) {
     return xcd_grid_size(mp.xcd_slices, mp.ncoltiles, per_tile);
 }
@@ -1150,31 +1108,8 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
 scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *rowptr, const int32_t *colidx,
                                const float *vals, const float *B, int64_t ldb, float *C, int64_t ldc,
                                hipStream_t stream) {
-    // Column slices dealt over the XCDs (tile_of_workgroup) need no plan, only the shape: with B of 8 MB or more every
-    // XCD walks all rows for one slice of columns at a time, so that the part of B it gathers from is 1/s of B.  Measured
-    // on the plan-free call: uniform 1 % pattern, n = 128: 90 -> 69 us with 64-column slices; pruned 4096 x 16384 weight,
-    // n = 2048: 5.03 -> 2.26 ms with 128-column slices (64 columns: 3.0 ms, 32: 4.3 ms, 256: 4.2 ms); mid-size graph,
-    // n = 128: 168 -> 166 us.  A ragged last slice costs more than it gains, hence the multiples.
-    int slice_cols = 0;
-    if ((int64_t)k * n * 4 >= (8ll << 20)) {
-        if (n >= 256 && n % 128 == 0) slice_cols = 128;
-        else if (n >= 128 && n % 64 == 0) slice_cols = 64;
-    }
-    Mapping mp = pick_mapping(n, B, ldb, C, ldc, slice_cols);
-    // Few rows, up to 2048 pairs of a row and a 32-column tile: a workgroup for each pair (spmm_row_kernel).  Measured with
-    // n = 256: 64 rows of 2458 entries 62.0 -> 11.7 us, 16 rows of 6000 66 -> 8.8, 256 rows (2048 pairs) of 5000 71 -> 58,
-    // of 1000 even; with twice the pairs the run kernel is ahead for long rows (256 rows of 5000, n = 512: 98 against 114).
-    const int row_tile = 8 * mp.V;
-    const int64_t row_units = (int64_t)m * ((n + row_tile - 1) / row_tile);
-    const bool row_kernel = row_units <= 2048;
-    // More rows than that, but fewer than two wavefronts per SIMD at one row each: narrower column tiles, at least 8
-    // lanes wide (1024 rows, n = 128, mean 1024 / 256 entries: one tile 32.4 / 16.6 us, two 21.0 / 10.7, four 26.1 / 10.6).
-    while (!row_kernel && mp.G * mp.T > 8 && (int64_t)m * mp.ncoltiles < 2048) {
-        if (mp.T == 2) mp.T = 1;
-        else mp.G /= 2;
-        mp.ncoltiles = (n + mp.G * mp.V - 1) / (mp.G * mp.V);
-        mp.xcd_slices = 1;
-    }
+    const NaturalMapping nm = natural_mapping(m, k, n, B, ldb, C, ldc);
+    Mapping mp = nm.mp;
     ExecArgs a{};
     a.rowptr = rowptr;
     a.colidx = colidx;
@@ -1185,9 +1120,9 @@ scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *r
     a.ldc = ldc;
     a.m = m;
     a.n = n;
-    if (row_kernel) {
+    if (nm.row_kernel) {
         // up to 256 pairs, one per compute unit, get 16 wavefronts each (16 rows of 6000 entries, n = 32: 10.4 -> 8.6 us)
-        const int waves = row_units <= 256 ? 16 : kWavesPerBlock;
+        const int waves = nm.row_units <= 256 ? 16 : kWavesPerBlock;
         mp.T = 1;
         mp.G = std::min(mp.G, 8);
         a.ncoltiles = (n + mp.G * mp.V - 1) / (mp.G * mp.V);
@@ -1221,11 +1156,8 @@ scorch_status_t launch_natural(int32_t m, int32_t k, int32_t n, const int32_t *r
         set_error("launch grid of %lld workgroups exceeds the HIP limit", (long long)grid);
         return SCORCH_ERR_UNSUPPORTED;
     }
-    // Gathers in flight per group of a scout: 16, which takes 84 to 124 VGPRs, or 8, which leaves room for one or two more wavefronts
-    // per SIMD.  us with 16 / 8: groups of 8 lanes, 169 343 rows, n = 32 49.4 / 40.4; 64-column slices, 30 000 rows, n = 128 31.0 / 28.5,
-    // 169 343 128.6 / 123.6; but n = 192 190.9 / 193.2, 300 000 rows of 30, n = 128 510 / 517; whole rows, 30 000 rows, n = 64 23.2 / 25.9.
-    kernel_fn fn = mp.G == 16 && slice_cols == 64 && (int64_t)m * mp.ncoltiles < 400000 ? spmm_natural_kernel<4, 16, 1, 8, 1, false, 8>
-                                                                                       : pick_natural(mp.V, mp.G, mp.T, mp.UA);
+    const kernel_fn fn = nm.scout_gathers == 8 && mp.G == 16 ? spmm_natural_kernel<4, 16, 1, 8, 1, false, 8>
+                                                             : pick_natural(mp.V, mp.G, mp.T, mp.UA);
     hipLaunchKernelGGL(fn, dim3((uint32_t)grid), dim3(kBlock), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "launch spmm_natural_kernel");

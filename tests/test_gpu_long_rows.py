@@ -2,8 +2,9 @@
 clusters, at regular distances and first of all, for every run length and way of dealing them to workgroups."""
 import numpy as np
 import pytest
+import torch
 
-from workloads import csr_from_row_lengths, integer_valued
+from workloads import csr_from_row_lengths, integer_valued, with_padding
 
 from gpu_util import DeviceProblem, check_against_oracle
 
@@ -69,3 +70,18 @@ def test_long_rows_with_column_slices_on_either_side_of_the_scouts_rule(m, n):
     p = integer_valued(csr_from_row_lengths(lens, 17000, n, seed=m, duplicates=True), seed=n)
     d = DeviceProblem(p)
     check_against_oracle(p, d.run_natural(), d.ldc, exact=True, label=f"m={m} n={n}")
+
+
+@pytest.mark.parametrize("m,k,n", [(1500, 17000, 128), (700, 11000, 192)])  # shapes with 64-column slices, groups of 16 lanes either way
+@pytest.mark.parametrize("ldb,ldc,shift", [(0, 0, 0), (1, 0, 0), (0, 1, 0), (1, 3, 0), (4, 4, 0), (0, 0, 1), (2, 0, 3)])
+def test_few_rows_with_operands_of_any_alignment(m, k, n, ldb, ldc, shift):
+    """Padded rows of B or C, or a B that starts `shift` floats into its array, take the loads and stores for any alignment."""
+    lens = np.random.default_rng(m).integers(0, 40, size=m)
+    lens[[1, m // 2, m - 1]] = [300, 2100, 700]
+    p = integer_valued(with_padding(csr_from_row_lengths(lens, k, n, seed=m, duplicates=True), n + ldb), seed=n)
+    d = DeviceProblem(p, ldc=n + ldc)
+    if shift:
+        moved = torch.empty(d.Bfull.numel() + shift, device=d.dev)[shift:].view_as(d.Bfull)
+        moved.copy_(d.Bfull)
+        d.Bfull = moved
+    check_against_oracle(p, d.run_natural(), d.ldc, exact=True, label=f"m={m} n={n} +{ldb} +{ldc} at {shift}")

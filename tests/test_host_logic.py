@@ -1,6 +1,6 @@
-"""Host-side logic of the library that needs no GPU.  Four pieces of plain integer or text handling live in headers
+"""Host-side logic of the library that needs no GPU.  Pieces of plain integer or text handling live in headers
 without HIP dependencies -- the workgroup -> (column tile, row work) mapping of the XCD-sliced launches, the dealing of
-long rows to workgroups of the plan-free kernel, the range of row pointers a key of a coordinate list fills, and the parser of the tuning text -- and small C++ checkers under
+long rows to workgroups of the plan-free kernel, the lane mapping, the layout of rows cut by columns, the range of row pointers a key of a coordinate list fills, and the parser of the tuning text -- and small C++ checkers under
 tests/host/ are compiled with the host compiler and run on the CPU, once plainly and once under the address and
 undefined-behaviour sanitizers.  The C oracles get the same sanitizer pass through a driver that hands them every
 operand in a heap block of exactly its size."""
@@ -55,6 +55,11 @@ def test_row_pointer_fill_ranges_stay_inside_rowptr(repo_root, tmp_path, sanitiz
 @pytest.mark.parametrize("sanitize", [False, True])
 def test_long_rows_are_dealt_evenly_and_every_row_is_looked_at_once(repo_root, tmp_path, sanitize):
     run_checker(build_checker(repo_root, tmp_path, "scouts_check", sanitize), sanitize)
+
+
+@pytest.mark.parametrize("sanitize", [False, True])
+def test_lane_mapping_takes_aligned_vectors_only_for_aligned_operands(repo_root, tmp_path, sanitize):
+    run_checker(build_checker(repo_root, tmp_path, "lane_mapping_check", sanitize), sanitize)
 
 
 @pytest.mark.parametrize("sanitize", [False, True])
