@@ -1014,8 +1014,8 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
     // One or two columns, mean row of up to 32 entries: medium rows stay with their windows.  Bound by L2 requests, one per entry, and the
     // chain of reads of every wavefront: fewer of both.  us before / after, n = 1: 169 343 rows, 2.5 M entries 19.2 / 16.7; 600 000 rows of 8
     // 35.2 / 29.2, of 25 115 / 97; 1.5 M rows of 4 56 / 47; 20 000 of 5 5.2 / 5.1.  Rows of 164 (all medium) 11.2 / 15.8, 600 000 of 40 even,
-    // hence the mean.
-    a.whole_rows = mp.G == 1 && mp.V <= 2 && plan->params.CH <= kWholeMax && plan->nnz <= kLaneRow * (int64_t)plan->m;
+    // hence the mean.  Rows beyond CH are among the items: with a smaller CH they would be a window's too.
+    a.whole_rows = mp.G == 1 && mp.V <= 2 && plan->params.CH == kWholeMax && plan->nnz <= kLaneRow * (int64_t)plan->m;
     if (a.whole_rows) {
         a.nb_wave = 0;
         a.nb_win = (int32_t)ceil_div64(plan->layout.n_windows, kWavesPerBlock);

@@ -44,3 +44,32 @@ def test_few_rows(lens):
     plan = d.make_plan()
     check_against_oracle(p, d.run_planned(plan), d.ldc, exact=True, label=str(lens[:4]))
     plan.destroy()
+
+
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("ch", [64, 128, 255])
+def test_rows_beyond_a_smaller_ch_are_summed_by_one_workgroup_in_its_order(n, ch):
+    """Rows of more than `ch` entries belong to the workgroups of long rows: an entry per lane of four wavefronts, the lanes in pairs,
+    then pairs of pairs, then the wavefronts.  If a window stored such a row as well, its bits would depend on who is last."""
+    lens = np.random.default_rng(ch).integers(0, 20, size=900)
+    lens[::30] = np.resize([ch + 1, 200, 256], lens[::30].size)
+    long_rows = np.flatnonzero(lens > ch)
+    p = csr_from_row_lengths(lens, 700, n, seed=ch, duplicates=True)
+    assert p.nnz <= 32 * p.m
+    d = DeviceProblem(p)
+    with tuning(f"ch={ch}"):
+        plan = d.make_plan()
+    want = np.zeros((long_rows.size, n), dtype=np.float32)
+    for i, r in enumerate(long_rows):
+        e = slice(p.rowptr[r], p.rowptr[r + 1])
+        prod = np.zeros((256, n), dtype=np.float32)
+        prod[:lens[r]] = p.vals[e, None] * p.B[p.colidx[e], :n]
+        waves = prod.reshape(4, 64, n)
+        for off in (1, 2, 4, 8, 16, 32):
+            waves = waves + waves[:, np.arange(64) ^ off]
+        want[i] = ((waves[0, 0] + waves[1, 0]) + waves[2, 0]) + waves[3, 0]
+    for _ in range(4):
+        got = d.run_planned(plan)
+        check_against_oracle(p, got, d.ldc, label=f"n={n} ch={ch}")
+        assert np.array_equal(got[long_rows], want)
+    plan.destroy()
