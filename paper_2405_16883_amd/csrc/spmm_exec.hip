@@ -488,7 +488,10 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
             const int i = __builtin_ctzll(todo);
             const int q0 = __builtin_amdgcn_readlane(rp, i) - first, n = __builtin_amdgcn_readlane(len, i);
             vec sum[1] = {vzero<V>()};
-            for (int e = lane; e < n; e += kWave) vadd<V>(sum[0], prod[q0 + e]);
+            // every lane still holds its values and gathered elements: fused multiply-adds, as everywhere for rows of this length
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s)
+                if ((uint32_t)(lane + s * kWave - q0) < (uint32_t)n) vfma<V>(sum[0], v[s], x[s]);
             reduce_groups<V, G, 1>(sum);
             if (lane == 0) vstore<V, NTC, UA>(a.C + (int64_t)(r0 + i) * a.ldc + coff[0], apply_epilogue<V>(sum[0], bias, a.act));
         }

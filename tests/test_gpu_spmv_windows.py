@@ -1,4 +1,6 @@
 """One and two columns: rows of every length a window's wavefront may meet, and means on either side of the rule."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -72,4 +74,30 @@ def test_rows_beyond_a_smaller_ch_are_summed_by_one_workgroup_in_its_order(n, ch
         got = d.run_planned(plan)
         check_against_oracle(p, got, d.ldc, label=f"n={n} ch={ch}")
         assert np.array_equal(got[long_rows], want)
+    plan.destroy()
+
+
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("length,at", [(65, 0), (100, 30), (128, 63), (256, 191)])
+def test_rows_of_more_than_64_entries_are_summed_by_fused_multiply_adds(n, length, at):
+    """Entries 64 apart are one lane's.  The first is -(1 + 2^-11), the second (1 + 2^-12)^2 = 1 + 2^-11 + 2^-24, the others add nothing:
+    2^-24 is left, unless the second product was rounded to 24 bits on the way."""
+    lens = np.random.default_rng(length).integers(0, 20, size=500)
+    rows = np.arange(3, 500, 50)
+    lens[rows] = length
+    p = csr_from_row_lengths(lens, 700, n, seed=length, duplicates=True)
+    vals, col, B = p.vals.copy(), p.colidx.copy(), p.B.copy()
+    B[0, :n], B[1, :n] = 1, 1 + 2.0 ** -12
+    for r in rows:
+        e = p.rowptr[r]
+        vals[e:e + length] = 0
+        first = e + min(at, length - 65)
+        vals[first], col[first] = -(1 + 2.0 ** -11), 0
+        vals[first + 64], col[first + 64] = 1 + 2.0 ** -12, 1
+    q = dataclasses.replace(p, vals=vals, colidx=col, B=B)
+    d = DeviceProblem(q)
+    plan = d.make_plan()
+    got = d.run_planned(plan)
+    check_against_oracle(q, got, d.ldc, label=f"n={n} length={length}")
+    assert (got[rows, :n] == 2.0 ** -24).all()
     plan.destroy()
