@@ -199,7 +199,7 @@ __device__ __forceinline__ void row_accumulate(typename Vec<V>::type (&acc)[T], 
 
 constexpr int smem_ints_per_wave() { return 2 * kStageMax + kWindowRowsMax + 2; }
 
-template <int V, int G, int T, int U, int NT, bool UA, bool HOT = false, int COLD = 0, bool CUT = false>
+template <int V, int G, int T, int U, int NT, bool UA, bool HOT = false, int COLD = 0, bool CUT = false, bool WHOLE = false>
 __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
     using vec = typename Vec<V>::type;
     constexpr int S = kWave / G;
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
     __shared__ int s_raw[kOneLane ? 1 : kWavesPerBlock * smem_ints_per_wave()];
     __shared__ float s_red[kWavesPerBlock * TW];
     // one-lane groups (n <= 4) only: the products of a window's entries, summed per row afterwards
-    constexpr int kProducts = V <= 2 ? kBNMax + kWholeMax : kStageMax;
+    constexpr int kProducts = WHOLE ? kBNMax + kWholeMax : kStageMax;
     __shared__ __attribute__((aligned(16))) float s_prod[G == 1 ? kWavesPerBlock * kProducts * V : 1];
     __shared__ int s_flag;  // piece of a split row: this workgroup drew the row's last ticket
 
@@ -447,7 +447,7 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
     const int r0 = a.win_row_start[w];
     const int r1 = a.win_row_start[w + 1];
     const int nr = min(r1 - r0, kWindowRowsMax);
-    if constexpr (G == 1 && V <= 2) if (a.whole_rows) {
+    if constexpr (WHOLE) {
         // One or two columns: a row of up to kWholeMax entries is walked here whatever its class, so that no entry between two short
         // rows is gathered in vain and medium rows need no wavefronts of their own.  A longer row can only be the last of its window
         // (rows start within kBNMax entries of each other).  A lane adds up a row of up to kLaneRow entries, the wavefront the others.
@@ -901,6 +901,17 @@ typedef void (*kernel_fn)(const ExecArgs);
     }
 
 static kernel_fn pick_fused(int V, int G, int T, int U, int NT, bool UA) { SCORCH_PICK(spmm_fused_kernel) }
+// Windows that walk whole rows: one lane per group, one or two columns.
+static kernel_fn pick_fused_whole(int V, int U, int NT) {
+#define SCORCH_WHOLE(V)                                                                                            \
+    return U >= 8 ? (NT & 1 ? spmm_fused_kernel<V, 1, 1, 8, 1, false, false, 0, false, true>                       \
+                            : spmm_fused_kernel<V, 1, 1, 8, 0, false, false, 0, false, true>)                      \
+                  : (NT & 1 ? spmm_fused_kernel<V, 1, 1, 4, 1, false, false, 0, false, true>                       \
+                            : spmm_fused_kernel<V, 1, 1, 4, 0, false, false, 0, false, true>);
+    if (V == 2) { SCORCH_WHOLE(2) }
+    SCORCH_WHOLE(1)
+#undef SCORCH_WHOLE
+}
 static kernel_fn pick_fused_hot(int G, int T, int cold) {
     // experiments with the cache policy of the cold rows: whole rows of 97..128 columns only
     if (G == 32 && T == 1 && cold == 1) return spmm_fused_kernel<4, 32, 1, 8, 1, false, true, 1>;
@@ -1015,11 +1026,14 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
     a.nb_wave = (int32_t)ceil_div64(plan->n_wave, kWavesPerBlock);
     a.nb_win = plan->n_short > 0 ? (int32_t)ceil_div64(plan->layout.n_windows, kWavesPerBlock) : 0;
     // One or two columns, mean row of up to 32 entries: medium rows stay with their windows.  Bound by L2 requests, one per entry, and the
-    // chain of reads of every wavefront: fewer of both.  us before / after, n = 1: 169 343 rows, 2.5 M entries 19.2 / 16.7; 600 000 rows of 8
-    // 35.2 / 29.2, of 25 115 / 97; 1.5 M rows of 4 56 / 47; 20 000 of 5 5.2 / 5.1.  Rows of 164 (all medium) 11.2 / 15.8, 600 000 of 40 even,
-    // hence the mean.  Rows beyond CH are among the items: with a smaller CH they would be a window's too.
-    a.whole_rows = mp.G == 1 && mp.V <= 2 && plan->params.CH == kWholeMax && plan->nnz <= kLaneRow * (int64_t)plan->m;
-    if (a.whole_rows) {
+    // chain of reads of every wavefront: fewer of both.  us before / after, n = 1: 169 343 rows, 2.5 M entries 18.9 / 16.3; 600 000 rows of 8
+    // 35.2 / 29.1, of 25 95 / 76; 1.5 M rows of 4 55 / 46; 120 000 of 7 8.7 / 8.1, of 4 6.8 / 6.8.  Rows of 164 (all medium) 11.2 / 15.8, 600 000 of
+    // 40 even, hence the mean.  A wavefront reads whole windows of 512 entries at once, which does not pay where windows are small (2000 rows of
+    // 4, n = 2 4.2 / 4.5; 20 000 of 5 5.1 / 5.3) or where hardly a row is medium (30 000 rows of 30 6.3 / 6.8, of 10 4.7 / 5.1).
+    // They have a kernel of their own: with both in one, rows of 30 took 7.6 instead of 7.1 us.  Rows beyond CH are among the items: with a smaller CH they would be a window's too.
+    const bool whole_rows = mp.G == 1 && mp.V <= 2 && plan->params.CH == kWholeMax && plan->params.BN >= 128 && plan->nnz <= kLaneRow * (int64_t)plan->m &&
+                   (int64_t)plan->n_wave * 256 >= plan->m;
+    if (whole_rows) {
         a.nb_wave = 0;
         a.nb_win = (int32_t)ceil_div64(plan->layout.n_windows, kWavesPerBlock);
     }
@@ -1053,8 +1067,9 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
         a.b_tile_stride = (int64_t)plan->k * kSliceCols;
     }
     if (grid > 0) {
-        kernel_fn fn = a.cut ? pick_fused_cut(mp.G, mp.T, mp.UA, false)
-                             : pick_fused(mp.V, mp.G, mp.T, plan->params.U, plan->params.NT, mp.UA);
+        kernel_fn fn = a.cut        ? pick_fused_cut(mp.G, mp.T, mp.UA, false)
+                       : whole_rows ? pick_fused_whole(mp.V, plan->params.U, plan->params.NT)
+                                    : pick_fused(mp.V, mp.G, mp.T, plan->params.U, plan->params.NT, mp.UA);
         if (plan->n_hot > 0 && mp.V == 4 && !mp.UA && mp.xcd_slices == 0 && mp.G >= 8 && plan->params.U >= 8 &&
             (plan->params.NT & 1)) {
             // hot/cold variant: rows of B outside the plan's hot set are read with the streaming policy

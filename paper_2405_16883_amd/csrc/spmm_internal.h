@@ -106,7 +106,6 @@ struct ExecArgs {
     const float *bias;      // epilogue: n floats added to every row of C, or nullptr
     int32_t act;            // epilogue: 0 identity, 1 ReLU
     const uint32_t *hotmask;  // one bit per column of A, set for the most referenced rows of B (hot/cold variants only)
-    bool whole_rows;          // one-lane groups: windows hold all rows of up to kWholeMax entries
     int32_t rows_per_wave;    // plan-free kernel only: consecutive rows taken by one wavefront (a power of two)
     int32_t scout_shift;      // plan-free kernel only: see scouts.h (nb_items: the scouts)
     float one_over_m;

@@ -59,7 +59,7 @@ def test_rows_beyond_a_smaller_ch_are_summed_by_one_workgroup_in_its_order(n, ch
     p = csr_from_row_lengths(lens, 700, n, seed=ch, duplicates=True)
     assert p.nnz <= 32 * p.m
     d = DeviceProblem(p)
-    with tuning(f"ch={ch}"):
+    with tuning(f"bn=256,ch={ch}"):
         plan = d.make_plan()
     want = np.zeros((long_rows.size, n), dtype=np.float32)
     for i, r in enumerate(long_rows):
@@ -96,8 +96,25 @@ def test_rows_of_more_than_64_entries_are_summed_by_fused_multiply_adds(n, lengt
         vals[first + 64], col[first + 64] = 1 + 2.0 ** -12, 1
     q = dataclasses.replace(p, vals=vals, colidx=col, B=B)
     d = DeviceProblem(q)
-    plan = d.make_plan()
+    with tuning("bn=256"):
+        plan = d.make_plan()
     got = d.run_planned(plan)
     check_against_oracle(q, got, d.ldc, label=f"n={n} length={length}")
     assert (got[rows, :n] == 2.0 ** -24).all()
     plan.destroy()
+
+
+@pytest.mark.parametrize("n", [1, 2])
+@pytest.mark.parametrize("spec", ["bn=256", "bn=128", "bn=64"])
+@pytest.mark.parametrize("medium", [0, 3, 4, 40])  # of 1024 rows: on either side of one in 256
+def test_windows_that_walk_whole_rows_or_short_ones_only(n, spec, medium):
+    lens = np.random.default_rng(medium).integers(0, 32, size=1024)
+    lens[np.arange(medium) * 25] = np.resize([33, 64, 200, 256], medium)
+    p = csr_from_row_lengths(lens, 900, n, seed=medium, duplicates=True)
+    for q, exact in ((p, False), (integer_valued(p, seed=n), True)):
+        d = DeviceProblem(q)
+        with tuning(spec):
+            plan = d.make_plan()
+        assert plan.info().n_wave_rows == medium
+        check_against_oracle(q, d.run_planned(plan), d.ldc, exact=exact, label=f"n={n} {spec} {medium}")
+        plan.destroy()
