@@ -93,10 +93,10 @@ scorch_status_t scorch_spmm_plan_workspace_bytes(int32_t m, int32_t k, int32_t n
  * holds the partial rows at execution; it must stay allocated and unmodified while the plan
  * lives.  `colidx` may be NULL; when given (device, nnz entries) it is inspected to see whether
  * every row stores its columns in strictly increasing order, which is what the panel kernel for
- * dense-ish matrices needs, and, for large B, to cut long rows by ranges of columns, one per accelerator die (with NULL, or with unsorted or repeated columns in a row, the gather
- * kernels are used).  The panel kernel (n >= 256) takes the columns of a call to be increasing as they were here; the others
- * take any.  The
- * call enqueues on `stream` and WAITS for it (it reads nnz and the list sizes back).  The plan is valid for exactly this rowptr content
+ * dense-ish matrices needs (with NULL, or with unsorted or repeated columns in a row, the gather
+ * kernels are used), and, for large B and plans too large for scorch_spmm_csr_static, to cut long rows by ranges of columns, one
+ * per accelerator die.  The panel kernel (n >= 256) takes the columns of a call to be increasing as they were here; the others
+ * take any.  The call enqueues on `stream` and WAITS for it (it reads nnz and the list sizes back).  The plan is valid for exactly this rowptr content
  * and this n, on the device that was current.
  * When B is more than three times the 256 MB memory-side cache, n >= 96 and colidx is given, the plan also counts how often
  * each column occurs and marks the most referenced columns (up to 64 MB of rows of B) as hot; execution then
@@ -164,8 +164,8 @@ scorch_status_t scorch_spmm_csr_planned_epilogue(const scorch_spmm_plan_t *plan,
  * process ends.  The call allocates nothing on the device (no hipMalloc, hipFree or allocating library routine).
  *   - A problem whose plan needs more than SCORCH_STATIC_SCRATCH_BYTES (see scorch_spmm_plan_workspace_bytes) is
  *     refused with SCORCH_ERR_UNSUPPORTED and a message naming both sizes; no work is left on the stream then.  Only the
- *     partial rows of kernels that keep chunks of B in LDS, and the pieces of rows cut by columns, may exceed it: they take
- *     turns in the array, some rows at a time.
+ *     partial rows of kernels that keep chunks of B in LDS may exceed it: they take turns in the array, block of rows by
+ *     block of rows.
  *   - The pattern is analysed at every call (the host waits for the list sizes, which are written to host memory
  *     that the library allocates at its first plan, and where they matter for a look at the columns), then the
  *     execution is enqueued and the call returns without waiting for it.

@@ -31,23 +31,18 @@ SCORCH_HOST_DEVICE inline int cut_class(int b, int finest) {
     return j < 0 ? 0 : (j < kCutClasses ? j : kCutClasses - 1);
 }
 
-// What the planner found, in the workspace.  Piece (x, s, i) of class j -- XCD x, s-th part of its columns, i-th row of the
+// What the planner found, in the workspace and in the plan.  Piece (x, s, i) of class j -- XCD x, s-th part of its columns, i-th row of the
 // class -- has the index x * pieces + piece_off[j] + s * rows[j] + i, in the order in which the XCDs take them: longest rows first,
 // one part of the columns after the other.
-struct CutHead {
+struct CutInfo {
     int32_t len;      // rows of at least this many entries are cut (INT32_MAX: none)
     int32_t pieces;   // per XCD
     int32_t n_rows;
     int32_t longest;  // longest piece; beyond `limit` the pieces are not used
     int32_t limit;
-};
-struct CutInfo : CutHead {
     int32_t rows[kCutClasses], row_off[kCutClasses], piece_off[kCutClasses];
     int32_t bound[kCutBounds];  // first column of every part of the finest division
 };
-
-// Where the rows are not cut, or one piece came out too long to be one wavefront's work, nothing is.
-SCORCH_HOST_DEVICE inline int32_t cut_len_in_use(const CutHead &c) { return c.longest <= c.limit ? c.len : INT32_MAX; }
 
 // Chooses the shortest rows to cut so that their pieces fit `cap_pieces` (over all XCDs), and lays the classes out.
 SCORCH_HOST_DEVICE inline void cut_layout(const int32_t (&rows_in)[kCutBuckets], int finest, int64_t cap_pieces, CutInfo &c) {
@@ -68,32 +63,6 @@ SCORCH_HOST_DEVICE inline void cut_layout(const int32_t (&rows_in)[kCutBuckets],
         c.n_rows += c.rows[j];
         c.pieces += c.rows[j] << j;
     }
-}
-
-// The rows that take their turn in round `turn` where only `budget` pieces per XCD (at least 2^(kCutClasses - 1)) have room at a time: the
-// next ones of the list, as a layout of their own.  false: there is no such round.
-SCORCH_HOST_DEVICE inline bool cut_turn(const CutInfo &all, int32_t budget, int32_t turn, CutInfo &c) {
-    int j = kCutClasses - 1, i = 0;
-    for (int t = 0; t <= turn; ++t) {
-        c.n_rows = c.pieces = 0;
-        for (int x = 0; x < kCutClasses; ++x) c.rows[x] = c.row_off[x] = c.piece_off[x] = 0;
-        for (; j >= 0; --j, i = 0) {
-            const int32_t left = all.rows[j] - i, fit = (budget - c.pieces) >> j;
-            c.rows[j] = left < fit ? left : fit;
-            c.row_off[j] = all.row_off[j] + i;
-            c.piece_off[j] = c.pieces;
-            c.n_rows += c.rows[j];
-            c.pieces += c.rows[j] << j;
-            i += c.rows[j];
-            if (i < all.rows[j]) break;
-        }
-        if (c.n_rows == 0) return false;
-    }
-    c.len = all.len;
-    c.limit = all.limit;
-    c.longest = 0;
-    for (int b = 0; b < kCutBounds; ++b) c.bound[b] = all.bound[b];
-    return true;
 }
 
 }  // namespace scorch

@@ -295,7 +295,6 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(const SddmmArgs a) {
     if (b < (uint32_t)a.nb_items) {
         // piece of a long row: the 4 wavefronts take interleaved chunks; entries are independent
         const int4 it = a.items[b];
-        if (CUT && a.rowptr[it.x + 1] - a.rowptr[it.x] >= a.cut_len) return;
         load_x<V, T, UA>(x, a.B + (int64_t)it.x * a.ldb, colok, coff, nmask);
         sddmm_row<V, G, T, false, UA>(x, lcol, lval, lane, grp, lig, it.y + wv * kWave, it.z, kBlock, a, Yc, colok, coff,
                                       nmask);
@@ -560,11 +559,11 @@ scorch_status_t launch_sddmm(const scorch_spmm_plan_t *plan, int32_t m, int32_t 
         if (plan->cut_pieces > 0 && V == 4) {
             fn = pick_sddmm_cut(G, T, UA);
             a.cut = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_info);
-            a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->off_cut_spans);
+            a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->layout.off_cut_spans);
             a.cut_rows = reinterpret_cast<const int32_t *>(ws + plan->layout.off_cut_rows);
             a.cut_len = plan->cut_len;
             a.cut_grid = (uint32_t)((plan->cut_pieces + kWavesPerBlock * kCutRun - 1) / (kWavesPerBlock * kCutRun)) * kXcds;
-            if (a.cut_len <= plan->params.CH + 1) a.nb_items = 0;
+            a.nb_items = 0;
         }
         grid = (int64_t)a.cut_grid + a.nb_items + a.nb_wave + a.nb_win;
     } else {

@@ -11,8 +11,7 @@
 // other columns at execution only cost reuse).  What bounds it: L2 misses, as without; 2.4 M nodes, 122 M entries, n = 100: 58.3 -> 45.0 GB
 // fetched (and 1.1 GB of partial rows written and read), 7.96 -> 6.60 ms; an LRU model of the L2s with 512 wavefronts per XCD gives
 // 58.4 -> 42.6 GB.  Rows of B are read with the default policy here: with the hot/cold split the cut rows take 4.26 instead of 3.23 ms.
-// Pieces of 8 / 16 / 32 entries in the mean: equal / best / 2 % slower.  Everything the planner finds stays on the device (CutInfo), so that a one-shot call
-// does not wait for it.
+// Pieces of 8 / 16 / 32 entries in the mean: equal / best / 2 % slower.
 #include "device_util.h"
 #include "spmm_internal.h"
 
@@ -27,7 +26,7 @@ struct CutPlanArgs {
     int32_t tiles_per_block;
     int32_t finest;  // see cut_class
     int32_t shift;   // columns per histogram bin (log2)
-    int64_t cap_layout, cap_pieces;  // pieces that are laid out at most; room for the ranges of so many
+    int64_t cap_pieces;  // room for so many
     int32_t *counts;  // [kCutBuckets][workgroups]
     int32_t *hist;
     CutInfo *info;
@@ -106,7 +105,7 @@ __global__ __launch_bounds__(kBlock) void cut_layout_kernel(const CutPlanArgs a,
         CutInfo c{};
         int rows[kCutBuckets];
         for (int b = 0; b < kCutBuckets; ++b) rows[b] = s_rows[b];
-        cut_layout(rows, a.finest, a.cap_layout, c);
+        cut_layout(rows, a.finest, a.cap_pieces, c);
         int64_t entries = 0;  // of the rows that are cut, about
         for (int b = 0; b < kCutBuckets; ++b)
             if (cut_bucket_len(b) >= c.len) entries += (int64_t)rows[b] * cut_bucket_len(b) * 5 / 4;
@@ -183,7 +182,7 @@ __global__ __launch_bounds__(kBlock) void cut_list_kernel(const CutPlanArgs a) {
     }
 }
 
-// Class of the r-th row of a layout, and its place among the layout's rows of the class.
+// Class of the r-th row that is cut, and its place among the rows of the class.
 __device__ __forceinline__ int class_of_row(const CutInfo &c, int r, int &i) {
     int j = kCutClasses - 1;
     while (j > 0 && r >= c.rows[j]) r -= c.rows[j--];
@@ -239,13 +238,8 @@ __global__ __launch_bounds__(kBlock) void cut_span_kernel(const CutPlanArgs a) {
     if (lane == 0 && longest > 0) atomicMax(&a.info->longest, longest);
 }
 
-// One thread: the layout of the rows of a round.
-__global__ void cut_turn_kernel(const CutInfo *all, int32_t budget, int32_t turn, CutInfo *out) {
-    CutInfo c{};
-    if (cut_turn(*all, budget, turn, c)) *out = c;
-}
-
-static CutPlanArgs cut_plan_args(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx) {
+scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, PlanResult *result,
+                                hipStream_t stream) {
     const WorkspaceLayout &L = plan->layout;
     char *ws = plan->workspace;
     const int64_t tiles = ((int64_t)plan->m + kBlock - 1) / kBlock;
@@ -258,22 +252,14 @@ static CutPlanArgs cut_plan_args(const scorch_spmm_plan_t *plan, const int32_t *
     a.tiles_per_block = (int32_t)((tiles + kPlanBlocksMax - 1) / kPlanBlocksMax);
     a.finest = plan->params.CUTJ;
     while (((int64_t)(plan->k - 1) >> a.shift) >= kCutBins) ++a.shift;
-    a.cap_pieces = a.cap_layout = L.cap_cut;
+    a.cap_pieces = L.cap_cut;
     a.counts = reinterpret_cast<int32_t *>(ws + L.off_cut_counts);
     a.hist = reinterpret_cast<int32_t *>(ws + L.off_cut_hist);
     a.info = reinterpret_cast<CutInfo *>(ws + L.off_cut_info);
     a.rows = reinterpret_cast<int32_t *>(ws + L.off_cut_rows);
-    a.spans = reinterpret_cast<int2 *>(ws + plan->off_cut_spans);
+    a.spans = reinterpret_cast<int2 *>(ws + L.off_cut_spans);
     a.max_len = plan->params.CH + 1;
     a.max_rows = (int32_t)(L.cap_cut / kXcds);
-    return a;
-}
-
-scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int64_t cap_pieces,
-                                PlanResult *result, hipStream_t stream) {
-    CutPlanArgs a = cut_plan_args(plan, rowptr, colidx);
-    a.cap_pieces = cap_pieces;
-    const int64_t tiles = ((int64_t)plan->m + kBlock - 1) / kBlock;
     const uint32_t nblk = (uint32_t)((tiles + a.tiles_per_block - 1) / a.tiles_per_block);
     const uint32_t g = (uint32_t)std::min<int64_t>(std::max<int64_t>(1, (a.max_rows + kWavesPerBlock - 1) / kWavesPerBlock), 256 * 8);
     hipLaunchKernelGGL(cut_count_kernel, dim3(nblk), dim3(kBlock), 0, stream, a);
@@ -281,22 +267,8 @@ scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *r
     hipLaunchKernelGGL(cut_list_kernel, dim3(nblk), dim3(kBlock), 0, stream, a);
     hipLaunchKernelGGL(cut_span_kernel, dim3(g), dim3(kBlock), 0, stream, a);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && result)
-        e = hipMemcpyAsync(&result->cut, a.info, sizeof(result->cut), hipMemcpyDeviceToHost, stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(&result->cut, a.info, sizeof(result->cut), hipMemcpyDeviceToHost, stream);
     if (e != hipSuccess) return hip_fail(e, "launch the kernels that cut rows");
-    return SCORCH_OK;
-}
-
-scorch_status_t launch_cut_turn(const scorch_spmm_plan_t *plan, int32_t turn, const int32_t *rowptr, const int32_t *colidx, hipStream_t stream) {
-    CutPlanArgs a = cut_plan_args(plan, rowptr, colidx);
-    const CutInfo *all = a.info;
-    a.info = reinterpret_cast<CutInfo *>(plan->workspace + plan->layout.off_cut_turn);
-    a.cap_pieces = (int64_t)plan->cut_budget * kXcds;
-    const uint32_t g = (uint32_t)std::min<int64_t>((plan->cut_budget + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 8);
-    hipLaunchKernelGGL(cut_turn_kernel, dim3(1), dim3(1), 0, stream, all, plan->cut_budget, turn, a.info);
-    hipLaunchKernelGGL(cut_span_kernel, dim3(g), dim3(kBlock), 0, stream, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "launch the kernels of a round of cut rows");
     return SCORCH_OK;
 }
 
@@ -317,7 +289,6 @@ struct CutSumArgs {
 __global__ __launch_bounds__(kBlock) void cut_sum_kernel(const CutSumArgs a) {
     typedef float f4 __attribute__((ext_vector_type(4)));
     const CutInfo &c = *a.cut;
-    if (c.longest > c.limit) return;
     const int per_block = kBlock / a.team;
     const int r = (int)blockIdx.x * per_block + (int)threadIdx.x / a.team;
     if (r >= c.n_rows) return;
@@ -364,13 +335,12 @@ __global__ __launch_bounds__(kBlock) void cut_sum_kernel(const CutSumArgs a) {
     }
 }
 
-scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, const CutInfo *info, int32_t max_rows, float *C, int64_t ldc, const float *bias,
-                               int32_t act, hipStream_t stream) {
+scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream) {
     const char *ws = plan->workspace;
     CutSumArgs a{};
-    a.cut = info;
+    a.cut = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_info);
     a.rows = reinterpret_cast<const int32_t *>(ws + plan->layout.off_cut_rows);
-    a.partials = reinterpret_cast<const float *>(ws + plan->off_cut_partials);
+    a.partials = reinterpret_cast<const float *>(ws + plan->layout.off_cut_partials);
     a.C = C;
     a.ldc = ldc;
     a.n = plan->n;
@@ -381,7 +351,7 @@ scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, const CutInfo *in
     a.act = act;
     a.aligned = plan->n % 4 == 0 && ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0;
     const int per_block = kBlock / a.team;
-    const uint32_t grid = (uint32_t)((max_rows + per_block - 1) / per_block);
+    const uint32_t grid = (uint32_t)((plan->cut_rows + per_block - 1) / per_block);
     hipLaunchKernelGGL(cut_sum_kernel, dim3(grid), dim3(kBlock), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "launch cut_sum_kernel");

@@ -276,11 +276,10 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
         // ---- pieces of rows cut by columns: kCutRun of them per wavefront, each to its partial row ----
         // Rows of B are read with the default cache policy here whatever the variant: they are used again.
         const int x = (int)(blockIdx.x & (kXcds - 1));
-        const int pieces = cut_len_in_use(*a.cut) == INT32_MAX ? 0 : a.cut->pieces;
         const int q0 = ((int)b * kWavesPerBlock + wv) * kCutRun;
-        const int nq = min(kCutRun, pieces - q0);
+        const int nq = min(kCutRun, a.cut_pieces - q0);
         if (nq <= 0) return;
-        const int64_t first = (int64_t)x * pieces + q0;
+        const int64_t first = (int64_t)x * a.cut_pieces + q0;
         const int2 span = a.cut_spans[first + min(lane, nq - 1)];
         // a piece of up to kCutShort entries is one lane group's (the sum of a piece depends on nothing but the piece)
         const int whole = lane < nq ? span.y - span.x : 0;
@@ -341,12 +340,10 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
         }
         return;
     }
-    const int cut_len = CUT ? cut_len_in_use(*a.cut) : INT32_MAX;
 
     if (b < (uint32_t)a.nb_items) {
         // ---- piece of a long row: 4 wavefronts, LDS tree, then C or a partial row ----
         const int4 it = a.items[b];
-        if (CUT && a.rowptr[it.x + 1] - a.rowptr[it.x] >= cut_len) return;
         row_accumulate<V, G, T, U, NTA, UA, HOT, COLD>(acc, lcol, lval, lane, grp, it.y + wv * kWave, it.z, kBlock, a.colidx,
                                                        a.vals, Bc, ldb, colok[0], boff, a.hotmask, cp);
         reduce_groups<V, G, T>(acc);
@@ -428,7 +425,7 @@ __global__ __launch_bounds__(kBlock) void spmm_fused_kernel(const ExecArgs a) {
         const int row = a.wave_rows[idx];
         const int2 span = a.wave_span[idx];  // the row's entry range, kept in the plan beside its id
         const int p0 = span.x, p1 = span.y;
-        if (CUT && p1 - p0 >= cut_len) return;
+        if (CUT && p1 - p0 >= a.cut_len) return;
         row_accumulate<V, G, T, U, NTA, UA, HOT, COLD>(acc, lcol, lval, lane, grp, p0, p1, kWave, a.colidx, a.vals, Bc, ldb,
                                                        colok[0], boff, a.hotmask, cp);
         reduce_groups<V, G, T>(acc);
@@ -849,7 +846,6 @@ __global__ __launch_bounds__(kBlock) void spmm_fixup_kernel(const FixupArgs a) {
     const int s = blockIdx.x;
     if (s >= a.n_split) return;
     const int4 d = a.split[s];
-    if (a.cut && a.rowptr[d.x + 1] - a.rowptr[d.x] >= cut_len_in_use(*a.cut)) return;
     const float *src = a.partials + (int64_t)d.y * a.partial_stride;
     float *dst = a.C + (int64_t)d.x * a.ldc;
     for (int c = threadIdx.x; c < a.n; c += kBlock) {
@@ -1043,14 +1039,14 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
     a.xcd_slices = mp.xcd_slices;
     a.bias = bias;
     a.act = act;
-    // every row that the plan keeps among the pieces is cut by columns instead
-    const bool no_items = plan->cut_pieces > 0 && plan->cut_len > 0 && plan->cut_len <= plan->params.CH + 1;
-    if (plan->cut_pieces > 0) {
-        a.cut = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_info);
-        a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->off_cut_spans);
-        a.cut_partials = reinterpret_cast<float *>(ws + plan->off_cut_partials);
-        a.cut_wgs = (int32_t)ceil_div64(plan->cut_turns > 0 ? plan->cut_budget : plan->cut_pieces, kWavesPerBlock * kCutRun);
-        if (no_items) a.nb_items = 0;
+    const bool cut = plan->cut_pieces > 0;
+    if (cut) {
+        a.cut_spans = reinterpret_cast<const int2 *>(ws + plan->layout.off_cut_spans);
+        a.cut_partials = reinterpret_cast<float *>(ws + plan->layout.off_cut_partials);
+        a.cut_pieces = plan->cut_pieces;
+        a.cut_len = plan->cut_len;
+        a.cut_wgs = (int32_t)ceil_div64(plan->cut_pieces, kWavesPerBlock * kCutRun);
+        a.nb_items = 0;  // every row among the items is cut by columns instead
     }
     const int64_t per_tile = (int64_t)a.nb_items + a.nb_wave + a.nb_win;
     const int64_t grid = grid_size(mp, per_tile) + (int64_t)a.cut_wgs * mp.ncoltiles * kXcds;
@@ -1067,7 +1063,7 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
         a.b_tile_stride = (int64_t)plan->k * kSliceCols;
     }
     if (grid > 0) {
-        kernel_fn fn = a.cut        ? pick_fused_cut(mp.G, mp.T, mp.UA, false)
+        kernel_fn fn = cut          ? pick_fused_cut(mp.G, mp.T, mp.UA, false)
                        : whole_rows ? pick_fused_whole(mp.V, plan->params.U, plan->params.NT)
                                     : pick_fused(mp.V, mp.G, mp.T, plan->params.U, plan->params.NT, mp.UA);
         if (plan->n_hot > 0 && mp.V == 4 && !mp.UA && mp.xcd_slices == 0 && mp.G >= 8 && plan->params.U >= 8 &&
@@ -1075,38 +1071,15 @@ scorch_status_t launch_planned(const scorch_spmm_plan_t *plan, const int32_t *ro
             // hot/cold variant: rows of B outside the plan's hot set are read with the streaming policy
             a.hotmask = reinterpret_cast<const uint32_t *>(ws + plan->layout.off_hotmask);
             a.b_bytes = (int64_t)plan->k * ldb * 4;
-            fn = a.cut ? pick_fused_cut(mp.G, mp.T, false, true) : pick_fused_hot(mp.G, mp.T, a.b_bytes < (1ll << 32) ? plan->tuning.cold : 0);
+            fn = cut ? pick_fused_cut(mp.G, mp.T, false, true) : pick_fused_hot(mp.G, mp.T, a.b_bytes < (1ll << 32) ? plan->tuning.cold : 0);
         }
-        if (plan->cut_turns > 0) {
-            // the pieces round by round: their ranges, the pieces, their sums; then the other rows
-            const CutInfo *info = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_turn);
-            ExecArgs r = a;
-            r.cut = info;
-            r.nb_items = r.nb_wave = r.nb_win = 0;
-            const uint32_t cuts = (uint32_t)((int64_t)a.cut_wgs * mp.ncoltiles * kXcds);
-            for (int32_t turn = 0; turn < plan->cut_turns; ++turn) {
-                scorch_status_t st = launch_cut_turn(plan, turn, rowptr, colidx, stream);
-                if (st != SCORCH_OK) return st;
-                hipLaunchKernelGGL(fn, dim3(cuts), dim3(kBlock), 0, stream, r);
-                hipError_t e = hipGetLastError();
-                if (e != hipSuccess) return hip_fail(e, "launch spmm_fused_kernel");
-                if ((st = launch_cut_sum(plan, info, plan->cut_budget, C, ldc, bias, act, stream)) != SCORCH_OK) return st;
-            }
-            a.cut_wgs = 0;
-        }
-        const int64_t left = per_tile > 0 || a.cut_wgs > 0 ? grid_size(mp, per_tile) + (int64_t)a.cut_wgs * mp.ncoltiles * kXcds : 0;
-        if (left > 0) hipLaunchKernelGGL(fn, dim3((uint32_t)left), dim3(kBlock), 0, stream, a);
+        hipLaunchKernelGGL(fn, dim3((uint32_t)grid), dim3(kBlock), 0, stream, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "launch spmm_fused_kernel");
     }
-    if (plan->cut_pieces > 0 && plan->cut_turns == 0) {
-        scorch_status_t st = launch_cut_sum(plan, a.cut, plan->cut_rows, C, ldc, bias, act, stream);
-        if (st != SCORCH_OK) return st;
-    }
-    if (plan->n_split > 0 && !fold && !no_items) {
+    if (cut) return launch_cut_sum(plan, C, ldc, bias, act, stream);
+    if (plan->n_split > 0 && !fold) {
         FixupArgs f{};
-        f.rowptr = rowptr;
-        f.cut = a.cut;
         f.split = reinterpret_cast<const int4 *>(ws + plan->layout.off_split);
         f.partials = a.partials;
         f.C = C;

@@ -46,7 +46,7 @@ struct PlanParams {
     int32_t PDIRECT; // panel kernel: 1 = fetch the panels from the caller's row-major B instead of a tile-major copy
     int32_t RES;    // >0: narrow B kept in LDS in chunks (spmm_resident.hip), rows padded to this many columns
     int32_t RESC;   // resident kernel: chunks of B
-    int32_t CUT;    // 1: long rows are cut by columns, a range of columns per XCD (spmm_cut.hip)
+    int32_t CUT;    // 1: long rows are cut by columns, a range of columns per XCD (spmm_cut.hip), if layout_workspace has room for them; 2: the same, forced
     int32_t CUTJ;   // finest class for the sake of reuse (see cut_class)
     int32_t HOT;    // >0: budget in KB for the most referenced rows of B, which alone keep the default cache policy
 };
@@ -58,8 +58,7 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
 struct WorkspaceLayout {
     uint64_t off_counts, off_totals, off_win, off_stage, off_wave, off_wave_span, off_items, off_split, off_partials, off_tickets, off_bpack,
         off_res_ptr, off_coldeg, off_hotmask, off_degbins, off_res_partials,
-        off_cut_info, off_cut_turn, off_cut_counts, off_cut_hist, off_cut_rows, off_cut_spans, off_cut_partials, total;
-    uint64_t off_turns;      // what a one-shot plan cannot do without ends here: partial rows after it may take turns
+        off_cut_info, off_cut_counts, off_cut_hist, off_cut_rows, off_cut_spans, off_cut_partials, total;
     uint64_t res_row_bytes;  // resident kernel: partial rows of one row of A (0: none, B fits one chunk)
     int64_t ticket_tiles;  // arrival counters per split row: one for every column tile a launch may use
     int64_t n_windows, nblk;
@@ -109,9 +108,10 @@ struct ExecArgs {
     int32_t rows_per_wave;    // plan-free kernel only: consecutive rows taken by one wavefront (a power of two)
     int32_t scout_shift;      // plan-free kernel only: see scouts.h (nb_items: the scouts)
     float one_over_m;
-    const CutInfo *cut;       // rows cut by columns (nullptr: none)
-    const int2 *cut_spans;    // entry range of every piece
+    const int2 *cut_spans;    // rows cut by columns: entry range of every piece
     float *cut_partials;
+    int32_t cut_pieces;       // per XCD
+    int32_t cut_len;          // rows of at least this many entries are cut
     int32_t cut_wgs;          // workgroups for them, per XCD and column tile (a multiple of 8 in all: they are the first of the grid)
     int64_t b_bytes;          // size of B in bytes (cache-policy experiments of the hot/cold variants only)
 };
@@ -162,8 +162,6 @@ struct FixupArgs {
     int32_t n, n_split, partial_stride;
     const float *bias;
     int32_t act;
-    const int32_t *rowptr;
-    const CutInfo *cut;  // rows cut by columns are left out (nullptr: there are none)
 };
 
 #if defined(__HIPCC__)
@@ -195,10 +193,8 @@ struct scorch_spmm_plan_s {
     uint64_t off_res_partials;  // resident kernel: where the partial rows of res_rows rows of A stand, as many as are taken at a time
     int32_t res_rows;
     int32_t n_hot;    // columns marked hot (0: every gather uses the default cache policy)
-    int32_t cut_pieces, cut_rows;  // rows cut by columns: pieces per XCD and rows, or upper bounds (one-shot plan); 0: none
-    int32_t cut_len;               // shortest of them (one-shot plan: not known)
-    int32_t cut_budget, cut_turns; // one-shot plan without room for all pieces: pieces per XCD at a time, and rounds (0: all at once)
-    uint64_t off_cut_spans, off_cut_partials;
+    int32_t cut_pieces, cut_rows;  // rows cut by columns: pieces per XCD, and rows (0: none)
+    int32_t cut_len;               // shortest of them; no longer than CH + 1, so that no row is left to the items
     float hot_share;  // share of the stored entries that point at a hot column
 };
 
@@ -243,13 +239,9 @@ scorch_status_t launch_resident(const scorch_spmm_plan_t *plan, const int32_t *c
 constexpr int kPlanBlocksMax = 1024;  // workgroups of a planning kernel
 constexpr int kCutRun = 4;            // pieces per wavefront
 constexpr int kCutShort = 32;         // pieces of up to so many entries are one lane group's
-// cap_pieces: room for the ranges of so many pieces (0: none are written); result: where the outcome is copied to, or nullptr
-scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, int64_t cap_pieces,
-                                PlanResult *result, hipStream_t stream);
-scorch_status_t launch_cut_turn(const scorch_spmm_plan_t *plan, int32_t turn, const int32_t *rowptr, const int32_t *colidx, hipStream_t stream);
-// info: the layout the pieces were made for (that of all rows, or of a round), max_rows rows at most
-scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, const CutInfo *info, int32_t max_rows, float *C, int64_t ldc, const float *bias,
-                               int32_t act, hipStream_t stream);
+scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *rowptr, const int32_t *colidx, PlanResult *result,
+                                hipStream_t stream);  // the outcome is copied to *result
+scorch_status_t launch_cut_sum(const scorch_spmm_plan_t *plan, float *C, int64_t ldc, const float *bias, int32_t act, hipStream_t stream);
 
 // sddmm_exec.hip (plan == nullptr: plan-free, one wavefront per row)
 scorch_status_t launch_sddmm(const scorch_spmm_plan_t *plan, int32_t m, int32_t d, const int32_t *rowptr,

@@ -569,13 +569,15 @@ __host__ __device__ static int32_t resident_balance(int32_t m, int32_t k, int64_
 constexpr int64_t kCutNnzMin = 1 << 20;
 
 // Cutting long rows by columns (spmm_cut.hip) pays where B is as large as the 8 L2s (32 MB) together, a row of it is more than one
-// 128-byte line, and the gathers are more than the second launch's 4 us.  Measured without / with, us: graph of 2.4 M nodes, degree 50,
-// n = 100 7960 / 6600; 1 M, 50, n = 64 1703 / 1336; 100 000, 50, n = 100 253 / 212; 400 000, 12, n = 33 141 / 130; 169 343, 15, n = 128
-// 121 / 111 (operands that change from call to call: 125 / 125), n = 100 126 / 113, n = 48 (32 MB) 62.5 / 60.9.  Rows that are all long, where
-// neither slices (n not a multiple of 4) nor panels serve: 4096 x 16 384, 10 % stored, n = 1001 3012 / 1158; 10 000 x 40 000, 3 %,
-// n = 229 1681 / 550; from 8 MB on where the mean row leaves 40 entries for a piece: 4000 x 8000, 5 %, n = 333 180 / 117; 1024 x 16 384, 50 %,
-// n = 201 628 / 293; 10 000 x 40 000, 1 %, n = 51 90 / 58; but rows of 164, n = 129 (8 MB) 95 / 109.  Not: n = 32, 169 343 (21 MB) 39.8 / 46.2, 2.4 M nodes of degree 3 212 / 225; 1.3 M entries, n = 64 41.1 / 43.7;
-// with 32-column slices (SLICED = 32) 121 / 145.  Plans get dearer by 0.1 ms (2.5 M entries) to 0.7 ms (122 M).
+// 128-byte line, and the gathers are more than the second launch's 4 us.  Not where a smaller plan would do (see layout_workspace).
+// Measured whole / cut, us, and what the plan takes longer: graph of 2.4 M nodes, degree 50, n = 100 7954 / 6673 (0.6 ms); 1 M, 50, n = 64
+// 1687 / 1345 (0.4); 300 000, 50, n = 100 952 / 708 (0.35); 600 000, 30, n = 100 1178 / 970 (0.35); 2.4 M, 20, n = 33 1556 / 1341 (0.4); 2.4 M, 10,
+// n = 64 849 / 794 (0.35); no row of 128 entries 0.06 ms for nothing.  Rows that are all long, where neither slices (n not a multiple of 4) nor
+// panels serve: 4096 x 16 384, 10 % stored, n = 1001 3026 / 1124 (0.13); 10 000 x 40 000, 3 %, n = 229 1678 / 501 (0.3); from 8 MB on where the mean
+// row leaves 40 entries for a piece: 8000 x 16 384, 5 %, n = 333 975 / 415 (0.27); 16 384 x 2000, 30 %, n = 1501 2411 / 2210 (0.3); 1500 x 8000, 30 %,
+// n = 1001 1561 / 541 (0.07); with less, rows of 164, n = 129 (8 MB) 95 / 109.  B below 8 MB can gain too (3000 x 12 000, 10 %, n = 101, 4.8 MB 122 / 73) but is
+// left alone: such plans are small.  Not: n = 32, 169 343 rows (21 MB) 39.8 / 46.2, 2.4 M nodes of degree 3 212 / 225; 1.3 M entries, n = 64 41.1 / 43.7;
+// with 32-column slices (SLICED = 32) 121 / 145.
 __host__ __device__ static bool want_cut(int32_t m, int32_t k, int64_t nnz, int32_t n, int32_t sliced) {
     const int64_t b_bytes = (int64_t)k * n * 4;
     return n > 32 && nnz * n >= 100000000 && (sliced == 0 || sliced == 64) &&
@@ -584,7 +586,7 @@ __host__ __device__ static bool want_cut(int32_t m, int32_t k, int64_t nnz, int3
 
 // Bytes that a plan cannot do without.
 __host__ __device__ static uint64_t bytes_needed(const WorkspaceLayout &L, bool one_shot) {
-    return one_shot ? L.off_turns : L.total;
+    return !one_shot ? L.total : L.cap_cut > 0 ? L.total : L.off_res_partials;
 }
 
 // Rows of A whose partial rows fit at a time, and where they stand (`off`), in a workspace of `bytes` that only a one-shot plan
@@ -597,19 +599,6 @@ __host__ __device__ static int32_t partial_rows_in(const WorkspaceLayout &L, int
         room = L.off_res_ptr;
     }
     return room >= L.res_row_bytes * m ? m : (int32_t)(room / L.res_row_bytes);
-}
-
-// Bytes that the ranges and partial rows of some pieces take.
-__host__ __device__ static uint64_t cut_room(const WorkspaceLayout &L, int64_t pieces) {
-    return ((uint64_t)pieces * 8 + 255) / 256 * 256 + (uint64_t)pieces * L.partial_stride * 4;
-}
-
-// Where the pieces of a round stand, and how many bytes there are for them: behind everything else, or in the place of the partial rows
-// of the pieces of at most BCH entries, of which there are none when rows are cut by columns (see CutPlanArgs::max_len).
-__host__ __device__ static uint64_t cut_turns_room(const WorkspaceLayout &L, uint64_t bytes, uint64_t &off) {
-    const uint64_t behind = bytes - L.off_cut_spans, instead = L.off_bpack - L.off_partials;
-    off = behind >= instead ? L.off_cut_spans : L.off_partials;
-    return behind >= instead ? behind : instead;
 }
 
 __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t) {
@@ -645,7 +634,7 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     p.CUT = p.CUTJ = 0;
     if ((nnz >= kCutNnzMin && t.cut != 0) || t.cut > 0) {  // the planning kernels evaluate this: one comparison for small matrices
         const bool possible = m > 0 && k > 0 && n > 16 && p.PANEL == 0 && p.RES == 0 && p.PACK == 0 && t.fix <= 0 && t.u <= 0 && t.nt < 0;
-        p.CUT = possible && (t.cut > 0 || want_cut(m, k, nnz, n, p.SLICED)) ? 1 : 0;
+        p.CUT = !possible ? 0 : t.cut > 0 ? 2 : want_cut(m, k, nnz, n, p.SLICED) ? 1 : 0;
         // parts of the columns of an XCD, up to 16 MB of B each: 122 MB in 1 / 4 / 8 / 16 parts 7100 / 6690 / 6600 / 6720 us,
         // 32 MB in 1 / 2 / 4 / 8 1356 / 1336 / 1356 / 1391, 5 MB in 1 / 2 / 4 212 / 226 / 237
         const int64_t xcd_bytes = (int64_t)k * (p.SLICED ? p.SLICED : n) * 4 / kXcds;
@@ -686,17 +675,6 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     p.RESC = p.RES ? resident_balance(m, k, nnz, p.RES) : 0;
     // scorch_spmm_csr_static takes what the gather kernels need no more than its scratch for, and gives the planned call's
     // bits: where the resident kernel does not run in the scratch either, it runs nowhere.
-    if (p.CUT) {
-        PlanParams gather = p;
-        gather.CUT = 0;
-        if (layout_workspace(m, k, nnz, n, gather).total <= SCORCH_STATIC_SCRATCH_BYTES) {
-            const WorkspaceLayout L = layout_workspace(m, k, nnz, n, p);
-            uint64_t off;
-            if (L.off_turns > SCORCH_STATIC_SCRATCH_BYTES ||
-                cut_turns_room(L, SCORCH_STATIC_SCRATCH_BYTES, off) < std::max<uint64_t>(2 << 20, cut_room(L, kCutBounds)))
-                p.CUT = 0;
-        }
-    }
     if (p.RES) {
         PlanParams gather = p;
         gather.RES = 0;
@@ -759,13 +737,17 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
     if (p.HOT) off = align_up(off + ((uint64_t)k / 32 + 2) * 4, 256);
     L.off_degbins = off;
     if (p.HOT) off = align_up(off + (uint64_t)kDegBins * 16, 256);
+    L.off_res_partials = off;  // a one-shot plan has fewer of them
+    off = align_up(off + L.res_row_bytes * m, 256);
     L.off_cut_info = off;
     // pieces of rows cut by columns: as many as cut_class gives at most; one for 40 stored entries at most where B is so large that an
     // XCD's range is divided (2.4 M nodes, 122 M entries: one for 20 / 40 / 64 6659 / 6625 / 6681 us), else one for 16
-    if (p.CUT) L.cap_cut = std::min<int64_t>(nnz / (p.CUTJ > 0 ? 40 : 16), std::min<int64_t>(m, nnz / kCutMinLen) * (kXcds << p.CUTJ) + nnz / 128);
+    // scorch_spmm_csr_static gives the planned call's bits and analyses at every call, so that no rows are cut where it serves.  One call, us,
+    // whole / cut: 169 343 rows of 15, n = 128 142 / 298; 100 000 of 50, n = 100 265 / 674; 4000 x 8000, 5 %, n = 333 200 / 390; 10 000 x 40 000, 3 %,
+    // n = 61 402 / 696 (the product alone 120 / 113, 246 / 194, 180 / 115, 377 / 158).
+    if (p.CUT == 2 || (p.CUT == 1 && off > SCORCH_STATIC_SCRATCH_BYTES))
+        L.cap_cut = std::min<int64_t>(nnz / (p.CUTJ > 0 ? 40 : 16), std::min<int64_t>(m, nnz / kCutMinLen) * (kXcds << p.CUTJ) + nnz / 128);
     if (L.cap_cut > 0) {
-        off = align_up(off + sizeof(CutInfo), 256);
-        L.off_cut_turn = off;
         off = align_up(off + sizeof(CutInfo), 256);
         L.off_cut_counts = off;
         off = align_up(off + (uint64_t)kCutBuckets * kPlanBlocksMax * 4, 256);
@@ -773,14 +755,11 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
         off = align_up(off + (uint64_t)kCutBins * 4, 256);
         L.off_cut_rows = off;
         off = align_up(off + (uint64_t)L.cap_cut / kXcds * 4, 256);
-        L.off_turns = L.off_cut_spans = off;
+        L.off_cut_spans = off;
         off = align_up(off + (uint64_t)L.cap_cut * 8, 256);
         L.off_cut_partials = off;
         off = align_up(off + (uint64_t)L.cap_cut * L.partial_stride * 4, 256);
     }
-    L.off_res_partials = off;  // last: a one-shot plan has fewer of them
-    if (L.off_turns == 0) L.off_turns = off;
-    off = align_up(off + L.res_row_bytes * m, 256);
     L.total = std::max<uint64_t>(off, 256);
     return L;
 }
@@ -917,40 +896,20 @@ static scorch_status_t build_plan_in(PlanResult *result, bool *lost, scorch_spmm
     }
     plan->cut_pieces = plan->cut_rows = 0;
     plan->cut_len = 0;
-    plan->cut_budget = plan->cut_turns = 0;
     if (plan->params.CUT && L.cap_cut > 0) {
-        // A one-shot plan with room for as many pieces as there can be leaves what it finds on the device; with less, it looks how many
-        // there are and lets the rows take turns.
-        int64_t cap = L.cap_cut;
-        plan->off_cut_spans = L.off_cut_spans;
-        if (L.off_cut_spans + cut_room(L, cap) > workspace_bytes) {
-            const uint64_t room = cut_turns_room(L, workspace_bytes, plan->off_cut_spans);
-            cap = std::min<int64_t>(cap - kXcds, (int64_t)((room - 256) / (8 + (uint64_t)L.partial_stride * 4))) / kXcds * kXcds;
-        }
-        const bool all = cap == L.cap_cut;
-        plan->off_cut_partials = align_up(plan->off_cut_spans + (uint64_t)cap * 8, 256);
-        st = launch_plan_cut(plan, rowptr, colidx, all ? cap : 0, one_shot && all ? nullptr : result, stream);
+        st = launch_plan_cut(plan, rowptr, colidx, result, stream);
         if (st != SCORCH_OK) return st;
-        if (one_shot && all) {
-            plan->cut_pieces = (int32_t)(L.cap_cut / kXcds);
-            plan->cut_rows = (int32_t)(L.cap_cut / kXcds);
-        } else {
-            e = hipStreamSynchronize(stream);
-            if (e != hipSuccess) {
-                *lost = true;
-                return hip_fail(e, "wait for the kernels that cut rows");
-            }
-            const CutInfo &c = result->cut;
-            if (cut_len_in_use(c) != INT32_MAX) {
-                plan->cut_pieces = c.pieces;
-                plan->cut_rows = c.n_rows;
-                plan->cut_len = c.len;
-                if (!all) {
-                    plan->cut_budget = (int32_t)(cap / kXcds);
-                    CutInfo round;
-                    while (cut_turn(c, plan->cut_budget, plan->cut_turns, round)) ++plan->cut_turns;
-                }
-            }
+        e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) {
+            *lost = true;
+            return hip_fail(e, "wait for the kernels that cut rows");
+        }
+        // where a piece came out too long to be one wavefront's work, no row is cut
+        const CutInfo &c = result->cut;
+        if (c.len != INT32_MAX && c.longest <= c.limit) {
+            plan->cut_pieces = c.pieces;
+            plan->cut_rows = c.n_rows;
+            plan->cut_len = c.len;
         }
     }
     plan->n_hot = 0;

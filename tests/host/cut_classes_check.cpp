@@ -54,26 +54,6 @@ int main() {
         }
         EXPECT(row == c.n_rows);
         for (char x : seen) EXPECT(x);
-        // rounds: every row once, in the list's order within its class, never more pieces than fit
-        const int32_t budget = (1 << (kCutClasses - 1)) + (int32_t)(rng() % 200);
-        std::vector<char> row_seen(c.n_rows, 0);
-        CutInfo r{};
-        for (int32_t turn = 0; cut_turn(c, budget, turn, r); ++turn) {
-            EXPECT(r.n_rows > 0 && r.pieces <= budget && r.len == c.len && r.longest == 0);
-            int place = 0, rows_of_round = 0;
-            for (int j = kCutClasses - 1; j >= 0; --j) {
-                if (r.rows[j] > 0) EXPECT(r.piece_off[j] == place);
-                place += r.rows[j] << j;
-                rows_of_round += r.rows[j];
-                for (int i = 0; i < r.rows[j]; ++i) {
-                    const int q = r.row_off[j] + i;
-                    EXPECT(q >= c.row_off[j] && q < c.row_off[j] + c.rows[j] && !row_seen[q]);
-                    row_seen[q] = 1;
-                }
-            }
-            EXPECT(place == r.pieces && rows_of_round == r.n_rows && turn < 10000);
-        }
-        for (char x : row_seen) EXPECT(x);
     }
     std::printf("ok\n");
     return 0;

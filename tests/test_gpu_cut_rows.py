@@ -84,26 +84,25 @@ def test_cut_rows_of_any_columns_and_the_one_shot_call(kind):
         plan.destroy()
 
 
-@pytest.mark.parametrize("n", [100, 101])
-def test_cut_rows_by_the_planners_own_choice_in_all_calls_and_graphs(n):
-    """A matrix large enough for it, skewed rows: planned, one-shot and replayed calls agree to the bit."""
+@pytest.mark.parametrize("n", [1001, 1002])
+def test_cut_rows_by_the_planners_own_choice_and_in_graphs(n):
+    """A matrix large enough for it, skewed rows: planned and replayed calls agree to the bit; the one-shot call does not serve it."""
     rng = np.random.default_rng(n)
-    lens = np.minimum(3000, (4.0 / rng.random(90000) ** 0.7).astype(np.int64))
-    p = csr_from_row_lengths(lens, 90000, n, seed=n)
+    lens = np.minimum(6000, (36.0 / rng.random(24000) ** 0.7).astype(np.int64))
+    p = csr_from_row_lengths(lens, 24000, n, seed=n)
     assert p.nnz >= 1 << 20
     d = DeviceProblem(p)
     plan = d.make_plan()
     got = d.run_planned(plan)
-    check_against_oracle(p, got, d.ldc, rows=np.argsort(lens)[-300:], label="longest rows")
-    check_against_oracle(p, got, d.ldc, rows=rng.integers(0, p.m, size=500), label="any rows")
+    check_against_oracle(p, got, d.ldc, rows=np.argsort(lens)[-100:], label="longest rows")
+    check_against_oracle(p, got, d.ldc, rows=rng.integers(0, p.m, size=200), label="any rows")
     with tuning("cut=0"):
         whole = d.make_plan()
+    assert whole.info().workspace_bytes_used > sp.STATIC_SCRATCH_BYTES
     assert not np.array_equal(d.run_planned(whole), got)
     whole.destroy()
-    d.reset_C()
-    sp.scorch_spmm_csr_static(p.m, p.k, p.n, d.rowptr, d.colidx, d.vals, d._B_arg(), d._C_arg())
-    torch.cuda.synchronize()
-    assert np.array_equal(d.Cfull.cpu().numpy(), got)
+    with pytest.raises(sp.ScorchError):
+        sp.scorch_spmm_csr_static(p.m, p.k, p.n, d.rowptr, d.colidx, d.vals, d._B_arg(), d._C_arg())
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         sp.scorch_spmm_csr_planned(plan, d.rowptr, d.colidx, d.vals, d._B_arg(), d._C_arg())
@@ -113,29 +112,6 @@ def test_cut_rows_by_the_planners_own_choice_in_all_calls_and_graphs(n):
         torch.cuda.synchronize()
         assert np.array_equal(d.Cfull.cpu().numpy(), got)
     plan.destroy()
-
-
-@pytest.mark.parametrize("m,k,n,length", [(2500, 6000, 300, 500), (600, 9000, 1001, 2500), (3000, 20000, 90, (64, 3000)),
-                                          (2500, 8000, 333, 1600)])  # the last: in the place of 10 MB of other partial rows
-def test_pieces_that_take_turns_in_the_one_shot_call(m, k, n, length):
-    """Partial rows of more than the static scratch: the one-shot call goes round by round and keeps the planned call's bits."""
-    rng = np.random.default_rng(m)
-    lens = np.full(m, length) if np.isscalar(length) else rng.integers(*length, size=m)
-    lens[rng.integers(0, m, size=m // 10)] = rng.integers(0, 64, size=m // 10)
-    p = csr_from_row_lengths(lens, k, n, seed=n, duplicates=False)
-    for q, exact in ((p, False), (integer_valued(p, seed=1), True)):
-        with tuning("cut=1,res=0,panel=0,sliced=0"):
-            d = DeviceProblem(q)
-            plan = d.make_plan()
-            assert plan.info().workspace_bytes_used > sp.STATIC_SCRATCH_BYTES
-            got = d.run_planned(plan)
-            check_against_oracle(q, got, d.ldc, exact=exact, label=f"m={m} n={n}")
-            for _ in range(2):
-                d.reset_C()
-                sp.scorch_spmm_csr_static(q.m, q.k, q.n, d.rowptr, d.colidx, d.vals, d._B_arg(), d._C_arg())
-                torch.cuda.synchronize()
-                assert np.array_equal(d.Cfull.cpu().numpy(), got)
-            plan.destroy()
 
 
 @pytest.mark.parametrize("m", [1, 64, 400])

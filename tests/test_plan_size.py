@@ -1,0 +1,37 @@
+"""What a plan takes, by the sizes alone (no GPU needed): the workspace says whether rows may be cut by columns, since their pieces
+stand in it."""
+import random
+
+import paper_2405_16883_amd as sp
+
+
+def size(monkeypatch, m, k, n, nnz, tune=None):
+    monkeypatch.delenv("SCORCH_SPMM_TUNE", raising=False)
+    if tune:
+        monkeypatch.setenv("SCORCH_SPMM_TUNE", tune)
+    return sp.scorch_spmm_plan_workspace_bytes(m, k, n, nnz)
+
+
+SHAPES = [(169343, 169343, 128, 2489000), (169343, 169343, 100, 2489000), (100000, 100000, 100, 5000000), (400000, 400000, 33, 4800000),
+          (60000, 60000, 256, 3000000), (4000, 8000, 333, 1600000), (1024, 16384, 201, 8388608), (10000, 40000, 61, 12000000),
+          (2000, 20000, 150, 4000000), (2000, 4000, 777, 2400000)]
+
+
+def drawn(count):
+    rng = random.Random(5)
+    for _ in range(count):
+        m, k, n = int(10 ** rng.uniform(2.5, 6.5)), int(10 ** rng.uniform(2.5, 6.5)), int(10 ** rng.uniform(1.5, 3.2))
+        yield m, k, n, min(m * k, int(10 ** rng.uniform(6, 8.5)))
+
+
+def test_no_rows_are_cut_where_the_one_shot_call_serves(monkeypatch):
+    """It analyses at every call, which costs more than the cut gives, and has the planned call's bits."""
+    served = cut = 0
+    for m, k, n, nnz in [*SHAPES, *drawn(2000)]:
+        whole = size(monkeypatch, m, k, n, nnz, "cut=0")
+        if whole <= sp.STATIC_SCRATCH_BYTES:
+            served += 1
+            assert size(monkeypatch, m, k, n, nnz) == whole, (m, k, n, nnz)
+        else:
+            cut += size(monkeypatch, m, k, n, nnz) > whole
+    assert served > 100 and cut > 100
