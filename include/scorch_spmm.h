@@ -73,7 +73,11 @@ scorch_status_t scorch_spmm_csr(int32_t m, int32_t k, int32_t n,
 /*
  * (Plumbing of this library; the paper has no counterpart: its kernels are generated per call on the CPU.)
  * Size, in bytes, of the device workspace a plan for an m x k matrix with nnz stored entries and
- * n dense columns needs (row lists, partial rows, and for some shapes a repacked copy of B).
+ * n dense columns needs (row lists, partial rows, and for some shapes a repacked copy of B).  Where rows may be cut by columns
+ * (see scorch_spmm_plan) it includes room for their pieces, which is most of it: n floats for a piece, for at most half as many
+ * pieces as B and C have rows (2.4 M nodes, n = 100: 1.1 GB, without 80 MB), or, from 320 entries per row in the mean, for up to one
+ * for 16 entries.  scorch_spmm_plan takes a smaller workspace too, down to the size without the pieces (that with
+ * cut=0 in the tuning text), and then cuts no rows.
  * It depends on the tuning read from the environment (see scorch_spmm_plan); call both with
  * the same environment.  Host-only; touches no device.
  */
@@ -89,7 +93,7 @@ scorch_status_t scorch_spmm_plan_workspace_bytes(int32_t m, int32_t k, int32_t n
  *     block  (len > CH)         cut into pieces of at most BCH entries, one workgroup per piece;
  *                               rows with several pieces are summed from partial rows in a
  *                               fixed order (no floating-point atomics)
- * `workspace` (device, 256-byte aligned, at least the bound above) receives the row lists and
+ * `workspace` (device, 256-byte aligned, of the size above) receives the row lists and
  * holds the partial rows at execution; it must stay allocated and unmodified while the plan
  * lives.  `colidx` may be NULL; when given (device, nnz entries) it is inspected to see whether
  * every row stores its columns in strictly increasing order, which is what the panel kernel for

@@ -12,6 +12,7 @@ constexpr int kCutMinLen = 128;  // shorter rows are never cut: a piece per XCD 
 constexpr int kCutBuckets = 15;  // row lengths from kCutMinLen on, two buckets per power of two; the last holds 16 384 and more
 constexpr int kCutClasses = 5;   // class j: 2^j pieces per XCD
 constexpr int kCutBounds = kXcds << (kCutClasses - 1);  // finest division of the columns
+constexpr int kCutAllLong = 320; // mean row from which all rows are taken to be long: 40 entries for each of 8 pieces
 constexpr int kCutBins = 2048;   // column histogram that the division is read off
 
 // Bucket of a row of `len` >= kCutMinLen entries, and the shortest row of a bucket.
@@ -43,6 +44,18 @@ struct CutInfo {
     int32_t rows[kCutClasses], row_off[kCutClasses], piece_off[kCutClasses];
     int32_t bound[kCutBounds];  // first column of every part of the finest division
 };
+
+// Pieces that there is room for, over all XCDs: as many as cut_class gives at most, but one for 40 stored entries where B is so large that
+// an XCD's range of columns is divided (2.4 M nodes, 122 M entries, n = 100: one for 20 / 40 / 64 6659 / 6625 / 6681 us), else one for 16.  A
+// piece leaves a row of n floats.  Where not all rows are long there are no more of them than half the rows of B and C together, so that a
+// plan takes no more than half of what those take, whatever the lengths turn out to be.
+SCORCH_HOST_DEVICE inline int64_t cut_capacity(int32_t m, int32_t k, int64_t nnz, int finest) {
+    const int64_t rows = nnz / kCutMinLen < m ? nnz / kCutMinLen : m;
+    int64_t cap = rows * (kXcds << finest) + nnz / 128;
+    if (cap > nnz / (finest > 0 ? 40 : 16)) cap = nnz / (finest > 0 ? 40 : 16);
+    if (nnz < kCutAllLong * (int64_t)m && cap > ((int64_t)m + k) / 2) cap = ((int64_t)m + k) / 2;
+    return cap;
+}
 
 // Chooses the shortest rows to cut so that their pieces fit `cap_pieces` (over all XCDs), and lays the classes out.
 SCORCH_HOST_DEVICE inline void cut_layout(const int32_t (&rows_in)[kCutBuckets], int finest, int64_t cap_pieces, CutInfo &c) {

@@ -110,7 +110,7 @@ scorch_status_t scorch_spmm_plan(int32_t m, int32_t k, int32_t n, const int32_t 
     if (st != SCORCH_OK) {
         if (st == SCORCH_ERR_WORKSPACE_TOO_SMALL)
             set_error("workspace of %zu bytes is smaller than the %llu needed", workspace_bytes,
-                      (unsigned long long)plan->layout.total);
+                      (unsigned long long)plan->layout.without_cut);
         delete plan;
         return st;
     }

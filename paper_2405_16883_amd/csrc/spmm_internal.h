@@ -59,6 +59,7 @@ struct WorkspaceLayout {
     uint64_t off_counts, off_totals, off_win, off_stage, off_wave, off_wave_span, off_items, off_split, off_partials, off_tickets, off_bpack,
         off_res_ptr, off_coldeg, off_hotmask, off_degbins, off_res_partials,
         off_cut_info, off_cut_counts, off_cut_hist, off_cut_rows, off_cut_spans, off_cut_partials, total;
+    uint64_t without_cut;    // what a plan cannot do without; with less than `total` no rows are cut
     uint64_t res_row_bytes;  // resident kernel: partial rows of one row of A (0: none, B fits one chunk)
     int64_t ticket_tiles;  // arrival counters per split row: one for every column tile a launch may use
     int64_t n_windows, nblk;

@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kBlock) void plan_build_kernel(const PlanArgs a) {
             if (last_tile && tid == 0) win_row_start[L.n_windows] = a.m;
         }
     }
-    if (last_block && fits && L.cap_cut > 0)
+    if (last_block && fits && L.cap_cut > 0 && L.total <= a.workspace_bytes)
         for (int i = tid; i < kCutBins; i += kBlock) reinterpret_cast<int32_t *>(a.workspace + L.off_cut_hist)[i] = 0;
     if (last_block && tid == 0) {
         if (fits) *reinterpret_cast<int32_t *>(a.workspace + L.off_totals) = 0;  // for the kernels that look at the columns
@@ -581,12 +581,12 @@ constexpr int64_t kCutNnzMin = 1 << 20;
 __host__ __device__ static bool want_cut(int32_t m, int32_t k, int64_t nnz, int32_t n, int32_t sliced) {
     const int64_t b_bytes = (int64_t)k * n * 4;
     return n > 32 && nnz * n >= 100000000 && (sliced == 0 || sliced == 64) &&
-           (b_bytes >= 32ll << 20 || (b_bytes >= 8ll << 20 && nnz >= 320 * (int64_t)m));
+           (b_bytes >= 32ll << 20 || (b_bytes >= 8ll << 20 && nnz >= kCutAllLong * (int64_t)m));
 }
 
 // Bytes that a plan cannot do without.
 __host__ __device__ static uint64_t bytes_needed(const WorkspaceLayout &L, bool one_shot) {
-    return !one_shot ? L.total : L.cap_cut > 0 ? L.total : L.off_res_partials;
+    return !one_shot ? L.without_cut : L.cap_cut > 0 ? L.total : L.off_res_partials;
 }
 
 // Rows of A whose partial rows fit at a time, and where they stand (`off`), in a workspace of `bytes` that only a one-shot plan
@@ -739,14 +739,12 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
     if (p.HOT) off = align_up(off + (uint64_t)kDegBins * 16, 256);
     L.off_res_partials = off;  // a one-shot plan has fewer of them
     off = align_up(off + L.res_row_bytes * m, 256);
+    L.without_cut = std::max<uint64_t>(off, 256);
     L.off_cut_info = off;
-    // pieces of rows cut by columns: as many as cut_class gives at most; one for 40 stored entries at most where B is so large that an
-    // XCD's range is divided (2.4 M nodes, 122 M entries: one for 20 / 40 / 64 6659 / 6625 / 6681 us), else one for 16
     // scorch_spmm_csr_static gives the planned call's bits and analyses at every call, so that no rows are cut where it serves.  One call, us,
     // whole / cut: 169 343 rows of 15, n = 128 142 / 298; 100 000 of 50, n = 100 265 / 674; 4000 x 8000, 5 %, n = 333 200 / 390; 10 000 x 40 000, 3 %,
     // n = 61 402 / 696 (the product alone 120 / 113, 246 / 194, 180 / 115, 377 / 158).
-    if (p.CUT == 2 || (p.CUT == 1 && off > SCORCH_STATIC_SCRATCH_BYTES))
-        L.cap_cut = std::min<int64_t>(nnz / (p.CUTJ > 0 ? 40 : 16), std::min<int64_t>(m, nnz / kCutMinLen) * (kXcds << p.CUTJ) + nnz / 128);
+    if (p.CUT == 2 || (p.CUT == 1 && off > SCORCH_STATIC_SCRATCH_BYTES)) L.cap_cut = cut_capacity(m, k, nnz, p.CUTJ);
     if (L.cap_cut > 0) {
         off = align_up(off + sizeof(CutInfo), 256);
         L.off_cut_counts = off;
@@ -874,6 +872,10 @@ static scorch_status_t build_plan_in(PlanResult *result, bool *lost, scorch_spmm
     // The panel and resident kernels need every row's columns in strictly increasing order; without colidx this cannot be
     // verified, so the mode is dropped.
     if (!colidx || plan->m == 0 || plan->nnz == 0) plan->params.PANEL = plan->params.RES = plan->params.CUT = 0;
+    if (L.cap_cut > 0 && L.total > workspace_bytes) {  // no room for the pieces
+        plan->params.CUT = 0;
+        plan->layout.total = L.without_cut;
+    }
     if (plan->params.PANEL || plan->params.RES) {
         int32_t *seen = reinterpret_cast<int32_t *>(ws + L.off_totals);  // cleared by plan_build_kernel
         const uint32_t g = (uint32_t)std::min<int64_t>(((int64_t)plan->m + kWavesPerBlock - 1) / kWavesPerBlock, 256 * 16);
@@ -896,7 +898,7 @@ static scorch_status_t build_plan_in(PlanResult *result, bool *lost, scorch_spmm
     }
     plan->cut_pieces = plan->cut_rows = 0;
     plan->cut_len = 0;
-    if (plan->params.CUT && L.cap_cut > 0) {
+    if (plan->params.CUT && L.cap_cut > 0) {  // there is room for the pieces
         st = launch_plan_cut(plan, rowptr, colidx, result, stream);
         if (st != SCORCH_OK) return st;
         e = hipStreamSynchronize(stream);

@@ -23,6 +23,22 @@ int main() {
     }
     EXPECT(cut_bucket_len(0) == kCutMinLen && cut_bucket(INT32_MAX) == kCutBuckets - 1);
     std::mt19937 rng(1);
+    for (int i = 0; i < 100000; ++i) {
+        const int32_t m = 1 + (int32_t)(rng() >> (1 + rng() % 30)), k = 1 + (int32_t)(rng() >> (1 + rng() % 30));
+        const int64_t nnz = rng() >> (1 + rng() % 30);
+        const int finest = (int)(rng() % kCutClasses);
+        const int64_t cap = cut_capacity(m, k, nnz, finest);
+        EXPECT(cap >= 0 && cap <= nnz / (finest > 0 ? 40 : 16) && cap / kXcds <= INT32_MAX);
+        EXPECT(nnz >= kCutAllLong * (int64_t)m ? cap <= (int64_t)m * (kXcds << finest) + nnz / 128 : cap <= ((int64_t)m + k) / 2);
+        // rows that are all long and alike are cut whenever the finest division leaves it at 8 pieces for each
+        if (nnz >= kCutAllLong * (int64_t)m && finest == 0) {
+            int32_t rows[kCutBuckets] = {};
+            rows[cut_bucket((int32_t)(nnz / m))] = m;
+            CutInfo c{};
+            cut_layout(rows, finest, cap, c);
+            EXPECT(c.n_rows == m);
+        }
+    }
     for (int round = 0; round < 3000; ++round) {
         int32_t rows[kCutBuckets];
         for (int b = 0; b < kCutBuckets; ++b) rows[b] = rng() % 3 ? (int32_t)(rng() % 40) : 0;

@@ -114,6 +114,31 @@ def test_cut_rows_by_the_planners_own_choice_and_in_graphs(n):
     plan.destroy()
 
 
+def test_a_workspace_without_room_for_the_pieces_leaves_the_rows_whole():
+    rng = np.random.default_rng(7)
+    n = 1001
+    lens = np.minimum(6000, (36.0 / rng.random(24000) ** 0.7).astype(np.int64))
+    p = csr_from_row_lengths(lens, 24000, n, seed=7)
+    d = DeviceProblem(p)
+    with tuning("cut=0"):
+        least = sp.scorch_spmm_plan_workspace_bytes(p.m, p.k, n, p.nnz)
+        plan = d.make_plan()
+    whole = d.run_planned(plan)
+    plan.destroy()
+    full = sp.scorch_spmm_plan_workspace_bytes(p.m, p.k, n, p.nnz)
+    assert full > least
+    for size in (least, least + 1000, full - 1, full):
+        ws = torch.empty(full + 4096, dtype=torch.uint8, device=d.dev)
+        ws[size:] = 77
+        plan = sp.scorch_spmm_plan(p.m, p.k, n, d.rowptr, p.nnz, colidx=d.colidx, workspace=ws[:size])
+        assert plan.info().workspace_bytes_used == (full if size == full else least)
+        assert np.array_equal(d.run_planned(plan), whole) == (size < full)
+        assert bool((ws[size:] == 77).all())
+        plan.destroy()
+    with pytest.raises(sp.ScorchError):
+        sp.scorch_spmm_plan(p.m, p.k, n, d.rowptr, p.nnz, colidx=d.colidx, workspace=torch.empty(least - 1, dtype=torch.uint8, device=d.dev))
+
+
 @pytest.mark.parametrize("m", [1, 64, 400])
 def test_cut_where_no_or_every_row_is_long(m):
     for length in (0, 63, 64, 3000):

@@ -35,3 +35,10 @@ def test_no_rows_are_cut_where_the_one_shot_call_serves(monkeypatch):
         else:
             cut += size(monkeypatch, m, k, n, nnz) > whole
     assert served > 100 and cut > 100
+
+
+def test_the_pieces_take_no_more_than_half_of_b_and_c_unless_rows_are_long(monkeypatch):
+    for m, k, n, nnz in [(2449029, 2449029, 100, 122200000), (1000000, 1000000, 100, 100000000), (1000000, 1000000, 256, 25000000), *drawn(2000)]:
+        whole, full = size(monkeypatch, m, k, n, nnz, "cut=0"), size(monkeypatch, m, k, n, nnz)
+        stride, pieces = (n + 3) // 4 * 4, (m + k) // 2 if nnz < 320 * m else nnz // 16
+        assert full - whole <= pieces * (stride * 4 + 8 + 1) + 100000, (m, k, n, nnz)
