@@ -601,6 +601,13 @@ __host__ __device__ static int32_t partial_rows_in(const WorkspaceLayout &L, int
     return room >= L.res_row_bytes * m ? m : (int32_t)(room / L.res_row_bytes);
 }
 
+// Whether a one-shot plan of the resident kernel runs in so many bytes.
+__host__ __device__ static bool resident_runs_in(uint64_t bytes, int32_t m, int32_t k, int64_t nnz, int32_t n, const PlanParams &p) {
+    const WorkspaceLayout L = layout_workspace(m, k, nnz, n, p);
+    uint64_t off;
+    return L.off_res_partials <= bytes && partial_rows_in(L, m, bytes, off) >= std::min(m, 64);
+}
+
 __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t) {
     PlanParams p;
     p.ALPHA = 4;
@@ -674,15 +681,16 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     p.NT &= 1;
     p.RESC = p.RES ? resident_balance(m, k, nnz, p.RES) : 0;
     // scorch_spmm_csr_static takes what the gather kernels need no more than its scratch for, and gives the planned call's
-    // bits: where the resident kernel does not run in the scratch either, it runs nowhere.
+    // bits: where the resident kernel does not run in the scratch either, with as many chunks as are best or with the fewest (whose
+    // table of row pointers is smaller), it runs nowhere.
     if (p.RES) {
         PlanParams gather = p;
         gather.RES = 0;
         if (layout_workspace(m, k, nnz, n, gather).total <= SCORCH_STATIC_SCRATCH_BYTES) {
-            const WorkspaceLayout L = layout_workspace(m, k, nnz, n, p);
-            uint64_t off;
-            if (L.off_res_partials > SCORCH_STATIC_SCRATCH_BYTES || partial_rows_in(L, m, SCORCH_STATIC_SCRATCH_BYTES, off) < std::min(m, 64))
-                p.RES = 0;
+            if (!resident_runs_in(SCORCH_STATIC_SCRATCH_BYTES, m, k, nnz, n, p)) {
+                p.RESC = resident_chunks(k, p.RES);
+                if (!resident_runs_in(SCORCH_STATIC_SCRATCH_BYTES, m, k, nnz, n, p)) p.RES = 0;
+            }
         }
     }
     return p;

@@ -2,6 +2,8 @@
 stand in it."""
 import random
 
+import pytest
+
 import paper_2405_16883_amd as sp
 
 
@@ -42,3 +44,10 @@ def test_the_pieces_take_no_more_than_half_of_b_and_c_unless_rows_are_long(monke
         whole, full = size(monkeypatch, m, k, n, nnz, "cut=0"), size(monkeypatch, m, k, n, nnz)
         stride, pieces = (n + 3) // 4 * 4, (m + k) // 2 if nnz < 320 * m else nnz // 16
         assert full - whole <= pieces * (stride * 4 + 8 + 1) + 100000, (m, k, n, nnz)
+
+
+@pytest.mark.parametrize("m,k,n,nnz", [(14126, 34665, 36, 76700000), (8763, 23237, 51, 85000000), (26500, 16390, 22, 148600000),
+                                       (20534, 28154, 64, 52700000), (4096, 16384, 16, 6710886)])
+def test_narrow_b_is_kept_in_lds_with_fewer_chunks_where_more_do_not_fit(monkeypatch, m, k, n, nnz):
+    """The table of row pointers per chunk of B stands in the workspace, and the one-shot call has to run in its scratch too."""
+    assert size(monkeypatch, m, k, n, nnz) > size(monkeypatch, m, k, n, nnz, "res=0")
