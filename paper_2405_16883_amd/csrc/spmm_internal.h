@@ -60,6 +60,7 @@ struct WorkspaceLayout {
         off_res_ptr, off_coldeg, off_hotmask, off_degbins, off_res_partials,
         off_cut_info, off_cut_counts, off_cut_hist, off_cut_rows, off_cut_spans, off_cut_partials, total;
     uint64_t without_cut;    // what a plan cannot do without; with less than `total` no rows are cut
+    uint64_t one_shot;       // what a one-shot plan cannot do without: the resident kernel's partial rows may take turns
     uint64_t res_row_bytes;  // resident kernel: partial rows of one row of A (0: none, B fits one chunk)
     int64_t ticket_tiles;  // arrival counters per split row: one for every column tile a launch may use
     int64_t n_windows, nblk;

@@ -586,7 +586,7 @@ __host__ __device__ static bool want_cut(int32_t m, int32_t k, int64_t nnz, int3
 
 // Bytes that a plan cannot do without.
 __host__ __device__ static uint64_t bytes_needed(const WorkspaceLayout &L, bool one_shot) {
-    return !one_shot ? L.without_cut : L.cap_cut > 0 ? L.total : L.off_res_partials;
+    return one_shot ? L.one_shot : L.without_cut;
 }
 
 // Rows of A whose partial rows fit at a time, and where they stand (`off`), in a workspace of `bytes` that only a one-shot plan
@@ -767,6 +767,7 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
         off = align_up(off + (uint64_t)L.cap_cut * L.partial_stride * 4, 256);
     }
     L.total = std::max<uint64_t>(off, 256);
+    L.one_shot = L.cap_cut > 0 ? L.total : L.off_res_partials;
     return L;
 }
 
