@@ -73,7 +73,7 @@ scorch_status_t scorch_spmm_plan_workspace_bytes(int32_t m, int32_t k, int32_t n
         set_error("nnz = %lld does not fit int32 indices", (long long)nnz);
         return SCORCH_ERR_UNSUPPORTED;
     }
-    const PlanParams p = choose_params(m, k, nnz, n, read_tuning_from_env());
+    const PlanParams p = choose_plan(m, k, nnz, n, read_tuning_from_env());
     *bytes_out = (size_t)layout_workspace(m, k, nnz, n, p).total;
     return SCORCH_OK;
 }

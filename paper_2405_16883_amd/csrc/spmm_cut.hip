@@ -262,11 +262,13 @@ scorch_status_t launch_plan_cut(const scorch_spmm_plan_t *plan, const int32_t *r
     a.max_rows = (int32_t)(L.cap_cut / kXcds);
     const uint32_t nblk = (uint32_t)((tiles + a.tiles_per_block - 1) / a.tiles_per_block);
     const uint32_t g = (uint32_t)std::min<int64_t>(std::max<int64_t>(1, (a.max_rows + kWavesPerBlock - 1) / kWavesPerBlock), 256 * 8);
+    hipError_t e = hipMemsetAsync(a.hist, 0, kCutBins * 4, stream);
+    if (e != hipSuccess) return hip_fail(e, "clear the column histogram");
     hipLaunchKernelGGL(cut_count_kernel, dim3(nblk), dim3(kBlock), 0, stream, a);
     hipLaunchKernelGGL(cut_layout_kernel, dim3(1), dim3(kBlock), 0, stream, a, (int)nblk);
     hipLaunchKernelGGL(cut_list_kernel, dim3(nblk), dim3(kBlock), 0, stream, a);
     hipLaunchKernelGGL(cut_span_kernel, dim3(g), dim3(kBlock), 0, stream, a);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(&result->cut, a.info, sizeof(result->cut), hipMemcpyDeviceToHost, stream);
     if (e != hipSuccess) return hip_fail(e, "launch the kernels that cut rows");
     return SCORCH_OK;

@@ -53,7 +53,8 @@ struct PlanParams {
 
 // SCORCH_SPMM_TUNE, parsed (only scorch_spmm_plan and scorch_spmm_plan_workspace_bytes call this)
 Tuning read_tuning_from_env();
-__host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t);
+__host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t);  // all but RESC, CUT, CUTJ
+PlanParams choose_plan(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t);
 
 struct WorkspaceLayout {
     uint64_t off_counts, off_totals, off_win, off_stage, off_wave, off_wave_span, off_items, off_split, off_partials, off_tickets, off_bpack,

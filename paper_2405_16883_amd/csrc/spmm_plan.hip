@@ -288,8 +288,6 @@ __global__ __launch_bounds__(kBlock) void plan_build_kernel(const PlanArgs a) {
             if (last_tile && tid == 0) win_row_start[L.n_windows] = a.m;
         }
     }
-    if (last_block && fits && L.cap_cut > 0 && L.total <= a.workspace_bytes)
-        for (int i = tid; i < kCutBins; i += kBlock) reinterpret_cast<int32_t *>(a.workspace + L.off_cut_hist)[i] = 0;
     if (last_block && tid == 0) {
         if (fits) *reinterpret_cast<int32_t *>(a.workspace + L.off_totals) = 0;  // for the kernels that look at the columns
         a.result->nnz = nnz;
@@ -548,7 +546,7 @@ __host__ __device__ static int32_t want_resident(int32_t m, int32_t k, int64_t n
 // of 16 cost as much as 16.  In ns, as fitted for want_resident: 8 per entry of a row's chunk and 400 per row and chunk of a wavefront; 2.7 per
 // 1000 floats of partial rows.  4096 x 16 384 with 10 % stored, n = 16: seven chunks, the last half full, 8 rows of 253 entries per wavefront;
 // eight even ones, 8 rows of 205.
-__host__ __device__ static int32_t resident_balance(int32_t m, int32_t k, int64_t nnz, int32_t W) {
+static int32_t resident_balance(int32_t m, int32_t k, int64_t nnz, int32_t W) {
     const int32_t fewest = resident_chunks(k, W);
     if (fewest == 1) return 1;  // no partial rows, no second launch
     int32_t best = fewest;
@@ -578,7 +576,7 @@ constexpr int64_t kCutNnzMin = 1 << 20;
 // n = 1001 1561 / 541 (0.07); with less, rows of 164, n = 129 (8 MB) 95 / 109.  B below 8 MB can gain too (3000 x 12 000, 10 %, n = 101, 4.8 MB 122 / 73) but is
 // left alone: such plans are small.  Not: n = 32, 169 343 rows (21 MB) 39.8 / 46.2, 2.4 M nodes of degree 3 212 / 225; 1.3 M entries, n = 64 41.1 / 43.7;
 // with 32-column slices (SLICED = 32) 121 / 145.
-__host__ __device__ static bool want_cut(int32_t m, int32_t k, int64_t nnz, int32_t n, int32_t sliced) {
+static bool want_cut(int32_t m, int32_t k, int64_t nnz, int32_t n, int32_t sliced) {
     const int64_t b_bytes = (int64_t)k * n * 4;
     return n > 32 && nnz * n >= 100000000 && (sliced == 0 || sliced == 64) &&
            (b_bytes >= 32ll << 20 || (b_bytes >= 8ll << 20 && nnz >= kCutAllLong * (int64_t)m));
@@ -591,7 +589,7 @@ __host__ __device__ static uint64_t bytes_needed(const WorkspaceLayout &L, bool 
 
 // Rows of A whose partial rows fit at a time, and where they stand (`off`), in a workspace of `bytes` that only a one-shot plan
 // uses: behind everything else, or over the lists of the gather kernels, which the resident kernel does not read.
-__host__ __device__ static int32_t partial_rows_in(const WorkspaceLayout &L, int32_t m, uint64_t bytes, uint64_t &off) {
+static int32_t partial_rows_in(const WorkspaceLayout &L, int32_t m, uint64_t bytes, uint64_t &off) {
     off = L.off_res_partials;
     uint64_t room = bytes - off;
     if (room < L.res_row_bytes * m && room < L.off_res_ptr) {
@@ -599,13 +597,6 @@ __host__ __device__ static int32_t partial_rows_in(const WorkspaceLayout &L, int
         room = L.off_res_ptr;
     }
     return room >= L.res_row_bytes * m ? m : (int32_t)(room / L.res_row_bytes);
-}
-
-// Whether a one-shot plan of the resident kernel runs in so many bytes.
-__host__ __device__ static bool resident_runs_in(uint64_t bytes, int32_t m, int32_t k, int64_t nnz, int32_t n, const PlanParams &p) {
-    const WorkspaceLayout L = layout_workspace(m, k, nnz, n, p);
-    uint64_t off;
-    return L.off_res_partials <= bytes && partial_rows_in(L, m, bytes, off) >= std::min(m, 64);
 }
 
 __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t) {
@@ -638,16 +629,6 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     p.PDIRECT = (p.PANEL && (t.pack != 1 || p.PANEL == 3)) ? 1 : 0;
     p.RES = p.PANEL == 0 ? want_resident(m, k, nnz, n) : 0;
     if (t.res >= 0) p.RES = (t.res > 0 && n <= 64 && k > 0 && m > 0 && p.PANEL == 0) ? resident_width(n) : 0;
-    p.CUT = p.CUTJ = 0;
-    if ((nnz >= kCutNnzMin && t.cut != 0) || t.cut > 0) {  // the planning kernels evaluate this: one comparison for small matrices
-        const bool possible = m > 0 && k > 0 && n > 16 && p.PANEL == 0 && p.RES == 0 && p.PACK == 0 && t.fix <= 0 && t.u <= 0 && t.nt < 0;
-        p.CUT = !possible ? 0 : t.cut > 0 ? 2 : want_cut(m, k, nnz, n, p.SLICED) ? 1 : 0;
-        // parts of the columns of an XCD, up to 16 MB of B each: 122 MB in 1 / 4 / 8 / 16 parts 7100 / 6690 / 6600 / 6720 us,
-        // 32 MB in 1 / 2 / 4 / 8 1356 / 1336 / 1356 / 1391, 5 MB in 1 / 2 / 4 212 / 226 / 237
-        const int64_t xcd_bytes = (int64_t)k * (p.SLICED ? p.SLICED : n) * 4 / kXcds;
-        while (p.CUTJ < kCutClasses - 1 && (xcd_bytes >> p.CUTJ) > (16ll << 20)) ++p.CUTJ;
-        if (t.cutj >= 0) p.CUTJ = std::min(t.cutj, kCutClasses - 1);
-    }
     // Enough independent wavefront tasks to fill 256 CUs several times over, but pieces long
     // enough that the per-piece overhead stays small.
     const int64_t coltiles = p.SLICED ? (n + p.SLICED - 1) / p.SLICED : std::max<int64_t>(1, (n + 511) / 512);
@@ -679,20 +660,7 @@ __host__ __device__ PlanParams choose_params(int32_t m, int32_t k, int64_t nnz, 
     p.BCH = std::max(p.BCH, 64);
     p.U = p.U >= 8 ? 8 : 4;
     p.NT &= 1;
-    p.RESC = p.RES ? resident_balance(m, k, nnz, p.RES) : 0;
-    // scorch_spmm_csr_static takes what the gather kernels need no more than its scratch for, and gives the planned call's
-    // bits: where the resident kernel does not run in the scratch either, with as many chunks as are best or with the fewest (whose
-    // table of row pointers is smaller), it runs nowhere.
-    if (p.RES) {
-        PlanParams gather = p;
-        gather.RES = 0;
-        if (layout_workspace(m, k, nnz, n, gather).total <= SCORCH_STATIC_SCRATCH_BYTES) {
-            if (!resident_runs_in(SCORCH_STATIC_SCRATCH_BYTES, m, k, nnz, n, p)) {
-                p.RESC = resident_chunks(k, p.RES);
-                if (!resident_runs_in(SCORCH_STATIC_SCRATCH_BYTES, m, k, nnz, n, p)) p.RES = 0;
-            }
-        }
-    }
+    p.RESC = p.CUT = p.CUTJ = 0;  // see choose_plan
     return p;
 }
 
@@ -769,6 +737,41 @@ __host__ __device__ WorkspaceLayout layout_workspace(int32_t m, int32_t k, int64
     L.total = std::max<uint64_t>(off, 256);
     L.one_shot = L.cap_cut > 0 ? L.total : L.off_res_partials;
     return L;
+}
+
+// Whether a one-shot plan of the resident kernel runs in so many bytes.
+static bool resident_runs_in(uint64_t bytes, int32_t m, int32_t k, int64_t nnz, int32_t n, const PlanParams &p) {
+    const WorkspaceLayout L = layout_workspace(m, k, nnz, n, p);
+    uint64_t off;
+    return L.off_res_partials <= bytes && partial_rows_in(L, m, bytes, off) >= std::min(m, 64);
+}
+
+// The parameters of a plan.  The planning kernels go by choose_params alone: what they write stands before everything that the chunks of the
+// resident kernel and the pieces of cut rows move, and working these out there (64-bit divisions) took 13 us per plan (pruned
+// 4096 x 16 384, n = 16).  What does not fit the workspace on account of them, the host finds.
+PlanParams choose_plan(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t) {
+    PlanParams p = choose_params(m, k, nnz, n, t);
+    if ((nnz >= kCutNnzMin && t.cut != 0) || t.cut > 0) {
+        const bool possible = m > 0 && k > 0 && n > 16 && p.PANEL == 0 && p.RES == 0 && p.PACK == 0 && t.fix <= 0 && t.u <= 0 && t.nt < 0;
+        p.CUT = !possible ? 0 : t.cut > 0 ? 2 : want_cut(m, k, nnz, n, p.SLICED) ? 1 : 0;
+        // parts of the columns of an XCD, up to 16 MB of B each: 122 MB in 1 / 4 / 8 / 16 parts 7100 / 6690 / 6600 / 6720 us,
+        // 32 MB in 1 / 2 / 4 / 8 1356 / 1336 / 1356 / 1391, 5 MB in 1 / 2 / 4 212 / 226 / 237
+        const int64_t xcd_bytes = (int64_t)k * (p.SLICED ? p.SLICED : n) * 4 / kXcds;
+        while (p.CUTJ < kCutClasses - 1 && (xcd_bytes >> p.CUTJ) > (16ll << 20)) ++p.CUTJ;
+        if (t.cutj >= 0) p.CUTJ = std::min(t.cutj, kCutClasses - 1);
+    }
+    if (!p.RES) return p;
+    p.RESC = resident_balance(m, k, nnz, p.RES);
+    // scorch_spmm_csr_static takes what the gather kernels need no more than its scratch for, and gives the planned call's
+    // bits: where the resident kernel does not run in the scratch either, with as many chunks as are best or with the fewest (whose
+    // table of row pointers is smaller), it runs nowhere.
+    PlanParams gather = p;
+    gather.RES = 0;
+    if (layout_workspace(m, k, nnz, n, gather).total <= SCORCH_STATIC_SCRATCH_BYTES && !resident_runs_in(SCORCH_STATIC_SCRATCH_BYTES, m, k, nnz, n, p)) {
+        p.RESC = resident_chunks(k, p.RES);
+        if (!resident_runs_in(SCORCH_STATIC_SCRATCH_BYTES, m, k, nnz, n, p)) p.RES = 0;
+    }
+    return p;
 }
 
 // How the rows are dealt to the workgroups of the planning kernels: at most kPlanBlocksMax workgroups, so that the
@@ -858,7 +861,7 @@ static scorch_status_t build_plan_in(PlanResult *result, bool *lost, scorch_spmm
         return SCORCH_ERR_INVALID_ARG;
     }
     plan->nnz = got.nnz;
-    plan->params = choose_params(plan->m, plan->k, plan->nnz, plan->n, plan->tuning);
+    plan->params = choose_plan(plan->m, plan->k, plan->nnz, plan->n, plan->tuning);
     plan->layout = layout_workspace(plan->m, plan->k, plan->nnz, plan->n, plan->params);
     const WorkspaceLayout &L = plan->layout;
     if (bytes_needed(L, one_shot) > workspace_bytes) return SCORCH_ERR_WORKSPACE_TOO_SMALL;  // the caller words the message
