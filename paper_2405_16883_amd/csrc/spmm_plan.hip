@@ -752,7 +752,8 @@ static bool resident_runs_in(uint64_t bytes, int32_t m, int32_t k, int64_t nnz, 
 PlanParams choose_plan(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tuning &t) {
     PlanParams p = choose_params(m, k, nnz, n, t);
     if ((nnz >= kCutNnzMin && t.cut != 0) || t.cut > 0) {
-        const bool possible = m > 0 && k > 0 && n > 16 && p.PANEL == 0 && p.RES == 0 && p.PACK == 0 && t.fix <= 0 && t.u <= 0 && t.nt < 0;
+        // the kernel for it is compiled for the default unroll depth and cache policies
+        const bool possible = m > 0 && k > 0 && n > 16 && p.PANEL == 0 && p.RES == 0 && p.PACK == 0 && t.fix <= 0 && t.u <= 0 && t.nt < 0 && t.cold == 0;
         p.CUT = !possible ? 0 : t.cut > 0 ? 2 : want_cut(m, k, nnz, n, p.SLICED) ? 1 : 0;
         // parts of the columns of an XCD, up to 16 MB of B each: 122 MB in 1 / 4 / 8 / 16 parts 7100 / 6690 / 6600 / 6720 us,
         // 32 MB in 1 / 2 / 4 / 8 1356 / 1336 / 1356 / 1391, 5 MB in 1 / 2 / 4 212 / 226 / 237

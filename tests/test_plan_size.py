@@ -51,3 +51,10 @@ def test_the_pieces_take_no_more_than_half_of_b_and_c_unless_rows_are_long(monke
 def test_narrow_b_is_kept_in_lds_with_fewer_chunks_where_more_do_not_fit(monkeypatch, m, k, n, nnz):
     """The table of row pointers per chunk of B stands in the workspace, and the one-shot call has to run in its scratch too."""
     assert size(monkeypatch, m, k, n, nnz) > size(monkeypatch, m, k, n, nnz, "res=0")
+
+
+@pytest.mark.parametrize("tune", ["cold=1", "cold=3", "fix=1", "u=4", "nt=0"])
+def test_experiments_with_the_gather_kernels_find_whole_rows(monkeypatch, tune):
+    shape = 2449029, 2449029, 100, 122200000
+    assert size(monkeypatch, *shape) > size(monkeypatch, *shape, "cut=0")
+    assert size(monkeypatch, *shape, tune) == size(monkeypatch, *shape, tune + ",cut=0")
