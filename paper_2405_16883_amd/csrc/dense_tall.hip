@@ -7,9 +7,10 @@
 // parts of up to 128 columns.  X goes straight from memory into the operand registers, a step of 16 columns ahead, once
 // per part.  The product is formed as Y^T = W^T X^T: the first operand of the instruction is W^T, so that a lane ends with four
 // consecutive columns of one row of Y and stores them as one vector.  Bias and activation are applied on the way out:
-// left to passes of their own they read and write Y once more.  The first rows of X are requested before W is staged, four rounds of
-// W at a time: 169 343 rows, 128 -> 128 72.5 -> 63.6 us, 128 -> 64 46 -> 38, 64 -> 128 47 -> 42.  What is left there: one or two units per
-// wavefront, so that start, product and store hardly overlap (1 M rows: 104 TFLOP/s, the dense library 94).  Column parts of 64
+// left to passes of their own they read and write Y once more.  W is staged before the first rows of X are requested: the other way round,
+// or with four rounds of W at a time, the start takes longer (8000 rows, 100 -> 128 10.2 / 10.9 / 10.5 us, both 11.4; many rows even).
+// What is left at 169 343 rows (128 -> 128 56.5 us): one or two units per
+// wavefront, so that start, product and store hardly overlap (1 M rows: 107 TFLOP/s, the dense library 96).  Column parts of 64
 // instead of 128 (1 M rows 315 -> 330 us) and three or four workgroups per CU are no faster.  Scalar loads of X instead of vectors: 5-35 % more.
 // Lane l of a wavefront reads, of 16 columns of X, the four from 4 (l / 16) onwards, one vector; two exchanges between the
 // 16-lane rows of the wavefront (order_x) then give it columns 2 (l / 16) and the next, of each half of the 16, so that every
@@ -102,10 +103,7 @@ __global__ __launch_bounds__(kDenseThreads, 4) void dense_tall_kernel(const Dens
     };
     // units are dealt wavefront by wavefront over the workgroups, so that a last incomplete round is spread over the chip
     const int u0 = wv * nblk + first, du = kDenseWaves * nblk;
-    rows_of(u0);
-    fetch(0);  // on its way while W is staged
     // four rows of W at one column per thread; neighbouring threads read neighbouring columns
-#pragma unroll 4
     for (int i = tid; i < 16 * NT * steps * 4; i += kDenseThreads) {
         const int c = i % (16 * NT), quad = i / (16 * NT);
         const int k0 = quad / 4 * 16 + quad % 4 * 2;  // rows k0, k0 + 1, k0 + 8, k0 + 9: see order_x
@@ -123,6 +121,8 @@ __global__ __launch_bounds__(kDenseThreads, 4) void dense_tall_kernel(const Dens
     __syncthreads();
 
     if (u0 >= a.units) return;
+    rows_of(u0);
+    fetch(0);
     for (int64_t u = u0; u < a.units; u += du) {
 #pragma unroll
         for (int c = 0; c < NT; ++c)
@@ -209,8 +209,9 @@ scorch_status_t launch_dense_tall(int32_t m, int32_t k, int32_t n, const float *
     a.parts = (all_tiles + kDenseTilesMax - 1) / kDenseTilesMax;
     const int32_t tiles = (all_tiles + a.parts - 1) / a.parts;
     // Two 16-row tiles per wavefront (each fragment of W out of LDS feeds both) unless one gives fewer rounds of the resident
-    // wavefronts, with 4 % for the second reading of W: 169 343 x 128 -> 128, 1.3 rounds of two or 2.6 of one: 71.1 / 68.9 us, 1 M rows
-    // 337 / 342.
+    // wavefronts, with 4 % for the second reading of W.  us with two from 1024 units of two on / now: 169 343 rows (1.3 rounds of two or 2.6 of
+    // one) 128 -> 128 62.7 / 56.5, 64 -> 128 39.8 / 33.9, 40 -> 100 32.1 / 26.4; 60 000 rows 64 -> 128 18.9 / 16.6; 1 M rows 128 -> 128 318 / 306 (and 337 / 342
+    // with two / one).
     const int64_t waves = (int64_t)2 * kCus / a.parts * kDenseWaves;
     auto rounds = [&](int t) { return (((int64_t)m + 16 * t - 1) / (16 * t) + waves - 1) / std::max<int64_t>(1, waves) * t; };
     const int rt = 100 * rounds(2) <= 104 * rounds(1) ? 2 : 1;
