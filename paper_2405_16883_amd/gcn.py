@@ -42,12 +42,14 @@ def _native_product(X: torch.Tensor, W: torch.Tensor, bias: Optional[torch.Tenso
 
 
 def _native_first(m: int, k: int, n: int) -> bool:
-    """Whether the dense product alone, m x k times k x n, is better made by scorch_dense_layer.  With k in multiples of 16 it adds up
-    in the dense library's usual order (the same bits as torch.mm on nearly all shapes tried), and over 13 widths, 3000 to 2.4 M rows,
-    it takes 0.2 to 1.0 of the time, us own / library: 64 -> 64 20 000 rows 7 / 18, 169 343 22 / 48, 1 M 122 / 167; 128 -> 128 16 / 23, 60 / 78,
-    312 / 341.  Not so where the library's tiles of a wide product come out in whole rounds over the chip: 128 -> 128 60 000 rows 26 / 24,
-    80 000 35 / 33, 131 072 48 / 46; 144 -> 128 60 000 28 / 25."""
-    return k % 16 == 0 and not (k * n >= 128 * 128 and 50000 <= m < 150000)
+    """Whether the dense product alone, m x k times k x n with n <= k, is better made by scorch_dense_layer.  With k in multiples of 16 it
+    adds up in the dense library's usual order (the same bits as torch.mm on nearly all shapes tried).  Drawn from sweeps of 45 to 67 row
+    counts from 2000 to 2.4 M for 33 pairs of widths, time own / library: 0.1 to 1.0 for k <= 112 or n <= 48.  Wider, the library's time jumps
+    by half from one row count to the next and back (tiles of several heights that do or do not come out in whole rounds over the chip), and
+    the own kernel is behind at its best ones: 128 -> 128 45 000 rows 1.21, 62 000 1.08, 80 000 1.04, 97 551 1.19, 131 072 1.01, 229 376 1.03
+    (but 52 000 0.70, 86 000 0.72); 128 -> 64 97 551 1.11; 144 -> 96 46 000 1.06; 144 -> 144 21 754 1.04.  So only where no row count
+    was behind: below 40 000 rows 0.4 to 1.0, 133 000 to 215 000 0.6 to 1.0 (169 343, 128 -> 128 0.83), from 232 000 on 0.6 to 1.0, twice 1.02."""
+    return k % 16 == 0 and (k <= 112 or n <= 48 or (m < 40000 and n <= 128) or 133000 <= m < 215000 or m >= 232000)
 
 
 def _unwatched() -> bool:

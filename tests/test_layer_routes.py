@@ -25,3 +25,14 @@ def test_modes_and_transforms_are_seen():
 def test_a_torch_without_one_of_these_names_keeps_the_product(monkeypatch, owner, name):
     monkeypatch.delattr(owner, name)
     assert not gcn._unwatched()
+
+
+@pytest.mark.parametrize("m,k,n", [(45000, 128, 128), (62973, 128, 128), (80867, 144, 128), (97551, 128, 128), (97551, 128, 64), (86084, 144, 64),
+                                   (46000, 144, 96), (131072, 144, 144), (21754, 144, 144), (229376, 128, 128), (100000, 128, 40 * 2), (20000, 40, 40)])
+def test_products_that_the_library_makes_faster_stay_there(m, k, n):
+    assert not gcn._native_first(m, k, n)
+
+
+@pytest.mark.parametrize("m,k,n", [(169343, 128, 128), (20000, 64, 64), (62973, 112, 112), (97551, 128, 47), (1000000, 128, 128), (2000, 144, 128)])
+def test_products_that_the_own_kernel_makes_faster(m, k, n):
+    assert gcn._native_first(m, k, n)
