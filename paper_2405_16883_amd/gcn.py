@@ -46,10 +46,10 @@ def _native_first(m: int, k: int, n: int) -> bool:
     adds up in the dense library's usual order (the same bits as torch.mm on nearly all shapes tried).  Drawn from sweeps of 45 to 67 row
     counts from 2000 to 2.4 M for 33 pairs of widths, time own / library: 0.1 to 1.0 for k <= 112 or n <= 48.  Wider, the library's time jumps
     by half from one row count to the next and back (tiles of several heights that do or do not come out in whole rounds over the chip), and
-    the own kernel is behind at its best ones: 128 -> 128 45 000 rows 1.21, 62 000 1.08, 80 000 1.04, 97 551 1.19, 131 072 1.01, 229 376 1.03
+    the own kernel is behind at its best ones: 128 -> 128 45 000 rows 1.21, 62 000 1.08, 80 000 1.04, 97 551 1.19, 131 072 1.01, 214 772 1.04, 229 376 1.03
     (but 52 000 0.70, 86 000 0.72); 128 -> 64 97 551 1.11; 144 -> 96 46 000 1.06; 144 -> 144 21 754 1.04.  So only where no row count
-    was behind: below 40 000 rows 0.4 to 1.0, 133 000 to 215 000 0.6 to 1.0 (169 343, 128 -> 128 0.83), from 232 000 on 0.6 to 1.0, twice 1.02."""
-    return k % 16 == 0 and (k <= 112 or n <= 48 or (m < 40000 and n <= 128) or 133000 <= m < 215000 or m >= 232000)
+    was behind: below 40 000 rows 0.4 to 1.0, 133 000 to 210 000 0.6 to 1.0 (169 343, 128 -> 128 0.83), from 232 000 on 0.6 to 1.0, twice 1.02."""
+    return k % 16 == 0 and (k <= 112 or n <= 48 or (m < 40000 and n <= 128) or 133000 <= m < 210000 or m >= 232000)
 
 
 def _unwatched() -> bool:

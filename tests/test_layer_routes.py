@@ -28,7 +28,7 @@ def test_a_torch_without_one_of_these_names_keeps_the_product(monkeypatch, owner
 
 
 @pytest.mark.parametrize("m,k,n", [(45000, 128, 128), (62973, 128, 128), (80867, 144, 128), (97551, 128, 128), (97551, 128, 64), (86084, 144, 64),
-                                   (46000, 144, 96), (131072, 144, 144), (21754, 144, 144), (229376, 128, 128), (100000, 128, 40 * 2), (20000, 40, 40)])
+                                   (46000, 144, 96), (131072, 144, 144), (21754, 144, 144), (229376, 128, 128), (214772, 144, 128), (100000, 128, 40 * 2), (20000, 40, 40)])
 def test_products_that_the_library_makes_faster_stay_there(m, k, n):
     assert not gcn._native_first(m, k, n)
 
