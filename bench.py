@@ -507,7 +507,7 @@ def main():
     roofline = {
         "bound": "hbm",
         "kernel": ("spmm_panel_kernel (+ spmm_pack_b_kernel, same events)" if head["plan"]["mode"] == "lds_panel"
-                   else "spmm_fused_kernel (+ spmm_fixup_kernel, same events)"),
+                   else "spmm_fused_kernel (+ spmm_fixup_kernel, or cut_sum_kernel where rows are cut by columns, same events)"),
         "achieved": head["gbs_min_traffic"],
         "peak": HBM_PEAK_GBS,
         "unit": "GB/s",

@@ -90,8 +90,12 @@ inline NaturalMapping natural_mapping(int32_t m, int32_t k, int32_t n, const flo
         mp.xcd_slices = 1;
     }
     // Gathers in flight per group of a scout: 16, which takes 84 to 124 VGPRs, or 8, which leaves room for one or two more wavefronts
-    // per SIMD.  us with 16 / 8: groups of 8 lanes, 169 343 rows, n = 32 49.4 / 40.4; 64-column slices, 30 000 rows, n = 128 31.0 / 28.5,
-    // 169 343 128.6 / 123.6; but n = 192 190.9 / 193.2, 300 000 rows of 30, n = 128 510 / 517; whole rows, 30 000 rows, n = 64 23.2 / 25.9.
+    // per SIMD (2.7 -> 3.3 on the mid-size graph, n = 128).  More wavefronts hide more latency, and share the L2s with more rows of B: which
+    // counts for more was measured, us with 16 / 8.  Groups of 8 lanes, 169 343 rows, n = 32 49.6 / 41.4.  64-column slices, rows of 15: 30 000
+    // rows, n = 128 29.1 / 28.6, 100 000 76.5 / 70.4, 195 000 149 / 140, 250 000 200 / 199, 400 000 320 / 328; n = 192 130 000 rows 145 / 137, 169 343
+    // 191 / 192, 250 000 311 / 321; n = 320 79 000 rows 136 / 128, 250 000 506 / 500; n = 448 56 000 rows 136 / 121; rows of 6 5 to 16 % less, of 40 0 to 3 %.
+    // The line lies between the last gains and the first losses of n = 128 and 192; wider B still gains beyond it.  Whole rows, 30 000
+    // rows, n = 64 23.2 / 25.9.
     // Slices were asked for by the shape alone: rows that are not aligned have none, and keep the loads for any alignment.
     const bool slices_of_64 = slice_cols == 64 && mp.V == 4 && !mp.UA && mp.G == 16 && mp.T == 1;
     nm.scout_gathers = mp.G == 8 || (slices_of_64 && (int64_t)m * mp.ncoltiles < 400000) ? 8 : 16;

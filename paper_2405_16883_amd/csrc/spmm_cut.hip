@@ -8,8 +8,8 @@
 //
 // The ranges hold equal shares of the stored entries (column histogram).  A piece is a range of entries [p0, p1) found by binary
 // search over the row's columns; the pieces of a row cover each of its entries once whatever the columns are (columns out of order or
-// other columns at execution only cost reuse).  What bounds it: L2 misses, as without; 2.4 M nodes, 122 M entries, n = 100: 58.3 -> 45.0 GB
-// fetched (and 1.1 GB of partial rows written and read), 7.96 -> 6.60 ms; an LRU model of the L2s with 512 wavefronts per XCD gives
+// other columns at execution only cost reuse).  What bounds it: L2 misses, as without; 2.4 M nodes, 122 M entries, n = 100: 58.3 -> 44.4 GB
+// fetched (and 0.9 GB of partial rows written and 1.0 read), 7.95 -> 6.65 ms; an LRU model of the L2s with 512 wavefronts per XCD gives
 // 58.4 -> 42.6 GB.  Rows of B are read with the default policy here: with the hot/cold split the cut rows take 4.26 instead of 3.23 ms.
 // Pieces of 8 / 16 / 32 entries in the mean: equal / best / 2 % slower.
 #include "device_util.h"

@@ -8,7 +8,8 @@
 // that are not 16-byte aligned use the same loads at float alignment (template flag UA), and a row
 // whose length is not a multiple of 4 ends with a vector that overlaps its neighbour.
 //
-// Three paths share one launch; the workgroup index selects the path:
+// Up to four paths share one launch; the workgroup index selects the path:
+//   pieces  of long rows cut by columns (large graphs; spmm_cut.hip): a few per wavefront, each to a partial row
 //   items   one workgroup per piece of a long row; 4 wavefronts split the piece, partial sums are
 //           combined through LDS and written to C or to a partial row
 //   wave    one wavefront per medium row; the S groups take interleaved entries and are combined

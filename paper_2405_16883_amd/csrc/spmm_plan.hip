@@ -24,7 +24,8 @@ constexpr int kQ = 5;  // counted quantities: wave rows, items, split rows, slot
 
 // Arguments of the two planning kernels.  The number of stored entries is not known on the host when they are launched:
 // every workgroup reads it from rowptr[m] and works out the parameters and the workspace layout itself
-// (choose_params and layout_workspace are the same code on both sides), so that the host waits once, at the end.
+// (choose_params and layout_workspace are the same code on both sides; what stands behind the lists only the host knows, see
+// choose_plan), so that the host waits once, at the end.
 struct PlanArgs {
     const int32_t *rowptr;
     int32_t m, k, n;
@@ -782,7 +783,7 @@ PlanParams choose_plan(int32_t m, int32_t k, int64_t nnz, int32_t n, const Tunin
 constexpr int32_t kPlanRecount = 8;
 
 // Slots of host memory that the planning kernels write their result to: taken for the length of one call and given back
-// (as many as calls were in flight at once, 64 bytes each).
+// (as many as calls were in flight at once, under a kilobyte each).
 static std::mutex g_result_mutex;
 static PlanResult *g_result_free;  // linked through the slots themselves: nothing here can throw
 
