@@ -77,7 +77,8 @@ scorch_status_t scorch_spmm_csr(int32_t m, int32_t k, int32_t n,
  * (see scorch_spmm_plan) it includes room for their pieces, which is most of it: n floats for a piece, for at most half as many
  * pieces as B and C have rows (2.4 M nodes, n = 100: 1.1 GB, without 80 MB), or, from 320 entries per row in the mean, for up to one
  * for 16 entries.  scorch_spmm_plan takes a smaller workspace too, down to the size without the pieces (that with
- * cut=0 in the tuning text), and then cuts no rows.
+ * cut=0 in the tuning text), and then cuts no rows; where chunks of B are kept in LDS, down to the size for the fewest chunks.
+ * The result bits are those of scorch_spmm_csr_static with the full size only.
  * It depends on the tuning read from the environment (see scorch_spmm_plan); call both with
  * the same environment.  Host-only; touches no device.
  */

@@ -865,6 +865,10 @@ static scorch_status_t build_plan_in(PlanResult *result, bool *lost, scorch_spmm
     plan->nnz = got.nnz;
     plan->params = choose_plan(plan->m, plan->k, plan->nnz, plan->n, plan->tuning);
     plan->layout = layout_workspace(plan->m, plan->k, plan->nnz, plan->n, plan->params);
+    if (plan->params.RES && !one_shot && plan->layout.total > workspace_bytes) {  // what B needs at least, then
+        plan->params.RESC = resident_chunks(plan->k, plan->params.RES);
+        plan->layout = layout_workspace(plan->m, plan->k, plan->nnz, plan->n, plan->params);
+    }
     const WorkspaceLayout &L = plan->layout;
     if (bytes_needed(L, one_shot) > workspace_bytes) return SCORCH_ERR_WORKSPACE_TOO_SMALL;  // the caller words the message
     char *ws = plan->workspace;

@@ -159,3 +159,22 @@ def test_resident_with_more_chunks_than_b_needs(m, k, n):
             assert plan.info().mode == 3
             check_against_oracle(q, d.run_planned(plan), d.ldc, exact=exact, label=f"m={m} k={k} n={n}")
             plan.destroy()
+
+
+@pytest.mark.parametrize("m,k,n,length,more", [(4096, 16384, 16, 1638, 1), (1024, 9000, 33, 1800, 1), (1152, 7000, 64, 2500, 2)])
+def test_resident_with_room_for_the_fewest_chunks_only(m, k, n, length, more):
+    """More chunks than B needs take a larger table of row pointers and more partial rows; a workspace without room for them will do."""
+    p = integer_valued(csr_from_row_lengths([length] * m, k, n, seed=m, duplicates=False), seed=n)
+    d = DeviceProblem(p)
+    full = sp.scorch_spmm_plan_workspace_bytes(m, k, n, p.nnz)
+    width = 16 if n == 16 else 64
+    least = full - more * (m * 4 + m * width * 4)  # m: a multiple of 64, so that every section ends on 256 bytes
+    for size in (full, full - 1, least):
+        ws = torch.full((full + 4096,), 77, dtype=torch.uint8, device=d.dev)
+        plan = sp.scorch_spmm_plan(m, k, n, d.rowptr, p.nnz, colidx=d.colidx, workspace=ws[:size])
+        assert plan.info().mode == 3 and plan.info().workspace_bytes_used == (full if size == full else least)
+        check_against_oracle(p, d.run_planned(plan), d.ldc, exact=True, label=f"m={m} {size}")
+        assert bool((ws[size:] == 77).all())
+        plan.destroy()
+    with pytest.raises(sp.ScorchError):
+        sp.scorch_spmm_plan(m, k, n, d.rowptr, p.nnz, colidx=d.colidx, workspace=ws[:least - 1])
