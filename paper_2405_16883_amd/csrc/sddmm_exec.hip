@@ -556,6 +556,10 @@ scorch_status_t launch_sddmm(const scorch_spmm_plan_t *plan, int32_t m, int32_t 
         a.nb_win = plan->n_short > 0 ? (int32_t)((plan->layout.n_windows + kWavesPerBlock - 1) / kWavesPerBlock) : 0;
         a.LW = plan->params.LW;
         fn = pick_sddmm<true>(V, G, T, UA);
+        // Where the plan cuts rows by columns its pieces serve any d: an XCD's gathers stay within its range of Ct, and nothing is added up.
+        // Whole / cut, us: 2.4 M nodes of degree 50 (n = 100) d = 16 2217 / 2051, 64 4234 / 3439, 100 8283 / 6782; 2.4 M of 10 (n = 64) d = 32
+        // 480 / 480, 64 824 / 773; 300 000 of 50 d = 16 191 / 169, 256 2000 / 1577; 10 000 x 40 000, 3 %, d = 16 114 / 76, 256 1804 / 547.  d = 3 and
+        // less even (136 / 137), hence only vectors of four.
         if (plan->cut_pieces > 0 && V == 4) {
             fn = pick_sddmm_cut(G, T, UA);
             a.cut = reinterpret_cast<const CutInfo *>(ws + plan->layout.off_cut_info);
