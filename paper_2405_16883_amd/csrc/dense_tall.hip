@@ -16,6 +16,7 @@
 // 16-lane rows of the wavefront (order_x) then give it columns 2 (l / 16) and the next, of each half of the 16, so that every
 // instruction adds up the even or the odd columns of 8 in ascending order.  That is the order in which the dense library adds up
 // (each instruction is a chain of fused multiply-adds): the same bits wherever it takes its usual kernel, so that a layer may take either.
+#include "dense_tiles.h"
 #include "device_util.h"
 #include "spmm_internal.h"
 
@@ -208,13 +209,7 @@ scorch_status_t launch_dense_tall(int32_t m, int32_t k, int32_t n, const float *
     const int32_t all_tiles = (int32_t)(((int64_t)n + 15) / 16);
     a.parts = (all_tiles + kDenseTilesMax - 1) / kDenseTilesMax;
     const int32_t tiles = (all_tiles + a.parts - 1) / a.parts;
-    // Two 16-row tiles per wavefront (each fragment of W out of LDS feeds both) unless one gives fewer rounds of the resident
-    // wavefronts, with 4 % for the second reading of W.  us with two from 1024 units of two on / now: 169 343 rows (1.3 rounds of two or 2.6 of
-    // one) 128 -> 128 62.7 / 56.5, 64 -> 128 39.8 / 33.9, 40 -> 100 32.1 / 26.4; 60 000 rows 64 -> 128 18.9 / 16.6; 1 M rows 128 -> 128 318 / 306 (and 337 / 342
-    // with two / one).
-    const int64_t waves = (int64_t)2 * kCus / a.parts * kDenseWaves;
-    auto rounds = [&](int t) { return (((int64_t)m + 16 * t - 1) / (16 * t) + waves - 1) / std::max<int64_t>(1, waves) * t; };
-    const int rt = 100 * rounds(2) <= 104 * rounds(1) ? 2 : 1;
+    const int rt = dense_row_tiles(m, k, n, (int64_t)2 * kCus / a.parts * kDenseWaves);
     a.units = (int32_t)(((int64_t)m + 16 * rt - 1) / (16 * rt));
     const uint32_t lds = (uint32_t)(16 * tiles * (((k + 15) / 16) * 16 + 4 + 1) * 4);  // one more per column: the bias
     // as many workgroups as are resident at once, in whole rounds of 8 per part

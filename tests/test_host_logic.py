@@ -63,6 +63,11 @@ def test_lane_mapping_takes_aligned_vectors_only_for_aligned_operands(repo_root,
 
 
 @pytest.mark.parametrize("sanitize", [False, True])
+def test_dense_layer_takes_two_row_tiles_where_the_stores_decide(repo_root, tmp_path, sanitize):
+    run_checker(build_checker(repo_root, tmp_path, "dense_tiles_check", sanitize), sanitize)
+
+
+@pytest.mark.parametrize("sanitize", [False, True])
 def test_pieces_of_rows_cut_by_columns_fit_and_have_places_of_their_own(repo_root, tmp_path, sanitize):
     run_checker(build_checker(repo_root, tmp_path, "cut_classes_check", sanitize), sanitize)
 
