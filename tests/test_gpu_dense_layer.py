@@ -30,6 +30,12 @@ def test_dense_layer_matches_float64(m, k, n, pad, relu, with_bias):
     assert bool(whole[m:].isnan().all()) and bool(whole[:, n:].isnan().all()), "written outside Y"
 
 
+@pytest.mark.parametrize("m,k,n,pad", [(291683, 25, 208, 0), (291683, 25, 205, 3), (1000003, 16, 53, 0), (475007, 47, 100, 1)])
+def test_wide_results_beyond_the_memory_side_cache(m, k, n, pad):
+    """Two row tiles per wavefront although one has fewer rounds."""
+    test_dense_layer_matches_float64(m, k, n, pad, True, True)
+
+
 def test_dense_layer_keeps_nan_and_refuses_wide_x():
     X = torch.zeros((4, 8), device=DEV)
     X[1, 2] = float("nan")
