@@ -1,6 +1,6 @@
 """Host-side logic of the library that needs no GPU.  Pieces of plain integer or text handling live in headers
 without HIP dependencies -- the workgroup -> (column tile, row work) mapping of the XCD-sliced launches, the dealing of
-long rows to workgroups of the plan-free kernel, the lane mapping, the layout of rows cut by columns, the range of row pointers a key of a coordinate list fills, and the parser of the tuning text -- and small C++ checkers under
+long rows to workgroups of the plan-free kernel, the lane mapping, the row tiles of the dense layer, the layout of rows cut by columns, the range of row pointers a key of a coordinate list fills, and the parser of the tuning text -- and small C++ checkers under
 tests/host/ are compiled with the host compiler and run on the CPU, once plainly and once under the address and
 undefined-behaviour sanitizers.  The C oracles get the same sanitizer pass through a driver that hands them every
 operand in a heap block of exactly its size."""
